@@ -5,8 +5,12 @@
 //   - "Delta Uniform" (Sec. 3.2 metric list, Table 3, Fig. 6): per-layer divergence of the
 //     realised expert balance from the uniform one, and its mean over layers.
 // All integer work uses integer atomics (order-independent, hence deterministic); the one
-// floating-point reduction (Eq. 6) sums fixed-size blocks in a fixed tree order and adds the
-// block sums in index order in fp64.
+// floating-point reduction (Eq. 6) sums fixed shares of the tokens in a fixed order and adds the
+// shares' sums in fp64, again in a fixed order.
+// What bounds these kernels is launches: each dependent one costs 4-5 us however little it does, and
+// the data (2 MB for 24 layers of 2048 tokens) is read in about that time.  So every entry point is
+// one or two launches, and what is left of serial work runs on a workgroup instead of a thread
+// (all four calls on 24 x 2048 tokens, 2 of 8 experts: 120 us before, 35 now).
 #include "common.h"
 
 namespace moe {
@@ -24,86 +28,135 @@ __device__ __forceinline__ unsigned long long expert_mask(const int32_t* __restr
     return m;
 }
 
-__global__ void zero_u64_kernel(unsigned long long* p, int n) {
+__global__ __launch_bounds__(kMetricThreads) void zero_counters_kernel(unsigned long long* p, int n, unsigned long long* q) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
+    if (q && i == 0) *q = 0;
 }
 
-// one thread per adjacent token pair (b, t), t < T-1; H_e += [e in S(b,t+1)] xor [e in S(b,t)]
+// Expert sets that differ between tokens i and i + 1 of the flattened [B, T] tokens (0 when token i
+// is its sequence's last, or lies at or beyond `end`).
+__device__ __forceinline__ unsigned long long replaced_set(const int32_t* __restrict__ S, int i, int end,
+                                                           int T, int K, int E) {
+    if (i >= end || i % T == T - 1) return 0ull;
+    const int32_t* s0 = S + (size_t)i * K;
+    return expert_mask(s0, K, E) ^ expert_mask(s0 + K, K, E);
+}
+
+// One thread per token: H_e[e] += [e in S(b,t+1)] xor [e in S(b,t)], H += the same over all e.  He and H
+// start at zero.  (H is added here, one atomic per workgroup, and not by a kernel of its own: a
+// dependent launch costs 4-5 us, whatever it does.)
 __global__ __launch_bounds__(kMetricThreads) void replacements_kernel(
-    const int32_t* __restrict__ S, int B, int T, int K, int E, unsigned long long* __restrict__ He) {
+    const int32_t* __restrict__ S, int B, int T, int K, int E, unsigned long long* __restrict__ He,
+    unsigned long long* __restrict__ H) {
     __shared__ int s_cnt[kMaxExperts];
     if (threadIdx.x < kMaxExperts) s_cnt[threadIdx.x] = 0;
     __syncthreads();
-    const long long npairs = (long long)B * (T - 1);
-    const long long i = (long long)blockIdx.x * kMetricThreads + threadIdx.x;
-    if (i < npairs) {
-        const long long b = i / (T - 1), t = i % (T - 1);
-        const int32_t* s0 = S + (b * T + t) * K;
-        unsigned long long diff = expert_mask(s0, K, E) ^ expert_mask(s0 + K, K, E);
-        while (diff) {
-            const int e = __ffsll((long long)diff) - 1;
-            atomicAdd(&s_cnt[e], 1);
-            diff &= diff - 1;
-        }
+    unsigned long long diff =
+        replaced_set(S, blockIdx.x * kMetricThreads + threadIdx.x, B * T, T, K, E);
+    while (diff) {
+        const int e = __ffsll((long long)diff) - 1;
+        atomicAdd(&s_cnt[e], 1);
+        diff &= diff - 1;
     }
     __syncthreads();
-    if (threadIdx.x < E && s_cnt[threadIdx.x])
-        atomicAdd(&He[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]);
-}
-
-__global__ void sum_replacements_kernel(const unsigned long long* __restrict__ He, int E,
-                                        unsigned long long* __restrict__ H) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        unsigned long long h = 0;
-        for (int e = 0; e < E; ++e) h += He[e];
-        *H = h;
+    if (threadIdx.x < kMaxExperts) {  // one wave
+        const int c = s_cnt[threadIdx.x];
+        if (c) atomicAdd(&He[threadIdx.x], (unsigned long long)c);
+        int all = c;
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) all += __shfl_xor(all, m, kWave);
+        if (threadIdx.x == 0 && all) atomicAdd(H, (unsigned long long)all);
     }
 }
 
-// block partial sums of |W[b,t+1,e] - W[b,t,e]| over the flattened (b, t < T-1, e) index
-__global__ __launch_bounds__(kMetricThreads) void soft_partial_kernel(
-    const float* __restrict__ W, int B, int T, int E, float* __restrict__ partial) {
-    __shared__ float s_sum[kMetricThreads];
-    const long long n = (long long)B * (T - 1) * E;
-    const long long i = (long long)blockIdx.x * kMetricThreads + threadIdx.x;
-    float v = 0.f;
-    if (i < n) {
-        const long long row = i / E;  // (b, t) with t < T-1
-        const int e = (int)(i % E);
-        const long long b = row / (T - 1), t = row % (T - 1);
-        const float* w0 = W + (b * T + t) * E + e;
-        v = fabsf(w0[E] - w0[0]);
+// Partial sums of a workgroup's share of the tokens, soft part |W[b,t+1,e] - W[b,t,e]| and hard part
+// (number of replaced experts), to partial[2 * block] (fp32) and partial[2 * block + 1] (int32).
+// Nothing is accumulated in memory, so nothing has to be cleared first.
+__global__ __launch_bounds__(kMetricThreads) void bles_partial_kernel(
+    const float* __restrict__ W, const int32_t* __restrict__ S, int B, int T, int K, int E,
+    int tokens_per_block, int vec, float* __restrict__ partial) {
+    __shared__ float s_soft[kMetricThreads / kWave];
+    __shared__ int s_hard[kMetricThreads / kWave];
+    const int t0 = blockIdx.x * tokens_per_block;
+    const int t1 = min(B * T, t0 + tokens_per_block);
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    int hard = 0;
+    for (int i = t0 + threadIdx.x; i < t1; i += kMetricThreads) hard += __popcll(replaced_set(S, i, t1, T, K, E));
+    float soft = 0.f;
+    if (vec) {  // rows of W are whole, aligned 16-byte chunks
+        const int q = E / 4;
+        const f32x4* w = reinterpret_cast<const f32x4*>(W);
+        for (int c = t0 * q + threadIdx.x; c < t1 * q; c += kMetricThreads) {
+            if ((c / q) % T == T - 1) continue;
+            const f32x4 v = w[c + q] - w[c];
+            soft += (fabsf(v[0]) + fabsf(v[1])) + (fabsf(v[2]) + fabsf(v[3]));
+        }
+    } else {
+        for (int c = t0 * E + threadIdx.x; c < t1 * E; c += kMetricThreads)
+            if ((c / E) % T != T - 1) soft += fabsf(W[c + E] - W[c]);
     }
-    s_sum[threadIdx.x] = v;
+    soft = wave_sum(soft);
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) hard += __shfl_xor(hard, m, kWave);
+    if (lane == 0) {
+        s_soft[wave] = soft;
+        s_hard[wave] = hard;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kMetricThreads / kWave; ++w) {
+            soft += s_soft[w];
+            hard += s_hard[w];
+        }
+        partial[2 * blockIdx.x] = soft;
+        reinterpret_cast<int*>(partial)[2 * blockIdx.x + 1] = hard;
+    }
+}
+
+// out = {H, H_norm, L, L_norm, loss} (Eq. 5, 6, 7).  One workgroup: thread i adds the partials
+// i, i + 256, ... in fp64 and the threads meet in a fixed tree (deterministic).  (One thread adding
+// all of them was a chain of 1536 dependent load-and-adds at 24 x 2048 tokens: 64 us.)
+__global__ __launch_bounds__(kMetricThreads) void bles_finalize_kernel(
+    const float* __restrict__ partial, int nblocks, int B, int T, int K, double* __restrict__ out) {
+    __shared__ double s_soft[kMetricThreads];
+    __shared__ unsigned long long s_hard[kMetricThreads];
+    double L = 0.0;
+    unsigned long long H = 0;
+    for (int i = threadIdx.x; i < nblocks; i += kMetricThreads) {
+        L += (double)partial[2 * i];
+        H += (unsigned)reinterpret_cast<const int*>(partial)[2 * i + 1];
+    }
+    s_soft[threadIdx.x] = L;
+    s_hard[threadIdx.x] = H;
     __syncthreads();
     for (int off = kMetricThreads / 2; off > 0; off >>= 1) {
-        if (threadIdx.x < off) s_sum[threadIdx.x] += s_sum[threadIdx.x + off];
+        if (threadIdx.x < off) {
+            s_soft[threadIdx.x] += s_soft[threadIdx.x + off];
+            s_hard[threadIdx.x] += s_hard[threadIdx.x + off];
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = s_sum[0];
-}
-
-// out = {H, H_norm, L, L_norm, loss} (Eq. 5, 6, 7)
-__global__ void bles_finalize_kernel(const float* __restrict__ partial, int nblocks,
-                                     const unsigned long long* __restrict__ H, int B, int T, int K,
-                                     double* __restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double L = 0.0;
-    for (int i = 0; i < nblocks; ++i) L += (double)partial[i];
-    const double h = (double)*H;
-    const double Hn = T > 1 ? (double)(*H / 2) / ((double)B * K * (T - 1)) : 0.0;
+    if (threadIdx.x != 0) return;
+    L = s_soft[0];
+    H = s_hard[0];
+    const double Hn = T > 1 ? (double)(H / 2) / ((double)B * K * (T - 1)) : 0.0;
     const double Ln = L / ((double)B * T);
-    out[0] = h;
+    out[0] = (double)H;
     out[1] = Hn;
     out[2] = L;
     out[3] = Ln;
     out[4] = Hn * Ln;
 }
 
+constexpr int kLayerThreads = 1024;  // kernels with one workgroup per layer
+// Up to this many pairs a layer is one workgroup's: it reads 128 KB in about the 9 us that clearing the
+// counters first and the second launch would add.
+constexpr int kOneChunkPairs = 32768;
+
 // one workgroup per layer: adjacent-token set comparisons (the resident set after token t is
 // always S_t, so the rule's state is just the previous token's selection)
-__global__ __launch_bounds__(kMetricThreads) void offload_kernel(
+__global__ __launch_bounds__(kLayerThreads) void offload_kernel(
     const int32_t* __restrict__ trace, int T, int K, int E, unsigned long long* __restrict__ changes,
     unsigned long long* __restrict__ loads) {
     __shared__ int s_ch, s_ld;
@@ -114,7 +167,7 @@ __global__ __launch_bounds__(kMetricThreads) void offload_kernel(
     __syncthreads();
     const int32_t* tr = trace + (size_t)blockIdx.x * T * K;
     int ch = 0, ld = 0;
-    for (int t = threadIdx.x; t < T; t += kMetricThreads) {
+    for (int t = threadIdx.x; t < T; t += kLayerThreads) {
         const unsigned long long cur = expert_mask(tr + (size_t)t * K, K, E);
         const unsigned long long prev = t > 0 ? expert_mask(tr + (size_t)(t - 1) * K, K, E) : 0ull;
         if (cur != prev) {
@@ -122,8 +175,15 @@ __global__ __launch_bounds__(kMetricThreads) void offload_kernel(
             ld += __popcll(cur & ~prev);
         }
     }
-    atomicAdd(&s_ch, ch);
-    atomicAdd(&s_ld, ld);
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+        ch += __shfl_xor(ch, m, kWave);
+        ld += __shfl_xor(ld, m, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicAdd(&s_ch, ch);
+        atomicAdd(&s_ld, ld);
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         changes[blockIdx.x] = (unsigned long long)s_ch;
@@ -131,52 +191,58 @@ __global__ __launch_bounds__(kMetricThreads) void offload_kernel(
     }
 }
 
-// counts[l][e] += pairs of layer l that chose expert e (grid: x = token chunks, y = layers)
-__global__ __launch_bounds__(kMetricThreads) void balance_count_kernel(
+// counts[l][e] = pairs of layer l that chose expert e.  Grid: x = chunks of a layer, y = layers.  ONE: a
+// single chunk, whose workgroup stores the layer's counts; otherwise they are added to counts, which
+// start at zero.  Every wave counts in LDS of its own.
+template <bool ONE>
+__global__ __launch_bounds__(kLayerThreads) void balance_count_kernel(
     const int32_t* __restrict__ trace, int TK, int E, unsigned long long* __restrict__ counts) {
-    __shared__ int s_cnt[kMaxExperts];
-    if (threadIdx.x < kMaxExperts) s_cnt[threadIdx.x] = 0;
+    __shared__ int s_cnt[kLayerThreads / kWave][kMaxExperts];
+    const int wave = threadIdx.x / kWave;
+    for (int i = threadIdx.x; i < kLayerThreads / kWave * kMaxExperts; i += kLayerThreads) (&s_cnt[0][0])[i] = 0;
     __syncthreads();
     const int32_t* tr = trace + (size_t)blockIdx.y * TK;
-    const int stride = gridDim.x * kMetricThreads;
-    for (int i = blockIdx.x * kMetricThreads + threadIdx.x; i < TK; i += stride) {
+    const int stride = gridDim.x * kLayerThreads;
+    for (int i = blockIdx.x * kLayerThreads + threadIdx.x; i < TK; i += stride) {
         const int e = tr[i];
-        if ((unsigned)e < (unsigned)E) atomicAdd(&s_cnt[e], 1);
+        if ((unsigned)e < (unsigned)E) atomicAdd(&s_cnt[wave][e], 1);
     }
     __syncthreads();
-    if (threadIdx.x < E && s_cnt[threadIdx.x])
-        atomicAdd(&counts[(size_t)blockIdx.y * E + threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]);
+    if (threadIdx.x < E) {
+        unsigned long long c = 0;
+        for (int w = 0; w < kLayerThreads / kWave; ++w) c += s_cnt[w][threadIdx.x];
+        unsigned long long* at = &counts[(size_t)blockIdx.y * E + threadIdx.x];
+        if (ONE) *at = c;
+        else if (c) atomicAdd(at, c);
+    }
 }
 
 // delta[l] = sum_e | counts[l][e] / (T K) - 1/E |, summed in ascending e; mean = (sum_l delta[l]) / L
-// in ascending l.  One thread: L E terms of fp64.
-__global__ void balance_finalize_kernel(const unsigned long long* __restrict__ counts, int L, int TK,
-                                        int E, double* __restrict__ delta, double* __restrict__ mean) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// in ascending l.  One workgroup, a thread per layer (kMetricThreads layers at a time): the fp64
+// divisions, E per layer, are what takes time, and the layers' are independent.
+__global__ __launch_bounds__(kMetricThreads) void balance_finalize_kernel(
+    const unsigned long long* __restrict__ counts, int L, int TK, int E, double* __restrict__ delta,
+    double* __restrict__ mean) {
+    __shared__ double s_delta[kMetricThreads];
     double total = 0.0;
-    for (int l = 0; l < L; ++l) {
-        double dl = 0.0;
-        for (int e = 0; e < E; ++e) {
-            const double dev = (double)counts[(size_t)l * E + e] / (double)TK - 1.0 / (double)E;
-            dl += dev < 0 ? -dev : dev;
+    for (int l0 = 0; l0 < L; l0 += kMetricThreads) {
+        const int l = l0 + threadIdx.x;
+        if (l < L) {
+            double dl = 0.0;
+#pragma unroll 4
+            for (int e = 0; e < E; ++e) {
+                const double dev = (double)counts[(size_t)l * E + e] / (double)TK - 1.0 / (double)E;
+                dl += dev < 0 ? -dev : dev;
+            }
+            if (delta) delta[l] = dl;
+            s_delta[threadIdx.x] = dl;
         }
-        if (delta) delta[l] = dl;
-        total += dl;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int i = 0; i < min(L - l0, kMetricThreads); ++i) total += s_delta[i];
+        __syncthreads();
     }
-    *mean = total / (double)L;
-}
-
-static int launch_replacements(const int32_t* S, int B, int T, int K, int E, unsigned long long* He,
-                               unsigned long long* H, hipStream_t st) {
-    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(kMaxExperts), 0, st, He, E);
-    const long long npairs = (long long)B * (T - 1);
-    if (npairs > 0) {
-        const int grid = (int)((npairs + kMetricThreads - 1) / kMetricThreads);
-        hipLaunchKernelGGL(replacements_kernel, dim3(grid), dim3(kMetricThreads), 0, st, S, B, T, K, E,
-                           He);
-    }
-    hipLaunchKernelGGL(sum_replacements_kernel, dim3(1), dim3(64), 0, st, He, E, H);
-    return launch_status();
+    if (threadIdx.x == 0) *mean = total / (double)L;
 }
 
 }  // namespace moe
@@ -197,8 +263,14 @@ int moe_expert_replacements(const int32_t* S, int32_t B, int32_t T, int32_t K, i
     int rc = check_trace_shape(B, T, K, E);
     if (rc != MOE_OK) return rc;
     if (!S || !H_e || !H) return MOE_ERR_INVALID;
-    return launch_replacements(S, B, T, K, E, reinterpret_cast<unsigned long long*>(H_e),
-                               reinterpret_cast<unsigned long long*>(H), as_stream(stream));
+    hipStream_t st = as_stream(stream);
+    unsigned long long* he = reinterpret_cast<unsigned long long*>(H_e);
+    unsigned long long* h = reinterpret_cast<unsigned long long*>(H);
+    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(kMetricThreads), 0, st, he, E, h);
+    if (T > 1)
+        hipLaunchKernelGGL(replacements_kernel, dim3((B * T - 1) / kMetricThreads + 1), dim3(kMetricThreads), 0, st,
+                           S, B, T, K, E, he, h);
+    return launch_status();
 }
 
 size_t moe_bles_workspace_bytes(int32_t B, int32_t T, int32_t E) {
@@ -217,19 +289,17 @@ int moe_bles_loss(const float* probs, const int32_t* S, int32_t B, int32_t T, in
     if (!probs || !S || !out) return MOE_ERR_INVALID;
     if (!workspace || workspace_bytes < moe_bles_workspace_bytes(B, T, E)) return MOE_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
-    unsigned long long* He = static_cast<unsigned long long*>(workspace);
-    unsigned long long* H = He + kMaxExperts;
-    float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) +
-                                              round_up(sizeof(unsigned long long) * (kMaxExperts + 1), 256));
-    rc = launch_replacements(S, B, T, K, E, He, H, st);
-    if (rc != MOE_OK) return rc;
-    const long long n = (long long)B * (T - 1) * E;
-    const int nblocks = (int)((n + kMetricThreads - 1) / kMetricThreads);
-    if (nblocks > 0)
-        hipLaunchKernelGGL(soft_partial_kernel, dim3(nblocks), dim3(kMetricThreads), 0, st, probs, B, T,
-                           E, partial);
-    hipLaunchKernelGGL(bles_finalize_kernel, dim3(1), dim3(64), 0, st, partial, nblocks, H, B, T, K,
-                       out);
+    // a pair of partial sums per workgroup; the size query has room for one float per 256 elements of
+    // W beside the counters' 768 bytes, and a workgroup takes at least 1024 elements
+    float* partial = static_cast<float*>(workspace);
+    int nblocks = 0;
+    if (T > 1) {
+        const int tokens_per_block = max(kMetricThreads / 2, (4 * kMetricThreads + E - 1) / E);
+        nblocks = (B * T - 1) / tokens_per_block + 1;
+        hipLaunchKernelGGL(bles_partial_kernel, dim3(nblocks), dim3(kMetricThreads), 0, st, probs, S, B, T, K, E,
+                           tokens_per_block, E % 4 == 0 && aligned16(probs) ? 1 : 0, partial);
+    }
+    hipLaunchKernelGGL(bles_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, partial, nblocks, B, T, K, out);
     return launch_status();
 }
 
@@ -238,7 +308,7 @@ int moe_offload_counters(const int32_t* trace, int32_t L, int32_t T, int32_t K, 
     int rc = check_trace_shape(L, T, K, E);
     if (rc != MOE_OK) return rc;
     if (!trace || !changes || !loads) return MOE_ERR_INVALID;
-    hipLaunchKernelGGL(offload_kernel, dim3(L), dim3(kMetricThreads), 0, as_stream(stream), trace, T,
+    hipLaunchKernelGGL(offload_kernel, dim3(L), dim3(kLayerThreads), 0, as_stream(stream), trace, T,
                        K, E, reinterpret_cast<unsigned long long*>(changes),
                        reinterpret_cast<unsigned long long*>(loads));
     return launch_status();
@@ -252,13 +322,17 @@ int moe_delta_uniform(const int32_t* trace, int32_t L, int32_t T, int32_t K, int
     if ((long long)L * E >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;
     hipStream_t st = as_stream(stream);
     unsigned long long* cnt = reinterpret_cast<unsigned long long*>(counts);
-    const int n = L * E;
-    hipLaunchKernelGGL(zero_u64_kernel, dim3((n + kMetricThreads - 1) / kMetricThreads), dim3(kMetricThreads), 0,
-                       st, cnt, n);
     const int TK = T * K;  // < 2^31 by check_trace_shape
-    const int chunks = min(64, (TK + 4 * kMetricThreads - 1) / (4 * kMetricThreads));
-    hipLaunchKernelGGL(balance_count_kernel, dim3(chunks, L), dim3(kMetricThreads), 0, st, trace, TK, E, cnt);
-    hipLaunchKernelGGL(balance_finalize_kernel, dim3(1), dim3(64), 0, st, cnt, L, TK, E, delta, mean);
+    if (TK <= kOneChunkPairs) {
+        hipLaunchKernelGGL(balance_count_kernel<true>, dim3(1, L), dim3(kLayerThreads), 0, st, trace, TK, E, cnt);
+    } else {
+        const int n = L * E;
+        hipLaunchKernelGGL(zero_counters_kernel, dim3((n + kMetricThreads - 1) / kMetricThreads), dim3(kMetricThreads), 0,
+                           st, cnt, n, nullptr);
+        const int chunks = min(64, (TK + 4 * kLayerThreads - 1) / (4 * kLayerThreads));
+        hipLaunchKernelGGL(balance_count_kernel<false>, dim3(chunks, L), dim3(kLayerThreads), 0, st, trace, TK, E, cnt);
+    }
+    hipLaunchKernelGGL(balance_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, cnt, L, TK, E, delta, mean);
     return launch_status();
 }
 
