@@ -3,12 +3,8 @@
 // gate/up product's epilogue and weight-decomposed experts (Sec. 2.2, Eq. 1) expressed
 // as extra K-segments accumulated into the same output tile.
 //
-// One generic problem:   C[s, n] = epi( sum_seg  A_seg[row(s), :] . B_seg[e(s)][n, :] )
-//   PLAIN   one accumulator, C = acc
-//   SWIGLU  two accumulators over (A0,B0) and (A1,B1); C = silu(acc0) * acc1
-// A and B are both K-contiguous ("NT" GEMM), the natural layout of activations [rows, in]
-// and linear-layer weights [out, in], and exactly what an MFMA lane wants: 8 consecutive
-// k of one row per 16-byte read.
+// The problem and the tile enumeration are in gemm.h; both operands are K-contiguous, which is
+// exactly what an MFMA lane wants: 8 consecutive k of one row per 16-byte read.
 //
 // bf16 kernels: block tile BM x BN x BK on (BM / WM) * (BN / WN) waves, wave tile WM x WN built
 // from v_mfma_f32_32x32x16_bf16, fp32 accumulators in registers.  Global -> registers -> LDS
@@ -19,23 +15,10 @@
 // expert's m-tiles, and the workgroup id is remapped so that each XCD walks a contiguous
 // eighth of that order (consecutive tiles share a weight tile and hit in that XCD's L2).
 // run_gemm picks the tile shape from the pair count and the output width.
-//
-// fp32 problems (correctness-only configuration) use a plain LDS-tiled FMA kernel.
-#include <type_traits>
-#include <utility>
-
-#include "common.h"
+// fp32 problems: expert_gemm_f32.hip.
+#include "gemm.h"
 
 namespace moe {
-
-template <int... I, typename F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
-}
 
 // Products whose activation operand is the F-wide hidden tensor (down, rank-down): that operand is
 // as large as an expert's weights, so tiles are ordered in blocks of this many n-tiles with the
@@ -43,176 +26,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 // and a few B tiles instead of one B tile and every A tile (measured on the phone shape with
 // Zipf loads: down product 145 us with blocks of 8 or 16, 148 with 4, 153-157 with n-tile outer).
 constexpr int kHiddenOperandBlock = 8;
-
-struct GemmSeg {
-    const void* A0;     // [*, K]
-    const void* A1;     // A of the second accumulator (SWIGLU); may equal A0
-    const void* B0;     // [Eb, N, K]
-    const void* B1;
-    long long strideB;  // elements between experts; 0 = shared by all experts
-    int K;
-    int gather;         // 1: the A row of sorted slot s is row_map[s] / row_div
-};
-
-struct GemmArgs {
-    GemmSeg seg[2];
-    int nseg;
-    void* C;            // [P, N]
-    void* C1;           // PLAIN only, deep kernel: second product (A1 . B1) of the same shape, or NULL
-    int N;
-    const int32_t* offsets;  // [E+1]
-    const int32_t* row_map;  // [P] or NULL
-    int row_div;
-    int E;
-    int P;
-    int m_tiles_max;
-    int n_tiles;        // n-tiles of the launch (twice those of one product when C1 is set)
-    // SWIGLU, deep kernel: per-token rows added to the two accumulators before the activation
-    // (the token of sorted slot s is row_map[s] / row_div), [*, N] in the activation type, or NULL
-    const void* add0;
-    const void* add1;
-    int n_inner;        // tile order inside an expert: blocks of this many n-tiles (0 or 1: n-tile outer, m-tiles inner)
-    int split_slots;    // workgroups one XCD runs at a time; > 0: the tiles of its last, partial round are cut
-                        // into upper and lower halves when both halves still fit in one round (set by the launcher)
-    // PLAIN, one segment: the k-steps of every tile are cut into k_parts consecutive ranges, each
-    // computed by a workgroup of its own and stored to its own output [P, N] (part q at
-    // C + q * part_stride elements); whoever consumes C adds the parts.  In: the most parts the
-    // caller's output can take (0 or 1: none).  Out (set by run_gemm): the parts used.
-    int k_parts;
-    long long part_stride;
-};
-
-// Group e's row range; offsets == NULL means one group holding all P rows (a plain product).
-__device__ __forceinline__ int group_begin(const int32_t* __restrict__ offsets, int e) {
-    return offsets ? offsets[e] : 0;
-}
-__device__ __forceinline__ int group_end(const int32_t* __restrict__ offsets, int e, int P) {
-    return offsets ? offsets[e + 1] : P;
-}
-
-// Workgroup -> output tile.  Tiles are ordered expert-major, then n-tile, then the expert's
-// own m-tiles, so neighbouring tiles share the expert's activation rows (and, for equal
-// n-tile, its weight tile).  Workgroups are handed to the 8 XCDs round-robin by id; XCD x
-// takes the x-th contiguous eighth of that order, which keeps each XCD's L2 working set to
-// about one expert's rows plus the weight tiles it is streaming.  The grid is an upper
-// bound (group sizes live on the device); surplus workgroups return false.
-//
-// Tail split: an XCD runs split_slots workgroups at a time, so its tiles take
-// ceil(tiles / split_slots) rounds and the last round may be nearly empty.  When there is at
-// least one full round and the last one holds at most split_slots / 2 tiles, each of those is
-// cut into an upper and a lower half (BM / 2 rows) handled by two workgroups: the halves still
-// fit in one round and each is shorter than a whole tile (it fills half the activation rows
-// and multiplies half the blocks).
-__device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, int E, int P, int BM,
-                                          int n_tiles, int& e_out, int& row0, int& row_end,
-                                          int& nt_out, int n_inner = 0, int split_slots = 0) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    // Lane e of every wave fetches group e's bounds with ONE vector load (E <= 64); the sums below
-    // then run on scalar registers through readlane.  (A loop of dependent scalar loads over the
-    // offsets cost 2.6-3.3 us per tile here, a twentieth of a tile's whole duration.)
-    const int lane = threadIdx.x & (kWave - 1);
-    int lo = 0, hi = 0;
-    if (lane < E) {
-        lo = group_begin(offsets, lane);
-        hi = group_end(offsets, lane, P);
-    }
-    const int cnt = (hi - lo + BM - 1) / BM;  // m-tiles of group `lane` (0 beyond E)
-    int total = 0;
-    for (int e = 0; e < E; ++e) total += __builtin_amdgcn_readlane(cnt, e);
-    total *= n_tiles;
-#else
-    int total = 0;
-    for (int e = 0; e < E; ++e)
-        total += (group_end(offsets, e, P) - group_begin(offsets, e) + BM - 1) / BM;
-    total *= n_tiles;
-#endif
-    const int per_xcd = (total + 7) / 8;
-    const int slot = blockIdx.x >> 3;
-    const int first = (blockIdx.x & 7) * per_xcd;               // this XCD's first tile
-    const int mine = max(0, min(per_xcd, total - first));       // and how many it has
-    int local_tile = slot, half = -1;
-    if (split_slots > 0) {
-        const int whole = (mine / split_slots) * split_slots;   // tiles in full rounds
-        const int rem = mine - whole;
-        if (whole > 0 && rem > 0 && 2 * rem <= split_slots && slot >= whole) {
-            const int idx = slot - whole;
-            local_tile = whole + idx / 2;
-            half = idx & 1;
-        }
-    }
-    if (local_tile >= mine) return false;
-    const int L = first + local_tile;
-    int before = 0;
-    for (int e = 0; e < E; ++e) {
-#if defined(__HIP_DEVICE_COMPILE__)
-        const int mtiles = __builtin_amdgcn_readlane(cnt, e);
-#else
-        const int mtiles = (group_end(offsets, e, P) - group_begin(offsets, e) + BM - 1) / BM;
-#endif
-        const int here = mtiles * n_tiles;
-        if (L < before + here) {
-#if defined(__HIP_DEVICE_COMPILE__)
-            const int prev = __builtin_amdgcn_readlane(lo, e), next = __builtin_amdgcn_readlane(hi, e);
-#else
-            const int prev = group_begin(offsets, e), next = group_end(offsets, e, P);
-#endif
-            const int local = L - before;
-            e_out = e;
-            // blocks of n_inner n-tiles: block outer, the expert's m-tiles in the middle, the
-            // block's n-tiles inner (n_inner = 1: n-tile outer, m-tiles inner)
-            const int nb = max(n_inner, 1);
-            const int full = (n_tiles / nb) * nb * mtiles;  // tiles in whole blocks
-            int mt, nt;
-            if (local < full) {
-                const int rem = local % (mtiles * nb);
-                mt = rem / nb;
-                nt = (local / (mtiles * nb)) * nb + rem % nb;
-            } else {
-                const int nb_tail = n_tiles % nb;
-                const int rem = local - full;
-                mt = rem / nb_tail;
-                nt = (n_tiles / nb) * nb + rem % nb_tail;
-            }
-            nt_out = nt;
-            row0 = prev + mt * BM;
-            row_end = next;
-            if (half >= 0) {
-                row0 += half * (BM / 2);
-                row_end = min(next, row0 + BM / 2);
-                if (row0 >= row_end) return false;  // the tile had no rows in its lower half
-            }
-            return true;
-        }
-        before += here;
-    }
-    return false;
-}
-
-// m-tile index (over all experts, in expert order) -> expert and row range
-__device__ __forceinline__ bool find_m_tile(const int32_t* __restrict__ offsets, int E, int P, int BM,
-                                            int mt, int& e_out, int& row0, int& row_end) {
-    int acc = 0;
-    int prev = group_begin(offsets, 0);
-    for (int e = 0; e < E; ++e) {
-        const int next = group_end(offsets, e, P);
-        const int tiles = (next - prev + BM - 1) / BM;
-        if (mt < acc + tiles) {
-            e_out = e;
-            row0 = prev + (mt - acc) * BM;
-            row_end = next;
-            return true;
-        }
-        acc += tiles;
-        prev = next;
-    }
-    return false;
-}
-
-__device__ __forceinline__ int src_row(const GemmArgs& g, const GemmSeg& sg, int s) {
-    if (!sg.gather) return s;
-    const int p = min(max(g.row_map[s], 0), g.P - 1);
-    return p / g.row_div;
-}
 
 // ============================================================================= bf16 MFMA
 // LDS tile rows hold BK bf16 (BK/8 chunks of 16 bytes).  The chunk index is XOR-ed with a
@@ -750,65 +563,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
     }
 }
 
-// ============================================================================= generic tiled FMA
-// 64 x 64 output tile, 256 threads, 4 x 4 outputs each, K stepped by 16 through LDS.
-template <typename T, bool SWIGLU>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(const GemmArgs g) {
-    constexpr int TM = 64, TN = 64, TK = 16;
-    __shared__ float sA0[TK][TM + 1], sA1[TK][TM + 1], sB0[TK][TN + 1], sB1[TK][TN + 1];
-    const int mt = blockIdx.x % g.m_tiles_max;
-    const int nt = blockIdx.x / g.m_tiles_max;
-    int e, row0, row_end;
-    if (!find_m_tile(g.offsets, g.E, g.P, TM, mt, e, row0, row_end)) return;
-    const int n0 = nt * TN;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    float acc0[4][4] = {}, acc1[4][4] = {};
-    for (int sidx = 0; sidx < g.nseg; ++sidx) {
-        const GemmSeg& sg = g.seg[sidx];
-        const T* A0 = static_cast<const T*>(sg.A0);
-        const T* A1 = static_cast<const T*>(sg.A1);
-        const T* B0 = static_cast<const T*>(sg.B0) + (size_t)e * sg.strideB;
-        const T* B1 = SWIGLU ? static_cast<const T*>(sg.B1) + (size_t)e * sg.strideB : B0;
-        for (int k0 = 0; k0 < sg.K; k0 += TK) {
-            __syncthreads();
-            for (int i = threadIdx.x; i < TM * TK; i += 256) {
-                const int r = i / TK, kk = i % TK;
-                const int s = row0 + r;
-                const bool ok = s < row_end && k0 + kk < sg.K;
-                const size_t off = ok ? (size_t)src_row(g, sg, s) * sg.K + k0 + kk : 0;
-                sA0[kk][r] = ok ? Store<T>::to_f32(A0[off]) : 0.f;
-                if (SWIGLU) sA1[kk][r] = ok ? Store<T>::to_f32(A1[off]) : 0.f;
-                const int n = n0 + r;
-                const bool okb = n < g.N && k0 + kk < sg.K;
-                const size_t boff = okb ? (size_t)n * sg.K + k0 + kk : 0;
-                sB0[kk][r] = okb ? Store<T>::to_f32(B0[boff]) : 0.f;
-                if (SWIGLU) sB1[kk][r] = okb ? Store<T>::to_f32(B1[boff]) : 0.f;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int kk = 0; kk < TK; ++kk) {
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        acc0[a][b] = fmaf(sA0[kk][ty * 4 + a], sB0[kk][tx * 4 + b], acc0[a][b]);
-                        if (SWIGLU)
-                            acc1[a][b] = fmaf(sA1[kk][ty * 4 + a], sB1[kk][tx * 4 + b], acc1[a][b]);
-                    }
-            }
-        }
-    }
-    T* C = static_cast<T*>(g.C);
-    for (int a = 0; a < 4; ++a)
-        for (int b = 0; b < 4; ++b) {
-            const int row = row0 + ty * 4 + a, col = n0 + tx * 4 + b;
-            if (row < row_end && col < g.N) {
-                const float v = SWIGLU ? silu_f32(acc0[a][b]) * acc1[a][b] : acc0[a][b];
-                C[(size_t)row * g.N + col] = Store<T>::from_f32(v);
-            }
-        }
-}
-
 // ============================================================================= host side
 template <int BM, int BN, int BK, int WM, int WN, bool SWIGLU, bool DUAL_A, int NS = 2, int KG = 1, bool ADD = false,
           bool HF = false>
@@ -865,15 +619,6 @@ static int launch_bf16_deep(GemmArgs& g, hipStream_t st) {
     return launch(gemm_bf16_deep_kernel<BM, BN, BK, WM, WN, SWIGLU, DUAL_A, NS, KG, ADD, false, HF>, 0);
 }
 
-template <typename T, bool SWIGLU>
-static int launch_simple(GemmArgs& g, hipStream_t st) {
-    g.m_tiles_max = g.P / 64 + g.E;
-    g.n_tiles = (g.N + 63) / 64;
-    hipLaunchKernelGGL((gemm_simple_kernel<T, SWIGLU>), dim3(g.m_tiles_max * g.n_tiles), dim3(256),
-                       0, st, g);
-    return launch_status();
-}
-
 static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st) {
     if (g.P == 0) return MOE_OK;
     if (g.add0 && (!g.add1 || !g.row_map || !swiglu || s.act_dtype != MOE_BF16)) return MOE_ERR_INVALID;
@@ -897,8 +642,7 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
         const int rc = run_gemm(s, g, swiglu, st);
         return rc != MOE_OK ? rc : run_gemm(s, second, swiglu, st);
     }
-    if (s.act_dtype == MOE_F32)
-        return swiglu ? launch_simple<float, true>(g, st) : launch_simple<float, false>(g, st);
+    if (s.act_dtype == MOE_F32) return run_gemm_f32(g, swiglu, st);
     if (fast) {
         // Tile choice, measured on the 2048 / 5632 and 1024 / 2816 shapes with uniform and Zipf-skewed
         // groups, from 16 to 2048 tokens.  Enough 256 x 256 tiles to fill 256 CUs: those, on 8 waves
