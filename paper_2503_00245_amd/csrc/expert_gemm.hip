@@ -14,7 +14,8 @@
 // operand reads over all banks.  Tiles are enumerated expert-major, then n-tile, then the
 // expert's m-tiles, and the workgroup id is remapped so that each XCD walks a contiguous
 // eighth of that order (consecutive tiles share a weight tile and hit in that XCD's L2).
-// run_gemm picks the tile shape from the pair count and the output width.
+// run_gemm picks the tile shape from the pair count and the output width; products with enough rows
+// for 256-row tiles run in expert_gemm_pp.hip.
 // fp32 problems: expert_gemm_f32.hip.
 #include "gemm.h"
 
@@ -55,18 +56,11 @@ __device__ __forceinline__ int lds_off(int row, int chunk) {
 // TAIL: K need not be a multiple of BK (a separate instantiation, so that the loop of the common
 // case carries none of the tail's bookkeeping: with it the down product of a 2048 x 5632 layer
 // measured 3.5 % slower).
-// HF ("half fills"): the LDS stages hold k-steps of BK = 64 -- a row's share of a step is one whole
-// 128-byte line, where a step of 32 asks for every line twice, half each time -- but a step is
-// filled in two halves by rows (the upper and the lower half of the A and of the B tile), half a
-// step apart, each through its own small register set.  Registers per thread are those of the
-// BK = 32 pipeline (two full BK = 64 sets do not fit beside a 64 x 128 wave tile's accumulators),
-// the barriers per k are halved, and every load instruction covers 8 rows x 128 bytes.
 template <int BM, int BN, int BK, int WM, int WN, bool SWIGLU, bool DUAL_A, int NS, int KG, bool ADD = false,
-          bool TAIL = false, bool HF = false>
+          bool TAIL = false>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_deep_kernel(const GemmArgs g) {
     static_assert(!ADD || SWIGLU, "per-token addends belong to the SwiGLU epilogue");
     static_assert(!TAIL || KG == 1, "a K tail only without k-groups");
-    static_assert(!HF || (KG == 1 && NS == 2 && BK == 64), "half fills: 64-wide steps, two half sets, no k-groups");
     constexpr int WAVES_N = BN / WN;
     constexpr int NTHR = (BM / WM) * WAVES_N * 64;  // threads of one k-group
     constexpr int MT = WM / 32, NT = WN / 32;
@@ -138,11 +132,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
                 for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
     }
 
-    // passes (of RPP rows) one register set covers: all of a tile, or (HF) one half of it
-    constexpr int AP = HF ? AI / 2 : AI, BP = HF ? BI / 2 : BI;
-    static_assert(!HF || (AI % 2 == 0 && BI % 2 == 0), "half fills cut the fill passes in two");
-    struct Regs {
-        bf16x8 a[AP], a1[DUAL_A ? AP : 1], b[BP];
+    struct Regs {  // a tile's share of one thread: AI and BI fill passes of RPP rows
+        bf16x8 a[AI], a1[DUAL_A ? AI : 1], b[BI];
     };
 
     for (int sidx = 0; sidx < g.nseg; ++sidx) {
@@ -167,15 +158,9 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
         const bool tail_dead = TAIL && k_begin + k_last + ld_chunk * 8 >= K;    // per thread (never in a k-part before the last)
         const int k_last_t = tail_dead ? max(k_last - BK, -(ld_chunk * 8)) : k_last;
 
-        // Where a thread's rows start.  HF keeps 32-bit byte offsets from wave-uniform bases (the
-        // load then takes a scalar base and one vector register; its launcher checks that every
-        // operand stays below 4 GB): eight 64-bit pointers are registers this kernel does not have.
-        typedef typename std::conditional<HF, unsigned, const bf16_t*>::type rowref_t;
-        rowref_t pa[AI];
-        rowref_t pa1[DUAL_A ? AI : 1];
-        rowref_t pb[BI];
-        const char* const a0_base = static_cast<const char*>(second ? sg.A1 : sg.A0);
-        const char* const a1_base = static_cast<const char*>(sg.A1);
+        const bf16_t* pa[AI];
+        const bf16_t* pa1[DUAL_A ? AI : 1];
+        const bf16_t* pb[BI];
         // (the row-map lookups of all of a thread's rows are issued together: one latency, not AI)
         int arow[AI];
 #pragma unroll
@@ -189,79 +174,59 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
 #pragma unroll
         for (int i = 0; i < AI; ++i) {
             const size_t off = (size_t)arow[i] * K + k_begin + ld_chunk * 8;
-            if constexpr (HF) {
-                pa[i] = (unsigned)(off * 2);
-                if (DUAL_A) pa1[i] = (unsigned)(off * 2);
-            } else {
-                pa[i] = static_cast<const bf16_t*>(second ? sg.A1 : sg.A0) + off;
-                if (DUAL_A) pa1[i] = static_cast<const bf16_t*>(sg.A1) + off;
-            }
+            pa[i] = static_cast<const bf16_t*>(second ? sg.A1 : sg.A0) + off;
+            if (DUAL_A) pa1[i] = static_cast<const bf16_t*>(sg.A1) + off;
         }
 #pragma unroll
         for (int i = 0; i < BI; ++i) {
             const int j = ld_row + RPP * i;
             const int n = min(SWIGLU ? n0 + (j % (BN / 2)) : n0 + j, g.N - 1);
             const size_t off = (size_t)n * K + k_begin + ld_chunk * 8;
-            if constexpr (HF)
-                pb[i] = (unsigned)(off * 2);
-            else
-                pb[i] = ((SWIGLU && i >= BI / 2) ? B1 : B0) + off;
+            pb[i] = ((SWIGLU && i >= BI / 2) ? B1 : B0) + off;
         }
-        // one 16-byte chunk at k offset k0 (elements) of the row a reference stands for
-        auto ld16 = [&](const char* base, rowref_t ref, int k0) {
-            if constexpr (HF)
-                return *reinterpret_cast<const bf16x8*>(base + (size_t)k0 * 2 + ref);
-            else
-                return *reinterpret_cast<const bf16x8*>(ref + k0);
-        };
-
-        // half: which half of the tile's fill passes the set covers (HF; 0 otherwise)
-        auto gload = [&](Regs& r, int k0, int half = 0) {
+        auto gload = [&](Regs& r, int k0) {
 #pragma unroll
-            for (int i = 0; i < AP; ++i) {
-                r.a[i] = ld16(a0_base, pa[half * AP + i], k0);
-                if (DUAL_A && dual) r.a1[i] = ld16(a1_base, pa1[half * AP + i], k0);
+            for (int i = 0; i < AI; ++i) {
+                r.a[i] = *reinterpret_cast<const bf16x8*>(pa[i] + k0);
+                if (DUAL_A && dual) r.a1[i] = *reinterpret_cast<const bf16x8*>(pa1[i] + k0);
             }
 #pragma unroll
-            for (int i = 0; i < BP; ++i) {
-                const int pass = half * BP + i;
-                r.b[i] = ld16(reinterpret_cast<const char*>((SWIGLU && pass >= BI / 2) ? B1 : B0), pb[pass], k0);
-            }
+            for (int i = 0; i < BI; ++i) r.b[i] = *reinterpret_cast<const bf16x8*>(pb[i] + k0);
         };
         auto zero_dead = [&](Regs& r) {
             if (tail_dead) {
 #pragma unroll
-                for (int i = 0; i < AP; ++i) {
+                for (int i = 0; i < AI; ++i) {
                     r.a[i] = bf16x8{};
                     if (DUAL_A) r.a1[i] = bf16x8{};
                 }
 #pragma unroll
-                for (int i = 0; i < BP; ++i) r.b[i] = bf16x8{};
+                for (int i = 0; i < BI; ++i) r.b[i] = bf16x8{};
             }
         };
-        auto lstore = [&](int stage, const Regs& r, int half = 0) {
+        auto lstore = [&](int stage, const Regs& r) {
             char* base = gmem + stage * STAGE;
 #pragma unroll
-            for (int i = 0; i < AP; ++i) {
-                const int row = ld_row + RPP * (half * AP + i);
+            for (int i = 0; i < AI; ++i) {
+                const int row = ld_row + RPP * i;
                 *reinterpret_cast<bf16x8*>(base + lds_off<BK>(row, ld_chunk)) = r.a[i];
                 if (DUAL_A && dual)
                     *reinterpret_cast<bf16x8*>(base + A_BYTES + lds_off<BK>(row, ld_chunk)) = r.a1[i];
             }
             char* bb = base + A_BYTES * NA;
 #pragma unroll
-            for (int i = 0; i < BP; ++i)
-                *reinterpret_cast<bf16x8*>(bb + lds_off<BK>(ld_row + RPP * (half * BP + i), ld_chunk)) = r.b[i];
+            for (int i = 0; i < BI; ++i)
+                *reinterpret_cast<bf16x8*>(bb + lds_off<BK>(ld_row + RPP * i, ld_chunk)) = r.b[i];
         };
         // MA = how many of the wave's MT 32-row blocks hold rows of the group (the rest are skipped)
-        auto compute = [&](int stage, auto ma, int ks_begin = 0, int ks_end = BK / 16) {
+        auto compute = [&](int stage, auto ma) {
             constexpr int MA = decltype(ma)::value;
             const char* base = gmem + stage * STAGE;
             const char* a0b = base;
             const char* a1b = (DUAL_A && dual) ? base + A_BYTES : base;
             const char* bb = base + A_BYTES * NA;
 #pragma unroll
-            for (int ks = ks_begin; ks < ks_end; ++ks) {
+            for (int ks = 0; ks < BK / 16; ++ks) {
                 const int chunk = ks * 2 + (lane >> 5);
                 bf16x8 fa[MA], fa1[DUAL_A ? MA : 1], fb[NT];
 #pragma unroll
@@ -297,31 +262,13 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
         // tile kt+1 never also waits for the younger loads behind it.
         constexpr int UNR = (NS % 2 == 0) ? NS : 2 * NS;  // steps until (set, stage) repeat
         Regs r[NS];
-        if constexpr (HF) {
-            // r[0] / r[1] carry the upper / lower half of a tile: tile 0 goes to stage 0 through
-            // them, then they hold tile 1
-            gload(r[0], 0, 0);
-            gload(r[1], 0, 1);
-            if constexpr (TAIL) {
-                if (tail_kt == 0) {
-                    zero_dead(r[0]);
-                    zero_dead(r[1]);
-                }
-            }
-            __syncthreads();  // the previous segment's readers are done with both stages
-            lstore(0, r[0], 0);
-            gload(r[0], min(BK, k_last_t), 0);
-            lstore(0, r[1], 1);
-            gload(r[1], min(BK, k_last_t), 1);
-        } else {
 #pragma unroll
-            for (int q = 0; q < NS; ++q) gload(r[q], min(q * BK, k_last_t));
-            if constexpr (TAIL) {
-                if (tail_kt == 0) zero_dead(r[0]);
-            }
-            __syncthreads();  // the previous segment's readers are done with both stages
-            lstore(0, r[0]);
+        for (int q = 0; q < NS; ++q) gload(r[q], min(q * BK, k_last_t));
+        if constexpr (TAIL) {
+            if (tail_kt == 0) zero_dead(r[0]);
         }
+        __syncthreads();  // the previous segment's readers are done with both stages
+        lstore(0, r[0]);
         __syncthreads();
         // Issue order inside a step: the step's global loads and LDS writes are spread through
         // the MFMA sequence (one memory instruction in the shadow of each MFMA) instead of
@@ -346,32 +293,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
             }
 #endif
         };
-        // HF: a step writes the two halves of tile kt+1 to the other stage, the upper half at its
-        // start and the lower half in its middle, and refills each half's registers with tile
-        // kt+2 right after; memory instructions are spread one per two MFMAs in that order
-        auto interleave_hf = [&](auto ma) {
-#if defined(__HIP_DEVICE_COMPILE__)
-            constexpr int MA = decltype(ma)::value;
-            constexpr int NM = MA * NT * (BK / 16);           // MFMAs per step
-            constexpr int NR = (MA * NA + NT) * (BK / 16);    // LDS fragment reads per step
-            constexpr int NH = AP * NA + BP;                  // loads = LDS writes per half
-            constexpr int RPM = (NR + NM - 1) / NM;
-            constexpr int GAP = NM / (4 * NH) > 0 ? NM / (4 * NH) : 1;  // MFMAs per memory instruction
-            __builtin_amdgcn_sched_group_barrier(0x100, MA * NA + NT, 0);  // first fragments
-#pragma unroll
-            for (int i = 0; i < NM; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // one MFMA
-                __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);  // next fragments
-                if (i % GAP == 0) {
-                    const int op = i / GAP;  // 0 .. 4 NH - 1: writes of half 0, loads, writes of half 1, loads
-                    if (op < NH || (op >= 2 * NH && op < 3 * NH))
-                        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                    else if (op < 4 * NH)
-                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                }
-            }
-#endif
-        };
         // The wave multiplies only those of its 32-row blocks that hold rows of the group.  A wave
         // with none keeps filling LDS and meeting the barriers but issues no fragment reads or
         // MFMAs, which leaves its SIMD and the LDS read port to the waves that do have rows.
@@ -382,24 +303,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
             // kt + 1 (set (S + 1) % NS) to the other stage
             auto step = [&](auto sc, int kt) {
                 constexpr int S = decltype(sc)::value;
-                if constexpr (HF) {
-                    if constexpr (TAIL) {
-                        if (kt + 1 == tail_kt) {  // both halves of the tile this step writes to LDS
-                            zero_dead(r[0]);
-                            zero_dead(r[1]);
-                        }
-                    }
-                    const int k_next = min((kt + 2) * BK, k_last_t);
-                    lstore((S & 1) ^ 1, r[0], 0);
-                    gload(r[0], k_next, 0);
-                    if constexpr (MA > 0) compute(S & 1, ma, 0, BK / 32);
-                    lstore((S & 1) ^ 1, r[1], 1);
-                    gload(r[1], k_next, 1);
-                    if constexpr (MA > 0) compute(S & 1, ma, BK / 32, BK / 16);
-                    if constexpr (MA > 0) interleave_hf(ma);
-                    __syncthreads();
-                    return;
-                }
                 if constexpr (TAIL) {
                     if (kt + 1 == tail_kt) zero_dead(r[(S + 1) % NS]);  // the tile this step writes to LDS
                 }
@@ -564,20 +467,9 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
 }
 
 // ============================================================================= host side
-template <int BM, int BN, int BK, int WM, int WN, bool SWIGLU, bool DUAL_A, int NS = 2, int KG = 1, bool ADD = false,
-          bool HF = false>
+template <int BM, int BN, int BK, int WM, int WN, bool SWIGLU, bool DUAL_A, int NS = 2, int KG = 1, bool ADD = false>
 static int launch_bf16_deep(GemmArgs& g, hipStream_t st) {
     if ((g.add0 != nullptr) != ADD) return MOE_ERR_INVALID;
-    if constexpr (HF) {
-        // the half-fill kernel addresses rows by 32-bit byte offsets from the operand's base:
-        // an operand of 4 GB or more goes to the 32-wide pipeline with its 64-bit pointers
-        for (int i = 0; i < g.nseg; ++i) {
-            const GemmSeg& sg = g.seg[i];
-            const long long a_rows = sg.gather ? (g.P - 1) / (g.row_div > 0 ? g.row_div : 1) + 1 : g.P;
-            if (a_rows * sg.K * 2 >= (1ll << 32) || (long long)g.N * sg.K * 2 >= (1ll << 32))
-                return launch_bf16_deep<BM, BN, 32, WM, WN, SWIGLU, DUAL_A, NS, KG, ADD, false>(g, st);
-        }
-    }
     constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
     constexpr int NTHR = (BM / WM) * (BN / WN) * 64 * KG;
     static_assert(NTHR <= 1024, "workgroup size");
@@ -614,9 +506,9 @@ static int launch_bf16_deep(GemmArgs& g, hipStream_t st) {
         return launch_status();
     };
     if constexpr (KG == 1) {
-        if (tail) return launch(gemm_bf16_deep_kernel<BM, BN, BK, WM, WN, SWIGLU, DUAL_A, NS, KG, ADD, true, HF>, 1);
+        if (tail) return launch(gemm_bf16_deep_kernel<BM, BN, BK, WM, WN, SWIGLU, DUAL_A, NS, KG, ADD, true>, 1);
     }
-    return launch(gemm_bf16_deep_kernel<BM, BN, BK, WM, WN, SWIGLU, DUAL_A, NS, KG, ADD, false, HF>, 0);
+    return launch(gemm_bf16_deep_kernel<BM, BN, BK, WM, WN, SWIGLU, DUAL_A, NS, KG, ADD, false>, 0);
 }
 
 static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st) {
@@ -645,13 +537,12 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
     if (s.act_dtype == MOE_F32) return run_gemm_f32(g, swiglu, st);
     if (fast) {
         // Tile choice, measured on the 2048 / 5632 and 1024 / 2816 shapes with uniform and Zipf-skewed
-        // groups, from 16 to 2048 tokens.  Enough 256 x 256 tiles to fill 256 CUs: those, on 8 waves
-        // (64 x 128 per wave, two waves per SIMD), with 64-wide k-steps filled in halves where the
-        // kernel has one activation operand.  Below that the products are bound by streaming the
-        // weights, and what counts is enough workgroups to pull them with every CU: 128 x 128 x 64
-        // tiles (two workgroups per CU), 64-row tiles once the groups hold about 128 rows or
-        // fewer, and for a plain product with few tiles and a long K two k-groups per workgroup
-        // (on 64 x 64 tiles while the groups average 64 rows or less).
+        // groups, from 16 to 2048 tokens.  Enough 256-row tiles to fill 256 CUs: those (expert_gemm_pp.hip).
+        // Below that the products are bound by streaming the weights, and what counts is enough
+        // workgroups to pull them with every CU: 128 x 128 x 64 tiles (two workgroups per CU), 64-row
+        // tiles once the groups hold about 128 rows or fewer, and for a plain product with few tiles
+        // and a long K two k-groups per workgroup (on 64 x 64 tiles while the groups average 64 rows or
+        // less).
         const int n256 = (n_eff + (swiglu ? 127 : 255)) / (swiglu ? 128 : 256);
         const long long big_tiles = (long long)(g.P / 256 + (g.E + 1) / 2) * n256;
         // A plain product with a narrow output has too few 256 x 256 tiles for 256 CUs (the
@@ -665,7 +556,8 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
         // from 1024 tokens on.
         const int max_parts = g.k_parts;
         g.k_parts = 0;
-        if (!swiglu && !g.C1 && !g.add0 && g.nseg == 1 && max_parts >= 2 && g.P > 24 * g.E && big_tiles < 400 &&
+        const bool pp = gemm_pp_supported(g);
+        if (pp && !swiglu && !g.C1 && max_parts >= 2 && g.P > 24 * g.E && big_tiles < 400 &&
             g.seg[0].K % 32 == 0 && g.seg[0].K >= 32 * 64 && (long long)(g.P / 256 + g.E) * n256 * 4 >= 224) {
             const int steps = g.seg[0].K / 32;
             long long best = 0;
@@ -677,14 +569,12 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
                     g.k_parts = q;
                 }
             }
-            return launch_bf16_deep<256, 256, 64, 64, 128, false, false, 2, 1, false, true>(g, st);
+            return run_gemm_pp(g, false, st);
         }
-        if (swiglu && !dual && !g.add0 && g.P >= 128 * g.E && big_tiles >= 320)
-            return launch_bf16_deep<256, 256, 64, 64, 128, true, false, 2, 1, false, true>(g, st);
+        if (pp && swiglu && !dual && g.P >= 128 * g.E && big_tiles >= 320) return run_gemm_pp(g, true, st);
         if (g.P >= 384 * g.E && big_tiles >= 400) {  // enough 256 x 256 tiles to fill 256 CUs
+            if (pp) return run_gemm_pp(g, swiglu, st);
             if (swiglu && g.add0) return launch_bf16_deep<256, 256, 32, 64, 128, true, true, 2, 1, true>(g, st);
-            if (swiglu) return launch_bf16_deep<256, 256, 32, 64, 128, true, true>(g, st);  // two activation operands
-            return launch_bf16_deep<256, 256, 64, 64, 128, false, false, 2, 1, false, true>(g, st);
         }
         const bool small_groups = g.P <= 128 * g.E;
         if (swiglu && g.add0)

@@ -169,5 +169,8 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, i
 
 // fp32 problems (expert_gemm_f32.hip)
 int run_gemm_f32(GemmArgs& g, bool swiglu, hipStream_t st);
+// bf16 products on 256 x 256 tiles (expert_gemm_pp.hip)
+bool gemm_pp_supported(const GemmArgs& g);
+int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st);
 
 }  // namespace moe

@@ -256,6 +256,21 @@ def test_expert_ffn_dense_bf16(dev, oracle, d, F, offsets):
     _ffn_case(dev, oracle, cfg, np.array(offsets, np.int32), TOL["bf16"])
 
 
+@pytest.mark.parametrize("d,F,r,offsets", [
+    # gate/up products on 256-row tiles (two experts, 45 column tiles): one, two, three k-steps, tails of 8, 56
+    # and 8 columns, groups that end 1 and 255 rows into a tile
+    (64, 5760, 0, [0, 1537, 3072]), (72, 5760, 0, [0, 1537, 3072]), (120, 5760, 0, [0, 1700, 3100]),
+    (136, 5760, 0, [0, 1791, 3100]), (192, 5768, 0, [0, 1700, 3100]),
+    # plain products on them: 8192 and 8200 columns (a last column tile of 8), K of 72 and 200
+    (8192, 72, 0, [0, 1537, 3100]), (8200, 200, 0, [0, 1700, 3100]),
+    # two activation operands: K of one, one and a bit, and several k-steps, each walked twice
+    (128, 5760, 64, [0, 1537, 3072]), (128, 5760, 72, [0, 1700, 3100]), (128, 5760, 200, [0, 1791, 3100]),
+])
+def test_expert_ffn_on_256_row_tiles(dev, oracle, d, F, r, offsets):
+    cfg = _cfg(d=d, F=F, E=len(offsets) - 1, dtype="bf16", seed=430 + d + r, r=r, std=0.05)
+    _ffn_case(dev, oracle, cfg, np.array(offsets, np.int32), TOL["bf16"])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("base", [False, True])
 def test_expert_ffn_weight_decomposed(dev, oracle, dtype, base):
