@@ -40,10 +40,12 @@ static int validate_weights(const moe_shape& s, const moe_weights* w, bool need_
 struct Workspace {
     size_t topk_idx, topk_gate, offsets, perm, inv_perm, sort_scratch, y_perm, y_base, ffn_scratch,
         decode_scratch, stack_tmp, total;
+    SplitPlan plan;
 };
 
-static Workspace carve(const moe_shape& s) {
+static Workspace carve_for(const moe_shape& s, const SplitPlan& plan) {
     Workspace ws{};
+    ws.plan = plan;
     const size_t P = (size_t)s.n_tokens * s.top_k;
     size_t cur = 0;
     auto take = [&](size_t bytes) {
@@ -57,12 +59,32 @@ static Workspace carve(const moe_shape& s) {
     ws.perm = take(P * sizeof(int32_t));
     ws.inv_perm = take(P * sizeof(int32_t));
     ws.sort_scratch = take(permute_scratch_bytes((int)P, s.n_experts));
-    ws.y_perm = take(P * s.d_model * elt_size(s.act_dtype) * down_parts_capacity(s));  // room for partial outputs
     ws.y_base = take(token_base_supported(s) ? (size_t)s.n_tokens * s.d_model * elt_size(s.act_dtype) : 0);
     ws.ffn_scratch = take(ffn_scratch_bytes(s));
+    ws.y_perm = take(P * s.d_model * elt_size(s.act_dtype) * plan.down);  // its partial outputs
+    if (plan.rank_down > 1) {  // its parts start inside ffn_scratch and run through y_perm and beyond
+        const size_t end = ws.ffn_scratch + ffn_layout(s).tg + round_up(sizeof(float) * plan.rank_down * P * s.rank, 256);
+        if (end > cur) take(end - cur);
+    }
     ws.decode_scratch = take(decode_scratch_bytes(s));
     ws.stack_tmp = take((size_t)s.n_tokens * s.d_model * elt_size(s.act_dtype));
     ws.total = cur;
+    return ws;
+}
+
+// (Parts must not push a shape out of the allocation-free entry point's array: there the plan is cut
+// back until it fits.)
+static Workspace carve(const moe_shape& s) {
+    SplitPlan plan = split_plan(s);
+    Workspace ws = carve_for(s, plan);
+    if (ws.total <= (size_t)MOE_STATIC_WORKSPACE_BYTES ||
+        carve_for(s, SplitPlan{1, 1, 1}).total > (size_t)MOE_STATIC_WORKSPACE_BYTES)
+        return ws;
+    while (ws.total > (size_t)MOE_STATIC_WORKSPACE_BYTES) {
+        for (int* q : {&plan.down, &plan.rank_down, &plan.base_down})
+            if (*q > 1) --*q;
+        ws = carve_for(s, plan);
+    }
     return ws;
 }
 
@@ -88,17 +110,18 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
     const void* residual = (s.flags & MOE_FLAG_RESIDUAL) ? x : nullptr;
     if (token_base_supported(s)) {  // shared base: its products run once per token
         rc = launch_expert_ffn_token_base(s, w, x, perm, inv_perm, gate, offsets, wsp + ws.y_perm,
-                                          wsp + ws.y_base, wsp + ws.ffn_scratch, st, timer);
+                                          wsp + ws.y_base, wsp + ws.ffn_scratch, st, timer, ws.plan);
         if (rc != MOE_OK) return rc;
-        rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, wsp + ws.y_base);
+        const int parts = ws.plan.base_down;
+        const void* base = parts > 1 ? static_cast<void*>(ffn_scratch(s, wsp + ws.ffn_scratch).base_parts) : wsp + ws.y_base;
+        rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, base, 1, parts);
         stage_mark(timer, "combine");
         return rc;
     }
-    int y_parts = down_parts_capacity(s);  // the down projection may leave partial outputs for the combine to add
     rc = launch_expert_ffn(s, w, x, perm, s.top_k, offsets, wsp + ws.y_perm, wsp + ws.ffn_scratch, st,
-                           timer, &y_parts);
+                           timer, &ws.plan);
     if (rc != MOE_OK) return rc;
-    rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, nullptr, y_parts);
+    rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, nullptr, ws.plan.down);
     stage_mark(timer, "combine");
     return rc;
 }

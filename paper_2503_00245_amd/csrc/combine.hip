@@ -14,7 +14,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y_pe
                                                       const float* __restrict__ gate,
                                                       const T* __restrict__ residual,
                                                       const T* __restrict__ addend,
-                                                      T* __restrict__ y, int d, int k, int P, int parts) {
+                                                      T* __restrict__ y, int d, int k, int P, int parts,
+                                                      int addend_parts) {
     typedef Store<T> S;
     constexpr int VEC = S::VEC;
     typedef typename S::vec_t vec_t;
@@ -37,7 +38,17 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y_pe
 #pragma unroll
             for (int q = 0; q < VEC; ++q) acc[q] += S::get(r, q);
         }
-        if (addend) {
+        if (addend && addend_parts > 1) {
+            const float* a = reinterpret_cast<const float*>(addend) + (size_t)t * d + i;
+            for (int part = 0; part < addend_parts; ++part, a += (size_t)gridDim.x * d) {
+#pragma unroll
+                for (int q = 0; q < VEC; q += 4) {
+                    const f32x4 r = *reinterpret_cast<const f32x4*>(a + q);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[q + j] += r[j];
+                }
+            }
+        } else if (addend) {
             const vec_t r = *reinterpret_cast<const vec_t*>(addend + (size_t)t * d + i);
 #pragma unroll
             for (int q = 0; q < VEC; ++q) acc[q] += S::get(r, q);
@@ -51,18 +62,18 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y_pe
 
 int launch_combine(const moe_shape& s, const void* y_perm, const int32_t* inv_perm,
                    const float* topk_gate, const void* residual, void* y, hipStream_t st,
-                   const void* addend, int y_parts) {
+                   const void* addend, int y_parts, int addend_parts) {
     if (s.n_tokens == 0) return MOE_OK;
     const int P = s.n_tokens * s.top_k;
     dim3 grid(s.n_tokens), block(256);
     if (s.act_dtype == MOE_F32)
         hipLaunchKernelGGL(combine_kernel<float>, grid, block, 0, st, (const float*)y_perm, inv_perm,
                            topk_gate, (const float*)residual, (const float*)addend, (float*)y, s.d_model,
-                           s.top_k, P, y_parts);
+                           s.top_k, P, y_parts, addend_parts);
     else
         hipLaunchKernelGGL(combine_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)y_perm,
                            inv_perm, topk_gate, (const bf16_t*)residual, (const bf16_t*)addend, (bf16_t*)y,
-                           s.d_model, s.top_k, P, y_parts);
+                           s.d_model, s.top_k, P, y_parts, addend_parts);
     return launch_status();
 }
 

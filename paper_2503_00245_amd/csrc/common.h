@@ -132,24 +132,51 @@ int launch_permute(int P, int E, const int32_t* topk_idx, int32_t* offsets, int3
 int launch_gather_rows(const moe_shape& s, const int32_t* perm, const void* x, void* x_perm,
                        hipStream_t st);
 
-// addend: optional second per-token term [T, d] in the activation type (beside the residual).
+// addend: optional second per-token term [T, d] (beside the residual), in the activation type, or, with
+// addend_parts > 1, the sum of that many fp32 partial outputs [T, d], one after the other.
 // y_parts > 1: y_perm holds that many partial outputs [P, d], one after the other, to be added.
 int launch_combine(const moe_shape& s, const void* y_perm, const int32_t* inv_perm,
                    const float* topk_gate, const void* residual, void* y, hipStream_t st,
-                   const void* addend = nullptr, int y_parts = 1);
+                   const void* addend = nullptr, int y_parts = 1, int addend_parts = 1);
+
+// Products whose k-steps are cut into parts to fill the chip, by shape (bf16): the final down projection
+// (parts [P, d] in the activation type, added by the combine), the rank-down product of weight-decomposed
+// experts (fp32 parts [P, r], added by a kernel of its own) and the down projection of a shared base
+// (fp32 parts [T, d], added by the combine).  1: not cut.
+constexpr int kMaxParts = 4;
+struct SplitPlan {
+    int down, rank_down, base_down;
+};
+SplitPlan split_plan(const moe_shape& s);
+
+// Scratch of the expert FFN, in the activation type except for the parts.  The order is that of memory:
+// rank_parts ([rank_down][P, r] fp32) starts at tg, which is consumed by then, as are bg and bu, and runs on
+// into y_perm, not yet written, and what follows it; base_parts ([base_down][T, d] fp32) starts at h and
+// ends before y_perm.
+struct FfnScratch {
+    void *td, *z, *h, *tg, *tu, *bg, *bu;
+    float *rank_parts, *base_parts;
+};
+struct FfnLayout {  // byte offsets
+    size_t td, z, h, tg, tu, bg, bu, end;
+};
+FfnLayout ffn_layout(const moe_shape& s);
+inline FfnScratch ffn_scratch(const moe_shape& s, void* base) {
+    const FfnLayout l = ffn_layout(s);
+    char* b = static_cast<char*>(base);
+    return FfnScratch{b + l.td, b + l.z, b + l.h, b + l.tg, b + l.tu, b + l.bg, b + l.bu,
+                      reinterpret_cast<float*>(b + l.tg), reinterpret_cast<float*>(b + l.h)};
+}
 
 // Grouped expert FFN on P sorted rows.  a_row_map/a_row_div: optional gather of the input
 // rows (row of sorted slot s is x[a_row_map[s] / a_row_div]); NULL = x is already grouped.
-// y_parts: NULL = y_perm is one output [P, d].  Otherwise *y_parts says how many outputs [P, d]
-// y_perm has room for (down_parts_capacity) and receives how many partial outputs, to be added
-// by the consumer, were written: the last product may cut its k-steps into parts to fill the chip.
-constexpr int kMaxDownParts = 4;
-int down_parts_capacity(const moe_shape& s);
-size_t ffn_scratch_bytes(const moe_shape& s);
+// plan: NULL = nothing is cut, y_perm is one output [P, d].  Otherwise y_perm has room for plan->down outputs and
+// receives that many.
+inline size_t ffn_scratch_bytes(const moe_shape& s) { return ffn_layout(s).end; }
 int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
                       const int32_t* a_row_map, int a_row_div, const int32_t* offsets,
                       void* y_perm, void* scratch, hipStream_t st, StageTimer* timer = nullptr,
-                      int* y_parts = nullptr);
+                      const SplitPlan* plan = nullptr);
 
 // Shared-base experts M_e = M0 + L_e R_e (Sec. 2.2, Eq. 1 with a base shared by all experts), prefill,
 // with the token of every sorted slot known: the base products run once per token instead
@@ -159,7 +186,7 @@ bool token_base_supported(const moe_shape& s);
 int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const void* x,
                                  const int32_t* perm, const int32_t* inv_perm, const float* topk_gate,
                                  const int32_t* offsets, void* y_perm, void* y_base, void* scratch,
-                                 hipStream_t st, StageTimer* timer = nullptr);
+                                 hipStream_t st, StageTimer* timer, const SplitPlan& plan);
 
 // Single-token layer: experts chosen on the device from topk_idx, weights streamed once.
 size_t decode_scratch_bytes(const moe_shape& s);

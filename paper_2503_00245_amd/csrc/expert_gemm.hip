@@ -75,18 +75,11 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
     extern __shared__ __align__(16) char smem[];
 
     int e, row0, row_end, nt;
-    if (!find_tile(g.offsets, g.E, g.P, BM, g.n_tiles, e, row0, row_end, nt, g.n_inner, g.split_slots)) return;
+    if (!find_tile(g.offsets, g.E, g.P, BM, [&](int) { return g.n_tiles; }, e, row0, row_end, nt, g.n_inner, g.split_slots)) return;
     constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
     // two plain products in one launch: the upper half of the n-tiles belongs to (A1, B1, C1)
     const bool second = !SWIGLU && g.C1 != nullptr && nt >= g.n_tiles / 2;
     if (second) nt -= g.n_tiles / 2;
-    // k-parts ride on the n-tile index: n-tiles [q * n_base, (q + 1) * n_base) are part q
-    int part = 0;
-    if (!SWIGLU && KG == 1 && g.k_parts > 1) {
-        const int n_base = g.n_tiles / g.k_parts;
-        part = nt / n_base;
-        nt -= part * n_base;
-    }
     const int n0 = nt * BN_OUT;
 
     const int kg = threadIdx.x / NTHR;   // k-group of this wave
@@ -142,20 +135,15 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
         const bool dual = DUAL_A && sg.A1 != sg.A0;
         const bf16_t* B0 = static_cast<const bf16_t*>(second ? sg.B1 : sg.B0) + (size_t)e * sg.strideB;
         const bf16_t* B1 = SWIGLU ? static_cast<const bf16_t*>(sg.B1) + (size_t)e * sg.strideB : B0;
-        int nk = (K + BK * KG - 1) / (BK * KG);  // k-steps of this group (the same for every group)
-        int k_begin = kg * nk * BK;
-        if (!SWIGLU && KG == 1 && g.k_parts > 1) {  // this workgroup's share of the k-steps
-            const int s0 = nk * part / g.k_parts, s1 = nk * (part + 1) / g.k_parts;
-            k_begin = s0 * BK;
-            nk = s1 - s0;
-        }
+        const int nk = (K + BK * KG - 1) / (BK * KG);  // k-steps of this group (the same for every group)
+        const int k_begin = kg * nk * BK;
         const int k_last = (nk - 1) * BK;    // relative to k_begin
         // K tail (TAIL: K % BK != 0, a multiple of 8): in the last k-step a thread whose 16-byte
         // chunk lies at or beyond K reads an earlier chunk of its row instead (in bounds) and zeroes
         // its registers before they go to LDS.  Which threads those are never changes (a thread
         // always loads the same chunk of a tile), so the loop pays one vector min per step.
         const int tail_kt = (TAIL && K % BK != 0) ? nk - 1 : -1;               // wave-uniform
-        const bool tail_dead = TAIL && k_begin + k_last + ld_chunk * 8 >= K;    // per thread (never in a k-part before the last)
+        const bool tail_dead = TAIL && k_begin + k_last + ld_chunk * 8 >= K;    // per thread
         const int k_last_t = tail_dead ? max(k_last - BK, -(ld_chunk * 8)) : k_last;
 
         const bf16_t* pa[AI];
@@ -362,8 +350,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
     // ---- epilogue: accumulator element i of a 32x32 block sits at row (i/4)*8 + (lane/32)*4 + i%4,
     //      column lane%32 -------------------------------------------------------------------------
     // A block with no rows of the group is skipped.
-    bf16_t* const Ct = static_cast<bf16_t*>(second ? g.C1 : g.C) + (size_t)part * g.part_stride +
-                       (size_t)row0 * g.N + n0;  // wave-uniform
+    bf16_t* const Ct = static_cast<bf16_t*>(second ? g.C1 : g.C) + (size_t)row0 * g.N + n0;  // wave-uniform
     const unsigned ldc = (unsigned)g.N;
     if constexpr (KG == 1) {
         // Through LDS, so that the tile leaves in 16-byte stores (8 per wave and 32 x 64 block)
@@ -474,7 +461,7 @@ static int launch_bf16_deep(GemmArgs& g, hipStream_t st) {
     constexpr int NTHR = (BM / WM) * (BN / WN) * 64 * KG;
     static_assert(NTHR <= 1024, "workgroup size");
     g.m_tiles_max = g.P / BM + g.E;
-    g.n_tiles = (g.N + BN_OUT - 1) / BN_OUT * ((!SWIGLU && g.C1) ? 2 : 1) * (g.k_parts > 1 ? g.k_parts : 1);
+    g.n_tiles = (g.N + BN_OUT - 1) / BN_OUT * ((!SWIGLU && g.C1) ? 2 : 1);
     const int total = g.m_tiles_max * g.n_tiles;
     constexpr size_t lds = KG * 2 * ((size_t)BM * BK * 2 * (DUAL_A ? 2 : 1) + (size_t)BN * BK * 2);
     static_assert(lds <= 160 * 1024, "LDS stages exceed the CU's 160 KB");
@@ -517,11 +504,9 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
     for (int i = 0; g.add0 && i < g.nseg; ++i)
         if (g.seg[i].K % 8 != 0) return MOE_ERR_UNSUPPORTED;  // addends exist only in the deep kernels
     const int n_eff = g.N * (g.C1 ? 2 : 1);  // output columns of the launch
-    bool dual = false, fast = s.act_dtype != MOE_F32;
-    for (int i = 0; i < g.nseg; ++i) {
-        dual |= swiglu && g.seg[i].A1 != g.seg[i].A0;
-        fast &= g.seg[i].K >= 8 && g.seg[i].K % 8 == 0;  // the deep pipeline reads 16-byte chunks
-    }
+    bool fast = s.act_dtype != MOE_F32;
+    for (int i = 0; i < g.nseg; ++i) fast &= g.seg[i].K >= 8 && g.seg[i].K % 8 == 0;  // rows are read in 16-byte chunks
+    if (!fast || !gemm_pp_supported(g)) g.k_parts = 0;
     if (g.C1 && !fast) {  // only the deep kernel takes two products per launch: run them one by one
         GemmArgs second = g;
         second.C = g.C1;
@@ -535,65 +520,31 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
         return rc != MOE_OK ? rc : run_gemm(s, second, swiglu, st);
     }
     if (s.act_dtype == MOE_F32) return run_gemm_f32(g, swiglu, st);
+    if (fast && gemm_pp_supported(g)) return run_gemm_pp(g, swiglu, st);
     if (fast) {
-        // Tile choice, measured on the 2048 / 5632 and 1024 / 2816 shapes with uniform and Zipf-skewed
-        // groups, from 16 to 2048 tokens.  Enough 256-row tiles to fill 256 CUs: those (expert_gemm_pp.hip).
-        // Below that the products are bound by streaming the weights, and what counts is enough
-        // workgroups to pull them with every CU: 128 x 128 x 64 tiles (two workgroups per CU), 64-row
+        // What is left: products with per-token addends, with two segments, with K below 64 or operands of
+        // 4 GB and more.  256 x 256 tiles where they fill 256 CUs, else 128 x 128 (two workgroups per CU), 64-row
         // tiles once the groups hold about 128 rows or fewer, and for a plain product with few tiles
         // and a long K two k-groups per workgroup (on 64 x 64 tiles while the groups average 64 rows or
         // less).
         const int n256 = (n_eff + (swiglu ? 127 : 255)) / (swiglu ? 128 : 256);
         const long long big_tiles = (long long)(g.P / 256 + (g.E + 1) / 2) * n256;
-        // A plain product with a narrow output has too few 256 x 256 tiles for 256 CUs (the
-        // 2048-wide down projection of 4096 rows: 160), and smaller tiles move two to four times
-        // the operand bytes into the CUs.  If the consumer can add partial outputs, the k-steps
-        // of every tile are cut into 2-4 parts, each a workgroup's: the count that minimises
-        // rounds x (k-steps per part + about 12 k-steps of fixed cost per workgroup).  Worth it
-        // from about 24 rows per expert on, when four parts of every tile (one per expert at
-        // least) make some 220 workgroups: the 2048-wide down projection from 128 tokens on (45 us
-        // against 53, 79 against 111 at 1024 tokens, 116 against 142 at 2048), the 1024-wide one
-        // from 1024 tokens on.
-        const int max_parts = g.k_parts;
-        g.k_parts = 0;
-        const bool pp = gemm_pp_supported(g);
-        if (pp && !swiglu && !g.C1 && max_parts >= 2 && g.P > 24 * g.E && big_tiles < 400 &&
-            g.seg[0].K % 32 == 0 && g.seg[0].K >= 32 * 64 && (long long)(g.P / 256 + g.E) * n256 * 4 >= 224) {
-            const int steps = g.seg[0].K / 32;
-            long long best = 0;
-            for (int q = 2; q <= (max_parts < 4 ? max_parts : 4); ++q) {
-                const long long rounds = (big_tiles * q + 255) / 256;
-                const long long cost = rounds * (steps / q + 12);
-                if (g.k_parts == 0 || cost < best) {
-                    best = cost;
-                    g.k_parts = q;
-                }
-            }
-            return run_gemm_pp(g, false, st);
-        }
-        if (pp && swiglu && !dual && g.P >= 128 * g.E && big_tiles >= 320) return run_gemm_pp(g, true, st);
-        if (g.P >= 384 * g.E && big_tiles >= 400) {  // enough 256 x 256 tiles to fill 256 CUs
-            if (pp) return run_gemm_pp(g, swiglu, st);
+        if (g.P >= 384 * g.E && big_tiles >= 400) {
             if (swiglu && g.add0) return launch_bf16_deep<256, 256, 32, 64, 128, true, true, 2, 1, true>(g, st);
+            if (swiglu) return launch_bf16_deep<256, 256, 32, 64, 128, true, true>(g, st);
+            return launch_bf16_deep<256, 256, 32, 64, 128, false, false>(g, st);
         }
         const bool small_groups = g.P <= 128 * g.E;
         if (swiglu && g.add0)
             return small_groups ? launch_bf16_deep<64, 128, 64, 32, 64, true, true, 2, 1, true>(g, st)
                                 : launch_bf16_deep<128, 128, 64, 64, 64, true, true, 2, 1, true>(g, st);
-        if (swiglu) {
-            if (small_groups)
-                return dual ? launch_bf16_deep<64, 128, 64, 32, 64, true, true>(g, st)
-                            : launch_bf16_deep<64, 128, 64, 32, 64, true, false>(g, st);
-            return dual ? launch_bf16_deep<128, 128, 64, 64, 64, true, true>(g, st)
-                        : launch_bf16_deep<128, 128, 64, 64, 64, true, false>(g, st);
-        }
+        if (swiglu)
+            return small_groups ? launch_bf16_deep<64, 128, 64, 32, 64, true, true>(g, st)
+                                : launch_bf16_deep<128, 128, 64, 64, 64, true, true>(g, st);
         const long long tiles128 = (long long)(g.P / 128 + (g.E + 1) / 2) * ((n_eff + 127) / 128);
         bool k_pairs = true;
         for (int i = 0; i < g.nseg; ++i) k_pairs &= g.seg[i].K % 128 == 0;
         if (tiles128 < 160 && k_pairs) {
-            // (64 x 64: the 1024-wide down projection at 16 rows per expert 16.4 us against 20.1 with
-            // 64 x 128, at 32 rows 17.2 against 21.1, at 64 rows 18.1 against 21.8, at 128 rows 24.6
-            // against 22.3)
             if (g.P <= 64 * g.E) return launch_bf16_deep<64, 64, 64, 32, 32, false, false, 2, 2>(g, st);
             return launch_bf16_deep<64, 128, 64, 32, 64, false, false, 2, 2>(g, st);
         }
@@ -602,11 +553,23 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
     return MOE_ERR_UNSUPPORTED;  // bf16 rows that are not whole 16-byte chunks (the entry points reject them)
 }
 
-// Partial outputs the final down projection of this shape may leave (room the caller provides):
-// only tall groups are ever cut along K (see run_gemm).
-int down_parts_capacity(const moe_shape& s) {
+SplitPlan split_plan(const moe_shape& s) {
+    SplitPlan p{1, 1, 1};
+    if (s.act_dtype != MOE_BF16 || s.n_tokens == 0) return p;
     const long long P = (long long)s.n_tokens * s.top_k;
-    return (s.act_dtype == MOE_BF16 && P > 24ll * s.n_experts) ? kMaxDownParts : 1;
+    const bool base = s.flags & MOE_FLAG_SHARED_BASE, token_base = token_base_supported(s);
+    if (!base || token_base) {
+        const int K = s.rank > 0 ? s.rank : s.d_ff;
+        // (parts are rounded to the activation type: only where a tile's chain of k-steps is long)
+        p.down = token_base || K <= 1024 ? 1 : gemm_pp_split(P, s.n_experts, s.d_model, K, false, false);
+        if (s.rank > 0) p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, true, true);
+        if (token_base) {
+            p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff, true, false);
+            const FfnLayout l = ffn_layout(s);  // its parts lie in what h .. bu held
+            while (p.base_down > 1 && sizeof(float) * p.base_down * (size_t)s.n_tokens * s.d_model > l.end - l.h) --p.base_down;
+        }
+    }
+    return p;
 }
 
 // The per-token treatment of a shared base needs the deep bf16 kernels (every K a multiple of 8,
@@ -617,30 +580,42 @@ bool token_base_supported(const moe_shape& s) {
            s.d_model % 8 == 0 && s.d_ff % 8 == 0 && s.rank % 8 == 0;
 }
 
-// scratch: h [P,F], then (rank > 0) tg, tu, td [P,r]; with a per-token shared base also the base
-// gate and up products and the gate-mixed h [T,F] each; all in the activation type
-size_t ffn_scratch_bytes(const moe_shape& s) {
+FfnLayout ffn_layout(const moe_shape& s) {
     const size_t P = (size_t)s.n_tokens * s.top_k, es = elt_size(s.act_dtype);
-    size_t n = round_up(P * s.d_ff * es, 256) + 3 * round_up(P * s.rank * es, 256);
-    if (token_base_supported(s)) n += 3 * round_up((size_t)s.n_tokens * s.d_ff * es, 256);
-    return n;
+    const size_t rank = round_up(P * s.rank * es, 256), hidden = round_up(P * s.d_ff * es, 256);
+    const size_t base = token_base_supported(s) ? round_up((size_t)s.n_tokens * s.d_ff * es, 256) : 0;
+    FfnLayout l;
+    l.td = 0;
+    l.z = l.td + rank;
+    l.h = l.z + base;
+    l.tg = l.h + hidden;
+    l.tu = l.tg + rank;
+    l.bg = l.tu + rank;
+    l.bu = l.bg + base;
+    l.end = l.bu + base;
+    return l;
+}
+
+// td = h R_d^T, a product with few tiles and a long K: in parts that a kernel of its own adds, if the plan says so
+static int run_rank_down(const moe_shape& s, GemmArgs& g, const SplitPlan* plan, float* parts, hipStream_t st) {
+    if (plan && plan->rank_down > 1) {
+        g.k_parts = plan->rank_down;
+        g.parts_f32 = 1;
+        g.parts = parts;
+    }
+    const int rc = run_gemm(s, g, false, st);
+    if (rc != MOE_OK || g.k_parts <= 1) return rc;
+    return launch_sum_parts(parts, g.k_parts, (long long)g.P * g.N, g.C, st);
 }
 
 int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
                       const int32_t* a_row_map, int a_row_div, const int32_t* offsets,
-                      void* y_perm, void* scratch, hipStream_t st, StageTimer* timer, int* y_parts) {
+                      void* y_perm, void* scratch, hipStream_t st, StageTimer* timer, const SplitPlan* plan) {
     const int d = s.d_model, F = s.d_ff, r = s.rank, E = s.n_experts;
     const int P = s.n_tokens * s.top_k;
     if (P == 0) return MOE_OK;
-    const size_t es = elt_size(s.act_dtype);
-    char* sc = static_cast<char*>(scratch);
-    void* h = sc;
-    sc += round_up((size_t)P * F * es, 256);
-    void* tg = sc;
-    sc += round_up((size_t)P * r * es, 256);
-    void* tu = sc;
-    sc += round_up((size_t)P * r * es, 256);
-    void* td = sc;
+    const FfnScratch f = ffn_scratch(s, scratch);
+    void *h = f.h, *tg = f.tg, *tu = f.tu, *td = f.td;
     const bool base = (r == 0) || (s.flags & MOE_FLAG_SHARED_BASE);
     const int gather = a_row_map ? 1 : 0;
     int rc;
@@ -670,7 +645,7 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
         GemmArgs g = fresh();
         g.nseg = 1; g.N = r; g.C = td; g.n_inner = kHiddenOperandBlock;
         g.seg[0] = GemmSeg{h, h, w.rd, w.rd, (long long)r * F, F, 0};
-        if ((rc = run_gemm(s, g, false, st)) != MOE_OK) return rc;
+        if ((rc = run_rank_down(s, g, plan, f.rank_parts, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_rank_down");
     }
     {  // y_perm = M_down h   [P, d]
@@ -679,13 +654,11 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
         if (base) g.seg[ns++] = GemmSeg{h, h, w.w_down, w.w_down, r == 0 ? (long long)d * F : 0, F, 0};
         if (r > 0) g.seg[ns++] = GemmSeg{td, td, w.ld, w.ld, (long long)d * r, r, 0};
         g.nseg = ns; g.N = d; g.C = y_perm; g.n_inner = kHiddenOperandBlock;
-        // *y_parts in: how many outputs [P, d] the caller's y_perm has room for
-        if (y_parts) {
-            g.k_parts = *y_parts;
-            g.part_stride = (long long)P * d;
+        if (plan) {
+            g.k_parts = plan->down;
+            g.parts = y_perm;
         }
         if ((rc = run_gemm(s, g, false, st)) != MOE_OK) return rc;
-        if (y_parts) *y_parts = g.k_parts > 1 ? g.k_parts : 1;
         stage_mark(timer, "gemm_down");
     }
     return MOE_OK;
@@ -701,24 +674,12 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
 int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const void* x,
                                  const int32_t* perm, const int32_t* inv_perm, const float* topk_gate,
                                  const int32_t* offsets, void* y_perm, void* y_base, void* scratch,
-                                 hipStream_t st, StageTimer* timer) {
+                                 hipStream_t st, StageTimer* timer, const SplitPlan& plan) {
     const int d = s.d_model, F = s.d_ff, r = s.rank, E = s.n_experts, T = s.n_tokens;
     const int P = T * s.top_k;
     if (P == 0) return MOE_OK;
-    const size_t es = elt_size(s.act_dtype);
-    char* sc = static_cast<char*>(scratch);
-    auto take = [&](size_t bytes) {
-        void* at = sc;
-        sc += round_up(bytes, 256);
-        return at;
-    };
-    void* h = take((size_t)P * F * es);
-    void* tg = take((size_t)P * r * es);
-    void* tu = take((size_t)P * r * es);
-    void* td = take((size_t)P * r * es);
-    void* bg = take((size_t)T * F * es);
-    void* bu = take((size_t)T * F * es);
-    void* z = take((size_t)T * F * es);
+    const FfnScratch f = ffn_scratch(s, scratch);
+    void *h = f.h, *tg = f.tg, *tu = f.tu, *td = f.td, *bg = f.bg, *bu = f.bu, *z = f.z;
     int rc;
     auto grouped = [&]() {  // rows = pairs in expert order
         GemmArgs g{};
@@ -755,7 +716,7 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
         GemmArgs g = grouped();
         g.nseg = 1; g.N = r; g.C = td; g.n_inner = kHiddenOperandBlock;
         g.seg[0] = GemmSeg{h, h, w.rd, w.rd, (long long)r * F, F, 0};
-        if ((rc = run_gemm(s, g, false, st)) != MOE_OK) return rc;
+        if ((rc = run_rank_down(s, g, &plan, f.rank_parts, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_rank_down");
     }
     {  // z[t] = sum_j g_tj h[slot(t, j)]   [T, F]
@@ -768,6 +729,11 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
         GemmArgs g = per_token();
         g.nseg = 1; g.N = d; g.C = y_base; g.n_inner = kHiddenOperandBlock;
         g.seg[0] = GemmSeg{z, z, w.w_down, w.w_down, 0, F, 0};
+        if (plan.base_down > 1) {  // parts for the combine to add
+            g.k_parts = plan.base_down;
+            g.parts_f32 = 1;
+            g.parts = f.base_parts;
+        }
         if ((rc = run_gemm(s, g, false, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_base_down");
     }

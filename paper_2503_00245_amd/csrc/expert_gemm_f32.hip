@@ -22,7 +22,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N* KS * 64) void gemm_f32_kernel(con
     constexpr int WM = 16 * MI, WN = 16 * NI, BM = WM * WAVES_M, BN = WN * WAVES_N;
     constexpr int ND = SWIGLU ? 2 : 1;
     int e, row0, row_end, nt;
-    if (!find_tile(g.offsets, g.E, g.P, BM, g.n_tiles, e, row0, row_end, nt)) return;
+    if (!find_tile(g.offsets, g.E, g.P, BM, [&](int) { return g.n_tiles; }, e, row0, row_end, nt)) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ks = KS > 1 ? wave : 0;

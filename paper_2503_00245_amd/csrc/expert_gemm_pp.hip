@@ -25,7 +25,7 @@ namespace {
 
 #define INLINE __attribute__((always_inline))
 
-constexpr int BM = 256, BK = 64;
+constexpr int BK = 64;
 constexpr int kThreads = 512;
 
 typedef __attribute__((address_space(3))) char lds_char;
@@ -57,6 +57,14 @@ __device__ __forceinline__ int lane_again() {
     return 0;
 #endif
 }
+// integer divisions of wave-uniform values run on the vector unit; this brings their results back
+__device__ __forceinline__ int uniform(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_readfirstlane(v);
+#else
+    return v;
+#endif
+}
 __device__ __forceinline__ void phase_end() {
 #if defined(__HIP_DEVICE_COMPILE__)
     __builtin_amdgcn_sched_barrier(0);
@@ -69,33 +77,50 @@ __device__ __forceinline__ void phase_end() {
 // DUAL (SwiGLU with two activation operands, the rank products of a weight-decomposed expert): the tile
 // is BN gate rows for the first K / 64 steps, over A0, and the matching BN up rows for as many more, over A1,
 // into two sets of accumulators.
-template <int BN, int WAVES_M, bool SWIGLU, bool DUAL>
+// SA, SB: k-steps of A and of B in LDS.
+// F32: k-parts stored in fp32.
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_pp_kernel(const GemmArgs g) {
     static_assert(!DUAL || SWIGLU, "two activation operands only with the activation");
     constexpr int WAVES_N = 8 / WAVES_M;
     constexpr int MB = BM / 32 / WAVES_M;         // 32-row blocks of a wave
+    static_assert(MB >= 1 && SA >= 2 && SB >= 3, "a group reads one step while the other's is being fetched");
     constexpr int WN = BN / WAVES_N, NI = WN / 16;  // columns, 16-column blocks of a wave
     constexpr int NP = DUAL ? 2 : 1;
     constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
-    constexpr int SA = 2, SB = 3;                 // k-steps of A and of B in LDS
     constexpr int PA = BM / 32, PB = BN / 32;     // fill instructions per k-step of a wave of group 1 / 0
     constexpr bool SPLIT_B = SWIGLU && !DUAL;     // the B tile is half gate rows, half up rows
     constexpr int BN_OUT = SPLIT_B ? BN / 2 : BN;
     extern __shared__ __align__(16) char smem[];
 
     int e, row0, row_end, nt;
-    if (!find_tile(g.offsets, g.E, g.P, BM, g.n_tiles, e, row0, row_end, nt, g.n_inner, g.split_slots)) return;
-    // two plain products in one launch: the upper half of the n-tiles belongs to (A1, B1, C1)
-    const bool second = !SWIGLU && g.C1 != nullptr && nt >= g.n_tiles / 2;
-    if (second) nt -= g.n_tiles / 2;
-    // k-parts ride on the n-tile index: n-tiles [q * n_base, (q + 1) * n_base) are part q
-    int part = 0;
-    if (!SWIGLU && g.k_parts > 1) {
-        const int n_base = g.n_tiles / g.k_parts;
-        part = nt / n_base;
-        nt -= part * n_base;
-    }
-    const int n0 = nt * BN_OUT;
+    // Output columns of a tile and tiles across N.  fit_width: the m-tiles are known only here; where the
+    // launch is a few rounds of 256 workgroups, tiles are made narrower until the last round is full.
+    int width = BN_OUT, n_base = (g.N + BN_OUT - 1) / BN_OUT;
+    const int copies = SWIGLU ? 1 : g.C1 ? 2 : max(g.k_parts, 1);  // products, or k-parts, of the launch
+    bool fitted = false;
+    auto n_tiles_of = [&](int m_tiles) INLINE {
+        if (m_tiles > 0) {
+            const int m_all = m_tiles * copies;
+            const int rounds = (m_all * n_base + 255) / 256;
+            fitted = rounds <= g.fit_width;
+            if (fitted) {
+                const int n = uniform(256 * rounds / m_all);  // tiles across N that fit
+                width = uniform(max(8, ((g.N + n - 1) / n + 7) / 8 * 8));
+                n_base = uniform((g.N + width - 1) / width);
+            }
+        }
+        return n_base * copies;
+    };
+    if (!find_tile(g.offsets, g.E, g.P, BM, n_tiles_of, e, row0, row_end, nt, g.n_inner, g.split_slots)) return;
+    e = uniform(e), row0 = uniform(row0), row_end = uniform(row_end), nt = uniform(nt);
+    // the copies ride on the n-tile index: n-tiles [q n_base, (q + 1) n_base) are part q, or of two plain
+    // products in one launch (A0, B0, C) and (A1, B1, C1)
+    const int copy = !SWIGLU && copies > 1 ? uniform(nt / n_base) : 0;
+    nt -= copy * n_base;
+    const bool second = !SWIGLU && g.C1 != nullptr && copy == 1;
+    const int part = second ? 0 : copy;
+    const int n0 = nt * width;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = wave >> 2;                    // waves i and i + 4 share a SIMD
@@ -109,7 +134,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const char* B1 = SWIGLU ? static_cast<const char*>(sg.B1) + (size_t)e * sg.strideB * 2 : B0;
     int nk = (K + BK - 1) / BK, k_begin = 0;
     if (!SWIGLU && g.k_parts > 1) {
-        const int s0 = nk * part / g.k_parts, s1 = nk * (part + 1) / g.k_parts;
+        const int s0 = uniform(nk * part / g.k_parts), s1 = uniform(nk * (part + 1) / g.k_parts);
         k_begin = s0;
         nk = s1 - s0;
     }
@@ -143,7 +168,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
             const int j = f_row + 32 * p;
-            off[p] = __umul24(min(SPLIT_B ? n0 + j % (BN / 2) : n0 + j, g.N - 1), K * 2) + f_chunk * 16;
+            off[p] = __umul24(min(n0 + min(SPLIT_B ? j % (BN / 2) : j, width - 1), g.N - 1), K * 2) + f_chunk * 16;
         }
     }
     // what this wave fetches: instructions below PH from src_lo, the others from src_hi; in the second
@@ -161,12 +186,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         src += t * (BK * 2) - (t == nk - 1 ? tail_back : 0);
         dma16(lds0 + slot + p * 4096, src, off[p]);
     };
-    auto fill_all = [&](int v) INLINE {
-#pragma unroll
-        for (int p = 0; p < (PA > PB ? PA : PB); ++p)
-            if (p < (grp == 1 ? PA : PB)) fill(v, p);
-    };
-
     f32x4 acc[NP][2 * MB][NI];
 #pragma unroll
     for (int s = 0; s < NP; ++s)
@@ -177,33 +196,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     // A wave's 32-row blocks are wm, wm + WAVES_M, ... of the tile's eight: those that hold rows of the group
     // are spread over the waves.
-    const int live = min(MB, max(0, ((rows_here + 31) / 32 + WAVES_M - 1 - wm) / WAVES_M));
+    const int live = wn * (BN_OUT / WAVES_N) >= width ? -1 : min(MB, max(0, ((rows_here + 31) / 32 + WAVES_M - 1 - wm) / WAVES_M));
     // fragment reads: row lane % 16 of a 16-row block, chunk 4 ks + lane / 16
     const unsigned c16 = ((lane >> 4) ^ ((lane & 15) >> 1)) << 4;
     const unsigned ra = wm * 4096 + (lane & 15) * 128 + c16;
     const unsigned rb = SA * A_BYTES + wn * (SPLIT_B ? WN / 2 : WN) * 128 + (lane & 15) * 128 + c16;
 
     // Phases: group 0 reads step v's fragments in phase 2 v and multiplies in phase 2 v + 1, group 1 a phase
-    // later.  The LDS slots of step v are free from the end of phase 2 v + 1 on.  A of step v + 2 is fetched in
-    // phase 2 v + 2 by group 1, B of step v + 2 in phase 2 v + 1 by group 0; both have to have landed when
-    // phase 2 v + 4 begins.
-    fill_all(0);
-    if (nv > 1 && grp == 0) {
-        fill_all(1);
-        wait_vm<PB>();
-    } else {
-        wait_vm<0>();
-    }
-    phase_end();
-    if (grp == 1) {
-        if (nv > 1) fill_all(1);
-        phase_end();
-    }
-    // gc: the group, known at compile time where the groups' fills differ in number (a fill must not be
-    // conditional inside the loop)
+    // later.  The LDS slots of step v are free from the end of phase 2 v + 1 on: group 1, multiplying step v
+    // in phase 2 v + 2, fetches A of step v + SA; group 0, multiplying step v in phase 2 v + 1, fetches B of
+    // step v + SB - 1.  Step v + 1 has to have landed when phase 2 v + 2 begins.
+    // gc: the group, known at compile time: the groups' fills differ in number, and a fill must not be
+    // conditional inside the loop.
     auto k_loop = [&](auto ma, auto pass, auto gc) INLINE {
-        constexpr int MA = decltype(ma)::value;  // the wave's row blocks that hold rows of the group
-        constexpr int S = decltype(pass)::value, MR = MA > 0 ? MA : 1;
+        // the wave's row blocks that hold rows of the group; -1: none of its columns are the tile's
+        constexpr int MA = decltype(ma)::value > 0 ? decltype(ma)::value : 0;
+        constexpr bool NO_COLS = decltype(ma)::value < 0;
+        constexpr int S = decltype(pass)::value, GRP = decltype(gc)::value, MR = MA > 0 ? MA : 1;
+        // Fill instructions: all of B; of A those that can hold rows of the group (32 rows each: a wave of
+        // group 1 with MA live blocks belongs to a tile with at most this many).
+        constexpr int NF = GRP == 0 ? PB : NO_COLS || MA == MB ? PA : WAVES_M * (MA + 1) - 1 < PA ? WAVES_M * (MA + 1) - 1 : PA;
         bf16x8 fa[2][2 * MR], fb[2][NI];
         auto read = [&](int v) INLINE {
             const char* pa = smem + v % SA * A_BYTES;
@@ -233,7 +245,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         // the MFMAs of a step (the weights are the first operand: a lane's four results are neighbouring
         // columns of one row) with the fills of another between them
         auto multiply = [&](auto filling, int vf) INLINE {
-            constexpr int NF = decltype(gc)::value == 1 ? PA : PB;
             constexpr int NM = MA * 4 * NI, GAP = NM / NF > 0 ? NM / NF : 1;
             int p = 0;
 #pragma unroll
@@ -252,39 +263,55 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 for (; p < NF; ++p) fill(vf, p);
             }
         };
+        constexpr int AHEAD = GRP == 0 ? SB - 1 : SA;                     // the step fetched while v is multiplied
+        constexpr int FLY = (GRP == 0 ? SB - 2 : SA - 2) * NF;            // fills behind those of step v + 1
         int v = S * nk;
         const int v_end = v + nk;
-        for (; v < v_end && v + 2 < nv; ++v) {
+        if (S == 0) {  // the first steps
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q)
+                if (q < nv) {
+#pragma unroll
+                    for (int p = 0; p < NF; ++p) fill(q, p);
+                }
+            if (nv >= AHEAD) wait_vm<(AHEAD - 1) * NF>();  // step 0 has landed
+            else wait_vm<0>();
+            phase_end();
+            if (GRP == 1) phase_end();
+        }
+        for (; v < v_end && v + AHEAD < nv; ++v) {
             if (MA > 0) read(v);
             if (DUAL && S == 0 && v == v_end - 1 && tail_back > 0) clear_shared();
-            if (grp == 1) wait_vm<0>();  // A of step v + 1
+            if (GRP == 1) wait_vm<FLY>();  // A of step v + 1
             phase_end();
-            multiply(std::true_type{}, v + 2);
-            if (grp == 0) wait_vm<PB>();  // B of step v + 1
+            multiply(std::true_type{}, v + AHEAD);
+            if (GRP == 0) wait_vm<FLY>();  // B of step v + 1
             phase_end();
         }
         for (; v < v_end; ++v) {
             if (MA > 0) read(v);
             if (v == v_end - 1 && tail_back > 0) clear_shared();
-            if (grp == 1) wait_vm<0>();
+            if (GRP == 1) wait_vm<0>();
             phase_end();
             multiply(std::false_type{}, 0);
-            if (grp == 0) wait_vm<0>();
+            if (GRP == 0) wait_vm<0>();
             phase_end();
         }
     };
     auto loops = [&](auto ma) INLINE {
         typedef std::integral_constant<int, 0> c0;
         typedef std::integral_constant<int, 1> c1;
-        auto passes = [&](auto gc) INLINE {
-            k_loop(ma, c0{}, gc);
-            if constexpr (DUAL) k_loop(ma, c1{}, gc);
-        };
-        if (PA == PB || grp == 0) passes(c0{});
-        else passes(c1{});
+        if (grp == 0) {
+            k_loop(ma, c0{}, c0{});
+            if constexpr (DUAL) k_loop(ma, c1{}, c0{});
+        } else {
+            k_loop(ma, c0{}, c1{});
+            if constexpr (DUAL) k_loop(ma, c1{}, c1{});
+        }
     };
     if (live == MB) loops(std::integral_constant<int, MB>{});
     else if (live == 0) loops(std::integral_constant<int, 0>{});
+    else if (live < 0) loops(std::integral_constant<int, -1>{});
     else if (live == 1) loops(std::integral_constant<int, 1>{});
     else if (live == 2) loops(std::integral_constant<int, (MB > 2 ? 2 : 1)>{});
     else loops(std::integral_constant<int, (MB > 3 ? 3 : 1)>{});
@@ -293,9 +320,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // ---- epilogue: accumulator element i of a block is output column 4 (lane / 16) + i of row lane % 16.
     // Staged through LDS, 32 rows at a time in a region per wave, so that the tile leaves in 16-byte
     // stores.
-    bf16_t* const Ct = static_cast<bf16_t*>(second ? g.C1 : g.C) + (size_t)part * g.part_stride +
-                       (size_t)row0 * g.N + n0;
+    const size_t at0 = (size_t)part * ((size_t)g.P * g.N) + (size_t)row0 * g.N + n0;
     const unsigned ldc = (unsigned)g.N;
+    if constexpr (F32) {  // 16-byte stores straight from the accumulators
+        const int ln = lane_again();
+        float* const Ft = static_cast<float*>(g.parts) + at0;
+#pragma unroll
+        for (int mi = 0; mi < 2 * MB; ++mi) {
+            if (mi / 2 >= live) continue;
+            const int row = (WAVES_M * (mi / 2) + wm) * 32 + mi % 2 * 16 + (ln & 15);
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                const int col = wn * WN + ni * 16 + (ln >> 4) * 4;
+                if (row < rows_here && col < width && n0 + col < g.N)
+                    *reinterpret_cast<f32x4*>(Ft + (unsigned)row * ldc + (unsigned)col) = acc[0][mi][ni];
+            }
+        }
+        return;
+    }
+    bf16_t* const Ct = static_cast<bf16_t*>(second ? g.C1 : g.k_parts > 1 ? g.parts : g.C) + at0;
     constexpr int OC = BN_OUT / WAVES_N;             // output columns of a wave
     constexpr int PITCH = OC * 2 + 16;
     constexpr int LPR = OC / 8, RPI = 64 / LPR;      // lanes per staged row, rows per read instruction
@@ -325,22 +368,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int it = 0; it < 32 / RPI; ++it) {
             const int r = it * RPI + rd_row;
             const uint4 v = *reinterpret_cast<const uint4*>(region + r * PITCH + rd_chunk * 16);
-            if (rbk + r < rows_here && n0 + c0 < g.N)
+            if (rbk + r < rows_here && c0 < width && n0 + c0 < g.N)
                 *reinterpret_cast<uint4*>(Ct + (unsigned)(rbk + r) * ldc + (unsigned)c0) = v;
         }
     }
 }
 
-template <int BN, int WAVES_M, bool SWIGLU, bool DUAL>
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32 = false>
 int launch_pp(GemmArgs& g, hipStream_t st) {
     constexpr int BN_OUT = SWIGLU && !DUAL ? BN / 2 : BN;
     g.m_tiles_max = g.P / BM + g.E;
     g.n_tiles = (g.N + BN_OUT - 1) / BN_OUT * ((!SWIGLU && g.C1) ? 2 : 1) * (g.k_parts > 1 ? g.k_parts : 1);
-    constexpr size_t lds = (2 * BM + 3 * BN) * BK * 2;
+    int tiles = g.m_tiles_max * g.n_tiles;
+    if (tiles < 256 * g.fit_width) tiles = (tiles + 255) / 256 * 256;
+    constexpr size_t lds = (SA * BM + SB * BN) * BK * 2;
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
     g.split_slots = 32;  // one workgroup per CU
-    const int grid = ((g.m_tiles_max * g.n_tiles + 7) / 8 + g.split_slots / 2) * 8;
+    const int grid = ((tiles + 7) / 8 + g.split_slots / 2) * 8;
     static std::atomic<uint64_t> lds_allowed;
-    const auto kern = gemm_pp_kernel<BN, WAVES_M, SWIGLU, DUAL>;
+    const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, g);
     return launch_status();
@@ -348,23 +394,117 @@ int launch_pp(GemmArgs& g, hipStream_t st) {
 
 }  // namespace
 
-// One segment, no addends, operands whose rows are reached by 32-bit byte offsets (rows below 2^24 and
-// row lengths below 2^23 by the 24-bit multiply), at least one whole k-step.
+// Operands whose rows are reached by 32-bit byte offsets (a 24-bit multiply), at least one whole k-step
+static bool rows_supported(long long a_rows, long long N, long long K) {
+    return K >= BK && K < (1 << 23) && N < (1 << 24) && a_rows * K * 2 < (1ll << 32) && N * K * 2 < (1ll << 32);
+}
+
+// One segment, no addends
 bool gemm_pp_supported(const GemmArgs& g) {
     const GemmSeg& sg = g.seg[0];
-    if (g.nseg != 1 || g.add0 || sg.K < BK || sg.K >= (1 << 23) || g.N >= (1 << 24)) return false;
     const long long a_rows = sg.gather ? (g.P - 1) / (g.row_div > 0 ? g.row_div : 1) + 1 : g.P;
-    return a_rows * sg.K * 2 < (1ll << 32) && (long long)g.N * sg.K * 2 < (1ll << 32);
+    return g.nseg == 1 && !g.add0 && rows_supported(a_rows, g.N, sg.K);
+}
+
+// ---- rows per tile and parts of K, by a model of the launch in us ------------------------------------------
+// Rounds of 256 workgroups (one per CU), each with 6 us of fixed cost and its k-steps at what bounds them:
+// fills at 46 GB/s per CU, the matrix cores, or the latency from a fill of A to its use, which is shorter the
+// more k-steps of A LDS holds (two of 256 rows, four of 128 or 64).  Few rows per group and narrow outputs
+// want small tiles, large groups tall ones; cutting K pays where the tiles are too few for the CUs (the
+// 2048-wide down projection of 4096 rows has 160 of 256 x 256) or the chain of k-steps of a tile is long.
+// Parts are written and read at 6 TB/s; a launch of its own that adds them costs 5 us.
+// Checked against (us): gate/up of the 2048 / 5632 layer at 4 to 32 rows per expert 80 / 79 with 128 / 64 rows
+// against 82 with 256, at 64 rows 88 with 128 against 96; of the 1024 / 2816 layer at 128 rows 28 with
+// 256 against 38 with 128; down projection at 2048 tokens 99 in three parts, 115 in one.
+struct PpChoice {
+    int bm, parts;
+};
+static PpChoice choose(long long P, int E, int N, int K, int copies, bool swiglu, bool dual, int parts_max, bool f32,
+                       bool sum_launch) {
+    const double groups = P < E ? (double)P : (double)E, n = P / groups;
+    const int bn = swiglu && !dual ? 2 : 1;  // B rows per output column of a tile
+    const int cols = dual || bn == 2 ? 128 : 256, nb = (N + cols - 1) / cols;
+    const int steps = (K + BK - 1) / BK * (dual ? 2 : 1);
+    PpChoice best{256, 1};
+    double best_cost = 0;
+    for (int bm = 256; bm >= 64; bm /= 2) {
+        const double rows = n < bm ? n : bm, mt = groups * (n / bm + 0.5 > 1.0 ? n / bm + 0.5 : 1.0) * 1.05;
+        const double latency = bm == 256 ? 0.75 : bm == 128 ? 0.55 : 0.45;
+        for (int q = 1; q <= parts_max && (q == 1 || steps / q >= 4); ++q) {
+            const double m_all = mt * q * copies, rounds = (double)(long long)((m_all * nb + 255) / 256);
+            const double fit = (double)(long long)(256 * rounds / m_all), width = rounds > 2 || fit < nb ? (nb > 1 ? cols : N) : N / fit;
+            double step = (rows + width * bn) * (BK * 2) / 46e3;
+            const double mfma = rows * width * bn * (1.05 / 65536);
+            if (step < mfma) step = mfma;
+            if (step < latency) step = latency;
+            double cost = rounds * (steps * step / q + 6);
+            if (q > 1) cost += (double)(f32 ? q * 8 : (q - 1) * 4) * P * N / 6e6 + (sum_launch ? 5 : 0);
+            if ((bm == 256 && q == 1) || cost < best_cost) {
+                best_cost = cost;
+                best = PpChoice{bm, q};
+            }
+        }
+    }
+    return best;
+}
+
+int gemm_pp_split(long long P, int E, int N, int K, bool parts_f32, bool sum_launch) {
+    if (P <= 0 || !rows_supported(P, N, K)) return 1;
+    return choose(P, E, N, K, 1, false, false, kMaxParts, parts_f32, sum_launch).parts;
 }
 
 int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
-    if (!swiglu) return launch_pp<256, 2, false, false>(g, st);
-    if (g.seg[0].A0 != g.seg[0].A1) return launch_pp<128, 4, true, true>(g, st);
+    const bool dual = swiglu && g.seg[0].A0 != g.seg[0].A1;
+    const int parts = g.k_parts > 1 ? g.k_parts : 1;  // decided by the caller
+    const int bm = choose(g.P, g.E, g.N, g.seg[0].K / parts, parts * (!swiglu && g.C1 ? 2 : 1), swiglu, dual, 1, false, false).bm;
+    g.fit_width = 2;
+    if (!swiglu) {
+        const bool f32 = g.k_parts > 1 && g.parts_f32;
+        if (bm == 64)
+            return f32 ? launch_pp<64, 256, 2, 4, 4, false, false, true>(g, st) : launch_pp<64, 256, 2, 4, 4, false, false>(g, st);
+        if (bm == 128)
+            return f32 ? launch_pp<128, 256, 2, 4, 3, false, false, true>(g, st) : launch_pp<128, 256, 2, 4, 3, false, false>(g, st);
+        return f32 ? launch_pp<256, 256, 2, 2, 3, false, false, true>(g, st) : launch_pp<256, 256, 2, 2, 3, false, false>(g, st);
+    }
+    if (dual) {
+        if (bm == 64) return launch_pp<64, 128, 2, 8, 6, true, true>(g, st);
+        if (bm == 128) return launch_pp<128, 128, 4, 4, 5, true, true>(g, st);
+        return launch_pp<256, 128, 4, 2, 3, true, true>(g, st);
+    }
+    if (bm == 64) return launch_pp<64, 256, 2, 4, 4, true, false>(g, st);
+    if (bm == 128) return launch_pp<128, 256, 2, 4, 3, true, false>(g, st);
     // blocks of four n-tiles with the expert's m-tiles inside: the 32 tiles in flight on an XCD then share
     // eight A and four B tiles in its L2 instead of all m-tiles of one or two n-tiles (gate/up at 16384
     // tokens 1180 us from 1210; no difference at 2048, where an expert has up to seven m-tiles)
     g.n_inner = 4;
-    return launch_pp<256, 2, true, false>(g, st);
+    return launch_pp<256, 256, 2, 2, 3, true, false>(g, st);
+}
+
+// out = sum of the parts, in part order, rounded once; n a multiple of 8
+__global__ __launch_bounds__(256) void sum_parts_kernel(const f32x4* __restrict__ parts, int q, long long n8,
+                                                        bf16x8* __restrict__ out) {
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n8; i += (long long)gridDim.x * 256) {
+        f32x4 lo = parts[2 * i], hi = parts[2 * i + 1];
+        for (int p = 1; p < q; ++p) {
+            lo += parts[(p * n8 + i) * 2];
+            hi += parts[(p * n8 + i) * 2 + 1];
+        }
+        bf16x8 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o[j] = (bf16_t)lo[j];
+            o[4 + j] = (bf16_t)hi[j];
+        }
+        out[i] = o;
+    }
+}
+
+int launch_sum_parts(const float* parts, int q, long long n, void* out, hipStream_t st) {
+    const long long n8 = n / 8;
+    const int grid = (int)((n8 + 255) / 256 < 2048 ? (n8 + 255) / 256 : 2048);
+    hipLaunchKernelGGL(sum_parts_kernel, dim3(grid), dim3(256), 0, st, reinterpret_cast<const f32x4*>(parts), q, n8,
+                       static_cast<bf16x8*>(out));
+    return launch_status();
 }
 
 }  // namespace moe

@@ -53,12 +53,16 @@ struct GemmArgs {
     int n_inner;        // tile order inside an expert: blocks of this many n-tiles (0 or 1: n-tile outer, m-tiles inner)
     int split_slots;    // workgroups one XCD runs at a time; > 0: the tiles of its last, partial round are cut
                         // into upper and lower halves when both halves still fit in one round (set by the launcher)
-    // PLAIN, one segment: the k-steps of every tile are cut into k_parts consecutive ranges, each
-    // computed by a workgroup of its own and stored to its own output [P, N] (part q at
-    // C + q * part_stride elements); whoever consumes C adds the parts.  In: the most parts the
-    // caller's output can take (0 or 1: none).  Out (set by run_gemm): the parts used.
+    // PLAIN, one segment, expert_gemm_pp.hip: the k-steps of every tile are cut into k_parts consecutive
+    // ranges, each computed by a workgroup of its own and stored to its own output [P, N] (part q at
+    // parts + q * P * N elements, fp32 if parts_f32, else the activation type), to be added by the
+    // consumer.  0 or 1: one output, in C.
     int k_parts;
-    long long part_stride;
+    int parts_f32;
+    void* parts;
+    // expert_gemm_pp.hip: where the launch is at most this many rounds of 256 workgroups, the tiles are made
+    // narrower until they fill the last round (decided on the device, where the m-tiles are known)
+    int fit_width;
 };
 
 // Group e's row range; offsets == NULL means one group holding all P rows (a plain product).
@@ -82,8 +86,11 @@ __device__ __forceinline__ int group_end(const int32_t* __restrict__ offsets, in
 // cut into an upper and a lower half (BM / 2 rows) handled by two workgroups: the halves still
 // fit in one round and each is shorter than a whole tile (it fills half the activation rows
 // and multiplies half the blocks).
+//
+// n_tiles_of(m): the launch's n-tiles when all groups together have m m-tiles.
+template <typename NTiles>
 __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, int E, int P, int BM,
-                                          int n_tiles, int& e_out, int& row0, int& row_end,
+                                          NTiles n_tiles_of, int& e_out, int& row0, int& row_end,
                                           int& nt_out, int n_inner = 0, int split_slots = 0) {
 #if defined(__HIP_DEVICE_COMPILE__)
     // Lane e of every wave fetches group e's bounds with ONE vector load (E <= 64); the sums below
@@ -98,13 +105,13 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, i
     const int cnt = (hi - lo + BM - 1) / BM;  // m-tiles of group `lane` (0 beyond E)
     int total = 0;
     for (int e = 0; e < E; ++e) total += __builtin_amdgcn_readlane(cnt, e);
-    total *= n_tiles;
 #else
     int total = 0;
     for (int e = 0; e < E; ++e)
         total += (group_end(offsets, e, P) - group_begin(offsets, e) + BM - 1) / BM;
-    total *= n_tiles;
 #endif
+    const int n_tiles = n_tiles_of(total);
+    total *= n_tiles;
     const int per_xcd = (total + 7) / 8;
     const int slot = blockIdx.x >> 3;
     const int first = (blockIdx.x & 7) * per_xcd;               // this XCD's first tile
@@ -169,8 +176,11 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, i
 
 // fp32 problems (expert_gemm_f32.hip)
 int run_gemm_f32(GemmArgs& g, bool swiglu, hipStream_t st);
-// bf16 products on 256 x 256 tiles (expert_gemm_pp.hip)
+// bf16 products, fills straight into LDS (expert_gemm_pp.hip)
 bool gemm_pp_supported(const GemmArgs& g);
 int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st);
+// Parts into which it is worth cutting the k-steps of a plain product of P rows in E groups (k_parts above)
+int gemm_pp_split(long long P, int E, int N, int K, bool parts_f32, bool sum_launch);
+int launch_sum_parts(const float* parts, int q, long long n, void* out, hipStream_t st);
 
 }  // namespace moe

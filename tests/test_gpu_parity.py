@@ -271,6 +271,27 @@ def test_expert_ffn_on_256_row_tiles(dev, oracle, d, F, r, offsets):
     _ffn_case(dev, oracle, cfg, np.array(offsets, np.int32), TOL["bf16"])
 
 
+@pytest.mark.parametrize("d,F,r,offsets", [
+    # few rows per group (64- and 128-row tiles): single rows, 63 / 64 / 65 rows, an empty expert; K of one k-step,
+    # fewer steps than LDS holds, a tail; widths fitted to 256 workgroups down to 8 columns
+    (64, 264, 0, [0, 1, 1, 3, 4]), (136, 520, 0, [0, 63, 127, 192, 193]), (320, 1000, 0, [0, 64, 64, 129, 200]),
+    (200, 72, 0, [0, 96, 97, 160, 250]), (1024, 2816, 0, [0, 5, 9, 70, 71]),
+    (256, 448, 64, [0, 1, 65, 65, 70]), (200, 328, 104, [0, 40, 104, 169, 240]), (640, 640, 72, [0, 128, 256, 385, 400]),
+])
+def test_expert_ffn_on_small_tiles(dev, oracle, d, F, r, offsets):
+    cfg = _cfg(d=d, F=F, E=len(offsets) - 1, dtype="bf16", seed=460 + d + r, r=r, std=0.05)
+    _ffn_case(dev, oracle, cfg, np.array(offsets, np.int32), TOL["bf16"])
+
+
+@pytest.mark.parametrize("d,F,r,base,T", [
+    (256, 2120, 104, False, 5), (256, 2120, 104, False, 130), (512, 4104, 256, False, 300),  # rank-down in fp32 parts
+    (256, 2120, 64, True, 3), (264, 4104, 40, True, 90), (512, 2816, 64, True, 700),         # and the base's down
+])
+def test_forward_products_cut_along_k(dev, oracle, d, F, r, base, T):
+    cfg = _cfg(d=d, F=F, E=8, dtype="bf16", seed=480 + d + T, r=r, base=base, std=0.05)
+    _forward_case(dev, oracle, cfg, T)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("base", [False, True])
 def test_expert_ffn_weight_decomposed(dev, oracle, dtype, base):
