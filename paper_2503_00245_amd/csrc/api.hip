@@ -103,14 +103,17 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
     int32_t* offsets = reinterpret_cast<int32_t*>(wsp + ws.offsets);
     int32_t* perm = reinterpret_cast<int32_t*>(wsp + ws.perm);
     int32_t* inv_perm = reinterpret_cast<int32_t*>(wsp + ws.inv_perm);
-    rc = launch_permute(P, s.n_experts, idx, offsets, perm, inv_perm, wsp + ws.sort_scratch, st);
-    if (rc != MOE_OK) return rc;
-    stage_mark(timer, "permute");
+    const int32_t* keys = ffn_takes_keys(s, idx) ? idx : nullptr;  // the first product sorts the pairs itself
+    if (!keys) {
+        rc = launch_permute(P, s.n_experts, idx, offsets, perm, inv_perm, wsp + ws.sort_scratch, st);
+        if (rc != MOE_OK) return rc;
+        stage_mark(timer, "permute");
+    }
     // the gather of token rows into expert order is fused into the first GEMM's A loads
     const void* residual = (s.flags & MOE_FLAG_RESIDUAL) ? x : nullptr;
     if (token_base_supported(s)) {  // shared base: its products run once per token
         rc = launch_expert_ffn_token_base(s, w, x, perm, inv_perm, gate, offsets, wsp + ws.y_perm,
-                                          wsp + ws.y_base, wsp + ws.ffn_scratch, st, timer, ws.plan);
+                                          wsp + ws.y_base, wsp + ws.ffn_scratch, st, timer, ws.plan, keys);
         if (rc != MOE_OK) return rc;
         const int parts = ws.plan.base_down;
         const void* base = parts > 1 ? static_cast<void*>(ffn_scratch(s, wsp + ws.ffn_scratch).base_parts) : wsp + ws.y_base;
@@ -119,7 +122,7 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
         return rc;
     }
     rc = launch_expert_ffn(s, w, x, perm, s.top_k, offsets, wsp + ws.y_perm, wsp + ws.ffn_scratch, st,
-                           timer, &ws.plan);
+                           timer, &ws.plan, keys, inv_perm);
     if (rc != MOE_OK) return rc;
     rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, nullptr, ws.plan.down);
     stage_mark(timer, "combine");
@@ -209,7 +212,7 @@ int moe_expert_ffn(const moe_shape* shape, const moe_weights* weights, const voi
         return MOE_ERR_INVALID;
     if (!workspace || !aligned16(workspace)) return MOE_ERR_WORKSPACE;
     if (workspace_bytes < ffn_scratch_bytes(*shape)) return MOE_ERR_WORKSPACE;
-    return launch_expert_ffn(*shape, *weights, x_perm, nullptr, 1, expert_offsets, y_perm, workspace,
+    return launch_expert_ffn(*shape, *weights, x_perm, nullptr, 1, const_cast<int32_t*>(expert_offsets), y_perm, workspace,
                              as_stream(stream));
 }
 

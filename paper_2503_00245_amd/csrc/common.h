@@ -170,13 +170,16 @@ inline FfnScratch ffn_scratch(const moe_shape& s, void* base) {
 
 // Grouped expert FFN on P sorted rows.  a_row_map/a_row_div: optional gather of the input
 // rows (row of sorted slot s is x[a_row_map[s] / a_row_div]); NULL = x is already grouped.
+// keys: NULL, or the pairs' experts [P]: then a_row_map, offsets and inv_perm are not read but written, by the
+// first product (only where ffn_takes_keys).
+bool ffn_takes_keys(const moe_shape& s, const int32_t* keys);
 // plan: NULL = nothing is cut, y_perm is one output [P, d].  Otherwise y_perm has room for plan->down outputs and
 // receives that many.
 inline size_t ffn_scratch_bytes(const moe_shape& s) { return ffn_layout(s).end; }
 int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
-                      const int32_t* a_row_map, int a_row_div, const int32_t* offsets,
+                      int32_t* a_row_map, int a_row_div, int32_t* offsets,
                       void* y_perm, void* scratch, hipStream_t st, StageTimer* timer = nullptr,
-                      const SplitPlan* plan = nullptr);
+                      const SplitPlan* plan = nullptr, const int32_t* keys = nullptr, int32_t* inv_perm = nullptr);
 
 // Shared-base experts M_e = M0 + L_e R_e (Sec. 2.2, Eq. 1 with a base shared by all experts), prefill,
 // with the token of every sorted slot known: the base products run once per token instead
@@ -184,9 +187,9 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
 // projection and y_base [T, d] the shared part, to be added in the combine.
 bool token_base_supported(const moe_shape& s);
 int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const void* x,
-                                 const int32_t* perm, const int32_t* inv_perm, const float* topk_gate,
-                                 const int32_t* offsets, void* y_perm, void* y_base, void* scratch,
-                                 hipStream_t st, StageTimer* timer, const SplitPlan& plan);
+                                 int32_t* perm, int32_t* inv_perm, const float* topk_gate,
+                                 int32_t* offsets, void* y_perm, void* y_base, void* scratch,
+                                 hipStream_t st, StageTimer* timer, const SplitPlan& plan, const int32_t* keys);
 
 // Single-token layer: experts chosen on the device from topk_idx, weights streamed once.
 size_t decode_scratch_bytes(const moe_shape& s);

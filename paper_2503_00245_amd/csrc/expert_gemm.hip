@@ -21,13 +21,6 @@
 
 namespace moe {
 
-// Products whose activation operand is the F-wide hidden tensor (down, rank-down): that operand is
-// as large as an expert's weights, so tiles are ordered in blocks of this many n-tiles with the
-// expert's m-tiles inside a block -- the workgroups in flight on an XCD then share a few A tiles
-// and a few B tiles instead of one B tile and every A tile (measured on the phone shape with
-// Zipf loads: down product 145 us with blocks of 8 or 16, 148 with 4, 153-157 with n-tile outer).
-constexpr int kHiddenOperandBlock = 8;
-
 // ============================================================================= bf16 MFMA
 // LDS tile rows hold BK bf16 (BK/8 chunks of 16 bytes).  The chunk index is XOR-ed with a
 // function of the row chosen so that 16 consecutive rows read at one chunk index (an MFMA
@@ -36,6 +29,28 @@ template <int BK>
 __device__ __forceinline__ int lds_off(int row, int chunk) {
     constexpr int CPR = BK / 8;  // chunks per row
     return row * (BK * 2) + ((chunk ^ ((row / (16 / CPR)) % CPR)) << 4);
+}
+
+// LDS of a workgroup of the kernel below
+template <int BM, int BN, int BK, bool DUAL_A, int KG>
+constexpr size_t lds_bytes() {
+    return KG * 2 * ((size_t)BM * BK * 2 * (DUAL_A ? 2 : 1) + (size_t)BN * BK * 2);
+}
+// Workgroups of a kernel that one XCD (32 CUs) holds at a time, for the tail split: bounded by LDS and, for
+// these tiles (64 or more accumulator registers per lane), by two waves per SIMD; halves of BM / 2
+// rows only make sense when each wave's rows fall in one half.
+// (For kernels that run one or two workgroups per CU.  It needs a full round before the thin
+// one: with less than one round of tiles in all, halves -- which each still stream the whole
+// weight tile -- measured slower, down product at 512 tokens 94 us instead of 73.  Cutting the
+// halves once more along the columns, one wave of four left with work, was slower too:
+// down product at 2048 tokens 152 us against 144.)
+template <int BM, int BN, int BK, int WM, int WN, bool DUAL_A, int KG>
+constexpr int split_slots() {
+    constexpr int NTHR = (BM / WM) * (BN / WN) * 64 * KG;
+    constexpr int kWavesPerSimd = (WM * WN / 64 >= 64) ? 2 : 3;  // by accumulator registers per lane
+    constexpr int kByLds = (int)((160 * 1024) / lds_bytes<BM, BN, BK, DUAL_A, KG>()), kByWaves = kWavesPerSimd * 256 / NTHR;
+    constexpr int kPerCU = kByLds < kByWaves ? kByLds : kByWaves;
+    return (BM / 2) % WM == 0 && KG == 1 && kPerCU <= 2 ? 32 * kPerCU : 0;
 }
 
 // ============================================================================= bf16 MFMA, deep pipeline
@@ -75,7 +90,12 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
     extern __shared__ __align__(16) char smem[];
 
     int e, row0, row_end, nt;
-    if (!find_tile(g.offsets, g.E, g.P, BM, [&](int) { return g.n_tiles; }, e, row0, row_end, nt, g.n_inner, g.split_slots)) return;
+    constexpr int SPLIT = split_slots<BM, BN, BK, WM, WN, DUAL_A, KG>();
+    auto n_tiles_of = [&](int) { return g.n_tiles; };
+    int lo, hi;
+    group_bounds(g.offsets, g.E, g.P, lo, hi);
+    if (!(g.hidden_a ? find_tile<kHiddenOperandBlock, SPLIT>(lo, hi, g.E, BM, n_tiles_of, e, row0, row_end, nt)
+                    : find_tile<1, SPLIT>(lo, hi, g.E, BM, n_tiles_of, e, row0, row_end, nt))) return;
     constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
     // two plain products in one launch: the upper half of the n-tiles belongs to (A1, B1, C1)
     const bool second = !SWIGLU && g.C1 != nullptr && nt >= g.n_tiles / 2;
@@ -103,7 +123,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int row = min(row0 + wm * WM + mi * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3), row_end - 1);
-                tok[i] = min(max(g.row_map[row], 0), g.P - 1) / g.row_div;
+                tok[i] = quick_div(min(max(g.row_map[row], 0), g.P - 1), g.row_div);
             }
 #pragma unroll
             for (int ni = 0; ni < NT / 2; ++ni) {
@@ -157,7 +177,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KG) void gemm_bf16_dee
 #pragma unroll
             for (int i = 0; i < AI; ++i) arow[i] = g.row_map[arow[i]];
 #pragma unroll
-            for (int i = 0; i < AI; ++i) arow[i] = min(max(arow[i], 0), g.P - 1) / g.row_div;
+            for (int i = 0; i < AI; ++i) arow[i] = quick_div(min(max(arow[i], 0), g.P - 1), g.row_div);
         }
 #pragma unroll
         for (int i = 0; i < AI; ++i) {
@@ -463,21 +483,9 @@ static int launch_bf16_deep(GemmArgs& g, hipStream_t st) {
     g.m_tiles_max = g.P / BM + g.E;
     g.n_tiles = (g.N + BN_OUT - 1) / BN_OUT * ((!SWIGLU && g.C1) ? 2 : 1);
     const int total = g.m_tiles_max * g.n_tiles;
-    constexpr size_t lds = KG * 2 * ((size_t)BM * BK * 2 * (DUAL_A ? 2 : 1) + (size_t)BN * BK * 2);
+    constexpr size_t lds = lds_bytes<BM, BN, BK, DUAL_A, KG>();
     static_assert(lds <= 160 * 1024, "LDS stages exceed the CU's 160 KB");
-    // workgroups of this kernel that one XCD (32 CUs) holds at a time: bounded by LDS and, for
-    // these tiles (64 or more accumulator registers per lane), by two waves per SIMD; halves of
-    // BM / 2 rows only make sense when each wave's rows fall in one half
-    constexpr int kWavesPerSimd = (WM * WN / 64 >= 64) ? 2 : 3;  // by accumulator registers per lane
-    constexpr int kByLds = (int)((160 * 1024) / lds), kByWaves = kWavesPerSimd * 256 / NTHR;
-    constexpr int kPerCU = kByLds < kByWaves ? kByLds : kByWaves;
-    // (for kernels that run one or two workgroups per CU.  It needs a full round before the thin
-    // one: with less than one round of tiles in all, halves -- which each still stream the whole
-    // weight tile -- measured slower, down product at 512 tokens 94 us instead of 73.  Cutting the
-    // halves once more along the columns, one wave of four left with work, was slower too:
-    // down product at 2048 tokens 152 us against 144.)
-    g.split_slots = (BM / 2) % WM == 0 && KG == 1 && kPerCU <= 2 ? 32 * kPerCU : 0;
-    const int grid = ((total + 7) / 8 + g.split_slots / 2) * 8;
+    const int grid = ((total + 7) / 8 + split_slots<BM, BN, BK, WM, WN, DUAL_A, KG>() / 2) * 8;
     bool tail = false;
     for (int i = 0; i < g.nseg; ++i) {
         const int K = g.seg[i].K;  // rows are read in 16-byte chunks; a K tail only without k-groups
@@ -596,6 +604,17 @@ FfnLayout ffn_layout(const moe_shape& s) {
     return l;
 }
 
+// Whether the layer's first product can sort the pairs by expert itself (GemmArgs::keys)
+bool ffn_takes_keys(const moe_shape& s, const int32_t* keys) {
+    const int P = s.n_tokens * s.top_k, E = s.n_experts;
+    if (!aligned16(keys)) return false;
+    if (s.act_dtype == MOE_F32) return dispatch_in_product(P, kF32DispatchThreads);
+    GemmArgs g{};
+    g.P = P; g.E = E; g.row_div = s.top_k; g.N = s.rank > 0 ? s.rank : s.d_ff; g.nseg = 1;
+    g.seg[0].K = s.d_model; g.seg[0].gather = 1;
+    return dispatch_in_product(P, kPpThreads) && gemm_pp_supported(g);
+}
+
 // td = h R_d^T, a product with few tiles and a long K: in parts that a kernel of its own adds, if the plan says so
 static int run_rank_down(const moe_shape& s, GemmArgs& g, const SplitPlan* plan, float* parts, hipStream_t st) {
     if (plan && plan->rank_down > 1) {
@@ -609,8 +628,9 @@ static int run_rank_down(const moe_shape& s, GemmArgs& g, const SplitPlan* plan,
 }
 
 int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
-                      const int32_t* a_row_map, int a_row_div, const int32_t* offsets,
-                      void* y_perm, void* scratch, hipStream_t st, StageTimer* timer, const SplitPlan* plan) {
+                      int32_t* a_row_map, int a_row_div, int32_t* offsets,
+                      void* y_perm, void* scratch, hipStream_t st, StageTimer* timer, const SplitPlan* plan,
+                      const int32_t* keys, int32_t* inv_perm) {
     const int d = s.d_model, F = s.d_ff, r = s.rank, E = s.n_experts;
     const int P = s.n_tokens * s.top_k;
     if (P == 0) return MOE_OK;
@@ -629,6 +649,7 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
         GemmArgs g = fresh();
         g.nseg = 1; g.N = r; g.C = tg; g.C1 = tu;
         g.seg[0] = GemmSeg{x, x, w.rg, w.ru, (long long)r * d, d, gather};
+        g.keys = keys; g.inv_perm = inv_perm;
         if ((rc = run_gemm(s, g, false, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_rank_gate_up");
     }
@@ -638,12 +659,13 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
         if (base) g.seg[ns++] = GemmSeg{x, x, w.w_gate, w.w_up, r == 0 ? (long long)F * d : 0, d, gather};
         if (r > 0) g.seg[ns++] = GemmSeg{tg, tu, w.lg, w.lu, (long long)F * r, r, 0};
         g.nseg = ns; g.N = F; g.C = h;
+        if (r == 0) g.keys = keys, g.inv_perm = inv_perm;
         if ((rc = run_gemm(s, g, true, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_gate_up_swiglu");
     }
     if (r > 0) {  // td = h R_d^T   [P, r]
         GemmArgs g = fresh();
-        g.nseg = 1; g.N = r; g.C = td; g.n_inner = kHiddenOperandBlock;
+        g.nseg = 1; g.N = r; g.C = td; g.hidden_a = 1;
         g.seg[0] = GemmSeg{h, h, w.rd, w.rd, (long long)r * F, F, 0};
         if ((rc = run_rank_down(s, g, plan, f.rank_parts, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_rank_down");
@@ -653,7 +675,7 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
         int ns = 0;
         if (base) g.seg[ns++] = GemmSeg{h, h, w.w_down, w.w_down, r == 0 ? (long long)d * F : 0, F, 0};
         if (r > 0) g.seg[ns++] = GemmSeg{td, td, w.ld, w.ld, (long long)d * r, r, 0};
-        g.nseg = ns; g.N = d; g.C = y_perm; g.n_inner = kHiddenOperandBlock;
+        g.nseg = ns; g.N = d; g.C = y_perm; g.hidden_a = 1;
         if (plan) {
             g.k_parts = plan->down;
             g.parts = y_perm;
@@ -672,9 +694,9 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
 //             the combine, which also adds the shared part.
 // This halves the base work at k = 2 (6 T d F flops instead of 6 P d F).
 int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const void* x,
-                                 const int32_t* perm, const int32_t* inv_perm, const float* topk_gate,
-                                 const int32_t* offsets, void* y_perm, void* y_base, void* scratch,
-                                 hipStream_t st, StageTimer* timer, const SplitPlan& plan) {
+                                 int32_t* perm, int32_t* inv_perm, const float* topk_gate,
+                                 int32_t* offsets, void* y_perm, void* y_base, void* scratch,
+                                 hipStream_t st, StageTimer* timer, const SplitPlan& plan, const int32_t* keys) {
     const int d = s.d_model, F = s.d_ff, r = s.rank, E = s.n_experts, T = s.n_tokens;
     const int P = T * s.top_k;
     if (P == 0) return MOE_OK;
@@ -695,6 +717,7 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
         GemmArgs g = grouped();
         g.nseg = 1; g.N = r; g.C = tg; g.C1 = tu;
         g.seg[0] = GemmSeg{x, x, w.rg, w.ru, (long long)r * d, d, 1};
+        g.keys = keys; g.inv_perm = inv_perm;
         if ((rc = run_gemm(s, g, false, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_rank_gate_up");
     }
@@ -714,7 +737,7 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
     }
     {  // td = h R_d^T   [P, r]
         GemmArgs g = grouped();
-        g.nseg = 1; g.N = r; g.C = td; g.n_inner = kHiddenOperandBlock;
+        g.nseg = 1; g.N = r; g.C = td; g.hidden_a = 1;
         g.seg[0] = GemmSeg{h, h, w.rd, w.rd, (long long)r * F, F, 0};
         if ((rc = run_rank_down(s, g, &plan, f.rank_parts, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemm_rank_down");
@@ -727,7 +750,7 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
     }
     {  // y_base = z M0_down^T   [T, d]
         GemmArgs g = per_token();
-        g.nseg = 1; g.N = d; g.C = y_base; g.n_inner = kHiddenOperandBlock;
+        g.nseg = 1; g.N = d; g.C = y_base; g.hidden_a = 1;
         g.seg[0] = GemmSeg{z, z, w.w_down, w.w_down, 0, F, 0};
         if (plan.base_down > 1) {  // parts for the combine to add
             g.k_parts = plan.base_down;

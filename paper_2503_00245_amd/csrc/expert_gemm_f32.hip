@@ -22,7 +22,34 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N* KS * 64) void gemm_f32_kernel(con
     constexpr int WM = 16 * MI, WN = 16 * NI, BM = WM * WAVES_M, BN = WN * WAVES_N;
     constexpr int ND = SWIGLU ? 2 : 1;
     int e, row0, row_end, nt;
-    if (!find_tile(g.offsets, g.E, g.P, BM, [&](int) { return g.n_tiles; }, e, row0, row_end, nt)) return;
+    constexpr int NTHR = WAVES_M * WAVES_N * KS * 64;
+    static_assert(NTHR == kF32DispatchThreads, "dispatch by whole workgroups");
+    __shared__ int s_count[kKeyChunks * NTHR / kWave][kMaxExperts];
+    __shared__ int s_pair[BM];
+    int lo, hi;
+    PairKeys<NTHR> keys;
+    if (g.keys) {
+        keys.load(g.keys, g.P);
+        keys.bounds(g.E, s_count, lo, hi);
+        if (blockIdx.x == 0 && threadIdx.x < 64) {
+            if ((int)threadIdx.x < g.E) g.offsets[threadIdx.x] = lo;
+            if ((int)threadIdx.x == g.E - 1) g.offsets[g.E] = hi;
+        }
+    } else {
+        group_bounds(g.offsets, g.E, g.P, lo, hi);
+    }
+    if (!find_tile(lo, hi, g.E, BM, [&](int) { return g.n_tiles; }, e, row0, row_end, nt)) return;
+    if (g.keys) {
+        const int rows = min(row_end - row0, BM);
+        keys.rows(e, row0 - MOE_READLANE(lo, e), rows, s_count, s_pair);
+        if (nt == 0) {  // one column tile of each row tile writes the sorted order
+            for (int r = threadIdx.x; r < rows; r += NTHR) {
+                const int p = s_pair[r];
+                g.row_map[row0 + r] = p;
+                g.inv_perm[p] = row0 + r;
+            }
+        }
+    }
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ks = KS > 1 ? wave : 0;
@@ -50,7 +77,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N* KS * 64) void gemm_f32_kernel(con
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             int row = min(m0 + 16 * i + r, row_end - 1);
-            if (sg.gather) row = min(max(g.row_map[row], 0), g.P - 1) / g.row_div;
+            if (sg.gather) row = quick_div(min(max(g.keys ? s_pair[row - row0] : g.row_map[row], 0), g.P - 1), g.row_div);
             pa[0][i] = static_cast<const float*>(sg.A0) + (size_t)row * K;
             if (SWIGLU) pa[ND - 1][i] = static_cast<const float*>(sg.A1) + (size_t)row * K;
         }

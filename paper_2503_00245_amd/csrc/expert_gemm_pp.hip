@@ -26,7 +26,8 @@ namespace {
 #define INLINE __attribute__((always_inline))
 
 constexpr int BK = 64;
-constexpr int kThreads = 512;
+constexpr int kThreads = kPpThreads;
+constexpr int kSplitSlots = 32;  // one workgroup per CU
 
 typedef __attribute__((address_space(3))) char lds_char;
 
@@ -55,14 +56,6 @@ __device__ __forceinline__ int lane_again() {
     return v;
 #else
     return 0;
-#endif
-}
-// integer divisions of wave-uniform values run on the vector unit; this brings their results back
-__device__ __forceinline__ int uniform(int v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return __builtin_amdgcn_readfirstlane(v);
-#else
-    return v;
 #endif
 }
 __device__ __forceinline__ void phase_end() {
@@ -102,21 +95,44 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     auto n_tiles_of = [&](int m_tiles) INLINE {
         if (m_tiles > 0) {
             const int m_all = m_tiles * copies;
-            const int rounds = (m_all * n_base + 255) / 256;
+            const int rounds = (int)((unsigned)(m_all * n_base + 255) / 256u);
             fitted = rounds <= g.fit_width;
             if (fitted) {
-                const int n = uniform(256 * rounds / m_all);  // tiles across N that fit
-                width = uniform(max(8, ((g.N + n - 1) / n + 7) / 8 * 8));
-                n_base = uniform((g.N + width - 1) / width);
+                const int n = uniform_div(256 * rounds, m_all);  // tiles across N that fit
+                width = max(8, (uniform_div(g.N + n - 1, n) + 7) / 8 * 8);
+                n_base = uniform_div(g.N + width - 1, width);
             }
         }
         return n_base * copies;
     };
-    if (!find_tile(g.offsets, g.E, g.P, BM, n_tiles_of, e, row0, row_end, nt, g.n_inner, g.split_slots)) return;
-    e = uniform(e), row0 = uniform(row0), row_end = uniform(row_end), nt = uniform(nt);
+    // (in the last slot of B, which is first filled after the first phase)
+    int (*const s_count)[kMaxExperts] = reinterpret_cast<int (*)[kMaxExperts]>(smem + SA * A_BYTES + (SB - 1) * B_BYTES);
+    int* const s_pair = &s_count[kKeyChunks * kThreads / kWave][0];
+    static_assert((kKeyChunks * kThreads / kWave * kMaxExperts + BM) * 4 <= B_BYTES, "dispatch scratch");
+    int lo, hi;
+    PairKeys<kThreads> keys;
+    if (g.keys) {
+        keys.load(g.keys, g.P);
+        keys.bounds(g.E, s_count, lo, hi);
+        const int lane_ = threadIdx.x & 63;
+        if (blockIdx.x == 0 && threadIdx.x < 64) {
+            if (lane_ < g.E) g.offsets[lane_] = lo;
+            if (lane_ == g.E - 1) g.offsets[g.E] = hi;
+        }
+    } else {
+        group_bounds(g.offsets, g.E, g.P, lo, hi);
+    }
+    // SwiGLU products of 256-row tiles: blocks of four n-tiles with the expert's m-tiles inside, so that the 32
+    // tiles in flight on an XCD share eight A and four B tiles in its L2 instead of all m-tiles of one
+    // or two n-tiles (gate/up at 16384 tokens 1180 us from 1210; no difference at 2048, where an expert
+    // has up to seven m-tiles)
+    constexpr int INNER = SWIGLU && !DUAL && BM == 256 ? 4 : 1;
+    if (!(g.hidden_a ? find_tile<kHiddenOperandBlock, kSplitSlots>(lo, hi, g.E, BM, n_tiles_of, e, row0, row_end, nt)
+                     : find_tile<INNER, kSplitSlots>(lo, hi, g.E, BM, n_tiles_of, e, row0, row_end, nt)))
+        return;
     // the copies ride on the n-tile index: n-tiles [q n_base, (q + 1) n_base) are part q, or of two plain
     // products in one launch (A0, B0, C) and (A1, B1, C1)
-    const int copy = !SWIGLU && copies > 1 ? uniform(nt / n_base) : 0;
+    const int copy = !SWIGLU && copies > 1 ? uniform_div(nt, n_base) : 0;
     nt -= copy * n_base;
     const bool second = !SWIGLU && g.C1 != nullptr && copy == 1;
     const int part = second ? 0 : copy;
@@ -134,7 +150,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const char* B1 = SWIGLU ? static_cast<const char*>(sg.B1) + (size_t)e * sg.strideB * 2 : B0;
     int nk = (K + BK - 1) / BK, k_begin = 0;
     if (!SWIGLU && g.k_parts > 1) {
-        const int s0 = uniform(nk * part / g.k_parts), s1 = uniform(nk * (part + 1) / g.k_parts);
+        const int s0 = uniform_div(nk * part, g.k_parts), s1 = uniform_div(nk * (part + 1), g.k_parts);
         k_begin = s0;
         nk = s1 - s0;
     }
@@ -152,19 +168,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int f_chunk = (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4));
     const int rows_here = row_end - row0;
     unsigned off[PA > PB ? PA : PB];
-    if (grp == 1) {
-        int arow[PA];
-#pragma unroll
-        for (int p = 0; p < PA; ++p) arow[p] = min(row0 + f_row + 32 * p, row_end - 1);
-        if (sg.gather) {
-#pragma unroll
-            for (int p = 0; p < PA; ++p) arow[p] = g.row_map[arow[p]];
-#pragma unroll
-            for (int p = 0; p < PA; ++p) arow[p] = min(max(arow[p], 0), g.P - 1) / g.row_div;
-        }
-#pragma unroll
-        for (int p = 0; p < PA; ++p) off[p] = __umul24(arow[p], K * 2) + f_chunk * 16;
-    } else {
+    if (grp == 0) {
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
             const int j = f_row + 32 * p;
@@ -186,6 +190,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         src += t * (BK * 2) - (t == nk - 1 ? tail_back : 0);
         dma16(lds0 + slot + p * 4096, src, off[p]);
     };
+    if (grp == 0) {  // the first steps of B, before the rows of A are known
+#pragma unroll
+        for (int q = 0; q < SB - 1; ++q)
+            if (q < nv) {
+#pragma unroll
+                for (int p = 0; p < PB; ++p) fill(q, p);
+            }
+    }
+    if (g.keys) {
+        const int rows = min(rows_here, BM);
+        keys.rows(e, row0 - MOE_READLANE(lo, e), rows, s_count, s_pair);
+        if (nt == 0 && copy == 0) {  // one column tile of each row tile writes the sorted order
+            for (int r = threadIdx.x; r < rows; r += kThreads) {
+                const int p = s_pair[r];
+                g.row_map[row0 + r] = p;
+                g.inv_perm[p] = row0 + r;
+            }
+        }
+    }
+    if (grp == 1) {
+        int arow[PA];
+#pragma unroll
+        for (int p = 0; p < PA; ++p) arow[p] = min(row0 + f_row + 32 * p, row_end - 1);
+        if (sg.gather) {
+#pragma unroll
+            for (int p = 0; p < PA; ++p) arow[p] = g.keys ? s_pair[arow[p] - row0] : g.row_map[arow[p]];
+#pragma unroll
+            for (int p = 0; p < PA; ++p) arow[p] = quick_div(min(max(arow[p], 0), g.P - 1), g.row_div);
+        }
+#pragma unroll
+        for (int p = 0; p < PA; ++p) off[p] = __umul24(arow[p], K * 2) + f_chunk * 16;
+    }
     f32x4 acc[NP][2 * MB][NI];
 #pragma unroll
     for (int s = 0; s < NP; ++s)
@@ -267,9 +303,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         constexpr int FLY = (GRP == 0 ? SB - 2 : SA - 2) * NF;            // fills behind those of step v + 1
         int v = S * nk;
         const int v_end = v + nk;
-        if (S == 0) {  // the first steps
+        if (S == 0) {  // the first steps (of B: above)
 #pragma unroll
-            for (int q = 0; q < AHEAD; ++q)
+            for (int q = 0; q < (GRP == 1 ? AHEAD : 0); ++q)
                 if (q < nv) {
 #pragma unroll
                     for (int p = 0; p < NF; ++p) fill(q, p);
@@ -383,8 +419,7 @@ int launch_pp(GemmArgs& g, hipStream_t st) {
     if (tiles < 256 * g.fit_width) tiles = (tiles + 255) / 256 * 256;
     constexpr size_t lds = (SA * BM + SB * BN) * BK * 2;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
-    g.split_slots = 32;  // one workgroup per CU
-    const int grid = ((tiles + 7) / 8 + g.split_slots / 2) * 8;
+    const int grid = ((tiles + 7) / 8 + kSplitSlots / 2) * 8;
     static std::atomic<uint64_t> lds_allowed;
     const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
@@ -473,10 +508,6 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     }
     if (bm == 64) return launch_pp<64, 256, 2, 4, 4, true, false>(g, st);
     if (bm == 128) return launch_pp<128, 256, 2, 4, 3, true, false>(g, st);
-    // blocks of four n-tiles with the expert's m-tiles inside: the 32 tiles in flight on an XCD then share
-    // eight A and four B tiles in its L2 instead of all m-tiles of one or two n-tiles (gate/up at 16384
-    // tokens 1180 us from 1210; no difference at 2048, where an expert has up to seven m-tiles)
-    g.n_inner = 4;
     return launch_pp<256, 256, 2, 2, 3, true, false>(g, st);
 }
 

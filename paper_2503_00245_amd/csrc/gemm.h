@@ -39,8 +39,8 @@ struct GemmArgs {
     void* C;            // [P, N]
     void* C1;           // PLAIN only, deep kernel: second product (A1 . B1) of the same shape, or NULL
     int N;
-    const int32_t* offsets;  // [E+1]
-    const int32_t* row_map;  // [P] or NULL
+    int32_t* offsets;        // [E+1]
+    int32_t* row_map;        // [P] or NULL
     int row_div;
     int E;
     int P;
@@ -50,9 +50,7 @@ struct GemmArgs {
     // (the token of sorted slot s is row_map[s] / row_div), [*, N] in the activation type, or NULL
     const void* add0;
     const void* add1;
-    int n_inner;        // tile order inside an expert: blocks of this many n-tiles (0 or 1: n-tile outer, m-tiles inner)
-    int split_slots;    // workgroups one XCD runs at a time; > 0: the tiles of its last, partial round are cut
-                        // into upper and lower halves when both halves still fit in one round (set by the launcher)
+    int hidden_a;       // the activation operand is the F-wide hidden tensor (tile order: kHiddenOperandBlock)
     // PLAIN, one segment, expert_gemm_pp.hip: the k-steps of every tile are cut into k_parts consecutive
     // ranges, each computed by a workgroup of its own and stored to its own output [P, N] (part q at
     // parts + q * P * N elements, fp32 if parts_f32, else the activation type), to be added by the
@@ -63,7 +61,19 @@ struct GemmArgs {
     // expert_gemm_pp.hip: where the launch is at most this many rounds of 256 workgroups, the tiles are made
     // narrower until they fill the last round (decided on the device, where the m-tiles are known)
     int fit_width;
+    // Dispatch in the first product of a layer (expert_gemm_pp.hip, expert_gemm_f32.hip): keys [P] are the pairs'
+    // experts; offsets, row_map and inv_perm [P] are then outputs of the launch, as moe_permute states
+    // them, and its own rows are found from the keys.  NULL: offsets and row_map are inputs.
+    const int32_t* keys;
+    int32_t* inv_perm;
 };
+
+// Products whose activation operand is the F-wide hidden tensor (down, rank-down): that operand is
+// as large as an expert's weights, so tiles are ordered in blocks of this many n-tiles with the
+// expert's m-tiles inside a block -- the workgroups in flight on an XCD then share a few A tiles
+// and a few B tiles instead of one B tile and every A tile (measured on the phone shape with
+// Zipf loads: down product 145 us with blocks of 8 or 16, 148 with 4, 153-157 with n-tile outer).
+constexpr int kHiddenOperandBlock = 8;
 
 // Group e's row range; offsets == NULL means one group holding all P rows (a plain product).
 __device__ __forceinline__ int group_begin(const int32_t* __restrict__ offsets, int e) {
@@ -88,28 +98,57 @@ __device__ __forceinline__ int group_end(const int32_t* __restrict__ offsets, in
 // and multiplies half the blocks).
 //
 // n_tiles_of(m): the launch's n-tiles when all groups together have m m-tiles.
-template <typename NTiles>
-__device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, int E, int P, int BM,
-                                          NTiles n_tiles_of, int& e_out, int& row0, int& row_end,
-                                          int& nt_out, int n_inner = 0, int split_slots = 0) {
+// lo, hi: in lane e of every wave, group e's bounds (group_bounds; 0, 0 in lanes from E on).  The sums run on
+// scalar registers through readlane.  (A loop of dependent scalar loads over the offsets cost
+// 2.6-3.3 us per tile here, a twentieth of a 256 x 256 tile's duration.)
 #if defined(__HIP_DEVICE_COMPILE__)
-    // Lane e of every wave fetches group e's bounds with ONE vector load (E <= 64); the sums below
-    // then run on scalar registers through readlane.  (A loop of dependent scalar loads over the
-    // offsets cost 2.6-3.3 us per tile here, a twentieth of a tile's whole duration.)
+#define MOE_READLANE(v, l) __builtin_amdgcn_readlane(v, l)
+#else
+#define MOE_READLANE(v, l) (v)
+#endif
+__device__ __forceinline__ void group_bounds(const int32_t* __restrict__ offsets, int E, int P, int& lo, int& hi) {
     const int lane = threadIdx.x & (kWave - 1);
-    int lo = 0, hi = 0;
+    lo = hi = 0;
     if (lane < E) {
         lo = group_begin(offsets, lane);
         hi = group_end(offsets, lane, P);
     }
-    const int cnt = (hi - lo + BM - 1) / BM;  // m-tiles of group `lane` (0 beyond E)
-    int total = 0;
-    for (int e = 0; e < E; ++e) total += __builtin_amdgcn_readlane(cnt, e);
+}
+// a / b for a >= 0, b > 0: the estimate is off by a few hundred at most (2^31 times the rounding of the three
+// float steps), the second one, of the remainder, by one.  The compiler's integer division is forty
+// dependent instructions, and a workgroup makes half a dozen before its first load.
+__device__ __forceinline__ int quick_div(int a, int b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float inv = __builtin_amdgcn_rcpf((float)b);
+    int q = (int)((float)a * inv);
+    int r = (int)((unsigned)a - (unsigned)q * (unsigned)b);
+    const int more = (int)((float)r * inv);
+    q += more, r -= more * b;
+    q += (r >= b ? 1 : 0) - (r < 0 ? 1 : 0);
+    return q;
 #else
-    int total = 0;
-    for (int e = 0; e < E; ++e)
-        total += (group_end(offsets, e, P) - group_begin(offsets, e) + BM - 1) / BM;
+    return a / b;
 #endif
+}
+__device__ __forceinline__ int uniform_div(int a, int b) {  // wave-uniform a, b
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_readfirstlane(quick_div(a, b));
+#else
+    return a / b;
+#endif
+}
+// N_INNER (a power of two): tile order inside an expert in blocks of this many n-tiles, block outer, the
+// expert's m-tiles in the middle, the block's n-tiles inner (1: n-tile outer, m-tiles inner).
+template <int N_INNER = 1, int SPLIT_SLOTS = 0, typename NTiles>
+__device__ __forceinline__ bool find_tile(int lo, int hi, int E, int BM, NTiles n_tiles_of, int& e_out,
+                                          int& row0, int& row_end, int& nt_out) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int cnt = (hi - lo + BM - 1) / BM;  // m-tiles of group `lane` (0 beyond E)
+    int total = 0, before = 0;                // m-tiles of all groups, of those below `lane`
+    for (int e = 0; e < E; ++e) {
+        before = lane == e ? total : before;
+        total += MOE_READLANE(cnt, e);
+    }
     const int n_tiles = n_tiles_of(total);
     total *= n_tiles;
     const int per_xcd = (total + 7) / 8;
@@ -117,10 +156,11 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, i
     const int first = (blockIdx.x & 7) * per_xcd;               // this XCD's first tile
     const int mine = max(0, min(per_xcd, total - first));       // and how many it has
     int local_tile = slot, half = -1;
-    if (split_slots > 0) {
-        const int whole = (mine / split_slots) * split_slots;   // tiles in full rounds
+    if (SPLIT_SLOTS > 0) {
+        constexpr int SLOTS = SPLIT_SLOTS > 0 ? SPLIT_SLOTS : 1;
+        const int whole = (mine / SLOTS) * SLOTS;               // tiles in full rounds
         const int rem = mine - whole;
-        if (whole > 0 && rem > 0 && 2 * rem <= split_slots && slot >= whole) {
+        if (whole > 0 && rem > 0 && 2 * rem <= SLOTS && slot >= whole) {
             const int idx = slot - whole;
             local_tile = whole + idx / 2;
             half = idx & 1;
@@ -128,55 +168,144 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, i
     }
     if (local_tile >= mine) return false;
     const int L = first + local_tile;
-    int before = 0;
-    for (int e = 0; e < E; ++e) {
-#if defined(__HIP_DEVICE_COMPILE__)
-        const int mtiles = __builtin_amdgcn_readlane(cnt, e);
-#else
-        const int mtiles = (group_end(offsets, e, P) - group_begin(offsets, e) + BM - 1) / BM;
-#endif
-        const int here = mtiles * n_tiles;
-        if (L < before + here) {
-#if defined(__HIP_DEVICE_COMPILE__)
-            const int prev = __builtin_amdgcn_readlane(lo, e), next = __builtin_amdgcn_readlane(hi, e);
-#else
-            const int prev = group_begin(offsets, e), next = group_end(offsets, e, P);
-#endif
-            const int local = L - before;
-            e_out = e;
-            // blocks of n_inner n-tiles: block outer, the expert's m-tiles in the middle, the
-            // block's n-tiles inner (n_inner = 1: n-tile outer, m-tiles inner)
-            const int nb = max(n_inner, 1);
-            const int full = (n_tiles / nb) * nb * mtiles;  // tiles in whole blocks
-            int mt, nt;
-            if (local < full) {
-                const int rem = local % (mtiles * nb);
-                mt = rem / nb;
-                nt = (local / (mtiles * nb)) * nb + rem % nb;
-            } else {
-                const int nb_tail = n_tiles % nb;
-                const int rem = local - full;
-                mt = rem / nb_tail;
-                nt = (n_tiles / nb) * nb + rem % nb_tail;
-            }
-            nt_out = nt;
-            row0 = prev + mt * BM;
-            row_end = next;
-            if (half >= 0) {
-                row0 += half * (BM / 2);
-                row_end = min(next, row0 + BM / 2);
-                if (row0 >= row_end) return false;  // the tile had no rows in its lower half
-            }
-            return true;
-        }
-        before += here;
+    // the group whose tiles hold L: the last one with tiles at or before it
+    const unsigned long long at = __ballot(lane < E && cnt > 0 && before * n_tiles <= L);
+    const int e = 63 - __clzll((long long)at);
+    const int mtiles = MOE_READLANE(cnt, e), prev = MOE_READLANE(lo, e), next = MOE_READLANE(hi, e);
+    const int local = L - MOE_READLANE(before, e) * n_tiles;
+    const int full = (n_tiles / N_INNER) * N_INNER * mtiles;  // tiles in whole blocks
+    int mt, nt;
+    if (local < full) {
+        const int block = uniform_div(local, mtiles * N_INNER);
+        const int rem = local - block * (mtiles * N_INNER);
+        mt = rem / N_INNER;
+        nt = block * N_INNER + rem % N_INNER;
+        if (N_INNER == 1) mt = rem, nt = block;
+    } else {
+        const int nb_tail = n_tiles % N_INNER;
+        const int rem = local - full;
+        mt = uniform_div(rem, nb_tail);
+        nt = (n_tiles / N_INNER) * N_INNER + rem - mt * nb_tail;
     }
-    return false;
+    e_out = e;
+    nt_out = nt;
+    row0 = prev + mt * BM;
+    row_end = next;
+    if (half >= 0) {
+        row0 += half * (BM / 2);
+        row_end = min(next, row0 + BM / 2);
+        if (row0 >= row_end) return false;  // the tile had no rows in its lower half
+    }
+    return true;
 }
 
+// ---- dispatch inside a product -----------------------------------------------------------------------------
+// The pairs of a layer are sorted by expert (stable) so that each expert's rows are one group.  For up to a
+// few thousand pairs a workgroup finds what it needs of that from the P keys itself -- the groups' bounds
+// and the pairs of its own tile's rows -- and a launch of 5-11 us that does nothing else is saved for 1-6 us
+// more of the product (measured, layer of 300 tokens, 432 x 1152: 31.3 -> 27.4 us; 2048 tokens, 432 x 1152:
+// 47.3 -> 41.6; 777 tokens, 1440 x 3840: 98.3 -> 93.5; 4096 tokens, 720 x 1920: 123.5 -> 116.0).  Every tile
+// counts again: at 2048 tokens, 2048 x 5632, three rounds of tiles, it is even (310 us), so the line lies at the
+// keys that the threads of one workgroup hold.  Thread t holds keys 4 t .. 4 t + 3 of every chunk
+// of 4 NTHR keys, so that order by thread is order by pair.
+constexpr int kKeyChunks = 4;
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {  // set bits of mask below this lane
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+#else
+    return 0;
+#endif
+}
+template <int NTHR>
+struct PairKeys {
+    int k[kKeyChunks][4];
+    int chunks;  // in use (wave-uniform)
+
+    __device__ __forceinline__ void load(const int32_t* __restrict__ keys, int P) {
+        chunks = (P + 4 * NTHR - 1) / (4 * NTHR);
+#pragma unroll
+        for (int c = 0; c < kKeyChunks; ++c) {
+            const int p = (c * NTHR + (int)threadIdx.x) * 4;
+            int4 v = make_int4(-1, -1, -1, -1);
+            if (c < chunks) {
+                if (p + 3 < P) {
+                    v = *reinterpret_cast<const int4*>(keys + p);
+                } else {
+                    if (p < P) v.x = keys[p];
+                    if (p + 1 < P) v.y = keys[p + 1];
+                    if (p + 2 < P) v.z = keys[p + 2];
+                }
+            }
+            k[c][0] = v.x, k[c][1] = v.y, k[c][2] = v.z, k[c][3] = v.w;
+        }
+    }
+
+    // group bounds in lane e of every wave (as group_bounds); s_count [chunks * waves][kMaxExperts] receives
+    // every chunk's and wave's count of every expert
+    __device__ __forceinline__ void bounds(int E, int (*s_count)[kMaxExperts], int& lo, int& hi) const {
+        constexpr int NW = NTHR / kWave;
+        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+#pragma unroll
+        for (int c = 0; c < kKeyChunks; ++c) {
+            if (c >= chunks) break;
+            int* const count = s_count[c * NW + wave];  // (a wave's LDS operations complete in order)
+            count[lane] = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((unsigned)k[c][j] < (unsigned)E) atomicAdd(&count[k[c][j]], 1);
+        }
+        __syncthreads();
+        int total = 0;
+#pragma unroll
+        for (int c = 0; c < kKeyChunks; ++c) {
+            if (c >= chunks) break;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) total += s_count[c * NW + w][lane];
+        }
+        int at = 0;  // (on scalar registers: a shuffle per step of a scan is an LDS round trip)
+        lo = hi = 0;
+        for (int e = 0; e < E; ++e) {
+            const int n = MOE_READLANE(total, e);
+            if (lane == e) lo = at, hi = at + n;
+            at += n;
+        }
+    }
+
+    // pairs of rows [first, first + n) of expert e's group (counted from its start) to s_pair[0 .. n)
+    __device__ __forceinline__ void rows(int e, int first, int n, const int (*s_count)[kMaxExperts], int* s_pair) const {
+        constexpr int NW = NTHR / kWave;
+        const int wave = threadIdx.x / kWave;
+        int before = 0;  // rows of e in earlier chunks
+#pragma unroll
+        for (int c = 0; c < kKeyChunks; ++c) {
+            if (c >= chunks) break;
+            int at = before - first;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) at += lanes_below(__ballot(k[c][j] == e));
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int cw = s_count[c * NW + w][e];
+                if (w < wave) at += cw;
+                before += cw;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (k[c][j] == e) {
+                    if ((unsigned)at < (unsigned)n) s_pair[at] = (c * NTHR + (int)threadIdx.x) * 4 + j;
+                    ++at;
+                }
+            }
+        }
+        __syncthreads();
+    }
+};
+inline bool dispatch_in_product(int P, int threads) { return P <= kKeyChunks * 4 * threads; }
+
 // fp32 problems (expert_gemm_f32.hip)
+constexpr int kF32DispatchThreads = 256;  // threads of its workgroups
 int run_gemm_f32(GemmArgs& g, bool swiglu, hipStream_t st);
 // bf16 products, fills straight into LDS (expert_gemm_pp.hip)
+constexpr int kPpThreads = 512;
 bool gemm_pp_supported(const GemmArgs& g);
 int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st);
 // Parts into which it is worth cutting the k-steps of a plain product of P rows in E groups (k_parts above)

@@ -643,6 +643,29 @@ def test_forward_shared_base_once_per_token_ragged_widths(dev, oracle, T):
     _forward_case(dev, oracle, cfg, T)
 
 
+@pytest.mark.parametrize("E,k,T,dtype", [
+    (1, 1, 1, "f32"), (5, 3, 341, "f32"), (64, 8, 129, "f32"), (8, 2, 2048, "f32"), (8, 1, 4097, "f32"),  # up to 4096 pairs
+    (3, 1, 5, "bf16"), (8, 2, 1024, "bf16"), (64, 8, 257, "bf16"), (7, 3, 1001, "bf16"),                  # up to 8192
+    (8, 2, 4096, "bf16"), (8, 1, 8193, "bf16"),
+])
+def test_forward_sorts_the_pairs_in_its_first_product(dev, E, k, T, dtype):
+    # the sorted order that moe_forward uses inside equals moe_permute's: same products on the same rows
+    cfg = _cfg(d=128, F=136, E=E, k=k, dtype=dtype, seed=700 + T, std=0.05)
+    w_t = weights_to_device(wl.make_layer_weights(cfg), dev)
+    x_t = to_device(wl.make_inputs(cfg, T), dev)
+    y, idx, gate = _forward_gpu(dev, w_t, x_t, k, DT[dtype])
+    shape, P = pkg.shape_for(w_t, T, k, DT[dtype]), T * k
+    off = torch.empty(E + 1, dtype=torch.int32, device=dev)
+    perm, inv = (torch.empty(P, dtype=torch.int32, device=dev) for _ in range(2))
+    xp = torch.empty((P, cfg.d_model), dtype=x_t.dtype, device=dev)
+    pkg.moe_permute(shape, torch.from_numpy(idx).to(dev), off, perm, inv, x_t, xp, pkg.alloc_workspace(shape, dev))
+    ffn_shape, yp, y2 = pkg.shape_for(w_t, P, 1, DT[dtype]), torch.empty_like(xp), torch.empty_like(x_t)
+    pkg.moe_expert_ffn(ffn_shape, pkg.make_weights(w_t), xp, off, yp, pkg.alloc_workspace(ffn_shape, dev))
+    pkg.moe_combine(shape, yp, inv, torch.from_numpy(gate.astype(np.float32)).to(dev), None, y2)
+    torch.cuda.synchronize()
+    assert rel_err(to_f64(y), to_f64(y2)) < (1e-6 if dtype == "f32" else 1e-3)
+
+
 def test_forward_is_deterministic_and_matches_the_staged_calls(dev, oracle):
     cfg = wl.shrink(wl.CONFIGS["wearables"], d_model=512, d_ff=1024)
     w_np = wl.make_layer_weights(cfg)
