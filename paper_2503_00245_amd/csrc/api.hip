@@ -94,11 +94,11 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
     const Workspace ws = carve(s);
     int32_t* idx = topk_idx ? topk_idx : reinterpret_cast<int32_t*>(wsp + ws.topk_idx);
     float* gate = topk_gate ? topk_gate : reinterpret_cast<float*>(wsp + ws.topk_gate);
+    if (decode_supported(s))
+        return launch_decode(s, w, x, idx, gate, y, wsp + ws.decode_scratch, st, timer);
     int rc = launch_route(s, x, w.router_w, w.router_b, idx, gate, nullptr, st);
     if (rc != MOE_OK) return rc;
     stage_mark(timer, "route");
-    if (decode_supported(s))
-        return launch_decode_ffn(s, w, x, idx, gate, y, wsp + ws.decode_scratch, st, timer);
     const int P = s.n_tokens * s.top_k;
     int32_t* offsets = reinterpret_cast<int32_t*>(wsp + ws.offsets);
     int32_t* perm = reinterpret_cast<int32_t*>(wsp + ws.perm);

@@ -191,10 +191,9 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
                                  int32_t* offsets, void* y_perm, void* y_base, void* scratch,
                                  hipStream_t st, StageTimer* timer, const SplitPlan& plan, const int32_t* keys);
 
-// Single-token layer: experts chosen on the device from topk_idx, weights streamed once.
+// Single-token layer: routed, experts chosen on the device from topk_idx, weights streamed once.
 size_t decode_scratch_bytes(const moe_shape& s);
-int launch_decode_ffn(const moe_shape& s, const moe_weights& w, const void* x,
-                      const int32_t* topk_idx, const float* topk_gate, void* y, void* scratch,
-                      hipStream_t st, StageTimer* timer = nullptr);
+int launch_decode(const moe_shape& s, const moe_weights& w, const void* x, int32_t* topk_idx,
+                  float* topk_gate, void* y, void* scratch, hipStream_t st, StageTimer* timer = nullptr);
 
 }  // namespace moe

@@ -29,7 +29,7 @@
 // gemv_kernel is the general form (two segments, segments shared by all experts).
 #include <type_traits>
 
-#include "common.h"
+#include "gemv.h"
 
 namespace moe {
 
@@ -624,9 +624,8 @@ size_t decode_scratch_bytes(const moe_shape& s) {
 }
 
 template <typename T>
-static int decode_ffn_t(const moe_shape& s, const moe_weights& w, const void* x,
-                        const int32_t* idx, const float* gate, void* y, void* scratch,
-                        hipStream_t st, StageTimer* timer) {
+static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int32_t* idx, float* gate,
+                    void* y, void* scratch, hipStream_t st, StageTimer* timer) {
     // k: all (token, slot) pairs of the step; kk of them per token.  One token: its input vector is
     // shared by every pair (vstride 0); several: pair p reads token p / kk's row (vdiv).
     const int d = s.d_model, F = s.d_ff, r = s.rank, kk = s.top_k, k = s.n_tokens * s.top_k;
@@ -646,7 +645,18 @@ static int decode_ffn_t(const moe_shape& s, const moe_weights& w, const void* x,
     int rc;
     GemvArgs a;
 
-    if (r > 0) {  // rank-r inputs of the gate and up factors: tg = R_g x, tu = R_u x
+    // One token: the first stage routes it (expert_gemv_one.hip).
+    const bool first = decode_first_supported(s);
+    FirstStage f{x, w.router_w, w.router_b, nullptr, nullptr, 0, 0, d, s.n_experts, k, idx, gate, nullptr, nullptr, nullptr};
+    if (!first) {
+        if ((rc = launch_route(s, x, w.router_w, w.router_b, idx, gate, nullptr, st)) != MOE_OK) return rc;
+        stage_mark(timer, "route");
+    }
+    if (r > 0 && first) {
+        f.W0 = w.rg; f.W1 = w.ru; f.stride = (long long)r * d; f.rows = r; f.out0 = tg; f.out1 = tu;
+        if ((rc = launch_decode_first(s.act_dtype, f, false, st)) != MOE_OK) return rc;
+        stage_mark(timer, "gemv_rank_gate_up");
+    } else if (r > 0) {  // rank-r inputs of the gate and up factors: tg = R_g x, tu = R_u x
         a = GemvArgs{};
         a.nseg = 1;
         a.seg[0] = GemvSeg{w.rg, w.ru, (long long)r * d, x, x, 0, xs, d, xdiv};
@@ -654,7 +664,12 @@ static int decode_ffn_t(const moe_shape& s, const moe_weights& w, const void* x,
         if ((rc = launch_gemv<T>(a, GEMV_DUAL, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemv_rank_gate_up");
     }
-    {  // hidden vector h_j = silu(M_gate x) * (M_up x)
+    if (r == 0 && first) {
+        f.W0 = w.w_gate; f.W1 = w.w_up; f.stride = (long long)F * d; f.rows = F; f.out0 = h;
+        f.out0_act = h_act ? h : nullptr;
+        if ((rc = launch_decode_first(s.act_dtype, f, true, st)) != MOE_OK) return rc;
+        stage_mark(timer, "gemv_gate_up_swiglu");
+    } else {  // hidden vector h_j = silu(M_gate x) * (M_up x)
         a = GemvArgs{};
         int ns = 0;
         if (base) a.seg[ns++] = GemvSeg{w.w_gate, w.w_up, base_stride_gu, x, x, 0, xs, d, xdiv};
@@ -673,7 +688,14 @@ static int decode_ffn_t(const moe_shape& s, const moe_weights& w, const void* x,
         if ((rc = launch_gemv<T>(a, GEMV_PLAIN, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemv_rank_down");
     }
-    {  // y = sum_j gate_j M_down h_j (+ x)
+    const bool v_f32 = r > 0 || !h_act;
+    const int n_last = r > 0 ? r : F;
+    if (s.n_tokens == 1 && !(r > 0 && base) && decode_last_supported(s.act_dtype, v_f32, d, n_last, k)) {
+        const LastStage l{r > 0 ? w.ld : w.w_down, (long long)d * n_last, r > 0 ? td : h, d, n_last, s.n_experts, k, 1,
+                          idx, gate, (s.flags & MOE_FLAG_RESIDUAL) ? x : nullptr, y};
+        if ((rc = launch_decode_last(s.act_dtype, v_f32, l, st)) != MOE_OK) return rc;
+        stage_mark(timer, "gemv_down_combine");
+    } else {  // y = sum_j gate_j M_down h_j (+ x)
         a = GemvArgs{};
         int ns = 0;
         if (base) a.seg[ns++] = GemvSeg{w.w_down, nullptr, (r == 0) ? (long long)d * F : 0, h, h, h_act ? 0 : 1, F, F};
@@ -687,12 +709,11 @@ static int decode_ffn_t(const moe_shape& s, const moe_weights& w, const void* x,
     return MOE_OK;
 }
 
-int launch_decode_ffn(const moe_shape& s, const moe_weights& w, const void* x,
-                      const int32_t* topk_idx, const float* topk_gate, void* y, void* scratch,
-                      hipStream_t st, StageTimer* timer) {
+int launch_decode(const moe_shape& s, const moe_weights& w, const void* x, int32_t* topk_idx,
+                  float* topk_gate, void* y, void* scratch, hipStream_t st, StageTimer* timer) {
     if (s.act_dtype == MOE_F32)
-        return decode_ffn_t<float>(s, w, x, topk_idx, topk_gate, y, scratch, st, timer);
-    return decode_ffn_t<bf16_t>(s, w, x, topk_idx, topk_gate, y, scratch, st, timer);
+        return decode_t<float>(s, w, x, topk_idx, topk_gate, y, scratch, st, timer);
+    return decode_t<bf16_t>(s, w, x, topk_idx, topk_gate, y, scratch, st, timer);
 }
 
 }  // namespace moe
