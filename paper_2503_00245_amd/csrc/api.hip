@@ -1,6 +1,6 @@
 // extern "C" entry points of moe.h: argument checks on the host, workspace carving, and
 // the order in which the stage kernels are enqueued.  No kernel lives here.
-#include "common.h"
+#include "gemv.h"
 
 namespace moe {
 
@@ -94,8 +94,12 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
     const Workspace ws = carve(s);
     int32_t* idx = topk_idx ? topk_idx : reinterpret_cast<int32_t*>(wsp + ws.topk_idx);
     float* gate = topk_gate ? topk_gate : reinterpret_cast<float*>(wsp + ws.topk_gate);
-    if (decode_supported(s))
-        return launch_decode(s, w, x, idx, gate, y, wsp + ws.decode_scratch, st, timer);
+    if (decode_supported(s)) {
+        // (the prefill's scratch lies idle: a shared base's products go there)
+        float* base = decode_base_supported(s) && decode_base_bytes(s) <= ffn_scratch_bytes(s)
+                          ? reinterpret_cast<float*>(wsp + ws.ffn_scratch) : nullptr;
+        return launch_decode(s, w, x, idx, gate, y, wsp + ws.decode_scratch, base, st, timer);
+    }
     int rc = launch_route(s, x, w.router_w, w.router_b, idx, gate, nullptr, st);
     if (rc != MOE_OK) return rc;
     stage_mark(timer, "route");

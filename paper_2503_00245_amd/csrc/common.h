@@ -192,8 +192,10 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
                                  hipStream_t st, StageTimer* timer, const SplitPlan& plan, const int32_t* keys);
 
 // Single-token layer: routed, experts chosen on the device from topk_idx, weights streamed once.
+// base_scratch: decode_base_bytes (gemv.h) for a layer with a shared base, or NULL.
 size_t decode_scratch_bytes(const moe_shape& s);
 int launch_decode(const moe_shape& s, const moe_weights& w, const void* x, int32_t* topk_idx,
-                  float* topk_gate, void* y, void* scratch, hipStream_t st, StageTimer* timer = nullptr);
+                  float* topk_gate, void* y, void* scratch, float* base_scratch, hipStream_t st,
+                  StageTimer* timer = nullptr);
 
 }  // namespace moe

@@ -19,7 +19,9 @@
 // of the input vector straight from L1/L2, and reduces with a 64-lane butterfly.  Nothing is
 // staged in LDS, so the weight stream starts at once.
 //
-// Two kernels.  gemv_pairs_kernel serves the stages with one segment and a matrix of its own per
+// The first and last stages of one token, and all stages of one token with a shared base, have kernels of
+// their own where their rule takes the shape (expert_gemv_one.hip); the two here serve the rest.
+// gemv_pairs_kernel serves the stages with one segment and a matrix of its own per
 // expert (every stage of a dense or purely decomposed expert): it walks the row chunk by chunk
 // with the pairs inside, so a wave has the chunks of two experts (and of both matrices of a
 // gate/up product) in flight at once -- eight 1 KB loads -- and reads a shared input vector once
@@ -625,7 +627,7 @@ size_t decode_scratch_bytes(const moe_shape& s) {
 
 template <typename T>
 static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int32_t* idx, float* gate,
-                    void* y, void* scratch, hipStream_t st, StageTimer* timer) {
+                    void* y, void* scratch, float* base_scratch, hipStream_t st, StageTimer* timer) {
     // k: all (token, slot) pairs of the step; kk of them per token.  One token: its input vector is
     // shared by every pair (vstride 0); several: pair p reads token p / kk's row (vdiv).
     const int d = s.d_model, F = s.d_ff, r = s.rank, kk = s.top_k, k = s.n_tokens * s.top_k;
@@ -647,13 +649,30 @@ static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int
 
     // One token: the first stage routes it (expert_gemv_one.hip).
     const bool first = decode_first_supported(s);
-    FirstStage f{x, w.router_w, w.router_b, nullptr, nullptr, 0, 0, d, s.n_experts, k, idx, gate, nullptr, nullptr, nullptr};
+    FirstStage f{x, w.router_w, w.router_b, nullptr, nullptr, 0, 0, d, s.n_experts, k, idx, gate};
     if (!first) {
         if ((rc = launch_route(s, x, w.router_w, w.router_b, idx, gate, nullptr, st)) != MOE_OK) return rc;
         stage_mark(timer, "route");
     }
     if (r > 0 && first) {
         f.W0 = w.rg; f.W1 = w.ru; f.stride = (long long)r * d; f.rows = r; f.out0 = tg; f.out1 = tu;
+        if (base_scratch && base) {  // shared base, one token: four launches (expert_gemv_one.hip)
+            float *b0 = base_scratch, *b1 = b0 + F;
+            f.base_W0 = w.w_gate; f.base_W1 = w.w_up; f.base0 = b0; f.base1 = b1; f.base_rows = F;
+            if ((rc = launch_decode_first(s.act_dtype, f, false, st)) != MOE_OK) return rc;
+            stage_mark(timer, "gemv_base_and_rank_gate_up");
+            LowRankStage lr{w.lg, w.lu, (long long)F * r, tg, tu, b0, b1, h, F, r, s.n_experts, k, 0, idx, gate, nullptr, nullptr};
+            if ((rc = launch_decode_low_rank(lr, true, st)) != MOE_OK) return rc;
+            stage_mark(timer, "gemv_gate_up_swiglu");
+            const MidStage m{w.rd, w.w_down, (long long)r * F, h, b0, td, b1, F, r, d, s.n_experts, k, 0, idx};
+            if ((rc = launch_decode_mid(m, st)) != MOE_OK) return rc;
+            stage_mark(timer, "gemv_base_and_rank_down");
+            lr = LowRankStage{w.ld, nullptr, (long long)d * r, td, nullptr, b1, nullptr, nullptr, d, r, s.n_experts, k, 0,
+                              idx, gate, (s.flags & MOE_FLAG_RESIDUAL) ? x : nullptr, y};
+            if ((rc = launch_decode_low_rank(lr, false, st)) != MOE_OK) return rc;
+            stage_mark(timer, "gemv_down_combine");
+            return MOE_OK;
+        }
         if ((rc = launch_decode_first(s.act_dtype, f, false, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemv_rank_gate_up");
     } else if (r > 0) {  // rank-r inputs of the gate and up factors: tg = R_g x, tu = R_u x
@@ -710,10 +729,10 @@ static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int
 }
 
 int launch_decode(const moe_shape& s, const moe_weights& w, const void* x, int32_t* topk_idx,
-                  float* topk_gate, void* y, void* scratch, hipStream_t st, StageTimer* timer) {
+                  float* topk_gate, void* y, void* scratch, float* base_scratch, hipStream_t st, StageTimer* timer) {
     if (s.act_dtype == MOE_F32)
-        return decode_t<float>(s, w, x, topk_idx, topk_gate, y, scratch, st, timer);
-    return decode_t<bf16_t>(s, w, x, topk_idx, topk_gate, y, scratch, st, timer);
+        return decode_t<float>(s, w, x, topk_idx, topk_gate, y, scratch, base_scratch, st, timer);
+    return decode_t<bf16_t>(s, w, x, topk_idx, topk_gate, y, scratch, base_scratch, st, timer);
 }
 
 }  // namespace moe

@@ -20,7 +20,9 @@ constexpr int kOneCus = 256;
 // expert, and all of it in one round trip, in place of a launch that leaves 255 CUs idle.  With one
 // workgroup per CU that is 16 MB out of the L2s.  A wave then takes (pair, row) units gw, gw + W, ...;
 // it holds the token's row in registers and requests both rows of its next unit (8 KB at 2048 wide)
-// before it sums the current one.
+// before it sums the current one.  2048 x 5632, 92 MB: 18.9 us with the routing, where a router launch and
+// a wave per row took 3.8 + 17.6; 1024 x 2816, 23 MB: 8.8 us for 3.1 + 8.9.  What is left beside the stream
+// (5.6 TB/s) is the prologue, 2-2.5 us.
 // NC: 1 KB chunks per row.
 template <typename T, int NC, bool SWIGLU>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_first_kernel(
@@ -33,6 +35,15 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int n = a.d;
     const T* x = static_cast<const T*>(a.x);
+    // workgroups from route_blocks on: the shared base's rows, one matrix pair that needs no routing
+    const bool base = !SWIGLU && (int)blockIdx.x >= a.route_blocks;
+    const int first_block = base ? a.route_blocks : 0;
+    const int blocks = base ? (int)gridDim.x - a.route_blocks : a.route_blocks;
+    const int k = base ? 1 : a.k, rows = base ? a.base_rows : a.rows;
+    const T* W0 = static_cast<const T*>(base ? a.base_W0 : a.W0);
+    const T* W1 = static_cast<const T*>(base ? a.base_W1 : a.W1);
+    float* out0 = base ? a.base0 : a.out0;
+    float* out1 = base ? a.base1 : a.out1;
 
     // only the last chunk can be ragged (n is a multiple of VEC): lanes beyond it read the row's last
     // vector and count as zero
@@ -49,17 +60,21 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int q = 0; q < VEC; ++q) out[q] = S::get(v, q);
     };
-    for (int e = wave; e < a.E; e += kOneWaves) {
-        const float b = a.router_b ? a.router_b[e] : 0.f;
-        float acc[1];
-        router_logits<VEC, 1, 4>(load_x, a.router_w + (size_t)e * n, n, lane, 1, acc);
-        if (lane == 0) s_logit[e] = acc[0] + b;
-    }
-    __syncthreads();
-    const RouterPick pick = router_select(lane, a.E, a.k, lane < a.E ? s_logit[lane] : 0.f);
-    if (blockIdx.x == 0 && wave == 0 && pick.slot >= 0) {
-        a.idx[pick.slot] = lane;
-        a.gate[pick.slot] = pick.p / pick.sel_sum;
+    int slot = lane == 0 ? 0 : -1;  // the pair whose expert this lane stands for
+    if (!base) {
+        for (int e = wave; e < a.E; e += kOneWaves) {
+            const float b = a.router_b ? a.router_b[e] : 0.f;
+            float acc[1];
+            router_logits<VEC, 1, 4>(load_x, a.router_w + (size_t)e * n, n, lane, 1, acc);
+            if (lane == 0) s_logit[e] = acc[0] + b;
+        }
+        __syncthreads();
+        const RouterPick pick = router_select(lane, a.E, k, lane < a.E ? s_logit[lane] : 0.f);
+        if (blockIdx.x == 0 && wave == 0 && pick.slot >= 0) {
+            a.idx[pick.slot] = lane;
+            a.gate[pick.slot] = pick.p / pick.sel_sum;
+        }
+        slot = pick.slot;
     }
 
     struct Unit {
@@ -68,19 +83,19 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     struct Rows {
         vec_t w0[NC], w1[NC];
     };
-    const int stride = gridDim.x * kOneWaves;
+    const int stride = blocks * kOneWaves;
     auto settle = [&](Unit u) {
-        while (u.row >= a.rows && u.j < a.k) {
-            u.row -= a.rows;
+        while (u.row >= rows && u.j < k) {
+            u.row -= rows;
             ++u.j;
         }
         return u;
     };
     auto load = [&](Rows& r, const Unit& u) {
-        const int e = max(__ffsll((unsigned long long)__ballot(pick.slot == u.j)) - 1, 0);
+        const int e = max(__ffsll((unsigned long long)__ballot(slot == u.j)) - 1, 0);
         const size_t at = (size_t)e * a.stride + (size_t)u.row * n;
-        const T* p0 = static_cast<const T*>(a.W0) + at;
-        const T* p1 = static_cast<const T*>(a.W1) + at;
+        const T* p0 = W0 + at;
+        const T* p1 = W1 + at;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             r.w0[c] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(p0 + off[c]));
@@ -102,16 +117,16 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
         s0 = wave_sum(s0);
         s1 = wave_sum(s1);
         if (lane == 0) {
-            const size_t at = (size_t)u.j * a.rows + u.row;
+            const size_t at = (size_t)u.j * rows + u.row;
             if (SWIGLU) {
                 const float h = silu_f32(s0) * s1;
                 if (a.out0_act)
                     static_cast<T*>(a.out0_act)[at] = S::from_f32(h);
                 else
-                    a.out0[at] = h;
+                    out0[at] = h;
             } else {
-                a.out0[at] = s0;
-                a.out1[at] = s1;
+                out0[at] = s0;
+                out1[at] = s1;
             }
         }
     };
@@ -121,16 +136,16 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
         for (int q = 0; q < VEC; ++q) xv[NC - 1][q] = S::from_f32(0.f);
     }
     Rows r0, r1;
-    Unit u0 = settle(Unit{0, (int)blockIdx.x * kOneWaves + wave});
-    if (u0.j < a.k) load(r0, u0);
-    while (u0.j < a.k) {
+    Unit u0 = settle(Unit{0, ((int)blockIdx.x - first_block) * kOneWaves + wave});
+    if (u0.j < k) load(r0, u0);
+    while (u0.j < k) {
         const Unit u1 = settle(Unit{u0.j, u0.row + stride});
-        if (u1.j < a.k) load(r1, u1);
+        if (u1.j < k) load(r1, u1);
         __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the sums
         finish(r0, u0);
-        if (u1.j >= a.k) break;
+        if (u1.j >= k) break;
         u0 = settle(Unit{u1.j, u1.row + stride});
-        if (u0.j < a.k) load(r0, u0);
+        if (u0.j < k) load(r0, u0);
         __builtin_amdgcn_sched_barrier(0);
         finish(r1, u1);
     }
@@ -139,6 +154,8 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
 // A wave takes one slice of one (row, pair): chunks slice, slice + slices, ... -- NC of them, all
 // requested before the first is used, the hidden vector's ahead of the expert's id.  16 waves hold
 // 16 / (k slices) rows; their sums meet in LDS and are added in slice and pair order.
+// 2048 x 5632, 46 MB: 10.0 us for 10.7, 1024 x 2816: 5.2 for 5.9 (there eight chunks at a time left a
+// remainder of up to three that came one after the other).
 // V: the stored type of the hidden vectors.
 template <typename T, typename V, int NC>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_last_kernel(
@@ -200,6 +217,143 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     }
 }
 
+// ---- a shared base (M_e = M0 + L_e R_e) ---------------------------------------------------------------
+// The base's products are the bytes of the layer and none of them waits for the low-rank ones: they run
+// beside the rank products in the first launch and beside the rank-down product in the third, and two
+// launches of this kernel add the low-rank part.  64 / lanes rows per wave (a row of L is r long: 128
+// bytes at rank 64), two pairs' rows requested at once.
+// The four launches take 11.2 + 4.1 + 8.5 + 3.4 us at 2048 x 5632, rank 64 (layer 25.4 us); five launches
+// one after the other took 40.8.
+//   HIDDEN: h_j = silu(b0 + L0_j t0_j) * (b1 + L1_j t1_j) and their mix b0 <- sum_j gate_j h_j
+//   else:   y = b0 + sum_j gate_j L0_j t0_j (+ residual)
+constexpr int kLowRankWaves = 4;
+template <typename T, bool HIDDEN>
+__global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(const LowRankStage a) {
+    typedef typename Store<T>::vec_t vec_t;
+    constexpr int VEC = Store<T>::VEC;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int group = lane / a.lanes, sub = lane - group * a.lanes, per_wave = kWave / a.lanes;
+    const int row_at = ((int)blockIdx.x * kLowRankWaves + (int)(threadIdx.x / kWave)) * per_wave + group;
+    const int row = min(row_at, a.rows - 1);
+    const bool mine = sub == 0 && row_at < a.rows;
+    const float b0 = a.b0[row], b1 = HIDDEN ? a.b1[row] : 0.f;
+    float res = 0.f;
+    if (!HIDDEN && a.residual) res = Store<T>::to_f32(static_cast<const T*>(a.residual)[row]);
+    float mix = 0.f;
+    for (int j0 = 0; j0 < a.k; j0 += 2) {
+        float acc[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+        const T* l[2][2];
+        const float* t[2][2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int j = min(j0 + p, a.k - 1);
+            const int e = min(max(a.idx[j], 0), a.E - 1);
+            const size_t at = (size_t)e * a.stride + (size_t)row * a.r;
+            l[p][0] = static_cast<const T*>(a.L0) + at;
+            t[p][0] = a.t0 + (size_t)j * a.r;
+            l[p][1] = HIDDEN ? static_cast<const T*>(a.L1) + at : l[p][0];
+            t[p][1] = HIDDEN ? a.t1 + (size_t)j * a.r : t[p][0];
+        }
+        for (int i = sub * VEC; i < a.r; i += a.lanes * VEC) {
+            vec_t w[2][2];
+            f32x4 v[2][2][VEC / 4];
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int m = 0; m < (HIDDEN ? 2 : 1); ++m) {
+                    w[p][m] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(l[p][m] + i));
+#pragma unroll
+                    for (int q = 0; q < VEC / 4; ++q) v[p][m][q] = *reinterpret_cast<const f32x4*>(t[p][m] + i + 4 * q);
+                }
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int m = 0; m < (HIDDEN ? 2 : 1); ++m)
+#pragma unroll
+                    for (int q = 0; q < VEC; ++q) acc[p][m] = fmaf(Store<T>::get(w[p][m], q), v[p][m][q / 4][q % 4], acc[p][m]);
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            for (int o = 1; o < a.lanes; o *= 2) {
+                acc[p][0] += __shfl_xor(acc[p][0], o, kWave);
+                if (HIDDEN) acc[p][1] += __shfl_xor(acc[p][1], o, kWave);
+            }
+            if (j0 + p < a.k) {
+                const float g = a.gate[j0 + p];
+                if (HIDDEN) {
+                    const float h = silu_f32(b0 + acc[p][0]) * (b1 + acc[p][1]);
+                    if (mine) a.h[(size_t)(j0 + p) * a.rows + row] = h;
+                    mix = fmaf(g, h, mix);
+                } else {
+                    mix = fmaf(g, acc[p][0], mix);
+                }
+            }
+        }
+    }
+    if (!mine) return;
+    if (HIDDEN)
+        a.b0[row] = mix;  // read above by this group of lanes alone
+    else
+        static_cast<T*>(a.y)[row] = Store<T>::from_f32(b0 + mix + res);
+}
+
+// td_j = R_d,j h_j for every pair, and y0 = M0_down mix: rows of one length against fp32 vectors, `slices`
+// waves each, NC chunks a wave and all of them requested at once.
+constexpr int kMidWaves = 8;
+template <typename T, int NC>
+__global__ __launch_bounds__(kMidWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void decode_mid_kernel(const MidStage a) {
+    typedef typename Store<T>::vec_t vec_t;
+    constexpr int VEC = Store<T>::VEC, CH = kWave * VEC, VL = VEC / 4;
+    __shared__ float s_part[kMidWaves];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int n = a.n, slice = wave % a.slices, rows_here = kMidWaves / a.slices;
+    const int low = a.k * a.r, units = low + a.d;
+    const int u_at = (int)blockIdx.x * rows_here + wave / a.slices, u = min(u_at, units - 1);
+    int off[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) off[c] = min((slice + c * a.slices) * CH + lane * VEC, n - VEC);
+    const bool tail_in = (slice + (NC - 1) * a.slices) * CH + lane * VEC < n;
+    const float* v;
+    const T* w;
+    float* out;
+    if (u < low) {
+        const int j = u / a.r, e = min(max(a.idx[j], 0), a.E - 1);
+        w = static_cast<const T*>(a.rd) + (size_t)e * a.stride + (size_t)(u - j * a.r) * n;
+        v = a.h + (size_t)j * n;
+        out = a.td + u;
+    } else {
+        w = static_cast<const T*>(a.w_down) + (size_t)(u - low) * n;
+        v = a.mix;
+        out = a.y0 + (u - low);
+    }
+    vec_t wv[NC];
+    f32x4 x[NC][VL];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) wv[c] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(w + off[c]));
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int l = 0; l < VL; ++l) x[c][l] = *reinterpret_cast<const f32x4*>(v + off[c] + 4 * l);
+    __builtin_amdgcn_sched_barrier(0);
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const bool in = c + 1 < NC || tail_in;
+            s = fmaf(in ? Store<T>::get(wv[c], i) : 0.f, in ? x[c][i / 4][i % 4] : 0.f, s);
+        }
+    s = wave_sum(s);
+    if (lane == 0) s_part[wave] = s;
+    __syncthreads();
+    if (slice == 0 && lane == 0 && u_at < units) {
+        float sum = 0.f;
+        for (int sl = 0; sl < a.slices; ++sl) sum += s_part[wave + sl];
+        *out = sum;
+    }
+}
+
 template <typename T>
 static constexpr int chunks_of(int n) { return (n + kWave * Store<T>::VEC - 1) / (kWave * Store<T>::VEC); }
 
@@ -223,9 +377,10 @@ static void launch_first_nc(const FirstStage& a, bool swiglu, dim3 grid, hipStre
 }
 
 template <typename T>
-static int launch_first_t(const FirstStage& a, bool swiglu, hipStream_t st) {
+static int launch_first_t(FirstStage a, bool swiglu, hipStream_t st) {
     const long long units = (long long)a.k * a.rows;
-    const dim3 grid((unsigned)std::min<long long>(kOneCus, (units + kOneWaves - 1) / kOneWaves));
+    a.route_blocks = (int)std::min<long long>(kOneCus, (units + kOneWaves - 1) / kOneWaves);
+    const dim3 grid(a.route_blocks + (a.base_W0 ? std::max(kOneCus / 2, kOneCus - a.route_blocks) : 0));
     switch (chunks_of<T>(a.d)) {
         case 1: launch_first_nc<T, 1>(a, swiglu, grid, st); break;
         case 2: launch_first_nc<T, 2>(a, swiglu, grid, st); break;
@@ -285,6 +440,51 @@ bool decode_last_supported(int act_dtype, bool v_f32, int rows, int n, int k) {
 int launch_decode_last(int act_dtype, bool v_f32, LastStage a, hipStream_t st) {
     if (act_dtype == MOE_F32) return launch_last_t<float, float>(a, st);
     return v_f32 ? launch_last_t<bf16_t, float>(a, st) : launch_last_t<bf16_t, bf16_t>(a, st);
+}
+
+static int mid_slices(int units, int n) {
+    const int chunks = chunks_of<bf16_t>(n);
+    int s = 1;
+    while ((chunks + s - 1) / s > last_max_chunks<bf16_t, float>()) s *= 2;
+    while ((long long)units * s * 2 <= kOneCus * kOneWaves && chunks >= 4 * s) s *= 2;
+    return s <= kMidWaves ? s : 0;
+}
+
+template <int NC>
+static int launch_mid_nc(const MidStage& a, int nc, hipStream_t st) {
+    if constexpr (NC > last_max_chunks<bf16_t, float>()) {
+        return MOE_ERR_UNSUPPORTED;
+    } else {
+        if (nc != NC) return launch_mid_nc<NC + 1>(a, nc, st);
+        const int rows_here = kMidWaves / a.slices;
+        const dim3 grid((a.k * a.r + a.d + rows_here - 1) / rows_here), block(kMidWaves * kWave);
+        hipLaunchKernelGGL((decode_mid_kernel<bf16_t, NC>), grid, block, 0, st, a);
+        return launch_status();
+    }
+}
+
+// (the output's fp32 sums go where the base's up product lay: no wider than that)
+bool decode_base_supported(const moe_shape& s) {
+    return decode_first_supported(s) && s.act_dtype == MOE_BF16 && token_base_supported(s) && s.d_model <= s.d_ff &&
+           (long long)s.top_k * s.rank + s.d_model < (1 << 24) && mid_slices(s.top_k * s.rank + s.d_model, s.d_ff) != 0;
+}
+
+int launch_decode_mid(MidStage a, hipStream_t st) {
+    a.slices = mid_slices(a.k * a.r + a.d, a.n);
+    if (!a.slices) return MOE_ERR_UNSUPPORTED;
+    return launch_mid_nc<1>(a, (chunks_of<bf16_t>(a.n) + a.slices - 1) / a.slices, st);
+}
+
+int launch_decode_low_rank(LowRankStage a, bool hidden, hipStream_t st) {
+    a.lanes = 1;
+    while (a.lanes < kWave && a.lanes * Store<bf16_t>::VEC < a.r) a.lanes *= 2;
+    const int per_block = kLowRankWaves * (kWave / a.lanes);
+    const dim3 grid((a.rows + per_block - 1) / per_block), block(kLowRankWaves * kWave);
+    if (hidden)
+        hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, true>), grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, false>), grid, block, 0, st, a);
+    return launch_status();
 }
 
 }  // namespace moe

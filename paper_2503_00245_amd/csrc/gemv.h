@@ -17,6 +17,11 @@ struct FirstStage {
     float* gate;          // [k], written
     float *out0, *out1;   // [k][rows]
     void* out0_act;       // SwiGLU: [k][rows] in the activation type, written instead of out0 (or NULL)
+    // without SwiGLU, beside those: base0 = base_W0 x, base1 = base_W1 x (or NULL)
+    const void *base_W0, *base_W1;  // [base_rows, d]
+    float *base0, *base1;
+    int base_rows;
+    int route_blocks;     // set by the launcher
 };
 bool decode_first_supported(const moe_shape& s);
 int launch_decode_first(int act_dtype, const FirstStage& a, bool swiglu, hipStream_t st);
@@ -35,5 +40,35 @@ struct LastStage {
 };
 bool decode_last_supported(int act_dtype, bool v_f32, int rows, int n, int k);
 int launch_decode_last(int act_dtype, bool v_f32, LastStage a, hipStream_t st);
+
+// Layers with a shared base: after a first stage that also forms base0 = W_gate x and base1 = W_up x,
+//   low rank (hidden)  h_j and their mix      mid  td_j = R_d h_j, y0 = W_down mix      low rank  y
+struct LowRankStage {
+    const void *L0, *L1;     // [E, rows, r]
+    long long stride;
+    const float *t0, *t1;    // [k][r]
+    float* b0;               // [rows]; hidden: replaced by the mix
+    const float* b1;         // [rows] (hidden)
+    float* h;                // [k][rows] (hidden)
+    int rows, r, E, k;
+    int lanes;               // lanes per row; set by the launcher
+    const int32_t* idx;
+    const float* gate;
+    const void* residual;
+    void* y;
+};
+struct MidStage {
+    const void *rd, *w_down;  // [E, r, n], [d, n]
+    long long stride;
+    const float *h, *mix;     // [k][n], [n]
+    float *td, *y0;           // [k][r], [d]
+    int n, r, d, E, k;
+    int slices;               // waves per row; set by the launcher
+    const int32_t* idx;
+};
+bool decode_base_supported(const moe_shape& s);
+inline size_t decode_base_bytes(const moe_shape& s) { return 2 * sizeof(float) * (size_t)s.d_ff; }
+int launch_decode_low_rank(LowRankStage a, bool hidden, hipStream_t st);
+int launch_decode_mid(MidStage a, hipStream_t st);
 
 }  // namespace moe

@@ -643,6 +643,24 @@ def test_forward_shared_base_once_per_token_ragged_widths(dev, oracle, T):
     _forward_case(dev, oracle, cfg, T)
 
 
+@pytest.mark.parametrize("d,F,E,k,r,base,dtype", [
+    # row lengths of one vector, one chunk less / more a vector, four chunks and one vector more (its own router launch)
+    (8, 8, 2, 1, 0, False, "bf16"), (504, 520, 4, 2, 0, False, "bf16"), (1032, 1544, 8, 4, 0, False, "bf16"),
+    (2048, 6144, 8, 2, 0, False, "bf16"), (2056, 6152, 8, 2, 0, False, "bf16"), (328, 8200, 16, 16, 0, False, "bf16"),
+    (264, 1000, 5, 3, 0, False, "bf16"), (64, 128, 64, 8, 0, False, "bf16"),
+    (8, 16, 2, 2, 0, False, "f32"), (264, 2056, 8, 4, 0, False, "f32"), (1024, 1032, 4, 1, 0, False, "f32"),
+    (1032, 264, 8, 2, 0, False, "f32"),
+    (200, 328, 8, 2, 104, False, "bf16"), (520, 1064, 4, 1, 264, False, "bf16"),          # rank factors
+    (8, 8, 2, 2, 8, True, "bf16"), (264, 520, 8, 3, 24, True, "bf16"), (1544, 4104, 16, 4, 136, True, "bf16"),  # shared base
+    (520, 512, 8, 2, 520, True, "bf16"),                                                  # d above F: the general kernels
+    (2048, 5632, 8, 2, 64, True, "bf16"),
+])
+@pytest.mark.parametrize("residual", [False, True])
+def test_forward_one_token(dev, oracle, d, F, E, k, r, base, dtype, residual):
+    cfg = _cfg(d=d, F=F, E=E, k=k, dtype=dtype, seed=520 + d + k, r=r, base=base, std=0.05)
+    _forward_case(dev, oracle, cfg, 1, residual=residual)
+
+
 @pytest.mark.parametrize("E,k,T,dtype", [
     (1, 1, 1, "f32"), (5, 3, 341, "f32"), (64, 8, 129, "f32"), (8, 2, 2048, "f32"), (8, 1, 4097, "f32"),  # up to 4096 pairs
     (3, 1, 5, "bf16"), (8, 2, 1024, "bf16"), (64, 8, 257, "bf16"), (7, 3, 1001, "bf16"),                  # up to 8192
