@@ -77,15 +77,11 @@ __device__ __forceinline__ void phase_end() {
 // into two sets of accumulators.
 // SA, SB: k-steps of A and of B in LDS.
 // F32: k-parts stored in fp32.
-template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32>
+// NT_B: weights past the caches (run_gemm_pp has the rule).
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_pp_kernel(const GemmArgs g) {
     static_assert(!DUAL || SWIGLU, "two activation operands only with the activation");
     constexpr int WAVES_N = 8 / WAVES_M;
-    // Weights past the caches where an expert has one or two m-tiles: a plain read of 335 MB in this pattern
-    // runs at 6.0 TB/s without the hint and at 6.7 with it.  (2048 / 5632 layer at 8 tokens 95 -> 86 us, 64
-    // tokens 124 -> 114, 256 tokens 129 -> 120; with it on 256-row tiles, whose m-tiles share the weights
-    // in L2, 2048 tokens 313 -> 326.)
-    constexpr bool NT_B = BM <= 128;
     constexpr int MB = BM / 32 / WAVES_M;         // 32-row blocks of a wave
     static_assert(MB >= 1 && SA >= 2 && SB >= 3, "a group reads one step while the other's is being fetched");
     constexpr int WN = BN / WAVES_N, NI = WN / 16;  // columns, 16-column blocks of a wave
@@ -421,7 +417,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32 = false>
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32 = false, bool NT_B = (BM <= 128)>
 int launch_pp(GemmArgs& g, hipStream_t st) {
     constexpr int BN_OUT = SWIGLU && !DUAL ? BN / 2 : BN;
     g.m_tiles_max = g.P / BM + g.E;
@@ -432,7 +428,7 @@ int launch_pp(GemmArgs& g, hipStream_t st) {
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     const int grid = ((tiles + 7) / 8 + kSplitSlots / 2) * 8;
     static std::atomic<uint64_t> lds_allowed;
-    const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32>;
+    const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, NT_B>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, g);
     return launch_status();
@@ -504,22 +500,30 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     const int parts = g.k_parts > 1 ? g.k_parts : 1;  // decided by the caller
     const int bm = choose(g.P, g.E, g.N, g.seg[0].K / parts, parts * (!swiglu && g.C1 ? 2 : 1), swiglu, dual, 1, false, false).bm;
     g.fit_width = 2;
+    // Weights past the caches where an expert has one or two m-tiles: a plain read of 335 MB in this pattern
+    // runs at 6.0 TB/s without the hint and at 6.7 with it.  (2048 / 5632 layer at 8 tokens 95 -> 86 us, 64
+    // tokens 124 -> 114, 256 tokens 129 -> 120; where the m-tiles of an expert share its weights in L2 it
+    // hurts: 2048 tokens 313 -> 326.)  Drawn at an average of 256 rows per expert, one tile of the tallest kind:
+    // 512 tokens 1024 / 2816 55.9 -> 51.9, 777 tokens 1440 / 3840 94.7 -> 91.7.
+    const bool nt = g.P <= 256 * g.E;
     if (!swiglu) {
         const bool f32 = g.k_parts > 1 && g.parts_f32;
         if (bm == 64)
             return f32 ? launch_pp<64, 256, 2, 4, 4, false, false, true>(g, st) : launch_pp<64, 256, 2, 4, 4, false, false>(g, st);
         if (bm == 128)
             return f32 ? launch_pp<128, 256, 2, 4, 3, false, false, true>(g, st) : launch_pp<128, 256, 2, 4, 3, false, false>(g, st);
+        if (nt)
+            return f32 ? launch_pp<256, 256, 2, 2, 3, false, false, true, true>(g, st) : launch_pp<256, 256, 2, 2, 3, false, false, false, true>(g, st);
         return f32 ? launch_pp<256, 256, 2, 2, 3, false, false, true>(g, st) : launch_pp<256, 256, 2, 2, 3, false, false>(g, st);
     }
     if (dual) {
         if (bm == 64) return launch_pp<64, 128, 2, 8, 6, true, true>(g, st);
         if (bm == 128) return launch_pp<128, 128, 4, 4, 5, true, true>(g, st);
-        return launch_pp<256, 128, 4, 2, 3, true, true>(g, st);
+        return nt ? launch_pp<256, 128, 4, 2, 3, true, true, false, true>(g, st) : launch_pp<256, 128, 4, 2, 3, true, true>(g, st);
     }
     if (bm == 64) return launch_pp<64, 256, 2, 4, 4, true, false>(g, st);
     if (bm == 128) return launch_pp<128, 256, 2, 4, 3, true, false>(g, st);
-    return launch_pp<256, 256, 2, 2, 3, true, false>(g, st);
+    return nt ? launch_pp<256, 256, 2, 2, 3, true, false, false, true>(g, st) : launch_pp<256, 256, 2, 2, 3, true, false>(g, st);
 }
 
 // out = sum of the parts, in part order, rounded once; n a multiple of 8
