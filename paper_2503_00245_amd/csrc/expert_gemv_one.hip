@@ -21,7 +21,7 @@ constexpr int kOneCus = 256;
 // workgroup per CU that is 16 MB out of the L2s.  A wave then takes (pair, row) units gw, gw + W, ...;
 // it holds the token's row in registers and requests both rows of its next unit (8 KB at 2048 wide)
 // before it sums the current one.  2048 x 5632, 92 MB: 18.9 us with the routing, where a router launch and
-// a wave per row took 3.8 + 17.6; 1024 x 2816, 23 MB: 8.8 us for 3.1 + 8.9.  What is left beside the stream
+// a wave per row took 3.8 + 17.6; 1024 x 2816, 23 MB: 8.4 us for 3.1 + 8.9.  What is left beside the stream
 // (5.6 TB/s) is the prologue, 2-2.5 us.
 // NC: 1 KB chunks per row.
 template <typename T, int NC, bool SWIGLU>
@@ -61,6 +61,7 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
         for (int q = 0; q < VEC; ++q) out[q] = S::get(v, q);
     };
     int slot = lane == 0 ? 0 : -1;  // the pair whose expert this lane stands for
+    float logit = 0.f, vmax = 0.f;
     if (!base) {
         for (int e = wave; e < a.E; e += kOneWaves) {
             const float b = a.router_b ? a.router_b[e] : 0.f;
@@ -69,12 +70,8 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
             if (lane == 0) s_logit[e] = acc[0] + b;
         }
         __syncthreads();
-        const RouterPick pick = router_select(lane, a.E, k, lane < a.E ? s_logit[lane] : 0.f);
-        if (blockIdx.x == 0 && wave == 0 && pick.slot >= 0) {
-            a.idx[pick.slot] = lane;
-            a.gate[pick.slot] = pick.p / pick.sel_sum;
-        }
-        slot = pick.slot;
+        logit = lane < a.E ? s_logit[lane] : 0.f;
+        slot = router_slots(lane, a.E, k, logit, vmax);
     }
 
     struct Unit {
@@ -138,6 +135,13 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     Rows r0, r1;
     Unit u0 = settle(Unit{0, ((int)blockIdx.x - first_block) * kOneWaves + wave});
     if (u0.j < k) load(r0, u0);
+    if (blockIdx.x == 0 && wave == 0) {  // the gates, for the last stage: behind the first requests
+        const RouterPick pick = router_weigh(lane, a.E, logit, slot, vmax);
+        if (slot >= 0) {
+            a.idx[slot] = lane;
+            a.gate[slot] = pick.p / pick.sel_sum;
+        }
+    }
     while (u0.j < k) {
         const Unit u1 = settle(Unit{u0.j, u0.row + stride});
         if (u1.j < k) load(r1, u1);

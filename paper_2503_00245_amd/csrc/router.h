@@ -70,14 +70,13 @@ struct RouterPick {
 };
 
 // One wave, lane e owning expert e (lanes >= E idle): k rounds of a (value, index) arg-max
-// butterfly on the logits; equal logits go to the lower index.
-__device__ __forceinline__ RouterPick router_select(int lane, int E, int k, float logit_of_lane) {
-    const bool valid = lane < E;
-    const float logit = valid ? logit_of_lane : -INFINITY;
-    float cand = logit;  // -inf once taken
-    float vmax = 0.f;
-    RouterPick r;
-    r.slot = -1;
+// butterfly on the logits; equal logits go to the lower index.  Returns this lane's slot; vmax: the
+// row's maximum.  With at most 16 experts the first row of 16 lanes has the answer after four
+// register exchanges, without the two that cross rows through the LDS unit.
+__device__ __forceinline__ int router_slots(int lane, int E, int k, float logit_of_lane, float& vmax) {
+    float cand = lane < E ? logit_of_lane : -INFINITY;  // -inf once taken
+    int slot = -1;
+    vmax = 0.f;
     for (int j = 0; j < k; ++j) {
         float bv = cand;
         int bi = lane;
@@ -92,18 +91,36 @@ __device__ __forceinline__ RouterPick router_select(int lane, int E, int k, floa
         take(dpp_f32<kDppSwap2>(bv), dpp_i32<kDppSwap2>(bi));
         take(dpp_f32<kDppHalfMirror>(bv), dpp_i32<kDppHalfMirror>(bi));
         take(dpp_f32<kDppMirror>(bv), dpp_i32<kDppMirror>(bi));
-        take(__shfl_xor(bv, 16, kWave), __shfl_xor(bi, 16, kWave));
-        take(__shfl_xor(bv, 32, kWave), __shfl_xor(bi, 32, kWave));
+        if (E <= 16) {
+            bv = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(bv)));
+            bi = __builtin_amdgcn_readfirstlane(bi);
+        } else {
+            take(__shfl_xor(bv, 16, kWave), __shfl_xor(bi, 16, kWave));
+            take(__shfl_xor(bv, 32, kWave), __shfl_xor(bi, 32, kWave));
+        }
         if (j == 0) vmax = bv;  // the first pick is the row maximum
         if (lane == bi) {
             cand = -INFINITY;
-            r.slot = j;
+            slot = j;
         }
     }
-    r.p = valid ? __expf(logit - vmax) : 0.f;
+    return slot;
+}
+
+// The exponentials that go with the slots (Eq. 2 relative to the maximum)
+__device__ __forceinline__ RouterPick router_weigh(int lane, int E, float logit_of_lane, int slot, float vmax) {
+    RouterPick r;
+    r.slot = slot;
+    r.p = lane < E ? __expf(logit_of_lane - vmax) : 0.f;
     r.den = wave_sum(r.p);
-    r.sel_sum = wave_sum(r.slot >= 0 ? r.p : 0.f);
+    r.sel_sum = wave_sum(slot >= 0 ? r.p : 0.f);
     return r;
+}
+
+__device__ __forceinline__ RouterPick router_select(int lane, int E, int k, float logit_of_lane) {
+    float vmax;
+    const int slot = router_slots(lane, E, k, logit_of_lane, vmax);
+    return router_weigh(lane, E, logit_of_lane, slot, vmax);
 }
 
 }  // namespace moe
