@@ -78,15 +78,15 @@ WORKLOADS = {
 # the summary and the kernel line the figures are read from (a CPU test keeps the two in step).
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 TRAFFIC_SOURCE = {
-    # gate/up grouped GEMM with the SiLU * mul epilogue (256 x 256 tiles, 64-wide k-steps filled in halves)
+    # gate/up grouped GEMM with the SiLU * mul epilogue (256 x 256 tiles, filled straight into LDS)
     "phone_prefill": ("phone_prefill_kernels_and_hbm_traffic.txt",
-                      r"gemm_bf16_deep_kernel<256, 256, 64, 64, 128, true, false"),
-    # gate/up matrix-vector products + SwiGLU of the single-token step
-    "phone_decode": ("phone_decode_kernels_and_hbm_traffic.txt", r"gemv_kernelIDF16bLi2E"),
+                      r"gemm_pp_kernel<256, 256, 2, 2, 3, true, false, false, false>"),
+    # routing, gate/up matrix-vector products and SwiGLU of the single-token step
+    "phone_decode": ("phone_decode_kernels_and_hbm_traffic.txt", r"decode_first_kernelIDF16bLi4ELb1E"),
 }
 MEASURED_KIB = {  # workload: (FETCH_SIZE mean, WRITE_SIZE mean), KiB per dispatch as the tool reports them
-    "phone_prefill": (289396.7, 46923.4),
-    "phone_decode": (45126.1, 44.0),
+    "phone_prefill": (331193.8, 45143.6),
+    "phone_decode": (45391.7, 23.7),
 }
 MEASURED_TRAFFIC_BYTES = {w: int((f * FETCH_SCALE + wr * WRITE_SCALE) * 1024) for w, (f, wr) in MEASURED_KIB.items()}
 
@@ -105,7 +105,10 @@ def dominant_kernel_work(cfg, T):
     d, F, k, r = cfg.d_model, cfg.d_ff, cfg.top_k, cfg.rank
     P = T * k
     if T == 1:
-        # single token: the gate/up product streams k experts' gate and up matrices once
+        # single token: the gate/up product streams k experts' gate and up matrices once; a shared base's
+        # two matrices stream beside the rank factors
+        if cfg.shared_base and k > 1:
+            return "gemv_base_and_rank_gate_up", "hbm", float(2 * F * d * 2 + k * 2 * r * d * 2), "GB/s"
         if r == 0:
             nbytes = k * 2 * F * d * 2
         else:
@@ -371,7 +374,8 @@ def main():
             # most T k of them, each once) -- report against the upper bound of those bytes
             n_sel = min(T * cfg.top_k, cfg.n_experts)
             per = 2 * cfg.d_ff * (cfg.rank if cfg.rank else cfg.d_model) * 2
-            kname, bound, work, unit = "gemv_gate_up_swiglu", "hbm", float(n_sel * per), "GB/s"
+            shared = 2 * cfg.d_ff * cfg.d_model * 2 if cfg.shared_base else 0
+            kname, bound, work, unit = "gemv_gate_up_swiglu", "hbm", float(n_sel * per + shared), "GB/s"
         if kname not in stages:  # a shape the per-token base path does not take: base work per pair
             kname, work = "gemm_gate_up_swiglu", 4.0 * T * cfg.top_k * cfg.d_ff * (cfg.rank + cfg.d_model)
         kms = stages[kname]
