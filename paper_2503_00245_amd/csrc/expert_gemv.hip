@@ -640,7 +640,8 @@ static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int
     // one of those reads goes to L2; from that size on they are kept in the activation type
     // (the prefill path rounds h the same way).  Measured on the 2048 / 5632 layer: down stage
     // 13.9 us instead of 15.4; below that size the fp32 form is the faster one.
-    const bool h_act = sizeof(T) == 2 && (size_t)k * F * sizeof(float) > 32 * 1024;
+    const bool rank_one = decode_rank_supported(s);  // its rank-down product takes fp32 hidden vectors of any length
+    const bool h_act = !rank_one && sizeof(T) == 2 && (size_t)k * F * sizeof(float) > 32 * 1024;
     float* tg = h + (size_t)k * F;
     float* tu = tg + (size_t)k * r;
     float* td = tu + (size_t)k * r;
@@ -688,6 +689,10 @@ static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int
         f.out0_act = h_act ? h : nullptr;
         if ((rc = launch_decode_first(s.act_dtype, f, true, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemv_gate_up_swiglu");
+    } else if (rank_one) {
+        const LowRankStage l{w.lg, w.lu, (long long)F * r, tg, tu, nullptr, nullptr, h, F, r, s.n_experts, k, 0, idx, gate, nullptr, nullptr};
+        if ((rc = launch_decode_hidden(l, st)) != MOE_OK) return rc;
+        stage_mark(timer, "gemv_gate_up_swiglu");
     } else {  // hidden vector h_j = silu(M_gate x) * (M_up x)
         a = GemvArgs{};
         int ns = 0;
@@ -699,7 +704,11 @@ static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int
         if ((rc = launch_gemv<T>(a, GEMV_SWIGLU, st)) != MOE_OK) return rc;
         stage_mark(timer, "gemv_gate_up_swiglu");
     }
-    if (r > 0) {  // td_j = R_d h_j
+    if (rank_one) {
+        const MidStage m{w.rd, nullptr, (long long)r * F, h, nullptr, td, nullptr, F, r, 0, s.n_experts, k, 0, idx};
+        if ((rc = launch_decode_mid(m, st)) != MOE_OK) return rc;
+        stage_mark(timer, "gemv_rank_down");
+    } else if (r > 0) {  // td_j = R_d h_j
         a = GemvArgs{};
         a.nseg = 1;
         a.seg[0] = GemvSeg{w.rd, nullptr, (long long)r * F, h, h, h_act ? 0 : 1, F, F};

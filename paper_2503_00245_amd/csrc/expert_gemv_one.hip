@@ -228,7 +228,8 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
 // bytes at rank 64), two pairs' rows requested at once.
 // The four launches take 11.2 + 4.1 + 8.5 + 3.4 us at 2048 x 5632, rank 64 (layer 25.4 us); five launches
 // one after the other took 40.8.
-//   HIDDEN: h_j = silu(b0 + L0_j t0_j) * (b1 + L1_j t1_j) and their mix b0 <- sum_j gate_j h_j
+//   HIDDEN: h_j = silu(b0 + L0_j t0_j) * (b1 + L1_j t1_j) and their mix b0 <- sum_j gate_j h_j; without a
+//           base (b0 NULL) the hidden vectors alone
 //   else:   y = b0 + sum_j gate_j L0_j t0_j (+ residual)
 constexpr int kLowRankWaves = 4;
 template <typename T, bool HIDDEN>
@@ -240,7 +241,8 @@ __global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(c
     const int row_at = ((int)blockIdx.x * kLowRankWaves + (int)(threadIdx.x / kWave)) * per_wave + group;
     const int row = min(row_at, a.rows - 1);
     const bool mine = sub == 0 && row_at < a.rows;
-    const float b0 = a.b0[row], b1 = HIDDEN ? a.b1[row] : 0.f;
+    const bool base = !HIDDEN || a.b0;
+    const float b0 = base ? a.b0[row] : 0.f, b1 = HIDDEN && base ? a.b1[row] : 0.f;
     float res = 0.f;
     if (!HIDDEN && a.residual) res = Store<T>::to_f32(static_cast<const T*>(a.residual)[row]);
     float mix = 0.f;
@@ -295,14 +297,87 @@ __global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(c
         }
     }
     if (!mine) return;
-    if (HIDDEN)
-        a.b0[row] = mix;  // read above by this group of lanes alone
-    else
+    if (HIDDEN) {
+        if (base) a.b0[row] = mix;  // read above by this group of lanes alone
+    } else
         static_cast<T*>(a.y)[row] = Store<T>::from_f32(b0 + mix + res);
 }
 
+// ---- rank experts without a base (M_e = L_e R_e) --------------------------------------------------------
+// h_j = silu(L0_j t0_j) * (L1_j t1_j) for rows of r > 256: a wave belongs to one pair, whose two rank vectors
+// it keeps in registers, and requests both rows of its next unit before it sums the current one.
+// NC: 1 KB chunks per row.
+template <typename T, int NC>
+__global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_hidden_kernel(
+    const LowRankStage a) {
+    typedef Store<T> S;
+    typedef typename S::vec_t vec_t;
+    constexpr int VEC = S::VEC, CH = kWave * VEC;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int at = (int)blockIdx.x * kOneWaves + wave, waves = (int)gridDim.x * kOneWaves / a.k;  // per pair
+    const int j = at % a.k, n = a.r;
+    int row = at / a.k;
+    if (row >= waves || row >= a.rows) return;
+    int off[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) off[c] = min(c * CH + lane * VEC, n - VEC);
+    const bool tail_in = (NC - 1) * CH + lane * VEC < n;
+    const int e = min(max(a.idx[j], 0), a.E - 1);
+    const T* L0 = static_cast<const T*>(a.L0) + (size_t)e * a.stride;
+    const T* L1 = static_cast<const T*>(a.L1) + (size_t)e * a.stride;
+    float* h = a.h + (size_t)j * a.rows;
+    struct Rows {
+        vec_t w0[NC], w1[NC];
+    };
+    auto load = [&](Rows& r, int i) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            r.w0[c] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(L0 + (size_t)i * n + off[c]));
+            r.w1[c] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(L1 + (size_t)i * n + off[c]));
+        }
+    };
+    Rows r0, r1;
+    load(r0, row);
+    f32x4 t0[NC][VEC / 4], t1[NC][VEC / 4];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < VEC / 4; ++q) {
+            t0[c][q] = *reinterpret_cast<const f32x4*>(a.t0 + (size_t)j * n + off[c] + 4 * q);
+            t1[c][q] = *reinterpret_cast<const f32x4*>(a.t1 + (size_t)j * n + off[c] + 4 * q);
+            if (c + 1 == NC && !tail_in) t0[c][q] = t1[c][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    auto finish = [&](Rows& r, int i) {
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                const bool in = c + 1 < NC || tail_in;
+                s0 = fmaf(in ? S::get(r.w0[c], q) : 0.f, t0[c][q / 4][q % 4], s0);
+                s1 = fmaf(in ? S::get(r.w1[c], q) : 0.f, t1[c][q / 4][q % 4], s1);
+            }
+        s0 = wave_sum(s0);
+        s1 = wave_sum(s1);
+        if (lane == 0) h[i] = silu_f32(s0) * s1;
+    };
+    for (;;) {
+        const int next = row + waves;
+        if (next < a.rows) load(r1, next);
+        __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the sums
+        finish(r0, row);
+        if (next >= a.rows) return;
+        row = next + waves;
+        if (row < a.rows) load(r0, row);
+        __builtin_amdgcn_sched_barrier(0);
+        finish(r1, next);
+        if (row >= a.rows) return;
+    }
+}
+
 // td_j = R_d,j h_j for every pair, and y0 = M0_down mix: rows of one length against fp32 vectors, `slices`
-// waves each, NC chunks a wave and all of them requested at once.
+// waves each, NC chunks a wave and all of them requested at once.  (d = 0: the pairs alone)
 constexpr int kMidWaves = 8;
 template <typename T, int NC>
 __global__ __launch_bounds__(kMidWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void decode_mid_kernel(const MidStage a) {
@@ -488,6 +563,26 @@ int launch_decode_low_rank(LowRankStage a, bool hidden, hipStream_t st) {
         hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, true>), grid, block, 0, st, a);
     else
         hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, false>), grid, block, 0, st, a);
+    return launch_status();
+}
+
+constexpr int kHiddenMaxChunks = 3;  // two rank vectors and two units of two rows in 128 registers
+
+bool decode_rank_supported(const moe_shape& s) {
+    return decode_first_supported(s) && s.act_dtype == MOE_BF16 && s.rank > 0 && !(s.flags & MOE_FLAG_SHARED_BASE) &&
+           s.top_k <= kOneCus && chunks_of<bf16_t>(s.rank) <= kHiddenMaxChunks && mid_slices(s.top_k * s.rank, s.d_ff) != 0;
+}
+
+int launch_decode_hidden(const LowRankStage& a, hipStream_t st) {
+    if (a.r <= kWave / 2 * Store<bf16_t>::VEC) return launch_decode_low_rank(a, true, st);  // two and more rows per wave
+    const long long units = (long long)a.k * a.rows;
+    const dim3 grid((unsigned)std::min<long long>(kOneCus, (units + kOneWaves - 1) / kOneWaves)), block(kOneWaves * kWave);
+    switch (chunks_of<bf16_t>(a.r)) {
+        case 1: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 1>), grid, block, 0, st, a); break;
+        case 2: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 2>), grid, block, 0, st, a); break;
+        case 3: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 3>), grid, block, 0, st, a); break;
+        default: return MOE_ERR_UNSUPPORTED;
+    }
     return launch_status();
 }
 

@@ -47,7 +47,7 @@ struct LowRankStage {
     const void *L0, *L1;     // [E, rows, r]
     long long stride;
     const float *t0, *t1;    // [k][r]
-    float* b0;               // [rows]; hidden: replaced by the mix
+    float* b0;               // [rows]; hidden: replaced by the mix, or NULL (no base)
     const float* b1;         // [rows] (hidden)
     float* h;                // [k][rows] (hidden)
     int rows, r, E, k;
@@ -70,5 +70,9 @@ bool decode_base_supported(const moe_shape& s);
 inline size_t decode_base_bytes(const moe_shape& s) { return 2 * sizeof(float) * (size_t)s.d_ff; }
 int launch_decode_low_rank(LowRankStage a, bool hidden, hipStream_t st);
 int launch_decode_mid(MidStage a, hipStream_t st);
+
+// Rank experts without a base: first stage, hidden (fp32 hidden vectors), mid with d = 0, last stage.
+bool decode_rank_supported(const moe_shape& s);
+int launch_decode_hidden(const LowRankStage& a, hipStream_t st);
 
 }  // namespace moe

@@ -651,6 +651,8 @@ def test_forward_shared_base_once_per_token_ragged_widths(dev, oracle, T):
     (8, 16, 2, 2, 0, False, "f32"), (264, 2056, 8, 4, 0, False, "f32"), (1024, 1032, 4, 1, 0, False, "f32"),
     (1032, 264, 8, 2, 0, False, "f32"),
     (200, 328, 8, 2, 104, False, "bf16"), (520, 1064, 4, 1, 264, False, "bf16"),          # rank factors
+    (8, 8, 3, 3, 8, False, "bf16"), (2048, 5632, 8, 2, 1024, False, "bf16"), (264, 8200, 8, 3, 520, False, "bf16"),
+    (328, 1064, 8, 4, 1544, False, "bf16"), (392, 72, 16, 7, 256, False, "bf16"), (72, 4104, 4, 2, 1536, False, "bf16"),
     (8, 8, 2, 2, 8, True, "bf16"), (264, 520, 8, 3, 24, True, "bf16"), (1544, 4104, 16, 4, 136, True, "bf16"),  # shared base
     (520, 512, 8, 2, 520, True, "bf16"),                                                  # d above F: the general kernels
     (2048, 5632, 8, 2, 64, True, "bf16"),
