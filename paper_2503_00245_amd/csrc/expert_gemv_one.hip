@@ -89,7 +89,8 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
         return u;
     };
     auto load = [&](Rows& r, const Unit& u) {
-        const int e = max(__ffsll((unsigned long long)__ballot(slot == u.j)) - 1, 0);
+        // (clamped: with NaN logits the lanes may disagree about a round, and lanes past E may win it)
+        const int e = min(max(__ffsll((unsigned long long)__ballot(slot == u.j)) - 1, 0), a.E - 1);
         const size_t at = (size_t)e * a.stride + (size_t)u.row * n;
         const T* p0 = W0 + at;
         const T* p1 = W1 + at;

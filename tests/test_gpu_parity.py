@@ -663,6 +663,17 @@ def test_forward_one_token(dev, oracle, d, F, E, k, r, base, dtype, residual):
     _forward_case(dev, oracle, cfg, 1, residual=residual)
 
 
+@pytest.mark.parametrize("E", [5, 40])
+def test_forward_one_token_with_nan_logits(dev, E):
+    # no order among NaN logits: whichever lanes a round names, the weights read are an expert's
+    cfg = _cfg(d=264, F=520, E=E, dtype="bf16", seed=560 + E, std=0.05)
+    w_t = weights_to_device(wl.make_layer_weights(cfg), dev)
+    x_t = to_device(wl.make_inputs(cfg, 1), dev)
+    y, _, _ = _forward_gpu(dev, w_t, torch.full_like(x_t, float("nan")), cfg.top_k, DT["bf16"])
+    assert torch.isnan(y).all()
+    assert np.all(np.isfinite(to_f64(_forward_gpu(dev, w_t, x_t, cfg.top_k, DT["bf16"])[0])))
+
+
 @pytest.mark.parametrize("E,k,T,dtype", [
     (1, 1, 1, "f32"), (5, 3, 341, "f32"), (64, 8, 129, "f32"), (8, 2, 2048, "f32"), (8, 1, 4097, "f32"),  # up to 4096 pairs
     (3, 1, 5, "bf16"), (8, 2, 1024, "bf16"), (64, 8, 257, "bf16"), (7, 3, 1001, "bf16"),                  # up to 8192
