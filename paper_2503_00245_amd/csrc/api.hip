@@ -61,7 +61,8 @@ static Workspace carve_for(const moe_shape& s, const SplitPlan& plan) {
     ws.sort_scratch = take(permute_scratch_bytes((int)P, s.n_experts));
     ws.y_base = take(token_base_supported(s) ? (size_t)s.n_tokens * s.d_model * elt_size(s.act_dtype) : 0);
     ws.ffn_scratch = take(ffn_scratch_bytes(s));
-    ws.y_perm = take(P * s.d_model * elt_size(s.act_dtype) * plan.down);  // its partial outputs
+    const size_t y_size = plan.down > 1 && plan.down_f32 ? sizeof(float) : elt_size(s.act_dtype);
+    ws.y_perm = take(P * s.d_model * y_size * plan.down);  // its partial outputs
     if (plan.rank_down > 1) {  // its parts start inside ffn_scratch and run through y_perm and beyond
         const size_t end = ws.ffn_scratch + ffn_layout(s).tg + round_up(sizeof(float) * plan.rank_down * P * s.rank, 256);
         if (end > cur) take(end - cur);
@@ -78,7 +79,7 @@ static Workspace carve(const moe_shape& s) {
     SplitPlan plan = split_plan(s);
     Workspace ws = carve_for(s, plan);
     if (ws.total <= (size_t)MOE_STATIC_WORKSPACE_BYTES ||
-        carve_for(s, SplitPlan{1, 1, 1}).total > (size_t)MOE_STATIC_WORKSPACE_BYTES)
+        carve_for(s, SplitPlan{1, 1, 1, true}).total > (size_t)MOE_STATIC_WORKSPACE_BYTES)
         return ws;
     while (ws.total > (size_t)MOE_STATIC_WORKSPACE_BYTES) {
         for (int* q : {&plan.down, &plan.rank_down, &plan.base_down})
@@ -121,14 +122,14 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
         if (rc != MOE_OK) return rc;
         const int parts = ws.plan.base_down;
         const void* base = parts > 1 ? static_cast<void*>(ffn_scratch(s, wsp + ws.ffn_scratch).base_parts) : wsp + ws.y_base;
-        rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, base, 1, parts);
+        rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, base, 1, true, parts);
         stage_mark(timer, "combine");
         return rc;
     }
     rc = launch_expert_ffn(s, w, x, perm, s.top_k, offsets, wsp + ws.y_perm, wsp + ws.ffn_scratch, st,
                            timer, &ws.plan, keys, inv_perm);
     if (rc != MOE_OK) return rc;
-    rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, nullptr, ws.plan.down);
+    rc = launch_combine(s, wsp + ws.y_perm, inv_perm, gate, residual, y, st, nullptr, ws.plan.down, ws.plan.down_f32);
     stage_mark(timer, "combine");
     return rc;
 }

@@ -8,16 +8,18 @@
 
 namespace moe {
 
-template <typename T>
-__global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y_perm,
+// PARTS: partial outputs of y_perm, of type Y (known at compile time, so that the loads of a row are all in flight
+// together: 8 tokens of a 1024 / 2816 layer 38.9 -> 37.1 us)
+template <typename T, typename Y, int PARTS>
+__global__ __launch_bounds__(256) void combine_kernel(const Y* __restrict__ y_perm,
                                                       const int32_t* __restrict__ inv_perm,
                                                       const float* __restrict__ gate,
                                                       const T* __restrict__ residual,
                                                       const T* __restrict__ addend,
-                                                      T* __restrict__ y, int d, int k, int P, int parts,
+                                                      T* __restrict__ y, int d, int k, int P,
                                                       int addend_parts) {
     typedef Store<T> S;
-    constexpr int VEC = S::VEC;
+    constexpr int VEC = S::VEC, YV = VEC / Store<Y>::VEC;  // loads of y_perm per chunk of y
     typedef typename S::vec_t vec_t;
     const int t = blockIdx.x;
     for (int i = threadIdx.x * VEC; i < d; i += blockDim.x * VEC) {
@@ -27,11 +29,16 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y_pe
         for (int j = 0; j < k; ++j) {
             const int s = min(max(inv_perm[(size_t)t * k + j], 0), P - 1);
             const float g = gate[(size_t)t * k + j];
-            for (int part = 0; part < parts; ++part) {
-                const vec_t v = *reinterpret_cast<const vec_t*>(y_perm + ((size_t)part * P + s) * d + i);
+            const Y* row = y_perm + (size_t)s * d + i;
+            typename Store<Y>::vec_t v[PARTS][YV];
 #pragma unroll
-                for (int q = 0; q < VEC; ++q) acc[q] = fmaf(g, S::get(v, q), acc[q]);
-            }
+            for (int part = 0; part < PARTS; ++part, row += (size_t)P * d)
+#pragma unroll
+                for (int q = 0; q < YV; ++q) v[part][q] = reinterpret_cast<const typename Store<Y>::vec_t*>(row)[q];
+#pragma unroll
+            for (int part = 0; part < PARTS; ++part)
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) acc[q] = fmaf(g, Store<Y>::get(v[part][q / Store<Y>::VEC], q % Store<Y>::VEC), acc[q]);
         }
         if (residual) {
             const vec_t r = *reinterpret_cast<const vec_t*>(residual + (size_t)t * d + i);
@@ -60,21 +67,29 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y_pe
     }
 }
 
+template <typename T, typename Y, int PARTS>
+static int combine_on(const moe_shape& s, const void* y_perm, const int32_t* inv_perm, const float* topk_gate,
+                      const void* residual, void* y, hipStream_t st, const void* addend, int addend_parts) {
+    hipLaunchKernelGGL((combine_kernel<T, Y, PARTS>), dim3(s.n_tokens), dim3(256), 0, st, (const Y*)y_perm, inv_perm,
+                       topk_gate, (const T*)residual, (const T*)addend, (T*)y, s.d_model, s.top_k, s.n_tokens * s.top_k,
+                       addend_parts);
+    return launch_status();
+}
+
 int launch_combine(const moe_shape& s, const void* y_perm, const int32_t* inv_perm,
                    const float* topk_gate, const void* residual, void* y, hipStream_t st,
-                   const void* addend, int y_parts, int addend_parts) {
+                   const void* addend, int y_parts, bool y_parts_f32, int addend_parts) {
     if (s.n_tokens == 0) return MOE_OK;
-    const int P = s.n_tokens * s.top_k;
-    dim3 grid(s.n_tokens), block(256);
-    if (s.act_dtype == MOE_F32)
-        hipLaunchKernelGGL(combine_kernel<float>, grid, block, 0, st, (const float*)y_perm, inv_perm,
-                           topk_gate, (const float*)residual, (const float*)addend, (float*)y, s.d_model,
-                           s.top_k, P, y_parts, addend_parts);
-    else
-        hipLaunchKernelGGL(combine_kernel<bf16_t>, grid, block, 0, st, (const bf16_t*)y_perm,
-                           inv_perm, topk_gate, (const bf16_t*)residual, (const bf16_t*)addend, (bf16_t*)y,
-                           s.d_model, s.top_k, P, y_parts, addend_parts);
-    return launch_status();
+    auto on = [&](auto run) { return run(s, y_perm, inv_perm, topk_gate, residual, y, st, addend, addend_parts); };
+    if (s.act_dtype == MOE_F32) return y_parts == 1 ? on(combine_on<float, float, 1>) : MOE_ERR_INVALID;
+    static_assert(kMaxParts == 4, "one to four parts");
+    switch (y_parts) {
+        case 1: return on(combine_on<bf16_t, bf16_t, 1>);
+        case 2: return on(y_parts_f32 ? combine_on<bf16_t, float, 2> : combine_on<bf16_t, bf16_t, 2>);
+        case 3: return on(y_parts_f32 ? combine_on<bf16_t, float, 3> : combine_on<bf16_t, bf16_t, 3>);
+        case 4: return on(y_parts_f32 ? combine_on<bf16_t, float, 4> : combine_on<bf16_t, bf16_t, 4>);
+        default: return MOE_ERR_INVALID;
+    }
 }
 
 }  // namespace moe

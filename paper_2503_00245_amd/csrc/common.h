@@ -134,18 +134,20 @@ int launch_gather_rows(const moe_shape& s, const int32_t* perm, const void* x, v
 
 // addend: optional second per-token term [T, d] (beside the residual), in the activation type, or, with
 // addend_parts > 1, the sum of that many fp32 partial outputs [T, d], one after the other.
-// y_parts > 1: y_perm holds that many partial outputs [P, d], one after the other, to be added.
+// y_parts > 1: y_perm holds that many partial outputs [P, d], fp32 or in the activation type, one after the
+// other, to be added.
 int launch_combine(const moe_shape& s, const void* y_perm, const int32_t* inv_perm,
                    const float* topk_gate, const void* residual, void* y, hipStream_t st,
-                   const void* addend = nullptr, int y_parts = 1, int addend_parts = 1);
+                   const void* addend = nullptr, int y_parts = 1, bool y_parts_f32 = true, int addend_parts = 1);
 
 // Products whose k-steps are cut into parts to fill the chip, by shape (bf16): the final down projection
-// (parts [P, d] in the activation type, added by the combine), the rank-down product of weight-decomposed
+// (parts [P, d], fp32 if down_f32, else in the activation type, added by the combine), the rank-down product of weight-decomposed
 // experts (fp32 parts [P, r], added by a kernel of its own) and the down projection of a shared base
 // (fp32 parts [T, d], added by the combine).  1: not cut.
 constexpr int kMaxParts = 4;
 struct SplitPlan {
     int down, rank_down, base_down;
+    bool down_f32;
 };
 SplitPlan split_plan(const moe_shape& s);
 
@@ -173,7 +175,7 @@ inline FfnScratch ffn_scratch(const moe_shape& s, void* base) {
 // keys: NULL, or the pairs' experts [P]: then a_row_map, offsets and inv_perm are not read but written, by the
 // first product (only where ffn_takes_keys).
 bool ffn_takes_keys(const moe_shape& s, const int32_t* keys);
-// plan: NULL = nothing is cut, y_perm is one output [P, d].  Otherwise y_perm has room for plan->down outputs and
+// plan: NULL = nothing is cut, y_perm is one output [P, d].  Otherwise y_perm has room for plan->down outputs (of plan->down_f32) and
 // receives that many.
 inline size_t ffn_scratch_bytes(const moe_shape& s) { return ffn_layout(s).end; }
 int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,

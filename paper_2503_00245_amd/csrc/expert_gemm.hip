@@ -561,18 +561,42 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
     return MOE_ERR_UNSUPPORTED;  // bf16 rows that are not whole 16-byte chunks (the entry points reject them)
 }
 
+// Parts of the final down projection are sums like any other and kept in fp32, except for tall groups with
+// enough 256-row tiles (four parts of each, one per expert at least, make some 220 workgroups) and a long K: there
+// they may be rounded to bf16, each like y_perm itself, because twice the traffic costs what the cut saves (fp32
+// against bf16 parts, whole layer: 2048 tokens 2048 / 5632 323 us against 311, 777 tokens 1440 / 3840 96.8 against 92.4,
+// 2048 tokens 1024 / 2816 107 against 101; below, fp32 parts cost nothing: 8 tokens 2048 / 5632 99.4 against 100.2, up to
+// 128 tokens within 1 %).  Rounding errors do not grow with it on independent data (2.3e-3 of the result either
+// way), but parts that cancel lose bits that one sum keeps, so the number of bf16 parts is also bounded by the
+// one that alone counts full rounds of 256 workgroups (steps of 32 and 12 of fixed cost each).  1: none.
+static int bf16_parts_max(long long P, int E, int N, int K) {
+    const int n256 = (N + 255) / 256, steps = K / 32;
+    const long long tiles = (P / 256 + (E + 1) / 2) * n256;
+    if (P <= 24 * E || tiles >= 400 || K % 32 != 0 || K < 2048 || (P / 256 + E) * n256 * 4 < 224) return 1;
+    int best = 1;
+    long long best_cost = 0;
+    for (int q = 2; q <= kMaxParts; ++q) {
+        const long long cost = (tiles * q + 255) / 256 * (steps / q + 12);
+        if (best == 1 || cost < best_cost) best_cost = cost, best = q;
+    }
+    return best;
+}
+
 SplitPlan split_plan(const moe_shape& s) {
-    SplitPlan p{1, 1, 1};
+    SplitPlan p{1, 1, 1, true};
     if (s.act_dtype != MOE_BF16 || s.n_tokens == 0) return p;
     const long long P = (long long)s.n_tokens * s.top_k;
     const bool base = s.flags & MOE_FLAG_SHARED_BASE, token_base = token_base_supported(s);
     if (!base || token_base) {
         const int K = s.rank > 0 ? s.rank : s.d_ff;
-        // (parts are rounded to the activation type: only where a tile's chain of k-steps is long)
-        p.down = token_base || K <= 1024 ? 1 : gemm_pp_split(P, s.n_experts, s.d_model, K, false, false);
-        if (s.rank > 0) p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, true, true);
+        if (!token_base && K > 1024) {  // (only where a tile's chain of k-steps is long)
+            const int bf16_max = bf16_parts_max(P, s.n_experts, s.d_model, K);
+            p.down_f32 = bf16_max == 1;
+            p.down = gemm_pp_split(P, s.n_experts, s.d_model, K, p.down_f32 ? kMaxParts : bf16_max, p.down_f32, false);
+        }
+        if (s.rank > 0) p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, kMaxParts, true, true);
         if (token_base) {
-            p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff, true, false);
+            p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff, kMaxParts, true, false);
             const FfnLayout l = ffn_layout(s);  // its parts lie in what h .. bu held
             while (p.base_down > 1 && sizeof(float) * p.base_down * (size_t)s.n_tokens * s.d_model > l.end - l.h) --p.base_down;
         }
@@ -678,6 +702,7 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
         g.nseg = ns; g.N = d; g.C = y_perm; g.hidden_a = 1;
         if (plan) {
             g.k_parts = plan->down;
+            g.parts_f32 = plan->down_f32;
             g.parts = y_perm;
         }
         if ((rc = run_gemm(s, g, false, st)) != MOE_OK) return rc;

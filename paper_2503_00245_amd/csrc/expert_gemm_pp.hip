@@ -454,10 +454,14 @@ bool gemm_pp_supported(const GemmArgs& g) {
 // more k-steps of A LDS holds (two of 256 rows, four of 128 or 64).  Few rows per group and narrow outputs
 // want small tiles, large groups tall ones; cutting K pays where the tiles are too few for the CUs (the
 // 2048-wide down projection of 4096 rows has 160 of 256 x 256) or the chain of k-steps of a tile is long.
-// Parts are written and read at 6 TB/s; a launch of its own that adds them costs 5 us.
+// Parts are written and read at 6 TB/s, in place of the 4 bytes of one bf16 output; a launch of its own that adds
+// them, and leaves that output all the same, costs 5 us.
 // Checked against (us): gate/up of the 2048 / 5632 layer at 4 to 32 rows per expert 80 / 79 with 128 / 64 rows
 // against 82 with 256, at 64 rows 88 with 128 against 96; of the 1024 / 2816 layer at 128 rows 28 with
-// 256 against 38 with 128; down projection at 2048 tokens 99 in three parts, 115 in one.
+// 256 against 38 with 128; down projection at 2048 tokens 107 in three bf16 parts, 115 in three fp32 ones, 124 in one.
+// fp32 parts forced to 1 to 4 at 36 sizes from 128 to 6000 tokens on four layers (432 to 2048 wide): the count taken
+// here is within 2 % of the fastest, 3 % once (whole layer, 1 / 2 / 3 / 4 parts: 2048 / 5632 at 128 tokens 127 / 115 /
+// 115 / 115; 1024 / 2816 at 128 tokens 49.9 / 43.5 / 41.4 / 40.6, at 512 tokens 59.8 / 56.2 / 53.8 / 53.8).
 struct PpChoice {
     int bm, parts;
 };
@@ -480,7 +484,7 @@ static PpChoice choose(long long P, int E, int N, int K, int copies, bool swiglu
             if (step < mfma) step = mfma;
             if (step < latency) step = latency;
             double cost = rounds * (steps * step / q + 6);
-            if (q > 1) cost += (double)(f32 ? q * 8 : (q - 1) * 4) * P * N / 6e6 + (sum_launch ? 5 : 0);
+            if (q > 1) cost += (double)(!f32 ? (q - 1) * 4 : sum_launch ? q * 8 : q * 8 - 4) * P * N / 6e6 + (sum_launch ? 5 : 0);
             if ((bm == 256 && q == 1) || cost < best_cost) {
                 best_cost = cost;
                 best = PpChoice{bm, q};
@@ -490,9 +494,9 @@ static PpChoice choose(long long P, int E, int N, int K, int copies, bool swiglu
     return best;
 }
 
-int gemm_pp_split(long long P, int E, int N, int K, bool parts_f32, bool sum_launch) {
+int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f32, bool sum_launch) {
     if (P <= 0 || !rows_supported(P, N, K)) return 1;
-    return choose(P, E, N, K, 1, false, false, kMaxParts, parts_f32, sum_launch).parts;
+    return choose(P, E, N, K, 1, false, false, parts_max, parts_f32, sum_launch).parts;
 }
 
 int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {

@@ -308,8 +308,9 @@ int run_gemm_f32(GemmArgs& g, bool swiglu, hipStream_t st);
 constexpr int kPpThreads = 512;
 bool gemm_pp_supported(const GemmArgs& g);
 int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st);
-// Parts into which it is worth cutting the k-steps of a plain product of P rows in E groups (k_parts above)
-int gemm_pp_split(long long P, int E, int N, int K, bool parts_f32, bool sum_launch);
+// Parts, up to parts_max, into which it is worth cutting the k-steps of a plain product of P rows in E groups
+// (k_parts above)
+int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f32, bool sum_launch);
 int launch_sum_parts(const float* parts, int q, long long n, void* out, hipStream_t st);
 
 }  // namespace moe

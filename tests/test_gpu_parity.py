@@ -593,6 +593,7 @@ def test_forward_seeded_prefill_sweep(dev, oracle, d, F, E, k, r, base, T):
     (256, 2048, 3, 2, 1500),   # 32 steps of 64 cut into 4 parts of 8
     (256, 2080, 2, 1, 2000),   # 32 whole steps and a tail of 32: only the last part holds the tail
     (512, 4128, 2, 2, 1100),   # 64.5 steps, two output tiles per row tile
+    (1792, 2048, 8, 2, 96), (1792, 2048, 8, 2, 97),   # parts in fp32 up to 24 rows per expert, in bf16 from there on
 ])
 def test_forward_down_projection_cut_along_k(dev, oracle, d, F, E, k, T):
     # tall groups, a narrow output and a long K: the down projection's 256 x 256 tiles are too few
@@ -622,7 +623,22 @@ def test_forward_down_projection_cut_along_k(dev, oracle, d, F, E, k, T):
     pkg.moe_combine(shape, yp, inv, gate, None, y3)
     torch.cuda.synchronize()
     assert np.array_equal(idx.cpu().numpy(), idx1)
-    assert rel_err(to_f64(y1), to_f64(y3)) < 1e-2  # parts are rounded to bf16 one by one
+    assert rel_err(to_f64(y1), to_f64(y3)) < 1e-2  # bf16 parts are rounded one by one
+
+
+@pytest.mark.parametrize("d,F,T", [(256, 2048, 3), (256, 2048, 90), (512, 4096, 16), (256, 1152, 500), (512, 4096, 700)])
+def test_forward_down_projection_whose_halves_of_k_cancel(dev, oracle, d, F, T):
+    # Hidden unit j + F/2 repeats unit j, and its column of the down projection is minus that of j but for a
+    # 128th: the halves of K are about a hundred times their sum.  One fp32 sum, or fp32 parts of it, is off by
+    # some 100 x 2^-24 x sqrt(F), far below the rounding of the result; parts rounded to bf16 (2^-9 each) would
+    # be off by half of it.
+    cfg = _cfg(name="cancel", d=d, F=F, E=4, k=2, dtype="bf16", seed=1300 + F + T, std=0.04)
+    w_np = wl.make_layer_weights(cfg, with_bias=False)
+    for name in ("w_gate", "w_up"):
+        w_np[name][:, F // 2:] = w_np[name][:, :F // 2]
+    w_np["w_down"][:, :, F // 2:] = wl.f32_to_bf16_bits(
+        wl.bf16_bits_to_f32(w_np["w_down"][:, :, :F // 2]) * np.float32(-127 / 128))
+    _forward_case(dev, oracle, cfg, T, w_np, sample=100)
 
 
 @pytest.mark.parametrize("k,E,T", [(2, 8, 2), (2, 8, 37), (2, 8, 600), (3, 5, 150), (8, 8, 64), (2, 16, 9)])
