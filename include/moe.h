@@ -170,7 +170,7 @@ MOE_API int moe_forward(const moe_shape* shape, const moe_weights* weights, cons
  * call on a device).  The call allocates and frees nothing.
  *   - shapes whose moe_workspace_bytes() exceeds MOE_STATIC_WORKSPACE_BYTES are refused with
  *     MOE_ERR_WORKSPACE before any launch (single-token steps of every size fit; a 2048 / 5632
- *     layer up to about 140 tokens);
+ *     layer up to 239 tokens);
  *   - every call on one GPU uses that GPU's one array: calls that overlap in time on the same GPU
  *     (two streams, two threads) race; calls on one stream, or otherwise ordered, are fine.
  *     Nothing in the array has to be cleared between calls.
@@ -256,7 +256,8 @@ MOE_API int moe_offload_counters(const int32_t* trace, int32_t L, int32_t T, int
 MOE_API int moe_delta_uniform(const int32_t* trace, int32_t L, int32_t T, int32_t K, int32_t E,
                               int64_t* counts, double* delta, double* mean, void* stream);
 
-/* Bytes of workspace that any entry point above needs for this shape (0 if invalid). */
+/* Bytes of workspace that any entry point above needs for this shape (0 if invalid).  Does not fall as n_tokens
+ * grows: a workspace for the largest batch serves every smaller one of the same layer. */
 MOE_API size_t moe_workspace_bytes(const moe_shape* shape);
 
 /* Static, NUL-terminated description of a status code. */

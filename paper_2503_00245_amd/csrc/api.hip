@@ -43,9 +43,27 @@ struct Workspace {
     SplitPlan plan;
 };
 
-static Workspace carve_for(const moe_shape& s, const SplitPlan& plan) {
+// Room for partial outputs (SplitPlan) beside the one output a product has anyway.  It grows with the number of
+// tokens and does not depend on whether a given number is worth a cut: a workspace sized for the largest
+// batch holds every smaller one.  y_perm: four fp32 parts up to 32 MB, two (or four in bf16) up to the
+// 200 MB of the largest product that bf16_parts_max cuts; larger ones fill the chip uncut.  Rank-down
+// (from tg on, see FfnScratch): four fp32 parts up to the same 200 MB.
+constexpr size_t kWidePartsBytes = 32u << 20, kPartsBytes = 200u << 20;
+static size_t parts_end(const moe_shape& s, size_t ffn_scratch, size_t y_perm) {
+    if (s.act_dtype != MOE_BF16) return 0;
+    const size_t P = (size_t)s.n_tokens * s.top_k, out = P * s.d_model, rank = P * s.rank;
+    size_t end = 0;
+    if (down_cut_supported(s)) {
+        const size_t wide = out * 16 < kWidePartsBytes ? out * 16 : kWidePartsBytes, two = out * 8 < kPartsBytes ? out * 8 : kPartsBytes;
+        end = y_perm + (wide > two ? wide : two);
+    }
+    const size_t rank_end = ffn_scratch + ffn_layout(s).tg + (rank * 16 < kPartsBytes ? rank * 16 : kPartsBytes);
+    if (s.rank > 0 && rank_end > end) end = rank_end;
+    return round_up(end, 256);
+}
+
+static Workspace carve(const moe_shape& s) {
     Workspace ws{};
-    ws.plan = plan;
     const size_t P = (size_t)s.n_tokens * s.top_k;
     size_t cur = 0;
     auto take = [&](size_t bytes) {
@@ -61,38 +79,30 @@ static Workspace carve_for(const moe_shape& s, const SplitPlan& plan) {
     ws.sort_scratch = take(permute_scratch_bytes((int)P, s.n_experts));
     ws.y_base = take(token_base_supported(s) ? (size_t)s.n_tokens * s.d_model * elt_size(s.act_dtype) : 0);
     ws.ffn_scratch = take(ffn_scratch_bytes(s));
-    const size_t y_size = plan.down > 1 && plan.down_f32 ? sizeof(float) : elt_size(s.act_dtype);
-    ws.y_perm = take(P * s.d_model * y_size * plan.down);  // its partial outputs
-    if (plan.rank_down > 1) {  // its parts start inside ffn_scratch and run through y_perm and beyond
-        const size_t end = ws.ffn_scratch + ffn_layout(s).tg + round_up(sizeof(float) * plan.rank_down * P * s.rank, 256);
-        if (end > cur) take(end - cur);
+    ws.y_perm = take(P * s.d_model * elt_size(s.act_dtype));
+    const bool decode = decode_supported(s);
+    const size_t stack_bytes = round_up((size_t)s.n_tokens * s.d_model * elt_size(s.act_dtype), 256);
+    const size_t tail = round_up(decode_scratch_bytes(s, 1), 256) + (stack_bytes ? stack_bytes : 256);
+    ws.plan = SplitPlan{1, 1, 1, true};
+    if (!decode) {
+        // (parts must not push a shape out of the allocation-free entry point's array)
+        size_t end = parts_end(s, ws.ffn_scratch, ws.y_perm);
+        if (cur + tail <= (size_t)MOE_STATIC_WORKSPACE_BYTES && end + tail > (size_t)MOE_STATIC_WORKSPACE_BYTES)
+            end = (size_t)MOE_STATIC_WORKSPACE_BYTES - tail;
+        if (end > cur) cur = end;
+        ws.plan = split_plan(s, cur - ws.y_perm, cur - ws.ffn_scratch - ffn_layout(s).tg);
     }
-    ws.decode_scratch = take(decode_scratch_bytes(s));
-    ws.stack_tmp = take((size_t)s.n_tokens * s.d_model * elt_size(s.act_dtype));
+    ws.decode_scratch = take(decode_scratch_bytes(s, 1));
+    // two tokens: back into y_perm and the FFN's scratch, which such a step leaves idle
+    if (decode) ws.decode_scratch = cur - round_up(decode_scratch_bytes(s, s.n_tokens), 256);
+    ws.stack_tmp = take(stack_bytes);
     ws.total = cur;
     return ws;
 }
 
-// (Parts must not push a shape out of the allocation-free entry point's array: there the plan is cut
-// back until it fits.)
-static Workspace carve(const moe_shape& s) {
-    SplitPlan plan = split_plan(s);
-    Workspace ws = carve_for(s, plan);
-    if (ws.total <= (size_t)MOE_STATIC_WORKSPACE_BYTES ||
-        carve_for(s, SplitPlan{1, 1, 1, true}).total > (size_t)MOE_STATIC_WORKSPACE_BYTES)
-        return ws;
-    while (ws.total > (size_t)MOE_STATIC_WORKSPACE_BYTES) {
-        for (int* q : {&plan.down, &plan.rank_down, &plan.base_down})
-            if (*q > 1) --*q;
-        ws = carve_for(s, plan);
-    }
-    return ws;
-}
-
 static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x, void* y,
-                        int32_t* topk_idx, float* topk_gate, char* wsp, hipStream_t st,
+                        int32_t* topk_idx, float* topk_gate, const Workspace& ws, char* wsp, hipStream_t st,
                         StageTimer* timer = nullptr) {
-    const Workspace ws = carve(s);
     int32_t* idx = topk_idx ? topk_idx : reinterpret_cast<int32_t*>(wsp + ws.topk_idx);
     float* gate = topk_gate ? topk_gate : reinterpret_cast<float*>(wsp + ws.topk_gate);
     if (decode_supported(s)) {
@@ -240,9 +250,9 @@ int moe_forward(const moe_shape* shape, const moe_weights* weights, const void* 
     if ((rc = validate_weights(*shape, weights, true)) != MOE_OK) return rc;
     if (shape->n_tokens == 0) return MOE_OK;
     if (!x || !y || x == y || !aligned16(x) || !aligned16(y)) return MOE_ERR_INVALID;
-    if (!workspace || !aligned16(workspace) || workspace_bytes < carve(*shape).total)
-        return MOE_ERR_WORKSPACE;
-    return forward_impl(*shape, *weights, x, y, topk_idx, topk_gate, static_cast<char*>(workspace),
+    const Workspace ws = carve(*shape);
+    if (!workspace || !aligned16(workspace) || workspace_bytes < ws.total) return MOE_ERR_WORKSPACE;
+    return forward_impl(*shape, *weights, x, y, topk_idx, topk_gate, ws, static_cast<char*>(workspace),
                         as_stream(stream));
 }
 
@@ -253,11 +263,12 @@ int moe_forward_static(const moe_shape* shape, const moe_weights* weights, const
     if ((rc = validate_weights(*shape, weights, true)) != MOE_OK) return rc;
     if (shape->n_tokens == 0) return MOE_OK;
     if (!x || !y || x == y || !aligned16(x) || !aligned16(y)) return MOE_ERR_INVALID;
-    if (carve(*shape).total > (size_t)MOE_STATIC_WORKSPACE_BYTES) return MOE_ERR_WORKSPACE;
+    const Workspace ws = carve(*shape);
+    if (ws.total > (size_t)MOE_STATIC_WORKSPACE_BYTES) return MOE_ERR_WORKSPACE;
     char* wsp = nullptr;
     if ((rc = static_scratch(&wsp)) != MOE_OK) return rc;
     // nothing in the workspace has to start at zero: every stage writes what the next one reads
-    return forward_impl(*shape, *weights, x, y, topk_idx, topk_gate, wsp, as_stream(stream));
+    return forward_impl(*shape, *weights, x, y, topk_idx, topk_gate, ws, wsp, as_stream(stream));
 }
 
 int moe_forward_timed(const moe_shape* shape, const moe_weights* weights, const void* x, void* y,
@@ -270,14 +281,14 @@ int moe_forward_timed(const moe_shape* shape, const moe_weights* weights, const 
     if ((rc = validate_weights(*shape, weights, true)) != MOE_OK) return rc;
     if (shape->n_tokens == 0) return MOE_OK;
     if (!x || !y || x == y || !aligned16(x) || !aligned16(y)) return MOE_ERR_INVALID;
-    if (!workspace || !aligned16(workspace) || workspace_bytes < carve(*shape).total)
-        return MOE_ERR_WORKSPACE;
+    const Workspace ws = carve(*shape);
+    if (!workspace || !aligned16(workspace) || workspace_bytes < ws.total) return MOE_ERR_WORKSPACE;
     StageTimer timer{};
     timer.st = as_stream(stream);
     for (auto& e : timer.ev)
         if (hipEventCreate(&e) != hipSuccess) return MOE_ERR_LAUNCH;
     (void)hipEventRecord(timer.ev[0], timer.st);
-    rc = forward_impl(*shape, *weights, x, y, nullptr, nullptr, static_cast<char*>(workspace),
+    rc = forward_impl(*shape, *weights, x, y, nullptr, nullptr, ws, static_cast<char*>(workspace),
                       timer.st, &timer);
     if (hipStreamSynchronize(timer.st) != hipSuccess && rc == MOE_OK) rc = MOE_ERR_LAUNCH;
     if (rc == MOE_OK) {
@@ -314,7 +325,7 @@ int moe_stack_forward(const moe_shape* shape, const moe_weights* layers, int32_t
         // ping-pong so that the last layer writes y and no layer reads what it writes
         void* out = ((n_layers - l) & 1) ? y : tmp;
         rc = forward_impl(s, layers[l], cur, out, topk_trace ? topk_trace + (size_t)l * Pk : nullptr,
-                          nullptr, wsp, as_stream(stream));
+                          nullptr, ws, wsp, as_stream(stream));
         if (rc != MOE_OK) return rc;
         cur = out;
     }

@@ -149,11 +149,13 @@ struct SplitPlan {
     int down, rank_down, base_down;
     bool down_f32;
 };
-SplitPlan split_plan(const moe_shape& s);
+bool down_cut_supported(const moe_shape& s);
+// down_bytes, rank_bytes: room for the down projection's and the rank-down product's outputs
+SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes);
 
 // Scratch of the expert FFN, in the activation type except for the parts.  The order is that of memory:
 // rank_parts ([rank_down][P, r] fp32) starts at tg, which is consumed by then, as are bg and bu, and runs on
-// into y_perm, not yet written, and what follows it; base_parts ([base_down][T, d] fp32) starts at h and
+// into y_perm, not yet written, and the room for parts behind it; base_parts ([base_down][T, d] fp32) starts at h and
 // ends before y_perm.
 struct FfnScratch {
     void *td, *z, *h, *tg, *tu, *bg, *bu;
@@ -195,7 +197,7 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
 
 // Single-token layer: routed, experts chosen on the device from topk_idx, weights streamed once.
 // base_scratch: decode_base_bytes (gemv.h) for a layer with a shared base, or NULL.
-size_t decode_scratch_bytes(const moe_shape& s);
+size_t decode_scratch_bytes(const moe_shape& s, int n_tokens);
 int launch_decode(const moe_shape& s, const moe_weights& w, const void* x, int32_t* topk_idx,
                   float* topk_gate, void* y, void* scratch, float* base_scratch, hipStream_t st,
                   StageTimer* timer = nullptr);

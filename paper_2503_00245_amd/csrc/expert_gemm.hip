@@ -582,24 +582,34 @@ static int bf16_parts_max(long long P, int E, int N, int K) {
     return best;
 }
 
-SplitPlan split_plan(const moe_shape& s) {
+// Whether the final down projection may be cut: only where a tile's chain of k-steps is long (and not the
+// low-rank term of a shared base, or a product of two segments)
+bool down_cut_supported(const moe_shape& s) {
+    return s.act_dtype == MOE_BF16 && !(s.flags & MOE_FLAG_SHARED_BASE) && (s.rank > 0 ? s.rank : s.d_ff) > 1024;
+}
+
+SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes) {
     SplitPlan p{1, 1, 1, true};
     if (s.act_dtype != MOE_BF16 || s.n_tokens == 0) return p;
     const long long P = (long long)s.n_tokens * s.top_k;
     const bool base = s.flags & MOE_FLAG_SHARED_BASE, token_base = token_base_supported(s);
-    if (!base || token_base) {
+    auto at_most = [](int parts, size_t room, long long out_bytes) {
+        return (long long)room < parts * out_bytes ? (int)((long long)room / out_bytes) : parts;
+    };
+    if (down_cut_supported(s)) {
         const int K = s.rank > 0 ? s.rank : s.d_ff;
-        if (!token_base && K > 1024) {  // (only where a tile's chain of k-steps is long)
-            const int bf16_max = bf16_parts_max(P, s.n_experts, s.d_model, K);
-            p.down_f32 = bf16_max == 1;
-            p.down = gemm_pp_split(P, s.n_experts, s.d_model, K, p.down_f32 ? kMaxParts : bf16_max, p.down_f32, false);
-        }
-        if (s.rank > 0) p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, kMaxParts, true, true);
-        if (token_base) {
-            p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff, kMaxParts, true, false);
-            const FfnLayout l = ffn_layout(s);  // its parts lie in what h .. bu held
-            while (p.base_down > 1 && sizeof(float) * p.base_down * (size_t)s.n_tokens * s.d_model > l.end - l.h) --p.base_down;
-        }
+        const int bf16_max = bf16_parts_max(P, s.n_experts, s.d_model, K);
+        p.down_f32 = bf16_max == 1;
+        p.down = gemm_pp_split(P, s.n_experts, s.d_model, K,
+                               at_most(p.down_f32 ? kMaxParts : bf16_max, down_bytes, P * s.d_model * (p.down_f32 ? 4 : 2)),
+                               p.down_f32, false);
+    }
+    if (s.rank > 0 && (!base || token_base))
+        p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, at_most(kMaxParts, rank_bytes, P * s.rank * 4), true, true);
+    if (token_base) {
+        const FfnLayout l = ffn_layout(s);  // its parts lie in what h .. bu held
+        p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff,
+                                    at_most(kMaxParts, l.end - l.h, (long long)s.n_tokens * s.d_model * 4), true, false);
     }
     return p;
 }

@@ -620,8 +620,8 @@ bool decode_supported(const moe_shape& s) {
 }
 
 // scratch: h [P][F] fp32 (in the activation type once P F floats outgrow the L1), then (rank > 0) tg, tu, td [P][r] fp32
-size_t decode_scratch_bytes(const moe_shape& s) {
-    const size_t P = decode_supported(s) ? (size_t)s.n_tokens * s.top_k : (size_t)s.top_k;
+size_t decode_scratch_bytes(const moe_shape& s, int n_tokens) {
+    const size_t P = (size_t)n_tokens * s.top_k;
     return round_up(sizeof(float) * P * ((size_t)s.d_ff + 3 * (size_t)s.rank), 256);
 }
 

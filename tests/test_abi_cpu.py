@@ -39,6 +39,33 @@ def test_workspace_bytes_by_shape():
     assert pkg.moe_workspace_bytes(pkg.make_shape(0, 128, 256, 4, 2)) > 0
 
 
+@pytest.mark.parametrize("d,F,E,k,r,act,flags", [
+    (2048, 5632, 8, 2, 0, pkg.MOE_BF16, 0), (1024, 2816, 8, 2, 0, pkg.MOE_BF16, 0), (1440, 3840, 16, 4, 0, pkg.MOE_BF16, 0),
+    (432, 1152, 4, 1, 0, pkg.MOE_BF16, 0), (8, 4096, 64, 40, 0, pkg.MOE_BF16, 0),
+    (2048, 5632, 8, 2, 1024, pkg.MOE_BF16, 0), (520, 1040, 8, 3, 1064, pkg.MOE_BF16, 0), (400, 1064, 8, 2, 200, pkg.MOE_BF16, 0),
+    (2048, 5632, 8, 2, 64, pkg.MOE_BF16, 1), (264, 520, 4, 1, 1064, pkg.MOE_BF16, 1), (64, 2056, 8, 8, 40, pkg.MOE_BF16, 1),
+    (128, 256, 4, 2, 0, pkg.MOE_F32, 0), (512, 1408, 8, 2, 256, pkg.MOE_F32, 1),
+])
+def test_a_workspace_for_more_tokens_holds_fewer(d, F, E, k, r, act, flags):
+    # a server sizes one workspace for its largest batch: the size must not fall as the tokens grow
+    tokens = list(range(1, 1200)) + list(range(1200, 20000, 13))
+    sizes = [pkg.moe_workspace_bytes(pkg.make_shape(t, d, F, E, k, r, act, flags)) for t in tokens]
+    falls = [t for t, a, b in zip(tokens[1:], sizes, sizes[1:]) if b < a]
+    assert not falls, f"{len(falls)} token counts need less than the one before, first {falls[:5]}"
+    # one token takes no part of the grouped products' cuts: what a step of its own kind needs
+    es = 4 if act == pkg.MOE_F32 else 2
+    per_token = k * (F + 3 * r + d) * es + (3 * F + d) * es * (flags & 1) + d * es + 5 * 4 * k
+    assert sizes[0] <= per_token + 4 * k * (F + 3 * r) + 4 * E + 16 * 256
+
+
+def test_parts_keep_within_the_allocation_free_entry_points_array():
+    # largest batches of the shapes that the array holds (no parts there), and the ones behind them
+    for (d, F, E, k, r, flags), t in (((2048, 5632, 8, 2, 0, 0), 239), ((1024, 2816, 8, 2, 0, 0), 479),
+                                      ((2048, 5632, 8, 2, 1024, 0), 176), ((2048, 5632, 8, 2, 64, 1), 113)):
+        assert pkg.moe_workspace_bytes(pkg.make_shape(t, d, F, E, k, r, pkg.MOE_BF16, flags)) <= pkg.STATIC_WORKSPACE_BYTES
+        assert pkg.moe_workspace_bytes(pkg.make_shape(t + 1, d, F, E, k, r, pkg.MOE_BF16, flags)) > pkg.STATIC_WORKSPACE_BYTES
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(top_k=0), -1), (dict(top_k=5), -1), (dict(n_tokens=-1), -1), (dict(rank=-8), -1),
     (dict(flags=1), -1),                 # shared base without a rank

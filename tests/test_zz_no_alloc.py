@@ -54,6 +54,22 @@ def test_static_entry_point_matches_moe_forward_on_two_calls_in_a_row(oracle, ki
         assert rel_err(to_f64(y1)[same], ref[same]) < 2e-2
 
 
+@pytest.mark.parametrize("T", [200, 300, 425])
+def test_static_entry_point_where_its_array_limits_the_parts(oracle, T):
+    # 19.5 KB of scratch per token and 4 KB per fp32 part: room for four parts of the down projection, for two, for none
+    dev = torch.device("cuda:0")
+    cfg = wl.shrink(wl.CONFIGS["wearables"], d_model=512, d_ff=4096)
+    w_np = wl.make_layer_weights(cfg, with_bias=False)
+    w_t = weights_to_device(w_np, dev)
+    x_np = wl.make_inputs(cfg, T)
+    (y0, i0, g0), (y1, i1, g1) = _both(dev, w_t, x_np, cfg.top_k, False)
+    assert torch.equal(i0, i1) and torch.equal(g0, g1) and torch.equal(y0, y1)
+    ref, ridx, _ = oracle.forward(w_np, x_np, cfg.top_k)
+    same = np.all(i1.cpu().numpy() == ridx, axis=1)
+    assert same.mean() > 0.97
+    assert rel_err(to_f64(y1)[same], ref[same]) < 2e-2
+
+
 def test_static_entry_point_refuses_large_shapes_and_leaves_outputs_alone():
     dev = torch.device("cuda:0")
     cfg = wl.shrink(wl.CONFIGS["wearables"], d_model=512, d_ff=1024)
