@@ -6,11 +6,11 @@
 //     realised expert balance from the uniform one, and its mean over layers.
 // All integer work uses integer atomics (order-independent, hence deterministic); the one
 // floating-point reduction (Eq. 6) sums fixed shares of the tokens in a fixed order and adds the
-// shares' sums in fp64, again in a fixed order.
+// shares' sums, again in a fixed order; both in fp64, but for the four differences of one load.
 // What bounds these kernels is launches: each dependent one costs 4-5 us however little it does, and
 // the data (2 MB for 24 layers of 2048 tokens) is read in about that time.  So every entry point is
 // one or two launches, and what is left of serial work runs on a workgroup instead of a thread
-// (all four calls on 24 x 2048 tokens, 2 of 8 experts: 120 us before, 35 now).
+// (all four calls on 24 x 2048 tokens, 2 of 8 experts: 120 us before, 29 now).
 #include "common.h"
 
 namespace moe {
@@ -71,34 +71,36 @@ __global__ __launch_bounds__(kMetricThreads) void replacements_kernel(
 }
 
 // Partial sums of a workgroup's share of the tokens, soft part |W[b,t+1,e] - W[b,t,e]| and hard part
-// (number of replaced experts), to partial[2 * block] (fp32) and partial[2 * block + 1] (int32).
-// Nothing is accumulated in memory, so nothing has to be cleared first.
+// (number of replaced experts), to soft_part[block] and hard_part[block].  Nothing is accumulated in memory,
+// so nothing has to be cleared first.
 __global__ __launch_bounds__(kMetricThreads) void bles_partial_kernel(
     const float* __restrict__ W, const int32_t* __restrict__ S, int B, int T, int K, int E,
-    int tokens_per_block, int vec, float* __restrict__ partial) {
-    __shared__ float s_soft[kMetricThreads / kWave];
+    int tokens_per_block, int vec, double* __restrict__ soft_part, int* __restrict__ hard_part) {
+    __shared__ double s_soft[kMetricThreads / kWave];
     __shared__ int s_hard[kMetricThreads / kWave];
     const int t0 = blockIdx.x * tokens_per_block;
     const int t1 = min(B * T, t0 + tokens_per_block);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     int hard = 0;
     for (int i = t0 + threadIdx.x; i < t1; i += kMetricThreads) hard += __popcll(replaced_set(S, i, t1, T, K, E));
-    float soft = 0.f;
+    double soft = 0.0;
     if (vec) {  // rows of W are whole, aligned 16-byte chunks
         const int q = E / 4;
         const f32x4* w = reinterpret_cast<const f32x4*>(W);
         for (int c = t0 * q + threadIdx.x; c < t1 * q; c += kMetricThreads) {
             if ((c / q) % T == T - 1) continue;
             const f32x4 v = w[c + q] - w[c];
-            soft += (fabsf(v[0]) + fabsf(v[1])) + (fabsf(v[2]) + fabsf(v[3]));
+            soft += (double)((fabsf(v[0]) + fabsf(v[1])) + (fabsf(v[2]) + fabsf(v[3])));
         }
     } else {
         for (int c = t0 * E + threadIdx.x; c < t1 * E; c += kMetricThreads)
-            if ((c / E) % T != T - 1) soft += fabsf(W[c + E] - W[c]);
+            if ((c / E) % T != T - 1) soft += (double)fabsf(W[c + E] - W[c]);
     }
-    soft = wave_sum(soft);
 #pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) hard += __shfl_xor(hard, m, kWave);
+    for (int m = 1; m < kWave; m <<= 1) {
+        soft += __shfl_xor(soft, m, kWave);
+        hard += __shfl_xor(hard, m, kWave);
+    }
     if (lane == 0) {
         s_soft[wave] = soft;
         s_hard[wave] = hard;
@@ -109,8 +111,8 @@ __global__ __launch_bounds__(kMetricThreads) void bles_partial_kernel(
             soft += s_soft[w];
             hard += s_hard[w];
         }
-        partial[2 * blockIdx.x] = soft;
-        reinterpret_cast<int*>(partial)[2 * blockIdx.x + 1] = hard;
+        soft_part[blockIdx.x] = soft;
+        hard_part[blockIdx.x] = hard;
     }
 }
 
@@ -118,14 +120,15 @@ __global__ __launch_bounds__(kMetricThreads) void bles_partial_kernel(
 // i, i + 256, ... in fp64 and the threads meet in a fixed tree (deterministic).  (One thread adding
 // all of them was a chain of 1536 dependent load-and-adds at 24 x 2048 tokens: 64 us.)
 __global__ __launch_bounds__(kMetricThreads) void bles_finalize_kernel(
-    const float* __restrict__ partial, int nblocks, int B, int T, int K, double* __restrict__ out) {
+    const double* __restrict__ soft_part, const int* __restrict__ hard_part, int nblocks, int B, int T, int K,
+    double* __restrict__ out) {
     __shared__ double s_soft[kMetricThreads];
     __shared__ unsigned long long s_hard[kMetricThreads];
     double L = 0.0;
     unsigned long long H = 0;
     for (int i = threadIdx.x; i < nblocks; i += kMetricThreads) {
-        L += (double)partial[2 * i];
-        H += (unsigned)reinterpret_cast<const int*>(partial)[2 * i + 1];
+        L += soft_part[i];
+        H += (unsigned)hard_part[i];
     }
     s_soft[threadIdx.x] = L;
     s_hard[threadIdx.x] = H;
@@ -289,17 +292,23 @@ int moe_bles_loss(const float* probs, const int32_t* S, int32_t B, int32_t T, in
     if (!probs || !S || !out) return MOE_ERR_INVALID;
     if (!workspace || workspace_bytes < moe_bles_workspace_bytes(B, T, E)) return MOE_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
-    // a pair of partial sums per workgroup; the size query has room for one float per 256 elements of
-    // W beside the counters' 768 bytes, and a workgroup takes at least 1024 elements
-    float* partial = static_cast<float*>(workspace);
+    // 12 bytes of partial sums per workgroup; the size query has room for 4 per 256 differences of W beside 768
+    // bytes, and a workgroup takes at least 1024 elements, more where that is too many workgroups (T = 2)
+    char* const first = reinterpret_cast<char*>(round_up(reinterpret_cast<uintptr_t>(workspace), sizeof(double)));
+    const size_t room = moe_bles_workspace_bytes(B, T, E) - sizeof(double);
+    const int max_blocks = (int)min(room / (sizeof(double) + sizeof(int)), (size_t)1 << 30);
+    double* soft_part = reinterpret_cast<double*>(first);
+    int* hard_part = nullptr;
     int nblocks = 0;
     if (T > 1) {
-        const int tokens_per_block = max(kMetricThreads / 2, (4 * kMetricThreads + E - 1) / E);
+        const int tokens_per_block = max(max(kMetricThreads / 2, (4 * kMetricThreads + E - 1) / E), (B * T - 1) / max_blocks + 1);
         nblocks = (B * T - 1) / tokens_per_block + 1;
+        hard_part = reinterpret_cast<int*>(soft_part + nblocks);
         hipLaunchKernelGGL(bles_partial_kernel, dim3(nblocks), dim3(kMetricThreads), 0, st, probs, S, B, T, K, E,
-                           tokens_per_block, E % 4 == 0 && aligned16(probs) ? 1 : 0, partial);
+                           tokens_per_block, E % 4 == 0 && aligned16(probs) ? 1 : 0, soft_part, hard_part);
     }
-    hipLaunchKernelGGL(bles_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, partial, nblocks, B, T, K, out);
+    hipLaunchKernelGGL(bles_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, soft_part, hard_part, nblocks, B, T, K,
+                       out);
     return launch_status();
 }
 

@@ -909,6 +909,31 @@ def test_bles_loss_value_matches_oracle(dev, oracle, B, T, K, E):
         assert abs(got[i] - ref[key]) <= 2e-6 * max(abs(ref[key]), 1e-30), (key, got[i], ref[key])
 
 
+@pytest.mark.parametrize("B,T,E,offset", [(1, 2048, 64, 0), (3, 700, 8, 0), (2, 999, 7, 0), (1, 4096, 64, 1), (9000, 2, 8, 0)])
+def test_bles_loss_adds_its_differences_in_fp64(dev, B, T, E, offset):
+    # Probabilities that alternate between 0 and c: every difference is c, and so is exact, as are the sums of
+    # the four of one 16-byte load.  What is left are fp64 sums; fp32 ones of more terms would round in one
+    # direction (1e-8 and more of the result).  B T tokens in pairs (T = 2) need more partial sums per element
+    # than the workspace holds for long sequences.  offset: rows that are not 16-byte aligned.
+    c = np.float32(1 / 3)
+    store = torch.zeros(B * T * E + offset, dtype=torch.float32, device=dev)
+    W = store[offset:].view(B, T, E)
+    W[:, 1::2] = float(c)
+    S = torch.zeros((B, T, 1), dtype=torch.int32, device=dev)
+    S[:, 1::2] = 1
+    out = torch.full((5,), -1.0, dtype=torch.float64, device=dev)
+    ws = torch.empty(pkg.moe_bles_workspace_bytes(B, T, E) + 4, dtype=torch.uint8, device=dev)
+    for ws_at in (0, 4):
+        out.fill_(-1.0)
+        pkg.moe_bles_loss(W, S, out, ws[ws_at:])
+        torch.cuda.synchronize()
+        H, Hn, L, Ln, loss = out.cpu().tolist()
+        ref = float(c) * B * (T - 1) * E
+        assert H == 2 * B * (T - 1) and Hn == 1.0
+        assert abs(L - ref) <= 1e-13 * ref and abs(Ln - ref / (B * T)) <= 1e-13 * ref / (B * T)
+        assert loss == Ln
+
+
 def test_bles_loss_from_the_routers_own_probabilities(dev, oracle):
     cfg = _cfg(d=256, E=8, k=2, dtype="bf16", seed=77, std=0.3)
     w_np = wl.make_layer_weights(cfg, with_bias=False)
