@@ -33,7 +33,9 @@ typedef __attribute__((address_space(3))) char lds_char;
 
 // 64 lanes x 16 bytes from memory straight to 1 KB of LDS at byte address lds (wave-uniform).  The compiler
 // does not see these loads: they are waited for by hand (wait_vm), and what it inserts for loads of
-// its own can only wait longer.  NT: the data is used once, here; it need not stay in the caches.
+// its own can only wait longer.  NT: the data is used once, here; it need not stay in the caches.  (m0 is
+// reserved to the compiler, which sets it right before an instruction of its own that reads it and accepts no
+// clobber of it; these kernels have no such instruction: every m0 in their assembly is one of these moves.)
 template <bool NT>
 __device__ __forceinline__ void dma16(unsigned lds, const char* base, unsigned off) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -41,8 +43,8 @@ __device__ __forceinline__ void dma16(unsigned lds, const char* base, unsigned o
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base)
                      : "memory");
     else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
-                 : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+                     : "memory");
 #endif
 }
 // at most N of the wave's memory loads are still in flight afterwards (they complete in order)
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32 = false, bool NT_B = (BM <= 128)>
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B>
 int launch_pp(GemmArgs& g, hipStream_t st) {
     constexpr int BN_OUT = SWIGLU && !DUAL ? BN / 2 : BN;
     g.m_tiles_max = g.P / BM + g.E;
@@ -432,6 +434,11 @@ int launch_pp(GemmArgs& g, hipStream_t st) {
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, g);
     return launch_status();
+}
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32 = false>
+int launch_pp(GemmArgs& g, bool nt, hipStream_t st) {
+    return nt ? launch_pp<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, true>(g, st)
+              : launch_pp<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, false>(g, st);
 }
 
 }  // namespace
@@ -509,25 +516,26 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     // tokens 124 -> 114, 256 tokens 129 -> 120; where the m-tiles of an expert share its weights in L2 it
     // hurts: 2048 tokens 313 -> 326.)  Drawn at an average of 256 rows per expert, one tile of the tallest kind:
     // 512 tokens 1024 / 2816 55.9 -> 51.9, 777 tokens 1440 / 3840 94.7 -> 91.7.
+    // The smaller tiles follow the same line (whole layer, us, hint at every size / by this rule: 1100 tokens 432 / 1152
+    // 37.9 / 33.2, 1024 / 2816 80.1 / 78.4, 400 / 1064 of rank 200 51.6 / 45.3; 2048 tokens on a shared base 282.8 / 280.4; two
+    // of 32 sizes were faster with it, 512 tokens on the shared base of 2048 / 5632 142.7 without and 138.3 with).
     const bool nt = g.P <= 256 * g.E;
     if (!swiglu) {
         const bool f32 = g.k_parts > 1 && g.parts_f32;
         if (bm == 64)
-            return f32 ? launch_pp<64, 256, 2, 4, 4, false, false, true>(g, st) : launch_pp<64, 256, 2, 4, 4, false, false>(g, st);
+            return f32 ? launch_pp<64, 256, 2, 4, 4, false, false, true>(g, nt, st) : launch_pp<64, 256, 2, 4, 4, false, false>(g, nt, st);
         if (bm == 128)
-            return f32 ? launch_pp<128, 256, 2, 4, 3, false, false, true>(g, st) : launch_pp<128, 256, 2, 4, 3, false, false>(g, st);
-        if (nt)
-            return f32 ? launch_pp<256, 256, 2, 2, 3, false, false, true, true>(g, st) : launch_pp<256, 256, 2, 2, 3, false, false, false, true>(g, st);
-        return f32 ? launch_pp<256, 256, 2, 2, 3, false, false, true>(g, st) : launch_pp<256, 256, 2, 2, 3, false, false>(g, st);
+            return f32 ? launch_pp<128, 256, 2, 4, 3, false, false, true>(g, nt, st) : launch_pp<128, 256, 2, 4, 3, false, false>(g, nt, st);
+        return f32 ? launch_pp<256, 256, 2, 2, 3, false, false, true>(g, nt, st) : launch_pp<256, 256, 2, 2, 3, false, false>(g, nt, st);
     }
     if (dual) {
-        if (bm == 64) return launch_pp<64, 128, 2, 8, 6, true, true>(g, st);
-        if (bm == 128) return launch_pp<128, 128, 4, 4, 5, true, true>(g, st);
-        return nt ? launch_pp<256, 128, 4, 2, 3, true, true, false, true>(g, st) : launch_pp<256, 128, 4, 2, 3, true, true>(g, st);
+        if (bm == 64) return launch_pp<64, 128, 2, 8, 6, true, true>(g, nt, st);
+        if (bm == 128) return launch_pp<128, 128, 4, 4, 5, true, true>(g, nt, st);
+        return launch_pp<256, 128, 4, 2, 3, true, true>(g, nt, st);
     }
-    if (bm == 64) return launch_pp<64, 256, 2, 4, 4, true, false>(g, st);
-    if (bm == 128) return launch_pp<128, 256, 2, 4, 3, true, false>(g, st);
-    return nt ? launch_pp<256, 256, 2, 2, 3, true, false, false, true>(g, st) : launch_pp<256, 256, 2, 2, 3, true, false>(g, st);
+    if (bm == 64) return launch_pp<64, 256, 2, 4, 4, true, false>(g, nt, st);
+    if (bm == 128) return launch_pp<128, 256, 2, 4, 3, true, false>(g, nt, st);
+    return launch_pp<256, 256, 2, 2, 3, true, false>(g, nt, st);
 }
 
 // out = sum of the parts, in part order, rounded once; n a multiple of 8
