@@ -105,7 +105,8 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 def _stream(device) -> int:
     """Handle of the device's current stream.  Read straight from the runtime's record of it: building the
     torch.cuda.Stream object around the same handle was a third of a call's host time, and calls of one
-    token or a few launches wait for the host."""
+    token or a few launches wait for the host.  (The function is private to torch; where it is missing, the
+    public object is made.)"""
     if _raw_stream is None or device.type != "cuda" or device.index is None:
         return torch.cuda.current_stream(device).cuda_stream
     return _raw_stream(device.index)

@@ -14,8 +14,9 @@
 // operand reads over all banks.  Tiles are enumerated expert-major, then n-tile, then the
 // expert's m-tiles, and the workgroup id is remapped so that each XCD walks a contiguous
 // eighth of that order (consecutive tiles share a weight tile and hit in that XCD's L2).
-// run_gemm picks the tile shape from the pair count and the output width; products with enough rows
-// for 256-row tiles run in expert_gemm_pp.hip.
+// run_gemm picks the tile shape from the pair count and the output width.  bf16 products of one K-segment of 64
+// or more without per-token addends run in expert_gemm_pp.hip; what is left for the kernel here are the
+// shared base's low-rank SwiGLU product (addends), its staged form (two segments) and small or huge K and N.
 // fp32 problems: expert_gemm_f32.hip.
 #include "gemm.h"
 
@@ -60,8 +61,9 @@ constexpr int split_slots() {
 // That puts two full steps of MFMA work between issuing a global load and first needing
 // its data.  Loads are unconditional (rows past the end of a group / matrix are clamped to
 // its last row and only feed outputs the epilogue never stores), so the loop has no
-// divergent control flow.  (Direct global->LDS loads were measured here and rejected:
-// on this chip they stall co-issued MFMAs far more than register loads do.)
+// divergent control flow.  (Direct global->LDS loads gained nothing in this
+// schedule, where a step's loads are issued together and hold back the MFMAs behind them;
+// expert_gemm_pp.hip spreads them between the MFMAs.)
 //
 // KG > 1: the workgroup holds KG groups of (BM / WM) * (BN / WN) waves.  Every group runs
 // the whole pipeline on its own 1/KG of the k-steps, with its own LDS stages, and the
@@ -515,7 +517,7 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
     bool fast = s.act_dtype != MOE_F32;
     for (int i = 0; i < g.nseg; ++i) fast &= g.seg[i].K >= 8 && g.seg[i].K % 8 == 0;  // rows are read in 16-byte chunks
     if (!fast || !gemm_pp_supported(g)) g.k_parts = 0;
-    if (g.C1 && !fast) {  // only the deep kernel takes two products per launch: run them one by one
+    if (g.C1 && !fast) {  // only the bf16 kernels take two products per launch: run them one by one
         GemmArgs second = g;
         second.C = g.C1;
         second.C1 = nullptr;

@@ -1,5 +1,5 @@
-// Grouped bf16 GEMM for products with enough rows per expert to be bound by the matrix cores (gemm.h
-// states the problem): 256-row tiles on eight waves, operands fetched from memory straight into LDS.
+// Grouped bf16 GEMM of one K-segment without addends (gemm.h states the problem): 256-, 128- or 64-row tiles on
+// eight waves, operands fetched from memory straight into LDS.
 //
 // What bounds it.  A 256 x 256 x 64 k-step is 2048 clocks of MFMA per SIMD; beside them go 64 KB of fills
 // (L1 takes about 64 B per clock: 1024 clocks) and 192 KB of fragment reads (128 B per clock: 1536).  All
@@ -11,9 +11,10 @@
 //   - fills go only between MFMAs, one per four 16-clock MFMAs or more, B by group 0 and A by group 1, and
 //     nothing in the loop branches (a scalar branch around each fill: 3600 clocks again);
 //   - B, the weights, has three k-steps in LDS and A two (160 KB): weights come from HBM.
-// 2320-2760 clocks per step, and then the board's power limit sets the clock (1.6-1.9 GHz from 2.2), so
-// what counts next is energy: 16 x 16 x 32 MFMAs move half the accumulator bytes of 32 x 32 x 16 ones and
-// run 5 % faster at the same schedule.
+// 2490 clocks per step (what 16 more steps per tile add at 16384 tokens; 16 K clocks per round of tiles beside
+// it), and then the board's power limit sets the clock (1.8 GHz there, from 2.2), so what counts next is
+// energy: 16 x 16 x 32 MFMAs move half the accumulator bytes of 32 x 32 x 16 ones and run 5 % faster at the
+// same schedule.
 // Measured on the 2048 / 5632 layer, Zipf loads (us; the register-staged kernel before / this one):
 // gate/up 222 / 189 and down 115 / 99 at 2048 tokens; 1410 / 1180 and 720 / 601 at 16384 tokens
 // (1.28 PFLOP/s).

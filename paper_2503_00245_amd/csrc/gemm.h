@@ -37,7 +37,7 @@ struct GemmArgs {
     GemmSeg seg[2];
     int nseg;
     void* C;            // [P, N]
-    void* C1;           // PLAIN only, deep kernel: second product (A1 . B1) of the same shape, or NULL
+    void* C1;           // PLAIN only, bf16 kernels: second product (A1 . B1) of the same shape, or NULL
     int N;
     int32_t* offsets;        // [E+1]
     int32_t* row_map;        // [P] or NULL
@@ -46,7 +46,7 @@ struct GemmArgs {
     int P;
     int m_tiles_max;
     int n_tiles;        // n-tiles of the launch (twice those of one product when C1 is set)
-    // SWIGLU, deep kernel: per-token rows added to the two accumulators before the activation
+    // SWIGLU, gemm_bf16_deep_kernel: per-token rows added to the two accumulators before the activation
     // (the token of sorted slot s is row_map[s] / row_div), [*, N] in the activation type, or NULL
     const void* add0;
     const void* add1;
