@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoe_mi355x.so")
 SOURCES = ["api.hip", "route.hip", "permute.hip", "combine.hip", "expert_gemv.hip", "expert_gemv_one.hip", "expert_gemm.hip", "expert_gemm_f32.hip",
-           "expert_gemm_pp.hip",
+           "expert_gemm_pp.hip", "expert_gemm_few.hip",
            "metrics.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -150,6 +150,7 @@ struct SplitPlan {
     bool down_f32;
 };
 bool down_cut_supported(const moe_shape& s);
+bool few_two_tokens(const moe_shape& s);  // two tokens take the prefill's stages
 // down_bytes, rank_bytes: room for the down projection's and the rank-down product's outputs
 SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes);
 

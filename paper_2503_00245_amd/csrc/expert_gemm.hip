@@ -516,7 +516,8 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
     const int n_eff = g.N * (g.C1 ? 2 : 1);  // output columns of the launch
     bool fast = s.act_dtype != MOE_F32;
     for (int i = 0; i < g.nseg; ++i) fast &= g.seg[i].K >= 8 && g.seg[i].K % 8 == 0;  // rows are read in 16-byte chunks
-    if (!fast || !gemm_pp_supported(g)) g.k_parts = 0;
+    const bool few = fast && gemm_few_supported(g);
+    if (!fast || !(few || gemm_pp_supported(g))) g.k_parts = 0;
     if (g.C1 && !fast) {  // only the bf16 kernels take two products per launch: run them one by one
         GemmArgs second = g;
         second.C = g.C1;
@@ -530,6 +531,7 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
         return rc != MOE_OK ? rc : run_gemm(s, second, swiglu, st);
     }
     if (s.act_dtype == MOE_F32) return run_gemm_f32(g, swiglu, st);
+    if (few) return run_gemm_few(g, swiglu, st);
     if (fast && gemm_pp_supported(g)) return run_gemm_pp(g, swiglu, st);
     if (fast) {
         // What is left: products with per-token addends, with two segments, with K below 64 or operands of
@@ -590,11 +592,26 @@ bool down_cut_supported(const moe_shape& s) {
     return s.act_dtype == MOE_BF16 && !(s.flags & MOE_FLAG_SHARED_BASE) && (s.rank > 0 ? s.rank : s.d_ff) > 1024;
 }
 
+// Rows that a group can have, for the kernels of few rows: a token meets an expert once
+static int few_rows(const moe_shape& s) {
+    return s.act_dtype == MOE_BF16 && gemm_few_rows((long long)s.n_tokens * s.top_k, s.top_k) ? s.n_tokens : 0;
+}
+
+// Two tokens of dense experts on those kernels (else on the matrix-vector path): where that path would not have
+// kept the hidden vectors in fp32 -- from there on it is the slower one, too, unless each token has one expert (us,
+// matrix-vector path / this: 2048 / 5632 60.5 / 52.0, 1024 / 2816 26.3 / 24.5, 4 of 16 experts 44.0 / 36.5, 4 of 4 42.6 / 25.2; 1
+// of 8 17.3 / 19.7)
+bool few_two_tokens(const moe_shape& s) {
+    return s.n_tokens == 2 && few_rows(s) && s.rank == 0 && s.top_k > 1 && 2ll * s.top_k * s.d_ff * 4 > 32 * 1024 &&
+           s.d_model <= 2048 && down_cut_supported(s) && gemm_few_split(s.d_ff, 2, kMaxParts);
+}
+
 SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes) {
     SplitPlan p{1, 1, 1, true};
     if (s.act_dtype != MOE_BF16 || s.n_tokens == 0) return p;
     const long long P = (long long)s.n_tokens * s.top_k;
     const bool base = s.flags & MOE_FLAG_SHARED_BASE, token_base = token_base_supported(s);
+    const bool few = few_rows(s) > 0;
     auto at_most = [](int parts, size_t room, long long out_bytes) {
         return (long long)room < parts * out_bytes ? (int)((long long)room / out_bytes) : parts;
     };
@@ -602,16 +619,22 @@ SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes) {
         const int K = s.rank > 0 ? s.rank : s.d_ff;
         const int bf16_max = bf16_parts_max(P, s.n_experts, s.d_model, K);
         p.down_f32 = bf16_max == 1;
-        p.down = gemm_pp_split(P, s.n_experts, s.d_model, K,
-                               at_most(p.down_f32 ? kMaxParts : bf16_max, down_bytes, P * s.d_model * (p.down_f32 ? 4 : 2)),
-                               p.down_f32, false);
+        p.down = few ? gemm_few_split(K, 2, at_most(kMaxParts, down_bytes, P * s.d_model * 4)) : 0;  // (in fp32: cut)
+        if (p.down) p.down_f32 = true;
+        else p.down = gemm_pp_split(P, s.n_experts, s.d_model, K,
+                                    at_most(p.down_f32 ? kMaxParts : bf16_max, down_bytes, P * s.d_model * (p.down_f32 ? 4 : 2)),
+                                    p.down_f32, false);
     }
-    if (s.rank > 0 && (!base || token_base))
-        p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, at_most(kMaxParts, rank_bytes, P * s.rank * 4), true, true);
+    if (s.rank > 0 && (!base || token_base)) {
+        const int room = at_most(kMaxParts, rank_bytes, P * s.rank * 4);
+        p.rank_down = few ? gemm_few_split(s.d_ff, 1, room) : 0;
+        if (!p.rank_down) p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, room, true, true);
+    }
     if (token_base) {
         const FfnLayout l = ffn_layout(s);  // its parts lie in what h .. bu held
-        p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff,
-                                    at_most(kMaxParts, l.end - l.h, (long long)s.n_tokens * s.d_model * 4), true, false);
+        const int room = at_most(kMaxParts, l.end - l.h, (long long)s.n_tokens * s.d_model * 4);
+        p.base_down = few ? gemm_few_split(s.d_ff, 2, room) : 0;
+        if (!p.base_down) p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff, room, true, false);
     }
     return p;
 }
@@ -679,6 +702,7 @@ int launch_expert_ffn(const moe_shape& s, const moe_weights& w, const void* x,
         GemmArgs g{};
         g.offsets = offsets; g.row_map = a_row_map; g.row_div = a_row_div > 0 ? a_row_div : 1;
         g.E = E; g.P = P;
+        g.few = few_rows(s);
         return g;
     };
     if (r > 0) {  // tg = x R_g^T, tu = x R_u^T   [P, r], both in one launch
@@ -743,11 +767,13 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
     auto grouped = [&]() {  // rows = pairs in expert order
         GemmArgs g{};
         g.offsets = offsets; g.row_map = perm; g.row_div = s.top_k; g.E = E; g.P = P;
+        g.few = few_rows(s);
         return g;
     };
     auto per_token = [&]() {  // rows = tokens, one group, one matrix
         GemmArgs g{};
         g.offsets = nullptr; g.row_map = nullptr; g.row_div = 1; g.E = 1; g.P = T;
+        g.few = few_rows(s);
         return g;
     };
     {  // tg = x R_g^T, tu = x R_u^T   [P, r]

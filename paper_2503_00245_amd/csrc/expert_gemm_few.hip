@@ -1,0 +1,438 @@
+// Grouped bf16 GEMM for few rows per group (gemm.h states the problem).
+//
+// What bounds it: the experts' weights, read once from HBM.  The direct-fill kernels read them behind barriers, a k-step of
+// 128 bytes per row at a time, and pay for two rounds of tiles: 8 tokens of 2048 / 5632, 290 MB of gate and up weights, took
+// 60 us there (4.8 TB/s) and take 49 here (5.9; a plain read of that size 47.5).  So here
+//   - one workgroup per CU walks an equal share of all (group, part of K, 16 output columns) units;
+//   - its eight waves split a unit's K, so that a wave's share of the activations stays in registers while the group's
+//     columns go by, and a unit ends in one sum over the waves through LDS, made by one wave in turn;
+//   - a wave has one to two chunks of eight 1 KB loads in flight, past the caches, in runs of 128 bytes and more per row: read in MFMA
+//     layout, 16 rows x 64 bytes per load, 288 MB come in at 5.0 TB/s, in whole lines at 6.3.  The way into MFMA
+//     layout is through a region of LDS of the wave's own, with no barrier;
+//   - the one barrier per unit waits for no load.
+#include "gemm.h"
+
+namespace moe {
+
+namespace {
+
+constexpr int kStepK = 32;      // k of one MFMA
+constexpr int kWaves = 8;       // per workgroup: two per SIMD, so a wave may hold 256 registers
+constexpr int kMaxSteps = 8;    // MFMA k-steps of a wave
+constexpr int kKeyWords = 4;    // pairs' keys per lane
+constexpr int kGrid = 256;      // one workgroup per CU
+
+__device__ __forceinline__ void lds_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
+
+// LDS written by one lane of a wave and read by another: the hardware keeps the order, the compiler has to
+__device__ __forceinline__ void wave_lds_order() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+#endif
+}
+// The lane index, counted anew: what is derived from it is computed where it is used, not kept in registers
+__device__ __forceinline__ int lane_again() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    int v = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(v));
+    return v;
+#else
+    return 0;
+#endif
+}
+__device__ __forceinline__ void wait_loads() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+#endif
+}
+
+// A unit's weights are requested in one or two chunks of up to eight loads.
+constexpr int chunk_steps(int s, bool pair) { return s * (pair ? 2 : 1) > 8 ? (s + 1) / 2 : s; }
+template <int MT, int S, bool PAIR>
+constexpr int region_bytes() {
+    constexpr int nm = PAIR ? 2 : 1, stage = nm * 16 * (chunk_steps(S, PAIR) * 64 + 16), part = nm * MT * kWave * 16;
+    return stage > part ? stage : part;
+}
+
+// NW: waves; wave w owns the w-th share of every row's k-steps (of the part's, where K is cut into parts).
+// MT: 16-row blocks of activations held.  S: k-steps of a wave, at most.
+// PAIR: two matrices (gate and up, or C and C1); SWIGLU: one output of both; DUAL: the second has activations of its own.
+// F32: k-parts in fp32.
+template <int NW, int MT, int S, bool PAIR, bool SWIGLU, bool DUAL, bool F32>
+__global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void gemm_few_kernel(const GemmArgs g) {
+    static_assert(!SWIGLU || PAIR, "the activation takes two products");
+    static_assert(!DUAL || PAIR, "two activation operands with two matrices");
+    constexpr int NM = PAIR ? 2 : 1, NX = DUAL ? 2 : 1, ROWS = 16 * MT;
+    constexpr int CS = chunk_steps(S, PAIR), CHUNKS = S > CS ? 2 : 1;
+    // LDS, per wave: two regions by turns, each first the weights on their way into MFMA layout, then the wave's
+    // partial sums [NM][MT][64]; and the group's pairs
+    constexpr int PITCH = CS * 64 + 16, REGION = region_bytes<MT, S, PAIR>();
+    extern __shared__ __align__(16) char smem[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int* const s_rows = reinterpret_cast<int*>(smem + 2 * NW * REGION) + wave * ROWS;
+    char* const my_region = smem + wave * REGION;
+
+    const GemmSeg& sg = g.seg[0];
+    const int K = sg.K, N = g.N, E = g.E;
+    const int parts = F32 ? g.k_parts : 1;
+    const int steps = (K + kStepK - 1) / kStepK, blocks = (N + 15) / 16;
+
+    // ---- groups: in lane e, group e's bounds
+    int lo, hi, key[kKeyWords];
+    if (g.keys) {
+#pragma unroll
+        for (int c = 0; c < kKeyWords; ++c) key[c] = c * kWave + lane < g.P ? g.keys[c * kWave + lane] : -1;
+        int at = 0;
+        lo = hi = 0;
+        int slot[kKeyWords];
+#pragma unroll
+        for (int c = 0; c < kKeyWords; ++c) slot[c] = -1;
+        for (int e = 0; e < E; ++e) {
+            if (lane == e) lo = at;
+#pragma unroll
+            for (int c = 0; c < kKeyWords; ++c) {
+                const unsigned long long same = __ballot(key[c] == e);
+                if (key[c] == e) slot[c] = at + lanes_below(same);
+                at += __popcll(same);
+            }
+            if (lane == e) hi = at;
+        }
+        if (blockIdx.x == 0 && wave == 0) {  // the sorted order, for later stages
+            if (lane < E) g.offsets[lane] = lo;
+            if (lane == E - 1) g.offsets[E] = hi;
+#pragma unroll
+            for (int c = 0; c < kKeyWords; ++c)
+                if (slot[c] >= 0) {
+                    g.row_map[slot[c]] = c * kWave + lane;
+                    g.inv_perm[c * kWave + lane] = slot[c];
+                }
+        }
+    } else {
+        group_bounds(g.offsets, E, g.P, lo, hi);
+    }
+
+    // ---- this workgroup's share of the units (group, part, 16 output columns), in that order
+    const int cnt = (hi - lo + ROWS - 1) / ROWS;  // a group of more than ROWS rows counts several times
+    int total = 0, before = 0;
+    for (int e = 0; e < E; ++e) {
+        before = lane == e ? total : before;
+        total += MOE_READLANE(cnt, e);
+    }
+    const int per_group = parts * blocks;
+    const long long units = (long long)total * per_group;
+    const int u_begin = (int)(units * blockIdx.x / kGrid), u_end = (int)(units * (blockIdx.x + 1) / kGrid);
+    if (u_begin >= u_end) return;
+
+    struct Unit {
+        int vg, e, row0, n;  // group counted with its repetitions; first sorted row and number of rows
+        int part, nb;
+        int s0, ns;  // the wave's k-steps
+    };
+    auto find_group = [&](Unit& u) {
+        const unsigned long long at = __ballot(lane < E && cnt > 0 && before <= u.vg);
+        u.e = 63 - __clzll((long long)at);
+        const int first = (u.vg - MOE_READLANE(before, u.e)) * ROWS;
+        u.row0 = MOE_READLANE(lo, u.e) + first;
+        u.n = min(ROWS, MOE_READLANE(hi, u.e) - u.row0);
+    };
+    auto find_steps = [&](Unit& u) {
+        const int p0 = uniform_div(steps * u.part, parts), p1 = uniform_div(steps * (u.part + 1), parts);
+        u.s0 = p0 + (p1 - p0) * wave / NW;
+        u.ns = p0 + (p1 - p0) * (wave + 1) / NW - u.s0;
+    };
+    auto next = [&](Unit u) {  // (asked for only if there is one)
+        if (++u.nb == blocks) {
+            u.nb = 0;
+            if (++u.part == parts) {
+                u.part = 0;
+                ++u.vg;
+                find_group(u);
+            }
+            if (F32) find_steps(u);
+        }
+        return u;
+    };
+
+    // ---- the wave's k-steps: step s covers bytes [64 (s0 + s), + 64) of every row.  What lies past the wave's share or the
+    // row's end is loaded from the last valid place and counts as zero in both operands; that can be part of the
+    // last two steps only.
+    struct Rows {
+        bf16x8 w[NM][CS];
+    };
+    auto pieces = [&](const Unit& u) { return min(u.ns * 4, K / 8 - u.s0 * 4); };  // valid 16-byte pieces of a row
+    // Load i of a chunk: rows lie in whole runs of H steps, first half of the chunk before the second (runs of
+    // 64 bytes, as MFMA operands lie, are read at 5.0 TB/s, of 128 and more at 6.3).
+    constexpr int H = CS > 4 ? (CS + 1) / 2 : CS;
+    auto piece = [&](int i, int ln, int& row, int& k) {
+        const bool tail = i >= H;
+        const int at = (tail ? i - H : i) * kWave + ln, len = 4 * (tail ? CS - H : H);
+        row = at / len;
+        k = at - row * len + (tail ? 4 * H : 0);
+    };
+    auto load = [&](auto chunk, Rows& r, const Unit& u) {
+        constexpr int C0 = decltype(chunk)::value * CS;
+        const int first = u.nb * 16, rows = min(N - first, 16), last = max(pieces(u) - 1, 0);
+        const size_t base = ((size_t)u.e * sg.strideB + (size_t)first * K) * 2 + (size_t)min(u.s0, steps - 1) * 64;
+        const int ln = lane_again();
+        const char* b[NM];
+        b[0] = static_cast<const char*>(sg.B0) + base;
+        if constexpr (PAIR) b[1] = static_cast<const char*>(sg.B1) + base;
+#pragma unroll
+        for (int i = 0; i < CS; ++i) {
+            int row, k;
+            piece(i, ln, row, k);
+            const unsigned off = (unsigned)min(row, rows - 1) * (unsigned)(K * 2) + (unsigned)min(C0 * 4 + k, last) * 16;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) r.w[m][i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(b[m] + off));
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the sums
+    };
+    bf16x8 x[NX][MT][S];
+    auto load_x = [&](const Unit& u) {
+        if (g.keys && sg.gather) {  // the group's pairs, in order
+            int rank = -u.row0 + MOE_READLANE(lo, u.e);
+#pragma unroll
+            for (int c = 0; c < kKeyWords; ++c) {
+                const unsigned long long same = __ballot(key[c] == u.e);
+                const int at = rank + lanes_below(same);
+                if (key[c] == u.e && (unsigned)at < (unsigned)ROWS) s_rows[at] = c * kWave + lane;
+                rank += __popcll(same);
+            }
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int m = min(mt * 16 + (lane & 15), u.n - 1);
+            int row = u.row0 + m;
+            if (sg.gather) {
+                row = g.keys ? s_rows[m] : g.row_map[row];
+                row = quick_div(min(max(row, 0), g.P - 1), g.row_div);
+            }
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                const char* a = static_cast<const char*>(i == 0 ? sg.A0 : sg.A1) + (size_t)row * (K * 2);
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const int k = s * 4 + (lane >> 4), n = pieces(u);
+                    x[i][mt][s] = *reinterpret_cast<const bf16x8*>(a + min(u.s0, steps - 1) * 64 + min(k, max(n - 1, 0)) * 16);
+                    if (s + 2 >= S && k >= n) x[i][mt][s] = bf16x8{};
+                }
+            }
+        }
+    };
+    int turn = 0;
+    f32x4 acc[NM][MT];
+    auto multiply = [&](auto chunk, const Rows& r, const Unit& u) {
+        constexpr int C0 = decltype(chunk)::value * CS, CN = S - C0 < CS ? S - C0 : CS;  // the chunk's first step, and steps
+        char* const stage = my_region + (turn & 1) * (NW * REGION);
+        const int n = pieces(u), ln = lane_again();
+        auto put = [&](auto whole) {
+#pragma unroll
+            for (int i = 0; i < CS; ++i) {
+                int row, k;
+                piece(i, ln, row, k);
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+                    *reinterpret_cast<bf16x8*>(stage + (m * 16 + row) * PITCH + k * 16) =
+                        decltype(whole)::value || C0 * 4 + k < n ? r.w[m][i] : bf16x8{};
+            }
+        };
+        if (n >= 4 * S) put(std::true_type{});
+        else put(std::false_type{});
+        wave_lds_order();
+#pragma unroll
+        for (int s = 0; s < CN; ++s)
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const bf16x8 w = *reinterpret_cast<const bf16x8*>(stage + (m * 16 + (lane & 15)) * PITCH + s * 64 + (lane >> 4) * 16);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[m][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x[DUAL ? m : 0][mt][C0 + s],
+                                                                         C0 + s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[m][mt], 0, 0, 0);
+            }
+        wave_lds_order();
+    };
+    auto finish = [&](const Unit& u) {
+        char* const buf = smem + (turn & 1) * (NW * REGION);
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<f32x4*>(buf + wave * REGION + ((m * MT + mt) * kWave + lane) * 16) = acc[m][mt];
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();  // (the other buffer's readers arrive here only when they have read it)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            if (wave != (turn * MT + mt) % NW) continue;
+            f32x4 sum[NM];
+#pragma unroll
+            for (int m = 0; m < NM; ++m) sum[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const char* at_w = buf + (mt * kWave + lane) * 16;
+#pragma unroll 1  // (all of them at once do not fit the registers beside the weights in flight)
+            for (int w0 = 0; w0 < NW; w0 += 4, at_w += 4 * REGION) {
+                f32x4 t[NM][4];
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) t[m][w] = *reinterpret_cast<const f32x4*>(at_w + w * REGION + m * (MT * kWave * 16));
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) sum[m] += t[m][w];
+            }
+            const int row = mt * 16 + (lane & 15), col = u.nb * 16 + (lane >> 4) * 4;
+            if (row < u.n && col < N) {
+                const size_t at = (size_t)(u.row0 + row) * N + col;
+                if constexpr (F32) {
+                    *reinterpret_cast<f32x4*>(static_cast<float*>(g.parts) + (size_t)u.part * ((size_t)g.P * N) + at) = sum[0];
+                } else {
+                    bf16x4 o, o1;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        o[j] = (bf16_t)(SWIGLU ? silu_f32(sum[0][j]) * sum[NM - 1][j] : sum[0][j]);
+                        o1[j] = (bf16_t)sum[NM - 1][j];
+                    }
+                    *reinterpret_cast<bf16x4*>(static_cast<bf16_t*>(g.C) + at) = o;
+                    if constexpr (PAIR && !SWIGLU) *reinterpret_cast<bf16x4*>(static_cast<bf16_t*>(g.C1) + at) = o1;
+                }
+            }
+        }
+        ++turn;
+    };
+
+    // (no load is conditional inside the loop, and a change of activations waits for them on the spot: what
+    // the compiler cannot count it waits for as a whole)
+    Rows r0, r1;
+    Unit u0, u1;
+    u0.vg = uniform_div(u_begin, per_group);
+    u0.part = uniform_div(u_begin - u0.vg * per_group, blocks);
+    u0.nb = u_begin - u0.vg * per_group - u0.part * blocks;
+    find_group(u0);
+    find_steps(u0);
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    load(c0, r0, u0);
+    load_x(u0);
+    auto change_x = [&](const Unit& from, const Unit& to) {
+        if (to.vg == from.vg && to.part == from.part) return;
+        load_x(to);
+        wait_loads();
+    };
+    if constexpr (CHUNKS == 1) {
+        for (int left = u_end - u_begin;;) {
+            if (--left == 0) {
+                multiply(c0, r0, u0);
+                finish(u0);
+                break;
+            }
+            u1 = next(u0);
+            load(c0, r1, u1);
+            multiply(c0, r0, u0);
+            finish(u0);
+            change_x(u0, u1);
+            if (--left == 0) {
+                multiply(c0, r1, u1);
+                finish(u1);
+                break;
+            }
+            u0 = next(u1);
+            load(c0, r0, u0);
+            multiply(c0, r1, u1);
+            finish(u1);
+            change_x(u1, u0);
+        }
+    } else {
+        for (int left = u_end - u_begin;;) {
+            load(c1, r1, u0);
+            multiply(c0, r0, u0);
+            if (--left == 0) break;
+            u1 = next(u0);
+            load(c0, r0, u1);
+            multiply(c1, r1, u0);
+            finish(u0);
+            change_x(u0, u1);
+            u0 = u1;
+        }
+        multiply(c1, r1, u0);
+        finish(u0);
+    }
+}
+
+// two activation operands: their registers beside the weights in flight
+constexpr bool dual_fits(int mt, int s) { return mt == 1 || s <= 6; }
+
+template <int MT, int S, bool PAIR, bool SWIGLU, bool DUAL, bool F32>
+int launch_few(const GemmArgs& g, hipStream_t st) {
+    constexpr int NW = kWaves;
+    constexpr size_t lds = 2 * NW * region_bytes<MT, S, PAIR>() + NW * 16 * MT * 4;
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    static std::atomic<uint64_t> lds_allowed;
+    const auto kern = gemm_few_kernel<NW, MT, S, PAIR, SWIGLU, DUAL, F32>;
+    if (lds > 64 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
+    hipLaunchKernelGGL(kern, dim3(kGrid), dim3(NW * kWave), lds, st, g);
+    return launch_status();
+}
+template <int MT, int S>
+int launch_few(const GemmArgs& g, bool swiglu, hipStream_t st) {
+    if (swiglu && g.seg[0].A0 != g.seg[0].A1) {
+        if constexpr (dual_fits(MT, S)) return launch_few<MT, S, true, true, true, false>(g, st);
+        else return MOE_ERR_UNSUPPORTED;
+    }
+    if (swiglu) return launch_few<MT, S, true, true, false, false>(g, st);
+    if (g.C1) return launch_few<MT, S, true, false, false, false>(g, st);
+    return g.k_parts > 1 ? launch_few<MT, S, false, false, false, true>(g, st) : launch_few<MT, S, false, false, false, false>(g, st);
+}
+template <int MT>
+int launch_few(const GemmArgs& g, int s, bool swiglu, hipStream_t st) {
+    switch (s) {
+        case 1: return launch_few<MT, 1>(g, swiglu, st);
+        case 2: return launch_few<MT, 2>(g, swiglu, st);
+        case 3: return launch_few<MT, 3>(g, swiglu, st);
+        case 4: return launch_few<MT, 4>(g, swiglu, st);
+        case 5: return launch_few<MT, 5>(g, swiglu, st);
+        case 6: return launch_few<MT, 6>(g, swiglu, st);
+        case 7: return launch_few<MT, 7>(g, swiglu, st);
+        case 8: return launch_few<MT, 8>(g, swiglu, st);
+        default: return MOE_ERR_UNSUPPORTED;
+    }
+}
+
+int few_steps(int K, int parts) {
+    const int steps = (K + kStepK - 1) / kStepK;
+    return ((steps + parts - 1) / parts + kWaves - 1) / kWaves;
+}
+
+}  // namespace
+
+// Where these kernels are taken: up to 32 rows in a group, two MFMA row blocks (a token meets an expert once, so 32
+// tokens).  Whole layer, us, against the direct-fill kernels: 2048 / 5632 8 tokens 112.5 / 96.0, 32 tokens 116.7 / 105.5; 1024 /
+// 2816 12 of 16 experts 62.4 / 61.6; 432 / 1152 8 tokens 20.6 / 16.6; rank 1024 16 tokens 96.7 / 83.0; shared base with rank
+// 64 94.1 / 70.0.  With four row blocks the activations do not fit the registers: 64 tokens 111 / 247.
+bool gemm_few_rows(long long P, int top_k) { return P <= kKeyWords * kWave && P <= 32ll * top_k; }
+
+int gemm_few_split(int K, int parts_min, int parts_max) {
+    int q = parts_min;
+    while (q <= parts_max && few_steps(K, q) > kMaxSteps) ++q;
+    return q <= parts_max ? q : 0;
+}
+
+bool gemm_few_supported(const GemmArgs& g) {
+    const GemmSeg& sg = g.seg[0];
+    const int s = few_steps(sg.K, g.k_parts > 1 ? g.k_parts : 1);
+    const bool dual = sg.A0 != sg.A1;
+    return g.nseg == 1 && !g.add0 && g.few > 0 && g.P <= kKeyWords * kWave && s <= kMaxSteps && sg.K >= 8 && sg.K % 8 == 0 &&
+           (g.k_parts <= 1 || g.parts_f32) && !(dual && (g.C1 || !dual_fits(g.few <= 16 ? 1 : 2, s))) && sg.K < (1 << 23) &&
+           (long long)g.N * sg.K * 2 < (1ll << 32);
+}
+
+int run_gemm_few(const GemmArgs& g, bool swiglu, hipStream_t st) {
+    const int s = few_steps(g.seg[0].K, g.k_parts > 1 ? g.k_parts : 1);
+    return g.few <= 16 ? launch_few<1>(g, s, swiglu, st) : launch_few<2>(g, s, swiglu, st);
+}
+
+}  // namespace moe

@@ -66,6 +66,8 @@ struct GemmArgs {
     // them, and its own rows are found from the keys.  NULL: offsets and row_map are inputs.
     const int32_t* keys;
     int32_t* inv_perm;
+    // expert_gemm_few.hip: no group holds more rows than this (a speed matter only).  0: not known
+    int few;
 };
 
 // Products whose activation operand is the F-wide hidden tensor (down, rank-down): that operand is
@@ -311,6 +313,12 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st);
 // Parts, up to parts_max, into which it is worth cutting the k-steps of a plain product of P rows in E groups
 // (k_parts above)
 int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f32, bool sum_launch);
+// bf16 products of few rows per group (expert_gemm_few.hip)
+bool gemm_few_rows(long long P, int top_k);
+// Parts of K, at least parts_min, that these kernels need, or 0 if that is more than parts_max
+int gemm_few_split(int K, int parts_min, int parts_max);
+bool gemm_few_supported(const GemmArgs& g);
+int run_gemm_few(const GemmArgs& g, bool swiglu, hipStream_t st);
 int launch_sum_parts(const float* parts, int q, long long n, void* out, hipStream_t st);
 
 }  // namespace moe

@@ -497,11 +497,45 @@ def test_forward_replayed_from_a_hip_graph_matches_eager(dev, static):
 
 @pytest.mark.parametrize("T", [2, 3, 5, 8])
 def test_forward_phone_config_few_tokens(dev, oracle, phone, T):
-    # two tokens take the matrix-vector path (their pairs are walked like one token's), three and
-    # more the grouped GEMM with a row or two per expert
+    # a row or two per expert
     cfg, w_np, w_t = phone
     _forward_case(dev, oracle, cfg, T, w_np, w_t)
     _forward_case(dev, oracle, cfg, T, w_np, w_t, residual=True)
+
+
+@pytest.mark.parametrize("d,F,E,k,r,base,T", [
+    # one and two MFMA row blocks: 15, 16, 17, 31 and 32 rows in a group (k = E puts every token in each), the
+    # first size past them; K of one piece of 16 bytes, a step and a bit, an odd number of steps per wave;
+    # 8 of 16 columns in the last block; one part of K or more
+    (40, 72, 3, 3, 0, False, 15), (264, 1160, 4, 4, 0, False, 16), (1032, 2056, 2, 2, 0, False, 17),
+    (2040, 4104, 2, 2, 0, False, 31), (488, 8184, 2, 2, 0, False, 32), (488, 8200, 2, 2, 0, False, 3), (264, 520, 4, 4, 0, False, 33),
+    (2048, 2824, 64, 1, 0, False, 3), (1440, 3840, 9, 7, 0, False, 2), (776, 2072, 64, 8, 0, False, 32), (776, 2072, 4, 2, 0, False, 2),
+    (2056, 1064, 4, 2, 0, False, 9), (136, 1056, 5, 2, 0, False, 1 + 8),
+    # rank factors (two activation operands), alone and beside a shared base
+    (520, 1384, 4, 2, 264, False, 3), (1600, 4264, 8, 2, 800, False, 17), (1800, 1048, 3, 3, 1544, False, 19), (264, 3080, 2, 2, 8, False, 32),
+    (520, 1384, 4, 2, 24, True, 2), (1000, 2728, 4, 3, 72, True, 20), (264, 1048, 4, 1, 40, True, 12),
+])
+def test_forward_few_rows_per_group(dev, oracle, d, F, E, k, r, base, T):
+    cfg = _cfg(name="few", d=d, F=F, E=E, k=k, dtype="bf16", seed=1700 + d + F + T, r=r, base=base, std=0.03)
+    _forward_case(dev, oracle, cfg, T, residual=bool(T % 2))
+
+
+@pytest.mark.parametrize("d,F,r,offsets", [
+    (72, 1000, 0, [0, 16, 16, 17]), (264, 520, 0, [0, 0, 31, 32]), (1032, 2056, 136, [0, 1, 20, 20, 27]), (2048, 96, 0, [0, 1]),
+])
+def test_expert_ffn_few_rows_per_group(dev, oracle, d, F, r, offsets):
+    cfg = _cfg(d=d, F=F, E=len(offsets) - 1, dtype="bf16", seed=1750 + d + r, r=r, std=0.04)
+    _ffn_case(dev, oracle, cfg, np.array(offsets, np.int32), TOL["bf16"])
+
+
+@pytest.mark.parametrize("T,k,E", [(32, 2, 5), (9, 3, 40)])
+def test_forward_few_tokens_with_nan_logits(dev, T, k, E):
+    # every pair may land in one expert or in none: the call ends and leaves other tokens' memory alone
+    cfg = _cfg(name="nan", d=264, F=520, E=E, k=k, dtype="bf16", seed=1790 + E)
+    w_t = weights_to_device(wl.make_layer_weights(cfg), dev)
+    w_t["router_w"].fill_(float("nan"))
+    y, _, _ = _forward_gpu(dev, w_t, to_device(wl.make_inputs(cfg, T), dev), k, pkg.MOE_BF16)
+    assert y.shape == (T, 264)
 
 
 @pytest.mark.parametrize("name,T", [("phone_wd", 2), ("phone_wd", 7), ("phone_wd_base", 2)])
