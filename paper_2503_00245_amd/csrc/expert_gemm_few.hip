@@ -6,9 +6,8 @@
 //   - one workgroup per CU walks an equal share of all (group, part of K, 16 output columns) units;
 //   - its eight waves split a unit's K, so that a wave's share of the activations stays in registers while the group's
 //     columns go by, and a unit ends in one sum over the waves through LDS, made by one wave in turn;
-//   - a wave has one to two chunks of eight 1 KB loads in flight, past the caches, in runs of 128 bytes and more per row: read in MFMA
-//     layout, 16 rows x 64 bytes per load, 288 MB come in at 5.0 TB/s, in whole lines at 6.3.  The way into MFMA
-//     layout is through a region of LDS of the wave's own, with no barrier;
+//   - a wave has one to two chunks of eight 1 KB loads in flight, past the caches, in the longest runs its share of a
+//     row gives (load, below); the way into MFMA layout is through a region of LDS of the wave's own, with no barrier;
 //   - the one barrier per unit waits for no load.
 #include "gemm.h"
 
@@ -51,27 +50,27 @@ __device__ __forceinline__ void wait_loads() {
 #endif
 }
 
-// A unit's weights are requested in one or two chunks of up to eight loads.
-constexpr int chunk_steps(int s, bool pair) { return s * (pair ? 2 : 1) > 8 ? (s + 1) / 2 : s; }
+// A unit's weights are requested in chunks of up to eight loads: both matrices at once, or one after the other.
+constexpr int chunks(int s, bool pair) { return pair && s > 4 ? 2 : 1; }
 template <int MT, int S, bool PAIR>
 constexpr int region_bytes() {
-    constexpr int nm = PAIR ? 2 : 1, stage = nm * 16 * (chunk_steps(S, PAIR) * 64 + 16), part = nm * MT * kWave * 16;
+    constexpr int nm = PAIR ? 2 : 1, stage = nm / chunks(S, PAIR) * 16 * (S * 64 + 16), part = nm * MT * kWave * 16;
     return stage > part ? stage : part;
 }
 
-// NW: waves; wave w owns the w-th share of every row's k-steps (of the part's, where K is cut into parts).
+// Wave w of the workgroup's NW owns the w-th share of every row's k-steps (of the part's, where K is cut into parts).
 // MT: 16-row blocks of activations held.  S: k-steps of a wave, at most.
 // PAIR: two matrices (gate and up, or C and C1); SWIGLU: one output of both; DUAL: the second has activations of its own.
 // F32: k-parts in fp32.
-template <int NW, int MT, int S, bool PAIR, bool SWIGLU, bool DUAL, bool F32>
-__global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void gemm_few_kernel(const GemmArgs g) {
+template <int MT, int S, bool PAIR, bool SWIGLU, bool DUAL, bool F32>
+__global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_few_kernel(const GemmArgs g) {
     static_assert(!SWIGLU || PAIR, "the activation takes two products");
     static_assert(!DUAL || PAIR, "two activation operands with two matrices");
-    constexpr int NM = PAIR ? 2 : 1, NX = DUAL ? 2 : 1, ROWS = 16 * MT;
-    constexpr int CS = chunk_steps(S, PAIR), CHUNKS = S > CS ? 2 : 1;
+    constexpr int NW = kWaves, NM = PAIR ? 2 : 1, NX = DUAL ? 2 : 1, ROWS = 16 * MT;
+    constexpr int CHUNKS = chunks(S, PAIR), CM = NM / CHUNKS;  // chunks of a unit, matrices of a chunk
     // LDS, per wave: two regions by turns, each first the weights on their way into MFMA layout, then the wave's
     // partial sums [NM][MT][64]; and the group's pairs
-    constexpr int PITCH = CS * 64 + 16, REGION = region_bytes<MT, S, PAIR>();
+    constexpr int PITCH = S * 64 + 16, REGION = region_bytes<MT, S, PAIR>();
     extern __shared__ __align__(16) char smem[];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -163,33 +162,31 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(NW / 
     // row's end is loaded from the last valid place and counts as zero in both operands; that can be part of the
     // last two steps only.
     struct Rows {
-        bf16x8 w[NM][CS];
+        bf16x8 w[CM][S];
     };
     auto pieces = [&](const Unit& u) { return min(u.ns * 4, K / 8 - u.s0 * 4); };  // valid 16-byte pieces of a row
-    // Load i of a chunk: rows lie in whole runs of H steps, first half of the chunk before the second (runs of
-    // 64 bytes, as MFMA operands lie, are read at 5.0 TB/s, of 128 and more at 6.3).
-    constexpr int H = CS > 4 ? (CS + 1) / 2 : CS;
+    // Load i of a chunk: 64 pieces of the 16 rows, row after row (runs of 64 bytes, as MFMA operands lie, are read at
+    // 5.0 TB/s, of 128 and more at 6.3; where rows are no multiples of a line, longer runs share fewer lines with other
+    // waves': 8 tokens of 2040 / 5624 116.7 us in runs of 256 bytes, 95.3 of 512; the direct-fill kernels' 128: 149.6).
     auto piece = [&](int i, int ln, int& row, int& k) {
-        const bool tail = i >= H;
-        const int at = (tail ? i - H : i) * kWave + ln, len = 4 * (tail ? CS - H : H);
-        row = at / len;
-        k = at - row * len + (tail ? 4 * H : 0);
+        const int at = i * kWave + ln;
+        row = at / (4 * S);
+        k = at - row * (4 * S);
     };
     auto load = [&](auto chunk, Rows& r, const Unit& u) {
-        constexpr int C0 = decltype(chunk)::value * CS;
+        constexpr int M0 = decltype(chunk)::value * CM;
         const int first = u.nb * 16, rows = min(N - first, 16), last = max(pieces(u) - 1, 0);
         const size_t base = ((size_t)u.e * sg.strideB + (size_t)first * K) * 2 + (size_t)min(u.s0, steps - 1) * 64;
         const int ln = lane_again();
-        const char* b[NM];
-        b[0] = static_cast<const char*>(sg.B0) + base;
-        if constexpr (PAIR) b[1] = static_cast<const char*>(sg.B1) + base;
 #pragma unroll
-        for (int i = 0; i < CS; ++i) {
+        for (int i = 0; i < S; ++i) {
             int row, k;
             piece(i, ln, row, k);
-            const unsigned off = (unsigned)min(row, rows - 1) * (unsigned)(K * 2) + (unsigned)min(C0 * 4 + k, last) * 16;
+            const unsigned off = (unsigned)min(row, rows - 1) * (unsigned)(K * 2) + (unsigned)min(k, last) * 16;
 #pragma unroll
-            for (int m = 0; m < NM; ++m) r.w[m][i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(b[m] + off));
+            for (int m = 0; m < CM; ++m)
+                r.w[m][i] = __builtin_nontemporal_load(
+                    reinterpret_cast<const bf16x8*>(static_cast<const char*>(M0 + m == 0 ? sg.B0 : sg.B1) + base + off));
         }
         __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the sums
     };
@@ -228,32 +225,31 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(NW / 
     int turn = 0;
     f32x4 acc[NM][MT];
     auto multiply = [&](auto chunk, const Rows& r, const Unit& u) {
-        constexpr int C0 = decltype(chunk)::value * CS, CN = S - C0 < CS ? S - C0 : CS;  // the chunk's first step, and steps
+        constexpr int M0 = decltype(chunk)::value * CM;
         char* const stage = my_region + (turn & 1) * (NW * REGION);
         const int n = pieces(u), ln = lane_again();
         auto put = [&](auto whole) {
 #pragma unroll
-            for (int i = 0; i < CS; ++i) {
+            for (int i = 0; i < S; ++i) {
                 int row, k;
                 piece(i, ln, row, k);
 #pragma unroll
-                for (int m = 0; m < NM; ++m)
-                    *reinterpret_cast<bf16x8*>(stage + (m * 16 + row) * PITCH + k * 16) =
-                        decltype(whole)::value || C0 * 4 + k < n ? r.w[m][i] : bf16x8{};
+                for (int m = 0; m < CM; ++m)
+                    *reinterpret_cast<bf16x8*>(stage + (m * 16 + row) * PITCH + k * 16) = decltype(whole)::value || k < n ? r.w[m][i] : bf16x8{};
             }
         };
         if (n >= 4 * S) put(std::true_type{});
         else put(std::false_type{});
         wave_lds_order();
 #pragma unroll
-        for (int s = 0; s < CN; ++s)
+        for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int m = 0; m < NM; ++m) {
+            for (int m = 0; m < CM; ++m) {
                 const bf16x8 w = *reinterpret_cast<const bf16x8*>(stage + (m * 16 + (lane & 15)) * PITCH + s * 64 + (lane >> 4) * 16);
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    acc[m][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x[DUAL ? m : 0][mt][C0 + s],
-                                                                         C0 + s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[m][mt], 0, 0, 0);
+                    acc[M0 + m][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x[DUAL ? M0 + m : 0][mt][s],
+                                                                              s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[M0 + m][mt], 0, 0, 0);
             }
         wave_lds_order();
     };
@@ -368,13 +364,12 @@ constexpr bool dual_fits(int mt, int s) { return mt == 1 || s <= 6; }
 
 template <int MT, int S, bool PAIR, bool SWIGLU, bool DUAL, bool F32>
 int launch_few(const GemmArgs& g, hipStream_t st) {
-    constexpr int NW = kWaves;
-    constexpr size_t lds = 2 * NW * region_bytes<MT, S, PAIR>() + NW * 16 * MT * 4;
+    constexpr size_t lds = 2 * kWaves * region_bytes<MT, S, PAIR>() + kWaves * 16 * MT * 4;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     static std::atomic<uint64_t> lds_allowed;
-    const auto kern = gemm_few_kernel<NW, MT, S, PAIR, SWIGLU, DUAL, F32>;
+    const auto kern = gemm_few_kernel<MT, S, PAIR, SWIGLU, DUAL, F32>;
     if (lds > 64 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3(kGrid), dim3(NW * kWave), lds, st, g);
+    hipLaunchKernelGGL(kern, dim3(kGrid), dim3(kWaves * kWave), lds, st, g);
     return launch_status();
 }
 template <int MT, int S>
@@ -387,18 +382,12 @@ int launch_few(const GemmArgs& g, bool swiglu, hipStream_t st) {
     if (g.C1) return launch_few<MT, S, true, false, false, false>(g, st);
     return g.k_parts > 1 ? launch_few<MT, S, false, false, false, true>(g, st) : launch_few<MT, S, false, false, false, false>(g, st);
 }
-template <int MT>
+template <int MT, int S>
 int launch_few(const GemmArgs& g, int s, bool swiglu, hipStream_t st) {
-    switch (s) {
-        case 1: return launch_few<MT, 1>(g, swiglu, st);
-        case 2: return launch_few<MT, 2>(g, swiglu, st);
-        case 3: return launch_few<MT, 3>(g, swiglu, st);
-        case 4: return launch_few<MT, 4>(g, swiglu, st);
-        case 5: return launch_few<MT, 5>(g, swiglu, st);
-        case 6: return launch_few<MT, 6>(g, swiglu, st);
-        case 7: return launch_few<MT, 7>(g, swiglu, st);
-        case 8: return launch_few<MT, 8>(g, swiglu, st);
-        default: return MOE_ERR_UNSUPPORTED;
+    if constexpr (S > kMaxSteps) {
+        return MOE_ERR_UNSUPPORTED;
+    } else {
+        return s == S ? launch_few<MT, S>(g, swiglu, st) : launch_few<MT, S + 1>(g, s, swiglu, st);
     }
 }
 
@@ -410,9 +399,9 @@ int few_steps(int K, int parts) {
 }  // namespace
 
 // Where these kernels are taken: up to 32 rows in a group, two MFMA row blocks (a token meets an expert once, so 32
-// tokens).  Whole layer, us, against the direct-fill kernels: 2048 / 5632 8 tokens 112.5 / 96.0, 32 tokens 116.7 / 105.5; 1024 /
-// 2816 12 of 16 experts 62.4 / 61.6; 432 / 1152 8 tokens 20.6 / 16.6; rank 1024 16 tokens 96.7 / 83.0; shared base with rank
-// 64 94.1 / 70.0.  With four row blocks the activations do not fit the registers: 64 tokens 111 / 247.
+// tokens).  Whole layer, us, against the direct-fill kernels: 2048 / 5632 8 tokens 111 / 95, 32 tokens 118 / 104; 2040 / 5624 150 / 95,
+// 161 / 102; 1024 / 2816 37.5 / 35.2, 38.5 / 39.1; 432 / 1152 23.2 / 18.7, 24.4 / 20.7; rank 1024 on 2040 / 5464, 16 tokens 104 / 83; shared
+// base with rank 64 94 / 70.  With four row blocks the activations do not fit the registers: 64 tokens 111 / 247.
 bool gemm_few_rows(long long P, int top_k) { return P <= kKeyWords * kWave && P <= 32ll * top_k; }
 
 int gemm_few_split(int K, int parts_min, int parts_max) {
@@ -432,7 +421,7 @@ bool gemm_few_supported(const GemmArgs& g) {
 
 int run_gemm_few(const GemmArgs& g, bool swiglu, hipStream_t st) {
     const int s = few_steps(g.seg[0].K, g.k_parts > 1 ? g.k_parts : 1);
-    return g.few <= 16 ? launch_few<1>(g, s, swiglu, st) : launch_few<2>(g, s, swiglu, st);
+    return g.few <= 16 ? launch_few<1, 1>(g, s, swiglu, st) : launch_few<2, 1>(g, s, swiglu, st);
 }
 
 }  // namespace moe
