@@ -1,5 +1,7 @@
 // extern "C" entry points of moe.h: argument checks on the host, workspace carving, and
 // the order in which the stage kernels are enqueued.  No kernel lives here.
+#include <algorithm>
+
 #include "gemv.h"
 
 namespace moe {
@@ -41,6 +43,7 @@ struct Workspace {
     size_t topk_idx, topk_gate, offsets, perm, inv_perm, sort_scratch, y_perm, y_base, ffn_scratch,
         decode_scratch, stack_tmp, total;
     SplitPlan plan;
+    bool token_layer;  // room for launch_token_layer_f32's vectors from ffn_scratch on
 };
 
 // Room for partial outputs (SplitPlan) beside the one output a product has anyway.  It grows with the number of
@@ -85,11 +88,13 @@ static Workspace carve(const moe_shape& s) {
     const size_t tail = round_up(decode_scratch_bytes(s, 1), 256) + (stack_bytes ? stack_bytes : 256);
     ws.plan = SplitPlan{1, 1, 1, true};
     if (!decode) {
-        // (parts must not push a shape out of the allocation-free entry point's array)
+        // (neither parts nor a small layer's vectors may push a shape out of the allocation-free entry point's array)
         size_t end = parts_end(s, ws.ffn_scratch, ws.y_perm);
+        if (token_layer_f32_shape(s)) end = round_up(ws.ffn_scratch + std::min(token_layer_bytes(s), kTokenLayerBytes), 256);
         if (cur + tail <= (size_t)MOE_STATIC_WORKSPACE_BYTES && end + tail > (size_t)MOE_STATIC_WORKSPACE_BYTES)
             end = (size_t)MOE_STATIC_WORKSPACE_BYTES - tail;
         if (end > cur) cur = end;
+        ws.token_layer = token_layer_f32_shape(s) && cur - ws.ffn_scratch >= token_layer_bytes(s);
         ws.plan = split_plan(s, cur - ws.y_perm, cur - ws.ffn_scratch - ffn_layout(s).tg);
     }
     ws.decode_scratch = take(decode_scratch_bytes(s, 1));
@@ -111,6 +116,9 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
                           ? reinterpret_cast<float*>(wsp + ws.ffn_scratch) : nullptr;
         return launch_decode(s, w, x, idx, gate, y, wsp + ws.decode_scratch, base, st, timer);
     }
+    const void* residual = (s.flags & MOE_FLAG_RESIDUAL) ? x : nullptr;
+    if (ws.token_layer && token_layer_f32_supported(s))
+        return launch_token_layer_f32(s, w, x, idx, gate, reinterpret_cast<float*>(wsp + ws.ffn_scratch), residual, y, st, timer);
     int rc = launch_route(s, x, w.router_w, w.router_b, idx, gate, nullptr, st);
     if (rc != MOE_OK) return rc;
     stage_mark(timer, "route");
@@ -125,7 +133,6 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
         stage_mark(timer, "permute");
     }
     // the gather of token rows into expert order is fused into the first GEMM's A loads
-    const void* residual = (s.flags & MOE_FLAG_RESIDUAL) ? x : nullptr;
     if (token_base_supported(s)) {  // shared base: its products run once per token
         rc = launch_expert_ffn_token_base(s, w, x, perm, inv_perm, gate, offsets, wsp + ws.y_perm,
                                           wsp + ws.y_base, wsp + ws.ffn_scratch, st, timer, ws.plan, keys);

@@ -196,6 +196,14 @@ int launch_expert_ffn_token_base(const moe_shape& s, const moe_weights& w, const
                                  int32_t* offsets, void* y_perm, void* y_base, void* scratch,
                                  hipStream_t st, StageTimer* timer, const SplitPlan& plan, const int32_t* keys);
 
+// Small fp32 layer of dense experts in two launches, every token with every expert; h: token_layer_bytes of scratch.
+constexpr size_t kTokenLayerBytes = 4u << 20;       // at most that
+bool token_layer_f32_shape(const moe_shape& s);      // whatever the number of tokens
+bool token_layer_f32_supported(const moe_shape& s);
+inline size_t token_layer_bytes(const moe_shape& s) { return sizeof(float) * (size_t)s.n_experts * s.n_tokens * s.d_ff; }
+int launch_token_layer_f32(const moe_shape& s, const moe_weights& w, const void* x, int32_t* idx, float* gate, float* h,
+                           const void* residual, void* y, hipStream_t st, StageTimer* timer);
+
 // Single-token layer: routed, experts chosen on the device from topk_idx, weights streamed once.
 // base_scratch: decode_base_bytes (gemv.h) for a layer with a shared base, or NULL.
 size_t decode_scratch_bytes(const moe_shape& s, int n_tokens);

@@ -13,6 +13,7 @@
 // 32-token, 128 / 256-wide layer -- 16 or fewer workgroups, a barrier pair per 16 of k.  Whole layer there
 // 76 us before, 19.6 now; 512 tokens of a 512 / 1400 layer with 8 experts 516 before, 91 now.)
 #include "gemm.h"
+#include "router.h"
 
 namespace moe {
 
@@ -185,6 +186,150 @@ int run_gemm_f32(GemmArgs& g, bool swiglu, hipStream_t st) {
     if (tiles(64) >= 256) return launch_f32<2, 2, 2, 2, 1>(g, swiglu, st);
     if (tiles(32) >= 256) return launch_f32<2, 2, 1, 1, 4>(g, swiglu, st);
     return launch_f32<1, 1, 1, 1, 4>(g, swiglu, st);
+}
+
+// ---- small layers of dense experts: two launches ----------------------------------------------------------------
+// What bounds a small layer is launches, each a chain of memory latencies: routing, sorting inside the gate/up product,
+// the down product and the combine took 16.0 us for 32 tokens of a 128 / 256 layer with 4 experts; the two launches here
+// take 9.9 (64 / 136 with 8 experts 15.0 and 8.7, 256 / 640 with 2 18.9 and 11.3).  Every token
+// meets every expert, so that no product waits for the routing: the tokens' rows are MFMA rows, h [E, T, F] holds them all,
+// the routing runs beside the first product, and who chose whom matters only where the last one adds up.
+//   token_gate_up  h[e, t] = silu(W_gate[e] x_t) * (W_up[e] x_t); the first route_blocks workgroups route
+//   token_down     y_t = sum_j gate_tj W_down[e_tj] h[e_tj, t] (+ residual_t)
+// Both on 16 x 16 tiles, the k-steps of one shared by waves, loads of D steps ahead of their MFMAs, tiles met in LDS.
+constexpr int kTokenWaves = 16;
+struct TokenLayer {
+    const float *x, *w_gate, *w_up, *w_down;
+    int T, d, F, E, k;
+    int32_t* idx;
+    float *gate, *h, *y;
+    const float* residual;
+    int slices;  // token_down: waves per expert
+};
+// acc[m] += A row of the lane . B[m] row of the lane over the k-steps first, first + stride, ... of K.  (The next D on
+// their way beside the present ones: slower, 17.3 -> 21.3 us for 32 tokens of 256 / 640, fewer waves fit.)
+template <int D, int NM>
+__device__ __forceinline__ void token_tile(const float* pa, const float* const (&pb)[NM], int K, int first, int stride, f32x4 (&acc)[NM]) {
+    const int quad = (threadIdx.x & (kWave - 1)) >> 4, steps = (K + 15) / 16;
+    for (int st = first; st < steps; st += D * stride) {
+        f32x4 a[D], b[NM][D];
+#pragma unroll
+        for (int q = 0; q < D; ++q) {  // (past the row's end: its last 16 bytes)
+            const int k = min((st + q * stride) * 16 + quad * 4, K - 4);
+            a[q] = *reinterpret_cast<const f32x4*>(pa + k);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) b[m][q] = *reinterpret_cast<const f32x4*>(pb[m] + k);
+        }
+#pragma unroll
+        for (int q = 0; q < D; ++q) {
+            if (st + q * stride >= steps) break;
+            const bool in = (st + q * stride) * 16 + quad * 4 < K;  // beyond K: both operands cleared
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a[q][c] : 0.f, in ? b[m][q][c] : 0.f, acc[m], 0, 0, 0);
+        }
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(const TokenLayer g, const float* __restrict__ rw,
+                                                                               const float* __restrict__ rb, int route_blocks) {
+    if ((int)blockIdx.x < route_blocks) {
+        route_tokens<float, 4, kRouteTok>(g.x, rw, rb, g.idx, g.gate, nullptr, g.T, g.d, g.E, g.k, blockIdx.x);
+        return;
+    }
+    __shared__ float s_part[2][kRouteWaves][16][17];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int blocks = (g.F + 15) / 16, at = (int)blockIdx.x - route_blocks;
+    const int te = at / blocks, f0 = (at - te * blocks) * 16, e = te % g.E, t0 = te / g.E * 16;
+    const int i = lane & 15, quad = lane >> 4;
+    const float* pa = g.x + (size_t)min(t0 + i, g.T - 1) * g.d;
+    const size_t row = ((size_t)e * g.F + min(f0 + i, g.F - 1)) * g.d;
+    const float* const pb[2] = {g.w_gate + row, g.w_up + row};
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    token_tile<D, 2>(pa, pb, g.d, wave, kRouteWaves, acc);
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s_part[m][wave][4 * quad + r][i] = acc[m][r];
+    __syncthreads();
+    const int t = threadIdx.x >> 4, c = threadIdx.x & 15;
+    if (t >= 16 || t0 + t >= g.T || f0 + c >= g.F) return;
+    float z[2] = {0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int w = 0; w < kRouteWaves; ++w) z[m] += s_part[m][w][t][c];
+    g.h[((size_t)e * g.T + t0 + t) * g.F + f0 + c] = silu_f32(z[0]) * z[1];
+}
+
+template <int D>
+__global__ __launch_bounds__(kTokenWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void token_down_f32_kernel(const TokenLayer g) {
+    __shared__ float s_part[kTokenWaves][16][17];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int n0 = blockIdx.x * 16, t0 = blockIdx.y * 16;
+    const int e = wave / g.slices, ks = wave - e * g.slices;
+    const int i = lane & 15, quad = lane >> 4;
+    const int t = t0 + (int)(threadIdx.x >> 4), n = n0 + (int)(threadIdx.x & 15);  // what the thread adds up
+    const bool mine = threadIdx.x < 256 && t < g.T && n < g.d;
+    float res = 0.f;
+    if (mine && g.residual) res = g.residual[(size_t)t * g.d + n];
+    f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
+    if (e < g.E) {
+        const float* const pb[1] = {g.w_down + ((size_t)e * g.d + min(n0 + i, g.d - 1)) * g.F};
+        token_tile<D, 1>(g.h + ((size_t)e * g.T + min(t0 + i, g.T - 1)) * g.F, pb, g.F, ks, g.slices, acc);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_part[wave][4 * quad + r][i] = acc[0][r];
+    __syncthreads();
+    if (!mine) return;
+    float total = 0.f;
+    for (int j = 0; j < g.k; ++j) {
+        const int ej = min(max(g.idx[t * g.k + j], 0), g.E - 1);
+        float sum = 0.f;
+        for (int sl = 0; sl < g.slices; ++sl) sum += s_part[ej * g.slices + sl][threadIdx.x >> 4][threadIdx.x & 15];
+        total = fmaf(g.gate[t * g.k + j], sum, total);
+    }
+    g.y[(size_t)t * g.d + n] = total + res;
+}
+
+// Where this is the faster way (whole layer, us, stage by stage / this): the down product's workgroups, one per 16 columns,
+// read the 16 rows of all experts, so E F is bounded -- 32 tokens, 2 of 8 experts of 256 / 640 22.0 / 27.0, 4 experts 21.3 / 17.3 --
+// and the products grow by E / k (32, 128, 256 tokens, 2 of 8 experts of 128 / 256 15.7 / 13.4, 17.4 / 16.6, 19.1 / 19.7; 1 of 4 of
+// 256 / 640 64 tokens 20.4 / 18.2, 128 tokens 21.5 / 21.0, 256 tokens 23.2 / 28.6).  Two tokens otherwise take the
+// matrix-vector path: 2 of 4 experts of 128 / 256 12.3 / 8.3.
+bool token_layer_f32_shape(const moe_shape& s) {
+    return s.act_dtype == MOE_F32 && s.rank == 0 && s.n_experts <= kTokenWaves && s.d_model <= 1024 &&
+           (long long)s.n_experts * s.d_ff <= 3072;
+}
+bool token_layer_f32_supported(const moe_shape& s) {
+    return token_layer_f32_shape(s) && s.n_tokens > 1 && token_layer_bytes(s) <= kTokenLayerBytes &&
+           (double)s.n_tokens * s.d_model * s.d_ff * s.n_experts * s.n_experts <= 200e6 * s.top_k;
+}
+int launch_token_layer_f32(const moe_shape& s, const moe_weights& w, const void* x, int32_t* idx, float* gate, float* h,
+                           const void* residual, void* y, hipStream_t st, StageTimer* timer) {
+    int slices = kTokenWaves;
+    while (slices * s.n_experts > kTokenWaves) slices /= 2;
+    const TokenLayer g{static_cast<const float*>(x), static_cast<const float*>(w.w_gate), static_cast<const float*>(w.w_up),
+                       static_cast<const float*>(w.w_down), s.n_tokens, s.d_model, s.d_ff, s.n_experts, s.top_k, idx, gate, h,
+                       static_cast<float*>(y), static_cast<const float*>(residual), slices};
+    const int tb = (s.n_tokens + 15) / 16, route_blocks = (s.n_tokens + kRouteTok - 1) / kRouteTok;
+    const dim3 grid(route_blocks + tb * s.n_experts * ((s.d_ff + 15) / 16));
+    if (s.d_model <= 16 * kRouteWaves)
+        hipLaunchKernelGGL(token_gate_up_f32_kernel<1>, grid, dim3(kRouteWaves * kWave), 0, st, g, w.router_w, w.router_b, route_blocks);
+    else
+        hipLaunchKernelGGL(token_gate_up_f32_kernel<4>, grid, dim3(kRouteWaves * kWave), 0, st, g, w.router_w, w.router_b, route_blocks);
+    int rc = launch_status();
+    if (rc != MOE_OK) return rc;
+    stage_mark(timer, "route_gate_up_swiglu");
+    hipLaunchKernelGGL(token_down_f32_kernel<4>, dim3((s.d_model + 15) / 16, tb), dim3(kTokenWaves * kWave), 0, st, g);
+    rc = launch_status();
+    stage_mark(timer, "gemm_down_combine");
+    return rc;
 }
 
 }  // namespace moe

@@ -615,6 +615,7 @@ static int launch_gemv(GemvArgs& a, int mode, hipStream_t st) {
 constexpr int kMaxDecodeTokens = 2;
 bool decode_supported(const moe_shape& s) {
     if (s.n_tokens == 1) return true;
+    if (token_layer_f32_supported(s)) return false;
     if (few_two_tokens(s)) return false;
     return s.n_tokens <= kMaxDecodeTokens && (long long)s.n_tokens * s.top_k <= kMaxExperts &&
            !(s.flags & MOE_FLAG_SHARED_BASE);

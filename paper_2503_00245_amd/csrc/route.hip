@@ -11,8 +11,6 @@
 
 namespace moe {
 
-constexpr int kRouteWaves = 8;
-constexpr int kRouteTok = 2;       // tokens per workgroup
 constexpr int kRouteTokLarge = 4;  // ... from kRouteLargeFrom tokens on
 constexpr int kRouteLargeFrom = 1024;
 
@@ -31,44 +29,7 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
     const T* __restrict__ x, const float* __restrict__ rw, const float* __restrict__ rb,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate, float* __restrict__ probs,
     int T_, int d, int E, int k) {
-    typedef Store<T> S;
-    constexpr int VEC = S::VEC;
-    __shared__ float s_logit[TOK][kMaxExperts];
-
-    const int t0 = blockIdx.x * TOK;
-    const int ntok = min(TOK, T_ - t0);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-
-    auto load_x = [&](int t, int i, float* out) {
-        const typename S::vec_t xv =
-            *reinterpret_cast<const typename S::vec_t*>(x + (size_t)(t0 + t) * d + i);
-#pragma unroll
-        for (int q = 0; q < VEC; ++q) out[q] = S::get(xv, q);
-    };
-    for (int e = wave; e < E; e += kRouteWaves) {
-        float acc[TOK];
-        // (the bias is requested before the row is streamed: at a single token, with a cold router,
-        // a load issued only after the reduction is a second full memory round trip)
-        const float b = rb ? rb[e] : 0.f;
-        router_logits<VEC, TOK, NB>(load_x, rw + (size_t)e * d, d, lane, ntok, acc);
-        if (lane == 0) {
-#pragma unroll
-            for (int t = 0; t < TOK; ++t) s_logit[t][e] = acc[t] + b;
-        }
-    }
-    __syncthreads();
-
-    for (int tt = wave; tt < ntok; tt += kRouteWaves) {
-        const int t = t0 + tt;
-        const RouterPick r = router_select(lane, E, k, lane < E ? s_logit[tt][lane] : 0.f);
-        if (probs && lane < E) probs[(size_t)t * E + lane] = r.p / r.den;
-        if (r.slot >= 0) {
-            topk_idx[(size_t)t * k + r.slot] = lane;
-            // (p/den) / (sum_sel p/den) with the common 1/den cancelled
-            topk_gate[(size_t)t * k + r.slot] = r.p / r.sel_sum;
-        }
-    }
+    route_tokens<T, NB, TOK>(x, rw, rb, topk_idx, topk_gate, probs, T_, d, E, k, blockIdx.x);
 }
 
 // Large batches: the whole router (E x d fp32) is staged in LDS once per workgroup and a wave

@@ -538,6 +538,35 @@ def test_forward_few_tokens_with_nan_logits(dev, T, k, E):
     assert y.shape == (T, 264)
 
 
+@pytest.mark.parametrize("d,F,E,k,T", [
+    # every token with every expert: 16-token blocks with 1, 2, 15, 16 and 17 tokens in the last, one expert and the most,
+    # an odd number, widths below a block and a k-step, a ragged k-step, eight k-steps and more per row
+    (128, 256, 4, 2, 2), (8, 8, 1, 1, 3), (24, 40, 3, 2, 15), (136, 264, 5, 5, 16), (128, 256, 4, 1, 17), (264, 184, 16, 4, 33),
+    (512, 1400, 2, 1, 31), (1024, 1024, 3, 3, 18), (64, 136, 8, 2, 256), (72, 376, 8, 8, 130),
+    # the first sizes past it: inner widths, model width, tokens
+    (64, 3080, 1, 1, 9), (1032, 72, 2, 1, 5), (256, 640, 4, 1, 200), (128, 184, 17, 2, 20),
+])
+def test_forward_small_fp32_layer(dev, oracle, d, F, E, k, T):
+    cfg = _cfg(name="small", d=d, F=F, E=E, k=k, dtype="f32", seed=1800 + d + F + T, std=0.05)
+    _forward_case(dev, oracle, cfg, T, residual=bool(T % 2))
+
+
+@pytest.mark.parametrize("T,k,E", [(20, 2, 5), (3, 4, 16)])
+def test_forward_small_fp32_layer_with_infinite_experts(dev, T, k, E):
+    # an expert that a token did not choose leaves no trace in it, whatever its weights
+    cfg = _cfg(name="inf", d=128, F=72, E=E, k=k, dtype="f32", seed=1890 + E, std=0.05)
+    w_t = weights_to_device(wl.make_layer_weights(cfg), dev)
+    x_t = to_device(wl.make_inputs(cfg, T), dev)
+    y0, idx, _ = _forward_gpu(dev, w_t, x_t, k, pkg.MOE_F32)
+    e = int(idx[0, 0])
+    w_t["w_gate"][e].fill_(float("nan"))
+    w_t["w_down"][e].fill_(float("inf"))
+    y1, idx1, _ = _forward_gpu(dev, w_t, x_t, k, pkg.MOE_F32)
+    assert np.array_equal(idx, idx1)
+    hit = torch.from_numpy((idx == e).any(axis=1))
+    assert torch.equal(y0.cpu()[~hit], y1.cpu()[~hit]) and bool(torch.isnan(y1.cpu()[hit]).all())
+
+
 @pytest.mark.parametrize("name,T", [("phone_wd", 2), ("phone_wd", 7), ("phone_wd_base", 2)])
 def test_forward_weight_decomposed_few_tokens(dev, oracle, name, T):
     # pure L R experts: four matrix-vector stages with per-token and per-pair inputs; a shared base
