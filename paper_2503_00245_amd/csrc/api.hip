@@ -128,7 +128,10 @@ static int forward_impl(const moe_shape& s, const moe_weights& w, const void* x,
     int32_t* inv_perm = reinterpret_cast<int32_t*>(wsp + ws.inv_perm);
     const int32_t* keys = ffn_takes_keys(s, idx) ? idx : nullptr;  // the first product sorts the pairs itself
     if (!keys) {
-        rc = launch_permute(P, s.n_experts, idx, offsets, perm, inv_perm, wsp + ws.sort_scratch, st);
+        // (in the products' scratch, idle until then and the larger one, or in what the sort has at least)
+        const bool idle = ffn_scratch_bytes(s) >= permute_scratch_bytes(P, s.n_experts);
+        rc = launch_permute(P, s.n_experts, idx, offsets, perm, inv_perm, wsp + (idle ? ws.ffn_scratch : ws.sort_scratch),
+                            idle ? ffn_scratch_bytes(s) : permute_scratch_bytes(P, s.n_experts), st);
         if (rc != MOE_OK) return rc;
         stage_mark(timer, "permute");
     }
@@ -218,7 +221,7 @@ int moe_permute(const moe_shape* shape, const int32_t* topk_idx, int32_t* expert
     const size_t need = permute_scratch_bytes(P, shape->n_experts);
     if (need > 0 && (!workspace || workspace_bytes < need)) return MOE_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
-    rc = launch_permute(P, shape->n_experts, topk_idx, expert_offsets, perm, inv_perm, workspace, st);
+    rc = launch_permute(P, shape->n_experts, topk_idx, expert_offsets, perm, inv_perm, workspace, workspace_bytes, st);
     if (rc != MOE_OK || !x) return rc;
     return launch_gather_rows(*shape, perm, x, x_perm, st);
 }

@@ -126,9 +126,10 @@ int validate_shape(const moe_shape* s);
 int launch_route(const moe_shape& s, const void* x, const float* rw, const float* rb,
                  int32_t* topk_idx, float* topk_gate, float* probs, hipStream_t st);
 
+// scratch: permute_scratch_bytes at least; more, up to 256 counts per expert, makes for more and shorter chunks
 size_t permute_scratch_bytes(int P, int E);
 int launch_permute(int P, int E, const int32_t* topk_idx, int32_t* offsets, int32_t* perm,
-                   int32_t* inv_perm, void* scratch, hipStream_t st);
+                   int32_t* inv_perm, void* scratch, size_t scratch_bytes, hipStream_t st);
 int launch_gather_rows(const moe_shape& s, const int32_t* perm, const void* x, void* x_perm,
                        hipStream_t st);
 

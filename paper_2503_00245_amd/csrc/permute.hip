@@ -2,19 +2,21 @@
 // sort by expert index (token-choice routing, Sec. 2.1 / Fig. 2: every token goes to its
 // own k experts, so each expert ends up with a contiguous, order-preserving group).
 //
-// Pairs are cut into chunks of kChunk consecutive p.  Chunk c, expert e:
-//   count[e][c] (histogram)  ->  base[e][c] = exclusive scan in (e major, c minor) order
-//   slot(p) = base[key][chunk] + #{p' < p in the chunk with the same key}
+// Pairs are cut into chunks of consecutive p.  Chunk c, expert e:
+//   count[c][e] (histogram)  ->  base(c, e) = pairs of lower experts + pairs of e in earlier chunks
+//   slot(p) = base(chunk, key) + #{p' < p in the chunk with the same key}
 // The in-chunk rank comes from wave ballots (lanes below me with my key) plus per-wave
 // counts held in LDS, so equal keys keep ascending p: the sort is stable by construction.
 // Small problems (one chunk) run all three phases in a single workgroup.
+#include <algorithm>
+
 #include "common.h"
 
 namespace moe {
 
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int kChunk = 8192;  // pairs per workgroup in the multi-block path
+constexpr int kChunk = 8192;  // pairs that one workgroup sorts alone; the scratch has a count per expert for each so many
 
 // In-wave stable rank: returns #lanes below this one holding the same key, and adds the
 // wave's per-key totals to s_wcount[wave][key].  Inactive lanes pass key = -1.
@@ -155,58 +157,62 @@ __global__ __launch_bounds__(kSortThreads) void permute_small_kernel(
 }
 
 // ---- multi-workgroup path ---------------------------------------------------------------------
+// Two launches: counts, then slots, for which every workgroup adds up the counts of the chunks before its own.  What takes the
+// time is the chain of passes over a chunk, 1024 pairs each, so chunks are as short as the room for
+// their counts and the number of CUs allow (32768 pairs of 8 experts: 4 chunks and a launch for the scan 35 us,
+// 32 chunks and none 10).
+constexpr int kMaxChunks = 256;
+
 __global__ __launch_bounds__(kSortThreads) void permute_hist_kernel(
-    const int32_t* __restrict__ keys, int P, int E, int n_chunks, int32_t* __restrict__ counts) {
+    const int32_t* __restrict__ keys, int P, int E, int chunk, int32_t* __restrict__ counts) {
     __shared__ int s_hist[kMaxExperts];
     if (threadIdx.x < kMaxExperts) s_hist[threadIdx.x] = 0;
     __syncthreads();
-    const int p0 = blockIdx.x * kChunk;
-    const int p1 = min(P, p0 + kChunk);
+    const int p0 = blockIdx.x * chunk;
+    const int p1 = min(P, p0 + chunk);
     for (int q = p0; q < p1; q += kSortThreads)
         wave_hist(load_key(keys, q + threadIdx.x, p1, E), threadIdx.x & (kWave - 1), s_hist);
     __syncthreads();
-    if (threadIdx.x < E) counts[(size_t)threadIdx.x * n_chunks + blockIdx.x] = s_hist[threadIdx.x];
-}
-
-// exclusive scan of counts[e][c] in row-major order, in place; also the expert offsets
-__global__ __launch_bounds__(kSortThreads) void permute_scan_kernel(
-    int32_t* __restrict__ counts, int n, int E, int n_chunks, int P,
-    int32_t* __restrict__ offsets) {
-    __shared__ int s_part[kSortThreads];
-    const int per = (n + kSortThreads - 1) / kSortThreads;
-    const int i0 = min(n, (int)threadIdx.x * per);
-    const int i1 = min(n, i0 + per);
-    int sum = 0;
-    for (int i = i0; i < i1; ++i) sum += counts[i];
-    s_part[threadIdx.x] = sum;
-    __syncthreads();
-    // Hillis-Steele inclusive scan over the per-thread partials
-    for (int off = 1; off < kSortThreads; off <<= 1) {
-        int v = threadIdx.x >= off ? s_part[threadIdx.x - off] : 0;
-        __syncthreads();
-        s_part[threadIdx.x] += v;
-        __syncthreads();
-    }
-    int run = s_part[threadIdx.x] - sum;
-    for (int i = i0; i < i1; ++i) {
-        const int c = counts[i];
-        counts[i] = run;
-        if (i % n_chunks == 0) offsets[i / n_chunks] = run;
-        run += c;
-    }
-    if (threadIdx.x == 0) offsets[E] = P;
+    if (threadIdx.x < E) counts[blockIdx.x * E + threadIdx.x] = s_hist[threadIdx.x];
 }
 
 __global__ __launch_bounds__(kSortThreads) void permute_scatter_kernel(
-    const int32_t* __restrict__ keys, int P, int E, int n_chunks,
-    const int32_t* __restrict__ base, int32_t* __restrict__ perm,
+    const int32_t* __restrict__ keys, int P, int E, int chunk, int n_chunks,
+    const int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
     int32_t* __restrict__ inv_perm) {
     __shared__ int s_run[kMaxExperts];
     __shared__ int s_wcount[kSortWaves][kMaxExperts];
-    if (threadIdx.x < E) s_run[threadIdx.x] = base[(size_t)threadIdx.x * n_chunks + blockIdx.x];
+    __shared__ int s_before[kSortWaves][kMaxExperts], s_all[kSortWaves][kMaxExperts];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    int before = 0, all = 0;  // of expert `lane`, over the wave's chunks
+    if (lane < E) {
+        for (int c = wave; c < n_chunks; c += kSortWaves) {
+            const int n = counts[c * E + lane];
+            all += n;
+            if (c < (int)blockIdx.x) before += n;
+        }
+    }
+    s_before[wave][lane] = before;
+    s_all[wave][lane] = all;
     __syncthreads();
-    const int p0 = blockIdx.x * kChunk;
-    scatter_chunk(keys, p0, min(P, p0 + kChunk), E, s_run, s_wcount, perm, inv_perm);
+    if (wave == 0) {
+        before = all = 0;
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) {
+            before += s_before[w][lane];
+            all += s_all[w][lane];
+        }
+        const int first = wave_inclusive_scan(all, lane) - all;
+        s_run[lane] = first + before;
+        if (blockIdx.x == 0) {
+            if (lane < E) offsets[lane] = first;
+            if (lane == E - 1) offsets[E] = first + all;
+        }
+    }
+    __syncthreads();
+    const int p0 = blockIdx.x * chunk;
+    scatter_chunk(keys, p0, min(P, p0 + chunk), E, s_run, s_wcount, perm, inv_perm);
 }
 
 size_t permute_scratch_bytes(int P, int E) {
@@ -215,20 +221,20 @@ size_t permute_scratch_bytes(int P, int E) {
 }
 
 int launch_permute(int P, int E, const int32_t* topk_idx, int32_t* offsets, int32_t* perm,
-                   int32_t* inv_perm, void* scratch, hipStream_t st) {
+                   int32_t* inv_perm, void* scratch, size_t scratch_bytes, hipStream_t st) {
     if (P <= kChunk) {
         hipLaunchKernelGGL(permute_small_kernel, dim3(1), dim3(kSortThreads), 0, st, topk_idx, P, E,
                            offsets, perm, inv_perm);
         return launch_status();
     }
-    const int n_chunks = (P + kChunk - 1) / kChunk;
+    const int most = (int)std::min<size_t>(scratch_bytes / (sizeof(int32_t) * E), kMaxChunks);
+    const int passes = (P + kSortThreads - 1) / kSortThreads;
+    const int chunk = (passes + most - 1) / most * kSortThreads, n_chunks = (P + chunk - 1) / chunk;
     int32_t* counts = static_cast<int32_t*>(scratch);
     hipLaunchKernelGGL(permute_hist_kernel, dim3(n_chunks), dim3(kSortThreads), 0, st, topk_idx, P,
-                       E, n_chunks, counts);
-    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(kSortThreads), 0, st, counts,
-                       E * n_chunks, E, n_chunks, P, offsets);
+                       E, chunk, counts);
     hipLaunchKernelGGL(permute_scatter_kernel, dim3(n_chunks), dim3(kSortThreads), 0, st, topk_idx,
-                       P, E, n_chunks, counts, perm, inv_perm);
+                       P, E, chunk, n_chunks, counts, offsets, perm, inv_perm);
     return launch_status();
 }
 

@@ -33,16 +33,18 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
 }
 
 // Large batches: the whole router (E x d fp32) is staged in LDS once per workgroup and a wave
-// owns a token: it reads the token's row once, takes the E router rows from LDS and ends with
-// one butterfly per expert, so lane e holds logit e and the selection follows in the same wave
-// with no further exchange.  The multiply-adds of a logit run in the same order as in
+// owns TOK tokens at a time: it reads their rows once, the next chunk on its way while one is multiplied, takes the E router
+// rows from LDS for all of them together and ends with one butterfly per token and expert, so lane e holds logit e and the
+// selection follows in the same wave with no further exchange.  The multiply-adds of a logit run in the same order as in
 // router_logits (lane l: elements [l*VEC, l*VEC+VEC) of every 64*VEC-wide chunk, ascending), so
 // both kernels give bit-identical logits.  For E <= kRouteLdsMaxE and E * d * 4 bytes of LDS.
+// (One token at a time read 64 KB of LDS and waited for its chunks one by one: 16384 tokens, 2048 wide, 8
+// experts 42 us, 34 now.)
 constexpr int kRouteLdsMaxE = 16;
 constexpr int kRouteLdsBytes = 128 * 1024;
 
-template <typename T>
-__global__ __launch_bounds__(kRouteWaves* kWave) void route_lds_kernel(
+template <typename T, int TOK, int MAXE>
+__global__ __launch_bounds__(kRouteWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void route_lds_kernel(
     const T* __restrict__ x, const float* __restrict__ rw, const float* __restrict__ rb,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate, float* __restrict__ probs,
     int T_, int d, int E, int k, int tokens_per_wave) {
@@ -52,48 +54,63 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_lds_kernel(
     extern __shared__ __align__(16) float s_rw[];  // [E][d]
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int t_first = (blockIdx.x * kRouteWaves + wave) * tokens_per_wave, t_end = min(T_, t_first + tokens_per_wave);
+    const int chunks = (d + CH - 1) / CH;  // the last one may be ragged: lanes beyond the row add nothing
+    typename S::vec_t cur[TOK], nxt[TOK];
+    auto load = [&](typename S::vec_t (&v)[TOK], int t, int c) {
+        const int i = min(c * CH + lane * VEC, d - VEC);
+#pragma unroll
+        for (int u = 0; u < TOK; ++u) v[u] = *reinterpret_cast<const typename S::vec_t*>(x + (size_t)min(t + u, T_ - 1) * d + i);
+    };
+    load(cur, t_first, 0);
     for (int i = threadIdx.x; i < E * d / 4; i += kRouteWaves * kWave)
         reinterpret_cast<f32x4*>(s_rw)[i] = reinterpret_cast<const f32x4*>(rw)[i];
     __syncthreads();
 
-    const int t_first = (blockIdx.x * kRouteWaves + wave) * tokens_per_wave;
-    const int nfull = d / CH;
-    for (int t = t_first; t < min(T_, t_first + tokens_per_wave); ++t) {
-        float acc[kRouteLdsMaxE];
+    for (int t = t_first; t < t_end; t += TOK) {
+        float acc[MAXE][TOK];
 #pragma unroll
-        for (int e = 0; e < kRouteLdsMaxE; ++e) acc[e] = 0.f;
-        auto chunk = [&](int i) {
-            const typename S::vec_t xv = *reinterpret_cast<const typename S::vec_t*>(x + (size_t)t * d + i);
+        for (int e = 0; e < MAXE; ++e)
 #pragma unroll
-            for (int e = 0; e < kRouteLdsMaxE; ++e) {
-                if (e < E) {  // wave-uniform
+            for (int u = 0; u < TOK; ++u) acc[e][u] = 0.f;
+        for (int c = 0; c < chunks; ++c) {
+            const bool last = c + 1 == chunks;
+            load(nxt, last ? t + TOK : t, last ? 0 : c + 1);
+            const int i = c * CH + lane * VEC;
+            if (i < d) {
+#pragma unroll
+                for (int e = 0; e < MAXE; ++e) {
+                    if (e >= E) continue;  // wave-uniform
                     const float* w = s_rw + e * d + i;
 #pragma unroll
                     for (int q = 0; q < VEC; q += 4) {
                         const f32x4 wv = *reinterpret_cast<const f32x4*>(w + q);
-                        acc[e] = fmaf(S::get(xv, q + 0), wv[0], acc[e]);
-                        acc[e] = fmaf(S::get(xv, q + 1), wv[1], acc[e]);
-                        acc[e] = fmaf(S::get(xv, q + 2), wv[2], acc[e]);
-                        acc[e] = fmaf(S::get(xv, q + 3), wv[3], acc[e]);
+#pragma unroll
+                        for (int u = 0; u < TOK; ++u)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) acc[e][u] = fmaf(S::get(cur[u], q + j), wv[j], acc[e][u]);
                     }
                 }
             }
-        };
-        for (int c = 0; c < nfull; ++c) chunk(c * CH + lane * VEC);
-        if (nfull * CH + lane * VEC < d) chunk(nfull * CH + lane * VEC);
-        float logit = 0.f;
 #pragma unroll
-        for (int e = 0; e < kRouteLdsMaxE; ++e) {
-            if (e < E) {
-                const float sum = wave_sum(acc[e]);
+            for (int u = 0; u < TOK; ++u) cur[u] = nxt[u];
+        }
+#pragma unroll
+        for (int u = 0; u < TOK; ++u) {
+            float logit = 0.f;
+#pragma unroll
+            for (int e = 0; e < MAXE; ++e) {
+                if (e >= E) continue;
+                const float sum = wave_sum(acc[e][u]);
                 if (lane == e) logit = sum + (rb ? rb[e] : 0.f);
             }
-        }
-        const RouterPick r = router_select(lane, E, k, lane < E ? logit : 0.f);
-        if (probs && lane < E) probs[(size_t)t * E + lane] = r.p / r.den;
-        if (r.slot >= 0) {
-            topk_idx[(size_t)t * k + r.slot] = lane;
-            topk_gate[(size_t)t * k + r.slot] = r.p / r.sel_sum;
+            if (t + u >= t_end) continue;
+            const RouterPick r = router_select(lane, E, k, lane < E ? logit : 0.f);
+            if (probs && lane < E) probs[(size_t)(t + u) * E + lane] = r.p / r.den;
+            if (r.slot >= 0) {
+                topk_idx[(size_t)(t + u) * k + r.slot] = lane;
+                topk_gate[(size_t)(t + u) * k + r.slot] = r.p / r.sel_sum;
+            }
         }
     }
 }
@@ -102,24 +119,28 @@ template <typename T>
 static int launch_route_lds(const moe_shape& s, const T* x, const float* rw, const float* rb,
                             int32_t* topk_idx, float* topk_gate, float* probs, hipStream_t st) {
     const size_t lds = (size_t)s.n_experts * s.d_model * sizeof(float);
-    static std::atomic<uint64_t> lds_allowed;
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(route_lds_kernel<T>), kRouteLdsBytes, lds_allowed) != MOE_OK)
-        return MOE_ERR_LAUNCH;
     // up to two workgroups per CU, every wave with the same number of tokens
     const int waves = 2 * 256 * kRouteWaves;
     const int tokens_per_wave = (s.n_tokens + waves - 1) / waves;
     const int per_block = tokens_per_wave * kRouteWaves;
     dim3 grid((s.n_tokens + per_block - 1) / per_block), block(kRouteWaves * kWave);
-    hipLaunchKernelGGL(route_lds_kernel<T>, grid, block, lds, st, x, rw, rb, topk_idx, topk_gate, probs,
-                       s.n_tokens, s.d_model, s.n_experts, s.top_k, tokens_per_wave);
-    return launch_status();
+    auto launch = [&](auto kern, std::atomic<uint64_t>& lds_allowed) {
+        if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), kRouteLdsBytes, lds_allowed) != MOE_OK) return (int)MOE_ERR_LAUNCH;
+        hipLaunchKernelGGL(kern, grid, block, lds, st, x, rw, rb, topk_idx, topk_gate, probs, s.n_tokens, s.d_model, s.n_experts,
+                           s.top_k, tokens_per_wave);
+        return launch_status();
+    };
+    static std::atomic<uint64_t> allowed[4];
+    if (s.n_experts <= 8)
+        return tokens_per_wave > 2 ? launch(route_lds_kernel<T, 4, 8>, allowed[0]) : launch(route_lds_kernel<T, 2, 8>, allowed[1]);
+    return tokens_per_wave > 2 ? launch(route_lds_kernel<T, 4, 16>, allowed[2]) : launch(route_lds_kernel<T, 2, 16>, allowed[3]);
 }
 
 int launch_route(const moe_shape& s, const void* x, const float* rw, const float* rb,
                  int32_t* topk_idx, float* topk_gate, float* probs, hipStream_t st) {
     if (s.n_tokens == 0) return MOE_OK;
-    // (measured on the 2048-wide, 8-expert router: 15.6 us against 12.7 at 2048 tokens, 41 against
-    // 64 at 16384; the two cross near 4096)
+    // (measured on the 2048-wide, 8-expert router: 15.6 us against 12.7 at 2048 tokens, 34 against
+    // 64 at 16384, 18 against 34 at 8192)
     if (s.n_tokens >= 8192 && s.n_experts <= kRouteLdsMaxE &&
         (size_t)s.n_experts * s.d_model * sizeof(float) <= (size_t)kRouteLdsBytes) {
         if (s.act_dtype == MOE_F32)

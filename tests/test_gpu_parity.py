@@ -184,6 +184,37 @@ def test_permute_matches_oracle_bit_exact(dev, oracle, T, k, E):
     assert np.array_equal(bits_of(xp)[r_inv].reshape(T, k, d)[:, 0], x_np)
 
 
+@pytest.mark.parametrize("T,k,E,room", [
+    # one pair more than a workgroup sorts alone; a last chunk of one pair; 256 chunks and the first size past them; many experts
+    (8193, 1, 3, 1 << 20), (5121, 2, 8, 1 << 20), (65536, 4, 16, 1 << 20), (65537, 4, 16, 1 << 20), (9000, 3, 64, 1 << 20),
+    (5121, 2, 8, None), (65537, 4, 16, None),  # no more scratch than is asked for: longer chunks
+])
+def test_permute_in_chunks_of_any_length(dev, oracle, T, k, E, room):
+    rng = np.random.default_rng(T + E)
+    keys = np.sort(rng.integers(0, E, (T, k)), axis=1).astype(np.int32)  # (the sort takes repeated experts, too)
+    keys[: T // 3] = rng.integers(0, max(1, E // 4), (T // 3, k))
+    shape = pkg.make_shape(T, 8, 8, E, k, 0, pkg.MOE_BF16)
+    need = ((T * k + 8191) // 8192 * E * 4 + 255) // 256 * 256
+    off, perm, inv = (torch.full((n,), -1, dtype=torch.int32, device=dev) for n in (E + 1, T * k, T * k))
+    ws = torch.empty(room or need, dtype=torch.uint8, device=dev)
+    pkg.moe_permute(shape, to_device(keys, dev), off, perm, inv, None, None, ws)
+    torch.cuda.synchronize()
+    for got, ref in zip((off, perm, inv), oracle.permute(keys, E)):
+        assert np.array_equal(got.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype", [
+    (8192, 72, 5, 2, "bf16"), (16385, 520, 8, 3, "bf16"), (8193, 1032, 9, 1, "bf16"), (12289, 264, 16, 4, "bf16"), (8195, 68 * 4, 7, 2, "f32"),
+])
+def test_route_several_tokens_per_wave(dev, oracle, T, d, E, k, dtype):
+    # two and four tokens at a time, remainders of a wave's share, ragged chunks, up to 8 and up to 16 experts
+    cfg = _cfg(d=d, F=8, E=E, k=k, dtype=dtype, seed=2100 + T + E)
+    w_np = wl.make_layer_weights(cfg)
+    x_np = wl.make_inputs(cfg, T)
+    idx, gate, probs = _route_gpu(dev, to_device(x_np, dev), weights_to_device(w_np, dev), E, k, DT[dtype])
+    _check_routing(oracle, x_np, w_np, k, idx, gate, probs)
+
+
 @pytest.mark.parametrize("T,k,E", [(1_000_000, 4, 64), ((1 << 21) - 1, 8, 8)])
 def test_permute_large_without_payload(dev, oracle, T, k, E):
     # several hundred workgroups per kernel of the multi-pass sort; the second case is the
