@@ -11,13 +11,13 @@ namespace moe {
 // PARTS: partial outputs of y_perm, of type Y (known at compile time, so that the loads of a row are all in flight
 // together: 8 tokens of a 1024 / 2816 layer 38.9 -> 37.1 us)
 template <typename T, typename Y, int PARTS>
-__global__ __launch_bounds__(256) void combine_kernel(const Y* __restrict__ y_perm,
-                                                      const int32_t* __restrict__ inv_perm,
-                                                      const float* __restrict__ gate,
-                                                      const T* __restrict__ residual,
-                                                      const T* __restrict__ addend,
-                                                      T* __restrict__ y, int d, int k, int P,
-                                                      int addend_parts) {
+__global__ __launch_bounds__(256) void combine_kernel(ptr_arg a_inv, ptr_arg a_gate, ptr_arg a_perm, int d, int k, int P, int addend_parts,
+                                                      ptr_arg a_residual, ptr_arg a_addend, ptr_arg a_y) {
+    const int32_t* const inv_perm = from_arg<const int32_t>(a_inv);
+    const float* const gate = from_arg<const float>(a_gate);
+    const Y* const y_perm = from_arg<const Y>(a_perm);
+    const T *const residual = from_arg<const T>(a_residual), *const addend = from_arg<const T>(a_addend);
+    T* const y = from_arg<T>(a_y);
     typedef Store<T> S;
     constexpr int VEC = S::VEC, YV = VEC / Store<Y>::VEC;  // loads of y_perm per chunk of y
     typedef typename S::vec_t vec_t;
@@ -70,9 +70,9 @@ __global__ __launch_bounds__(256) void combine_kernel(const Y* __restrict__ y_pe
 template <typename T, typename Y, int PARTS>
 static int combine_on(const moe_shape& s, const void* y_perm, const int32_t* inv_perm, const float* topk_gate,
                       const void* residual, void* y, hipStream_t st, const void* addend, int addend_parts) {
-    hipLaunchKernelGGL((combine_kernel<T, Y, PARTS>), dim3(s.n_tokens), dim3(256), 0, st, (const Y*)y_perm, inv_perm,
-                       topk_gate, (const T*)residual, (const T*)addend, (T*)y, s.d_model, s.top_k, s.n_tokens * s.top_k,
-                       addend_parts);
+    hipLaunchKernelGGL((combine_kernel<T, Y, PARTS>), dim3(s.n_tokens), dim3(256), 0, st, as_arg(inv_perm), as_arg(topk_gate),
+                       as_arg(y_perm), s.d_model, s.top_k, s.n_tokens * s.top_k, addend_parts, as_arg(residual), as_arg(addend),
+                       as_arg(y));
     return launch_status();
 }
 

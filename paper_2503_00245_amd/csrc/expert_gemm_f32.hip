@@ -205,6 +205,8 @@ struct TokenLayer {
     float *gate, *h, *y;
     const float* residual;
     int slices;  // token_down: waves per expert
+    const float *rw, *rb;
+    int route_blocks;
 };
 // acc[m] += A row of the lane . B[m] row of the lane over the k-steps first, first + stride, ... of K.  (The next D on
 // their way beside the present ones: slower, 17.3 -> 21.3 us for 32 tokens of 256 / 640, fewer waves fit.)
@@ -234,10 +236,10 @@ __device__ __forceinline__ void token_tile(const float* pa, const float* const (
 }
 
 template <int D>
-__global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(const TokenLayer g, const float* __restrict__ rw,
-                                                                               const float* __restrict__ rb, int route_blocks) {
+__global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(const TokenLayer g) {
+    const int route_blocks = g.route_blocks;
     if ((int)blockIdx.x < route_blocks) {
-        route_tokens<float, 4, kRouteTok>(g.x, rw, rb, g.idx, g.gate, nullptr, g.T, g.d, g.E, g.k, blockIdx.x);
+        route_tokens<float, 4, kRouteTok>(g.x, g.rw, g.rb, g.idx, g.gate, nullptr, g.T, g.d, g.E, g.k, blockIdx.x);
         return;
     }
     __shared__ float s_part[2][kRouteWaves][16][17];
@@ -314,15 +316,16 @@ int launch_token_layer_f32(const moe_shape& s, const moe_weights& w, const void*
                            const void* residual, void* y, hipStream_t st, StageTimer* timer) {
     int slices = kTokenWaves;
     while (slices * s.n_experts > kTokenWaves) slices /= 2;
+    const int route_blocks = (s.n_tokens + kRouteTok - 1) / kRouteTok;
     const TokenLayer g{static_cast<const float*>(x), static_cast<const float*>(w.w_gate), static_cast<const float*>(w.w_up),
                        static_cast<const float*>(w.w_down), s.n_tokens, s.d_model, s.d_ff, s.n_experts, s.top_k, idx, gate, h,
-                       static_cast<float*>(y), static_cast<const float*>(residual), slices};
-    const int tb = (s.n_tokens + 15) / 16, route_blocks = (s.n_tokens + kRouteTok - 1) / kRouteTok;
+                       static_cast<float*>(y), static_cast<const float*>(residual), slices, w.router_w, w.router_b, route_blocks};
+    const int tb = (s.n_tokens + 15) / 16;
     const dim3 grid(route_blocks + tb * s.n_experts * ((s.d_ff + 15) / 16));
     if (s.d_model <= 16 * kRouteWaves)
-        hipLaunchKernelGGL(token_gate_up_f32_kernel<1>, grid, dim3(kRouteWaves * kWave), 0, st, g, w.router_w, w.router_b, route_blocks);
+        hipLaunchKernelGGL(token_gate_up_f32_kernel<1>, grid, dim3(kRouteWaves * kWave), 0, st, g);
     else
-        hipLaunchKernelGGL(token_gate_up_f32_kernel<4>, grid, dim3(kRouteWaves * kWave), 0, st, g, w.router_w, w.router_b, route_blocks);
+        hipLaunchKernelGGL(token_gate_up_f32_kernel<4>, grid, dim3(kRouteWaves * kWave), 0, st, g);
     int rc = launch_status();
     if (rc != MOE_OK) return rc;
     stage_mark(timer, "route_gate_up_swiglu");

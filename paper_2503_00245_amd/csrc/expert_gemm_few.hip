@@ -63,7 +63,9 @@ constexpr int region_bytes() {
 // PAIR: two matrices (gate and up, or C and C1); SWIGLU: one output of both; DUAL: the second has activations of its own.
 // F32: k-parts in fp32.
 template <int MT, int S, bool PAIR, bool SWIGLU, bool DUAL, bool F32>
-__global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_few_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_few_kernel(
+    ptr_arg a_keys, ptr_arg a_offsets, int g_P, int g_E, const GemmArgs g) {
+    const int32_t *const g_keys = from_arg<const int32_t>(a_keys), *const g_offsets = from_arg<const int32_t>(a_offsets);
     static_assert(!SWIGLU || PAIR, "the activation takes two products");
     static_assert(!DUAL || PAIR, "two activation operands with two matrices");
     constexpr int NW = kWaves, NM = PAIR ? 2 : 1, NX = DUAL ? 2 : 1, ROWS = 16 * MT;
@@ -78,15 +80,15 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(2
     char* const my_region = smem + wave * REGION;
 
     const GemmSeg& sg = g.seg[0];
-    const int K = sg.K, N = g.N, E = g.E;
+    const int K = sg.K, N = g.N, E = g_E;
     const int parts = F32 ? g.k_parts : 1;
     const int steps = (K + kStepK - 1) / kStepK, blocks = (N + 15) / 16;
 
     // ---- groups: in lane e, group e's bounds
     int lo, hi, key[kKeyWords];
-    if (g.keys) {
+    if (g_keys) {
 #pragma unroll
-        for (int c = 0; c < kKeyWords; ++c) key[c] = c * kWave + lane < g.P ? g.keys[c * kWave + lane] : -1;
+        for (int c = 0; c < kKeyWords; ++c) key[c] = c * kWave + lane < g_P ? g_keys[c * kWave + lane] : -1;
         int at = 0;
         lo = hi = 0;
         int slot[kKeyWords];
@@ -113,7 +115,7 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(2
                 }
         }
     } else {
-        group_bounds(g.offsets, E, g.P, lo, hi);
+        group_bounds(g_offsets, E, g_P, lo, hi);
     }
 
     // ---- this workgroup's share of the units (group, part, 16 output columns), in that order
@@ -192,7 +194,7 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(2
     };
     bf16x8 x[NX][MT][S];
     auto load_x = [&](const Unit& u) {
-        if (g.keys && sg.gather) {  // the group's pairs, in order
+        if (g_keys && sg.gather) {  // the group's pairs, in order
             int rank = -u.row0 + MOE_READLANE(lo, u.e);
 #pragma unroll
             for (int c = 0; c < kKeyWords; ++c) {
@@ -207,7 +209,7 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(2
             const int m = min(mt * 16 + (lane & 15), u.n - 1);
             int row = u.row0 + m;
             if (sg.gather) {
-                row = g.keys ? s_rows[m] : g.row_map[row];
+                row = g_keys ? s_rows[m] : g.row_map[row];
                 row = quick_div(min(max(row, 0), g.P - 1), g.row_div);
             }
 #pragma unroll
@@ -369,7 +371,7 @@ int launch_few(const GemmArgs& g, hipStream_t st) {
     static std::atomic<uint64_t> lds_allowed;
     const auto kern = gemm_few_kernel<MT, S, PAIR, SWIGLU, DUAL, F32>;
     if (lds > 64 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3(kGrid), dim3(kWaves * kWave), lds, st, g);
+    hipLaunchKernelGGL(kern, dim3(kGrid), dim3(kWaves * kWave), lds, st, as_arg(g.keys), as_arg(g.offsets), g.P, g.E, g);
     return launch_status();
 }
 template <int MT, int S>

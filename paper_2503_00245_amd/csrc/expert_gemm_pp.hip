@@ -82,7 +82,9 @@ __device__ __forceinline__ void phase_end() {
 // F32: k-parts stored in fp32.
 // NT_B: weights past the caches (run_gemm_pp has the rule).
 template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_pp_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_pp_kernel(
+    ptr_arg a_keys, ptr_arg a_offsets, int g_P, int g_E, const GemmArgs g) {
+    const int32_t *const g_keys = from_arg<const int32_t>(a_keys), *const g_offsets = from_arg<const int32_t>(a_offsets);
     static_assert(!DUAL || SWIGLU, "two activation operands only with the activation");
     constexpr int WAVES_N = 8 / WAVES_M;
     constexpr int MB = BM / 32 / WAVES_M;         // 32-row blocks of a wave
@@ -120,16 +122,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     static_assert((kKeyChunks * kThreads / kWave * kMaxExperts + BM) * 4 <= B_BYTES, "dispatch scratch");
     int lo, hi;
     PairKeys<kThreads> keys;
-    if (g.keys) {
-        keys.load(g.keys, g.P);
-        keys.bounds(g.E, s_count, lo, hi);
+    if (g_keys) {
+        keys.load(g_keys, g_P);
+        keys.bounds(g_E, s_count, lo, hi);
         const int lane_ = threadIdx.x & 63;
         if (blockIdx.x == 0 && threadIdx.x < 64) {
             if (lane_ < g.E) g.offsets[lane_] = lo;
             if (lane_ == g.E - 1) g.offsets[g.E] = hi;
         }
     } else {
-        group_bounds(g.offsets, g.E, g.P, lo, hi);
+        group_bounds(g_offsets, g_E, g_P, lo, hi);
     }
     // SwiGLU products of 256-row tiles: blocks of four n-tiles with the expert's m-tiles inside, so that the 32
     // tiles in flight on an XCD share eight A and four B tiles in its L2 instead of all m-tiles of one
@@ -433,7 +435,7 @@ int launch_pp(GemmArgs& g, hipStream_t st) {
     static std::atomic<uint64_t> lds_allowed;
     const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, NT_B>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, g);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, as_arg(g.keys), as_arg(g.offsets), g.P, g.E, g);
     return launch_status();
 }
 template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32 = false>

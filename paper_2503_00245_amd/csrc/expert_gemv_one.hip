@@ -5,7 +5,8 @@
 //                        selected expert (gate / up projection with SwiGLU, or the two rank factors)
 //   decode_last_kernel   y = sum_j gate_j M_j h_j (+ residual) over the selected experts
 //
-// Both are bound by HBM: a CU has to keep its L1 full of requests from the first clock to the last.
+// Both are bound by HBM: a CU has to keep its L1 full of requests from the first clock to the last.  What the first loads
+// need stands at the head of every kernel's argument list: scalars there arrive in registers with the wave.
 #include <algorithm>
 
 #include "gemv.h"
@@ -26,19 +27,19 @@ constexpr int kOneCus = 256;
 // NC: 1 KB chunks per row.
 template <typename T, int NC, bool SWIGLU>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_first_kernel(
-    const FirstStage a) {
+    ptr_arg ax, ptr_arg aw, ptr_arg ab, int n, int E, int route_blocks, const FirstStage a) {
     typedef Store<T> S;
     typedef typename S::vec_t vec_t;
     constexpr int VEC = S::VEC, CH = kWave * VEC;
     __shared__ float s_logit[kMaxExperts];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int n = a.d;
-    const T* x = static_cast<const T*>(a.x);
+    const T* x = from_arg<const T>(ax);
+    const float *router_w = from_arg<const float>(aw), *router_b = from_arg<const float>(ab);
     // workgroups from route_blocks on: the shared base's rows, one matrix pair that needs no routing
-    const bool base = !SWIGLU && (int)blockIdx.x >= a.route_blocks;
-    const int first_block = base ? a.route_blocks : 0;
-    const int blocks = base ? (int)gridDim.x - a.route_blocks : a.route_blocks;
+    const bool base = !SWIGLU && (int)blockIdx.x >= route_blocks;
+    const int first_block = base ? route_blocks : 0;
+    const int blocks = base ? (int)gridDim.x - route_blocks : route_blocks;
     const int k = base ? 1 : a.k, rows = base ? a.base_rows : a.rows;
     const T* W0 = static_cast<const T*>(base ? a.base_W0 : a.W0);
     const T* W1 = static_cast<const T*>(base ? a.base_W1 : a.W1);
@@ -63,15 +64,15 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     int slot = lane == 0 ? 0 : -1;  // the pair whose expert this lane stands for
     float logit = 0.f, vmax = 0.f;
     if (!base) {
-        for (int e = wave; e < a.E; e += kOneWaves) {
-            const float b = a.router_b ? a.router_b[e] : 0.f;
+        for (int e = wave; e < E; e += kOneWaves) {
+            const float b = router_b ? router_b[e] : 0.f;
             float acc[1];
-            router_logits<VEC, 1, 4>(load_x, a.router_w + (size_t)e * n, n, lane, 1, acc);
+            router_logits<VEC, 1, 4>(load_x, router_w + (size_t)e * n, n, lane, 1, acc);
             if (lane == 0) s_logit[e] = acc[0] + b;
         }
         __syncthreads();
-        logit = lane < a.E ? s_logit[lane] : 0.f;
-        slot = router_slots(lane, a.E, k, logit, vmax);
+        logit = lane < E ? s_logit[lane] : 0.f;
+        slot = router_slots(lane, E, k, logit, vmax);
     }
 
     struct Unit {
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     };
     auto load = [&](Rows& r, const Unit& u) {
         // (clamped: with NaN logits the lanes may disagree about a round, and lanes past E may win it)
-        const int e = min(max(__ffsll((unsigned long long)__ballot(slot == u.j)) - 1, 0), a.E - 1);
+        const int e = min(max(__ffsll((unsigned long long)__ballot(slot == u.j)) - 1, 0), E - 1);
         const size_t at = (size_t)e * a.stride + (size_t)u.row * n;
         const T* p0 = W0 + at;
         const T* p1 = W1 + at;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     Unit u0 = settle(Unit{0, ((int)blockIdx.x - first_block) * kOneWaves + wave});
     if (u0.j < k) load(r0, u0);
     if (blockIdx.x == 0 && wave == 0) {  // the gates, for the last stage: behind the first requests
-        const RouterPick pick = router_weigh(lane, a.E, logit, slot, vmax);
+        const RouterPick pick = router_weigh(lane, E, logit, slot, vmax);
         if (slot >= 0) {
             a.idx[slot] = lane;
             a.gate[slot] = pick.p / pick.sel_sum;
@@ -164,38 +165,40 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
 // V: the stored type of the hidden vectors.
 template <typename T, typename V, int NC>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_last_kernel(
+    ptr_arg ai, ptr_arg av, ptr_arg aW, long long stride, int n, int k, int slices, int E, int rows,
     const LastStage a) {
+    const int32_t* idx = from_arg<const int32_t>(ai);
+    const T* W = from_arg<const T>(aW);
     typedef typename Store<T>::vec_t vec_t;
     typedef typename Store<V>::vec_t vvec_t;
     constexpr int VEC = Store<T>::VEC, CH = kWave * VEC, VL = VEC / Store<V>::VEC;
     __shared__ float s_part[kOneWaves];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int per_row = a.k * a.slices, rows_here = kOneWaves / per_row;
+    const int per_row = k * slices, rows_here = kOneWaves / per_row;
     const int local_row = wave / per_row, q = wave - local_row * per_row;
-    const int j = q / a.slices, slice = q - j * a.slices;
-    const int row = min((int)blockIdx.x * rows_here + local_row, a.rows - 1);
-    const int n = a.n;
+    const int j = q / slices, slice = q - j * slices;
+    const int row = min((int)blockIdx.x * rows_here + local_row, rows - 1);
 
     int off[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) off[c] = min((slice + c * a.slices) * CH + lane * VEC, n - VEC);
-    const bool tail_in = (slice + (NC - 1) * a.slices) * CH + lane * VEC < n;
-    const V* v = static_cast<const V*>(a.v) + (size_t)j * n;
+    for (int c = 0; c < NC; ++c) off[c] = min((slice + c * slices) * CH + lane * VEC, n - VEC);
+    const bool tail_in = (slice + (NC - 1) * slices) * CH + lane * VEC < n;
+    const V* v = from_arg<const V>(av) + (size_t)j * n;
     vvec_t x[NC][VL];
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int l = 0; l < VL; ++l) x[c][l] = *reinterpret_cast<const vvec_t*>(v + off[c] + l * Store<V>::VEC);
     __builtin_amdgcn_sched_barrier(0);
-    const int e = min(max(a.idx[j], 0), a.E - 1);
-    const T* w = static_cast<const T*>(a.W) + (size_t)e * a.stride + (size_t)row * n;
+    const int e = min(max(idx[j], 0), E - 1);
+    const T* w = W + (size_t)e * stride + (size_t)row * n;
     vec_t wv[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) wv[c] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(w + off[c]));
     // what the last step needs beside the sums
     const int my_row = (int)blockIdx.x * rows_here + (int)threadIdx.x;
-    const bool mine = (int)threadIdx.x < rows_here && my_row < a.rows;
+    const bool mine = (int)threadIdx.x < rows_here && my_row < rows;
     float res = 0.f;
     if (a.residual && mine) res = Store<T>::to_f32(static_cast<const T*>(a.residual)[my_row]);
     __builtin_amdgcn_sched_barrier(0);
@@ -213,9 +216,9 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     __syncthreads();
     if (mine) {
         float total = 0.f;
-        for (int jj = 0; jj < a.k; ++jj) {
+        for (int jj = 0; jj < k; ++jj) {
             float sum = 0.f;
-            for (int sl = 0; sl < a.slices; ++sl) sum += s_part[threadIdx.x * per_row + jj * a.slices + sl];
+            for (int sl = 0; sl < slices; ++sl) sum += s_part[threadIdx.x * per_row + jj * slices + sl];
             total = fmaf(a.gate[jj], sum, total);
         }
         static_cast<T*>(a.y)[my_row] = Store<T>::from_f32(total + res);
@@ -234,34 +237,39 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
 //   else:   y = b0 + sum_j gate_j L0_j t0_j (+ residual)
 constexpr int kLowRankWaves = 4;
 template <typename T, bool HIDDEN>
-__global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(const LowRankStage a) {
+__global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(
+    ptr_arg ai, ptr_arg aL, ptr_arg at0, long long stride, int r, int rows, int k, int lanes, int E,
+    const LowRankStage a) {
+    const int32_t* idx = from_arg<const int32_t>(ai);
+    const T* L0 = from_arg<const T>(aL);
+    const float* t0 = from_arg<const float>(at0);
     typedef typename Store<T>::vec_t vec_t;
     constexpr int VEC = Store<T>::VEC;
     const int lane = threadIdx.x & (kWave - 1);
-    const int group = lane / a.lanes, sub = lane - group * a.lanes, per_wave = kWave / a.lanes;
+    const int group = lane / lanes, sub = lane - group * lanes, per_wave = kWave / lanes;
     const int row_at = ((int)blockIdx.x * kLowRankWaves + (int)(threadIdx.x / kWave)) * per_wave + group;
-    const int row = min(row_at, a.rows - 1);
-    const bool mine = sub == 0 && row_at < a.rows;
+    const int row = min(row_at, rows - 1);
+    const bool mine = sub == 0 && row_at < rows;
     const bool base = !HIDDEN || a.b0;
     const float b0 = base ? a.b0[row] : 0.f, b1 = HIDDEN && base ? a.b1[row] : 0.f;
     float res = 0.f;
     if (!HIDDEN && a.residual) res = Store<T>::to_f32(static_cast<const T*>(a.residual)[row]);
     float mix = 0.f;
-    for (int j0 = 0; j0 < a.k; j0 += 2) {
+    for (int j0 = 0; j0 < k; j0 += 2) {
         float acc[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
         const T* l[2][2];
         const float* t[2][2];
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            const int j = min(j0 + p, a.k - 1);
-            const int e = min(max(a.idx[j], 0), a.E - 1);
-            const size_t at = (size_t)e * a.stride + (size_t)row * a.r;
-            l[p][0] = static_cast<const T*>(a.L0) + at;
-            t[p][0] = a.t0 + (size_t)j * a.r;
+            const int j = min(j0 + p, k - 1);
+            const int e = min(max(idx[j], 0), E - 1);
+            const size_t at = (size_t)e * stride + (size_t)row * r;
+            l[p][0] = L0 + at;
+            t[p][0] = t0 + (size_t)j * r;
             l[p][1] = HIDDEN ? static_cast<const T*>(a.L1) + at : l[p][0];
-            t[p][1] = HIDDEN ? a.t1 + (size_t)j * a.r : t[p][0];
+            t[p][1] = HIDDEN ? a.t1 + (size_t)j * r : t[p][0];
         }
-        for (int i = sub * VEC; i < a.r; i += a.lanes * VEC) {
+        for (int i = sub * VEC; i < r; i += lanes * VEC) {
             vec_t w[2][2];
             f32x4 v[2][2][VEC / 4];
 #pragma unroll
@@ -281,15 +289,15 @@ __global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(c
         }
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            for (int o = 1; o < a.lanes; o *= 2) {
+            for (int o = 1; o < lanes; o *= 2) {
                 acc[p][0] += __shfl_xor(acc[p][0], o, kWave);
                 if (HIDDEN) acc[p][1] += __shfl_xor(acc[p][1], o, kWave);
             }
-            if (j0 + p < a.k) {
+            if (j0 + p < k) {
                 const float g = a.gate[j0 + p];
                 if (HIDDEN) {
                     const float h = silu_f32(b0 + acc[p][0]) * (b1 + acc[p][1]);
-                    if (mine) a.h[(size_t)(j0 + p) * a.rows + row] = h;
+                    if (mine) a.h[(size_t)(j0 + p) * rows + row] = h;
                     mix = fmaf(g, h, mix);
                 } else {
                     mix = fmaf(g, acc[p][0], mix);
@@ -310,24 +318,26 @@ __global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(c
 // NC: 1 KB chunks per row.
 template <typename T, int NC>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_hidden_kernel(
+    ptr_arg ai, ptr_arg aL0, ptr_arg aL1, long long stride, int n, int rows, int k, int E,
     const LowRankStage a) {
+    const int32_t* idx = from_arg<const int32_t>(ai);
     typedef Store<T> S;
     typedef typename S::vec_t vec_t;
     constexpr int VEC = S::VEC, CH = kWave * VEC;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int at = (int)blockIdx.x * kOneWaves + wave, waves = (int)gridDim.x * kOneWaves / a.k;  // per pair
-    const int j = at % a.k, n = a.r;
-    int row = at / a.k;
-    if (row >= waves || row >= a.rows) return;
+    const int at = (int)blockIdx.x * kOneWaves + wave, waves = (int)gridDim.x * kOneWaves / k;  // per pair
+    const int j = at % k;
+    int row = at / k;
+    if (row >= waves || row >= rows) return;
     int off[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) off[c] = min(c * CH + lane * VEC, n - VEC);
     const bool tail_in = (NC - 1) * CH + lane * VEC < n;
-    const int e = min(max(a.idx[j], 0), a.E - 1);
-    const T* L0 = static_cast<const T*>(a.L0) + (size_t)e * a.stride;
-    const T* L1 = static_cast<const T*>(a.L1) + (size_t)e * a.stride;
-    float* h = a.h + (size_t)j * a.rows;
+    const int e = min(max(idx[j], 0), E - 1);
+    const T* L0 = from_arg<const T>(aL0) + (size_t)e * stride;
+    const T* L1 = from_arg<const T>(aL1) + (size_t)e * stride;
+    float* h = a.h + (size_t)j * rows;
     struct Rows {
         vec_t w0[NC], w1[NC];
     };
@@ -365,15 +375,15 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     };
     for (;;) {
         const int next = row + waves;
-        if (next < a.rows) load(r1, next);
+        if (next < rows) load(r1, next);
         __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the sums
         finish(r0, row);
-        if (next >= a.rows) return;
+        if (next >= rows) return;
         row = next + waves;
-        if (row < a.rows) load(r0, row);
+        if (row < rows) load(r0, row);
         __builtin_amdgcn_sched_barrier(0);
         finish(r1, next);
-        if (row >= a.rows) return;
+        if (row >= rows) return;
     }
 }
 
@@ -381,29 +391,32 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
 // waves each, NC chunks a wave and all of them requested at once.  (d = 0: the pairs alone)
 constexpr int kMidWaves = 8;
 template <typename T, int NC>
-__global__ __launch_bounds__(kMidWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void decode_mid_kernel(const MidStage a) {
+__global__ __launch_bounds__(kMidWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void decode_mid_kernel(
+    ptr_arg ai, ptr_arg ard, ptr_arg aw, long long stride, int n, int slices, int r, int k, int d, int E,
+    const MidStage a) {
+    const int32_t* idx = from_arg<const int32_t>(ai);
     typedef typename Store<T>::vec_t vec_t;
     constexpr int VEC = Store<T>::VEC, CH = kWave * VEC, VL = VEC / 4;
     __shared__ float s_part[kMidWaves];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int n = a.n, slice = wave % a.slices, rows_here = kMidWaves / a.slices;
-    const int low = a.k * a.r, units = low + a.d;
-    const int u_at = (int)blockIdx.x * rows_here + wave / a.slices, u = min(u_at, units - 1);
+    const int slice = wave % slices, rows_here = kMidWaves / slices;
+    const int low = k * r, units = low + d;
+    const int u_at = (int)blockIdx.x * rows_here + wave / slices, u = min(u_at, units - 1);
     int off[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) off[c] = min((slice + c * a.slices) * CH + lane * VEC, n - VEC);
-    const bool tail_in = (slice + (NC - 1) * a.slices) * CH + lane * VEC < n;
+    for (int c = 0; c < NC; ++c) off[c] = min((slice + c * slices) * CH + lane * VEC, n - VEC);
+    const bool tail_in = (slice + (NC - 1) * slices) * CH + lane * VEC < n;
     const float* v;
     const T* w;
     float* out;
     if (u < low) {
-        const int j = u / a.r, e = min(max(a.idx[j], 0), a.E - 1);
-        w = static_cast<const T*>(a.rd) + (size_t)e * a.stride + (size_t)(u - j * a.r) * n;
+        const int j = u / r, e = min(max(idx[j], 0), E - 1);
+        w = from_arg<const T>(ard) + (size_t)e * stride + (size_t)(u - j * r) * n;
         v = a.h + (size_t)j * n;
         out = a.td + u;
     } else {
-        w = static_cast<const T*>(a.w_down) + (size_t)(u - low) * n;
+        w = from_arg<const T>(aw) + (size_t)(u - low) * n;
         v = a.mix;
         out = a.y0 + (u - low);
     }
@@ -429,7 +442,7 @@ __global__ __launch_bounds__(kMidWaves* kWave) __attribute__((amdgpu_waves_per_e
     __syncthreads();
     if (slice == 0 && lane == 0 && u_at < units) {
         float sum = 0.f;
-        for (int sl = 0; sl < a.slices; ++sl) sum += s_part[wave + sl];
+        for (int sl = 0; sl < slices; ++sl) sum += s_part[wave + sl];
         *out = sum;
     }
 }
@@ -451,9 +464,9 @@ template <typename T, int NC>
 static void launch_first_nc(const FirstStage& a, bool swiglu, dim3 grid, hipStream_t st) {
     const dim3 block(kOneWaves * kWave);
     if (swiglu)
-        hipLaunchKernelGGL((decode_first_kernel<T, NC, true>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((decode_first_kernel<T, NC, true>), grid, block, 0, st, as_arg(a.x), as_arg(a.router_w), as_arg(a.router_b), a.d, a.E, a.route_blocks, a);
     else
-        hipLaunchKernelGGL((decode_first_kernel<T, NC, false>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((decode_first_kernel<T, NC, false>), grid, block, 0, st, as_arg(a.x), as_arg(a.router_w), as_arg(a.router_b), a.d, a.E, a.route_blocks, a);
 }
 
 template <typename T>
@@ -488,7 +501,7 @@ static int launch_last_nc(const LastStage& a, int nc, hipStream_t st) {
         if (nc != NC) return launch_last_nc<T, V, NC + 1>(a, nc, st);
         const int rows_here = kOneWaves / (a.k * a.slices);
         const dim3 grid((a.rows + rows_here - 1) / rows_here), block(kOneWaves * kWave);
-        hipLaunchKernelGGL((decode_last_kernel<T, V, NC>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((decode_last_kernel<T, V, NC>), grid, block, 0, st, as_arg(a.idx), as_arg(a.v), as_arg(a.W), a.stride, a.n, a.k, a.slices, a.E, a.rows, a);
         return launch_status();
     }
 }
@@ -538,7 +551,7 @@ static int launch_mid_nc(const MidStage& a, int nc, hipStream_t st) {
         if (nc != NC) return launch_mid_nc<NC + 1>(a, nc, st);
         const int rows_here = kMidWaves / a.slices;
         const dim3 grid((a.k * a.r + a.d + rows_here - 1) / rows_here), block(kMidWaves * kWave);
-        hipLaunchKernelGGL((decode_mid_kernel<bf16_t, NC>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((decode_mid_kernel<bf16_t, NC>), grid, block, 0, st, as_arg(a.idx), as_arg(a.rd), as_arg(a.w_down), a.stride, a.n, a.slices, a.r, a.k, a.d, a.E, a);
         return launch_status();
     }
 }
@@ -561,9 +574,9 @@ int launch_decode_low_rank(LowRankStage a, bool hidden, hipStream_t st) {
     const int per_block = kLowRankWaves * (kWave / a.lanes);
     const dim3 grid((a.rows + per_block - 1) / per_block), block(kLowRankWaves * kWave);
     if (hidden)
-        hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, true>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, true>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.t0), a.stride, a.r, a.rows, a.k, a.lanes, a.E, a);
     else
-        hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, false>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((decode_low_rank_kernel<bf16_t, false>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.t0), a.stride, a.r, a.rows, a.k, a.lanes, a.E, a);
     return launch_status();
 }
 
@@ -579,9 +592,9 @@ int launch_decode_hidden(const LowRankStage& a, hipStream_t st) {
     const long long units = (long long)a.k * a.rows;
     const dim3 grid((unsigned)std::min<long long>(kOneCus, (units + kOneWaves - 1) / kOneWaves)), block(kOneWaves * kWave);
     switch (chunks_of<bf16_t>(a.r)) {
-        case 1: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 1>), grid, block, 0, st, a); break;
-        case 2: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 2>), grid, block, 0, st, a); break;
-        case 3: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 3>), grid, block, 0, st, a); break;
+        case 1: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 1>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, a); break;
+        case 2: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 2>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, a); break;
+        case 3: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 3>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, a); break;
         default: return MOE_ERR_UNSUPPORTED;
     }
     return launch_status();

@@ -28,7 +28,8 @@ __device__ __forceinline__ unsigned long long expert_mask(const int32_t* __restr
     return m;
 }
 
-__global__ __launch_bounds__(kMetricThreads) void zero_counters_kernel(unsigned long long* p, int n, unsigned long long* q) {
+__global__ __launch_bounds__(kMetricThreads) void zero_counters_kernel(ptr_arg ap, int n, ptr_arg aq) {
+    unsigned long long *const p = from_arg<unsigned long long>(ap), *const q = from_arg<unsigned long long>(aq);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
     if (q && i == 0) *q = 0;
@@ -47,8 +48,9 @@ __device__ __forceinline__ unsigned long long replaced_set(const int32_t* __rest
 // start at zero.  (H is added here, one atomic per workgroup, and not by a kernel of its own: a
 // dependent launch costs 4-5 us, whatever it does.)
 __global__ __launch_bounds__(kMetricThreads) void replacements_kernel(
-    const int32_t* __restrict__ S, int B, int T, int K, int E, unsigned long long* __restrict__ He,
-    unsigned long long* __restrict__ H) {
+    ptr_arg aS, int B, int T, int K, int E, ptr_arg aHe, ptr_arg aH) {
+    const int32_t* const S = from_arg<const int32_t>(aS);
+    unsigned long long *const He = from_arg<unsigned long long>(aHe), *const H = from_arg<unsigned long long>(aH);
     __shared__ int s_cnt[kMaxExperts];
     if (threadIdx.x < kMaxExperts) s_cnt[threadIdx.x] = 0;
     __syncthreads();
@@ -74,8 +76,11 @@ __global__ __launch_bounds__(kMetricThreads) void replacements_kernel(
 // (number of replaced experts), to soft_part[block] and hard_part[block].  Nothing is accumulated in memory,
 // so nothing has to be cleared first.
 __global__ __launch_bounds__(kMetricThreads) void bles_partial_kernel(
-    const float* __restrict__ W, const int32_t* __restrict__ S, int B, int T, int K, int E,
-    int tokens_per_block, int vec, double* __restrict__ soft_part, int* __restrict__ hard_part) {
+    ptr_arg aW, ptr_arg aS, int B, int T, int K, int E, int tokens_per_block, int vec, ptr_arg a_soft, ptr_arg a_hard) {
+    const float* const W = from_arg<const float>(aW);
+    const int32_t* const S = from_arg<const int32_t>(aS);
+    double* const soft_part = from_arg<double>(a_soft);
+    int* const hard_part = from_arg<int>(a_hard);
     __shared__ double s_soft[kMetricThreads / kWave];
     __shared__ int s_hard[kMetricThreads / kWave];
     const int t0 = blockIdx.x * tokens_per_block;
@@ -120,8 +125,10 @@ __global__ __launch_bounds__(kMetricThreads) void bles_partial_kernel(
 // i, i + 256, ... in fp64 and the threads meet in a fixed tree (deterministic).  (One thread adding
 // all of them was a chain of 1536 dependent load-and-adds at 24 x 2048 tokens: 64 us.)
 __global__ __launch_bounds__(kMetricThreads) void bles_finalize_kernel(
-    const double* __restrict__ soft_part, const int* __restrict__ hard_part, int nblocks, int B, int T, int K,
-    double* __restrict__ out) {
+    ptr_arg a_soft, ptr_arg a_hard, int nblocks, int B, int T, int K, ptr_arg a_out) {
+    const double* const soft_part = from_arg<const double>(a_soft);
+    const int* const hard_part = from_arg<const int>(a_hard);
+    double* const out = from_arg<double>(a_out);
     __shared__ double s_soft[kMetricThreads];
     __shared__ unsigned long long s_hard[kMetricThreads];
     double L = 0.0;
@@ -160,8 +167,9 @@ constexpr int kOneChunkPairs = 32768;
 // one workgroup per layer: adjacent-token set comparisons (the resident set after token t is
 // always S_t, so the rule's state is just the previous token's selection)
 __global__ __launch_bounds__(kLayerThreads) void offload_kernel(
-    const int32_t* __restrict__ trace, int T, int K, int E, unsigned long long* __restrict__ changes,
-    unsigned long long* __restrict__ loads) {
+    ptr_arg a_trace, int T, int K, int E, ptr_arg a_changes, ptr_arg a_loads) {
+    const int32_t* const trace = from_arg<const int32_t>(a_trace);
+    unsigned long long *const changes = from_arg<unsigned long long>(a_changes), *const loads = from_arg<unsigned long long>(a_loads);
     __shared__ int s_ch, s_ld;
     if (threadIdx.x == 0) {
         s_ch = 0;
@@ -199,7 +207,9 @@ __global__ __launch_bounds__(kLayerThreads) void offload_kernel(
 // start at zero.  Every wave counts in LDS of its own.
 template <bool ONE>
 __global__ __launch_bounds__(kLayerThreads) void balance_count_kernel(
-    const int32_t* __restrict__ trace, int TK, int E, unsigned long long* __restrict__ counts) {
+    ptr_arg a_trace, int TK, int E, ptr_arg a_counts) {
+    const int32_t* const trace = from_arg<const int32_t>(a_trace);
+    unsigned long long* const counts = from_arg<unsigned long long>(a_counts);
     __shared__ int s_cnt[kLayerThreads / kWave][kMaxExperts];
     const int wave = threadIdx.x / kWave;
     for (int i = threadIdx.x; i < kLayerThreads / kWave * kMaxExperts; i += kLayerThreads) (&s_cnt[0][0])[i] = 0;
@@ -224,8 +234,9 @@ __global__ __launch_bounds__(kLayerThreads) void balance_count_kernel(
 // in ascending l.  One workgroup, a thread per layer (kMetricThreads layers at a time): the fp64
 // divisions, E per layer, are what takes time, and the layers' are independent.
 __global__ __launch_bounds__(kMetricThreads) void balance_finalize_kernel(
-    const unsigned long long* __restrict__ counts, int L, int TK, int E, double* __restrict__ delta,
-    double* __restrict__ mean) {
+    ptr_arg a_counts, int L, int TK, int E, ptr_arg a_delta, ptr_arg a_mean) {
+    const unsigned long long* const counts = from_arg<const unsigned long long>(a_counts);
+    double *const delta = from_arg<double>(a_delta), *const mean = from_arg<double>(a_mean);
     __shared__ double s_delta[kMetricThreads];
     double total = 0.0;
     for (int l0 = 0; l0 < L; l0 += kMetricThreads) {
@@ -269,10 +280,10 @@ int moe_expert_replacements(const int32_t* S, int32_t B, int32_t T, int32_t K, i
     hipStream_t st = as_stream(stream);
     unsigned long long* he = reinterpret_cast<unsigned long long*>(H_e);
     unsigned long long* h = reinterpret_cast<unsigned long long*>(H);
-    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(kMetricThreads), 0, st, he, E, h);
+    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(kMetricThreads), 0, st, as_arg(he), E, as_arg(h));
     if (T > 1)
         hipLaunchKernelGGL(replacements_kernel, dim3((B * T - 1) / kMetricThreads + 1), dim3(kMetricThreads), 0, st,
-                           S, B, T, K, E, he, h);
+                           as_arg(S), B, T, K, E, as_arg(he), as_arg(h));
     return launch_status();
 }
 
@@ -304,11 +315,11 @@ int moe_bles_loss(const float* probs, const int32_t* S, int32_t B, int32_t T, in
         const int tokens_per_block = max(max(kMetricThreads / 2, (4 * kMetricThreads + E - 1) / E), (B * T - 1) / max_blocks + 1);
         nblocks = (B * T - 1) / tokens_per_block + 1;
         hard_part = reinterpret_cast<int*>(soft_part + nblocks);
-        hipLaunchKernelGGL(bles_partial_kernel, dim3(nblocks), dim3(kMetricThreads), 0, st, probs, S, B, T, K, E,
-                           tokens_per_block, E % 4 == 0 && aligned16(probs) ? 1 : 0, soft_part, hard_part);
+        hipLaunchKernelGGL(bles_partial_kernel, dim3(nblocks), dim3(kMetricThreads), 0, st, as_arg(probs), as_arg(S), B, T, K, E,
+                           tokens_per_block, E % 4 == 0 && aligned16(probs) ? 1 : 0, as_arg(soft_part), as_arg(hard_part));
     }
-    hipLaunchKernelGGL(bles_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, soft_part, hard_part, nblocks, B, T, K,
-                       out);
+    hipLaunchKernelGGL(bles_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, as_arg(soft_part), as_arg(hard_part), nblocks, B, T, K,
+                       as_arg(out));
     return launch_status();
 }
 
@@ -317,9 +328,8 @@ int moe_offload_counters(const int32_t* trace, int32_t L, int32_t T, int32_t K, 
     int rc = check_trace_shape(L, T, K, E);
     if (rc != MOE_OK) return rc;
     if (!trace || !changes || !loads) return MOE_ERR_INVALID;
-    hipLaunchKernelGGL(offload_kernel, dim3(L), dim3(kLayerThreads), 0, as_stream(stream), trace, T,
-                       K, E, reinterpret_cast<unsigned long long*>(changes),
-                       reinterpret_cast<unsigned long long*>(loads));
+    hipLaunchKernelGGL(offload_kernel, dim3(L), dim3(kLayerThreads), 0, as_stream(stream), as_arg(trace), T,
+                       K, E, as_arg(changes), as_arg(loads));
     return launch_status();
 }
 
@@ -333,15 +343,15 @@ int moe_delta_uniform(const int32_t* trace, int32_t L, int32_t T, int32_t K, int
     unsigned long long* cnt = reinterpret_cast<unsigned long long*>(counts);
     const int TK = T * K;  // < 2^31 by check_trace_shape
     if (TK <= kOneChunkPairs) {
-        hipLaunchKernelGGL(balance_count_kernel<true>, dim3(1, L), dim3(kLayerThreads), 0, st, trace, TK, E, cnt);
+        hipLaunchKernelGGL(balance_count_kernel<true>, dim3(1, L), dim3(kLayerThreads), 0, st, as_arg(trace), TK, E, as_arg(cnt));
     } else {
         const int n = L * E;
         hipLaunchKernelGGL(zero_counters_kernel, dim3((n + kMetricThreads - 1) / kMetricThreads), dim3(kMetricThreads), 0,
-                           st, cnt, n, nullptr);
+                           st, as_arg(cnt), n, as_arg(nullptr));
         const int chunks = min(64, (TK + 4 * kLayerThreads - 1) / (4 * kLayerThreads));
-        hipLaunchKernelGGL(balance_count_kernel<false>, dim3(chunks, L), dim3(kLayerThreads), 0, st, trace, TK, E, cnt);
+        hipLaunchKernelGGL(balance_count_kernel<false>, dim3(chunks, L), dim3(kLayerThreads), 0, st, as_arg(trace), TK, E, as_arg(cnt));
     }
-    hipLaunchKernelGGL(balance_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, cnt, L, TK, E, delta, mean);
+    hipLaunchKernelGGL(balance_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, as_arg(cnt), L, TK, E, as_arg(delta), as_arg(mean));
     return launch_status();
 }
 

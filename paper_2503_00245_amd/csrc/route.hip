@@ -26,10 +26,9 @@ constexpr int kRouteLargeFrom = 1024;
 // 11.2-12.1 with eight); at 512 tokens two are the faster (128 workgroups do not fill the chip).
 template <typename T, int NB, int TOK>
 __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
-    const T* __restrict__ x, const float* __restrict__ rw, const float* __restrict__ rb,
-    int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate, float* __restrict__ probs,
-    int T_, int d, int E, int k) {
-    route_tokens<T, NB, TOK>(x, rw, rb, topk_idx, topk_gate, probs, T_, d, E, k, blockIdx.x);
+    ptr_arg x, ptr_arg rw, ptr_arg rb, int d, int E, int T_, int k, ptr_arg topk_idx, ptr_arg topk_gate, ptr_arg probs) {
+    route_tokens<T, NB, TOK>(from_arg<const T>(x), from_arg<const float>(rw), from_arg<const float>(rb), from_arg<int32_t>(topk_idx),
+                             from_arg<float>(topk_gate), from_arg<float>(probs), T_, d, E, k, blockIdx.x);
 }
 
 // Large batches: the whole router (E x d fp32) is staged in LDS once per workgroup and a wave
@@ -150,18 +149,18 @@ int launch_route(const moe_shape& s, const void* x, const float* rw, const float
     const bool small = s.n_tokens <= 256, large = s.n_tokens >= kRouteLargeFrom;
     const int tok = large ? kRouteTokLarge : kRouteTok;
     dim3 grid((s.n_tokens + tok - 1) / tok), block(kRouteWaves * kWave);
-    auto launch = [&](auto kern, auto* xp) {
-        hipLaunchKernelGGL(kern, grid, block, 0, st, xp, rw, rb, topk_idx, topk_gate, probs, s.n_tokens,
-                           s.d_model, s.n_experts, s.top_k);
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, 0, st, as_arg(x), as_arg(rw), as_arg(rb), s.d_model, s.n_experts, s.n_tokens, s.top_k,
+                           as_arg(topk_idx), as_arg(topk_gate), as_arg(probs));
     };
     if (s.act_dtype == MOE_F32) {
-        if (small) launch(route_kernel<float, 4, kRouteTok>, (const float*)x);
-        else if (!large) launch(route_kernel<float, MOE_ROUTE_NB_LARGE, kRouteTok>, (const float*)x);
-        else launch(route_kernel<float, MOE_ROUTE_NB_LARGE, kRouteTokLarge>, (const float*)x);
+        if (small) launch(route_kernel<float, 4, kRouteTok>);
+        else if (!large) launch(route_kernel<float, MOE_ROUTE_NB_LARGE, kRouteTok>);
+        else launch(route_kernel<float, MOE_ROUTE_NB_LARGE, kRouteTokLarge>);
     } else {
-        if (small) launch(route_kernel<bf16_t, 4, kRouteTok>, (const bf16_t*)x);
-        else if (!large) launch(route_kernel<bf16_t, MOE_ROUTE_NB_LARGE, kRouteTok>, (const bf16_t*)x);
-        else launch(route_kernel<bf16_t, MOE_ROUTE_NB_LARGE, kRouteTokLarge>, (const bf16_t*)x);
+        if (small) launch(route_kernel<bf16_t, 4, kRouteTok>);
+        else if (!large) launch(route_kernel<bf16_t, MOE_ROUTE_NB_LARGE, kRouteTok>);
+        else launch(route_kernel<bf16_t, MOE_ROUTE_NB_LARGE, kRouteTokLarge>);
     }
     return launch_status();
 }
