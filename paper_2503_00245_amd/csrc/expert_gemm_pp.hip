@@ -522,7 +522,13 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     // The smaller tiles follow the same line (whole layer, us, hint at every size / by this rule: 1100 tokens 432 / 1152
     // 37.9 / 33.2, 1024 / 2816 80.1 / 78.4, 400 / 1064 of rank 200 51.6 / 45.3; 2048 tokens on a shared base 282.8 / 280.4; two
     // of 32 sizes were faster with it, 512 tokens on the shared base of 2048 / 5632 142.7 without and 138.3 with).
-    const bool nt = g.P <= 256 * g.E;
+    // Rows that are no multiples of a line: a k-step ends inside a line, the next one reads that line again, and with the hint
+    // it comes from HBM again.  Whole layer, us, with / without: 2040 / 5624 40 tokens 161.7 / 125.6, 256 tokens 171.6 / 149.4,
+    // 1024 tokens 305.5 / 259.0; 1032 / 2760 54.2 / 47.4, 128 tokens 58.1 / 50.2, 1024 tokens 104.7 / 97.1; 520 / 1400, 4 experts,
+    // 150 tokens 24.7 / 21.5.  Where rows are whole half-lines only every other row is cut; there the hint stays while most
+    // groups are one tall tile (1440 / 3840 256 tokens 79.4 / 76.0, 777 tokens 91.0 / 93.6, 1000 tokens 124.4 / 119.2).
+    const int line = g.seg[0].K % 64;
+    const bool nt = line == 0 ? g.P <= 256 * g.E : line == 32 && g.P > 64 * g.E && g.P <= 240 * g.E;
     if (!swiglu) {
         const bool f32 = g.k_parts > 1 && g.parts_f32;
         if (bm == 64)
