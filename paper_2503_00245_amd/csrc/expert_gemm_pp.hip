@@ -20,6 +20,9 @@
 // (1.28 PFLOP/s).
 #include "gemm.h"
 
+#include <array>
+#include <cmath>
+
 namespace moe {
 
 namespace {
@@ -81,15 +84,20 @@ __device__ __forceinline__ void phase_end() {
 // SA, SB: k-steps of A and of B in LDS.
 // F32: k-parts stored in fp32.
 // NT_B: weights past the caches (run_gemm_pp has the rule).
-template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B>
+// LINES: rows of B that are no multiples of a cache line are fetched in whole lines all the same.  Line t of a row, counted
+// from the line that the row begins in, goes to slot t % SB; row r begins shift(r) 16-byte chunks into its line 0, so
+// step t is read from lines t and t + 1, and a line more than there are k-steps is fetched.
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B, bool LINES>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_pp_kernel(
     ptr_arg a_keys, ptr_arg a_offsets, int g_P, int g_E, const GemmArgs g) {
     const int32_t *const g_keys = from_arg<const int32_t>(a_keys), *const g_offsets = from_arg<const int32_t>(a_offsets);
     static_assert(!DUAL || SWIGLU, "two activation operands only with the activation");
     constexpr int WAVES_N = 8 / WAVES_M;
     constexpr int MB = BM / 32 / WAVES_M;         // 32-row blocks of a wave
+    static_assert(!LINES || (!DUAL && SB >= 4), "a step lies in two lines");
     static_assert(MB >= 1 && SA >= 2 && SB >= 3, "a group reads one step while the other's is being fetched");
     constexpr int WN = BN / WAVES_N, NI = WN / 16;  // columns, 16-column blocks of a wave
+    static_assert(NI % 2 == 0 || !SWIGLU || DUAL, "whole blocks of gate and of up columns");
     constexpr int NP = DUAL ? 2 : 1;
     constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     constexpr int PA = BM / 32, PB = BN / 32;     // fill instructions per k-step of a wave of group 1 / 0
@@ -177,21 +185,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int fw = wave & 3;
     const int f_row = fw * 8 + (lane >> 3);
     const int f_chunk = (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4));
+    // LINES: slot (m + row / 2 - shift) % 8 holds chunk m of the line, so that a fragment read finds chunk c of a step in
+    // slot (c + row / 2) % 8 of either line.  Tiles begin at multiples of 8 rows, of which all bytes are whole lines: the
+    // shift is a row's within the tile.
+    const int shift_f = f_row * (K >> 3) & 7;
     const int rows_here = row_end - row0;
     unsigned off[PA > PB ? PA : PB];
     if (grp == 0) {
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
             const int j = f_row + 32 * p;
-            off[p] = __umul24(min(n0 + min(SPLIT_B ? j % (BN / 2) : j, width - 1), g.N - 1), K * 2) + f_chunk * 16;
+            if constexpr (LINES) {  // (a row past the end is one of the last eight, of the same shift; + 128: fill takes it back)
+                const int r = SPLIT_B ? j % (BN / 2) : j, end = min(width, g.N - n0);
+                off[p] = (__umul24(n0 + (r < end ? r : end - 8 + (r & 7)), K * 2) & ~127u) + 128 + ((lane - (f_row >> 1) + shift_f) & 7) * 16;
+            } else {
+                off[p] = __umul24(min(n0 + min(SPLIT_B ? j % (BN / 2) : j, width - 1), g.N - 1), K * 2) + f_chunk * 16;
+            }
         }
     }
     // what this wave fetches: instructions below PH from src_lo, the others from src_hi; in the second
     // pass (DUAL) all from src_2
     constexpr int PH = SPLIT_B ? PB / 2 : PB;
     const size_t k_off = (size_t)k_begin * (BK * 2);
-    const char* const src_lo = (grp == 1 ? A0 : B0) + k_off;
-    const char* const src_hi = (grp == 1 ? A0 : SPLIT_B ? B1 : B0) + k_off;
+    const size_t b_off = LINES ? k_off - 128 : k_off;  // (the offsets are unsigned, and one may be a line less)
+    const char* const src_lo = grp == 1 ? A0 + k_off : B0 + b_off;
+    const char* const src_hi = grp == 1 ? A0 + k_off : (SPLIT_B ? B1 : B0) + b_off;
     const char* const src_2 = grp == 1 ? A1 : B1;
     const unsigned lds0 = (unsigned)(uintptr_t)(lds_char*)smem + fw * 1024;
     auto fill = [&](auto gc, int v, int p) INLINE {
@@ -199,13 +217,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const unsigned slot = GRP == 1 ? v % SA * A_BYTES : SA * A_BYTES + v % SB * B_BYTES;
         const int t = DUAL && v >= nk ? v - nk : v;
         const char* src = DUAL && v >= nk ? src_2 : p < PH ? src_lo : src_hi;
+        if constexpr (LINES && GRP == 0) {
+            // (the last line, where the row ends before it: the one before again)
+            const unsigned back = t == nk && shift_f * 16 <= tail_back ? 128 : 0;
+            dma16<NT_B>(lds0 + slot + p * 4096, src + t * (BK * 2), off[p] - back);
+            return;
+        }
         src += t * (BK * 2) - (t == nk - 1 ? tail_back : 0);
         dma16<GRP == 0 && NT_B>(lds0 + slot + p * 4096, src, off[p]);
     };
     if (grp == 0) {  // the first steps of B, before the rows of A are known
 #pragma unroll
         for (int q = 0; q < SB - 1; ++q)
-            if (q < nv) {
+            if (q < nv + LINES) {
 #pragma unroll
                 for (int p = 0; p < PB; ++p) fill(std::integral_constant<int, 0>{}, q, p);
             }
@@ -248,7 +272,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // fragment reads: row lane % 16 of a 16-row block, chunk 4 ks + lane / 16
     const unsigned c16 = ((lane >> 4) ^ ((lane & 15) >> 1)) << 4;
     const unsigned ra = wm * 4096 + (lane & 15) * 128 + c16;
-    const unsigned rb = SA * A_BYTES + wn * (SPLIT_B ? WN / 2 : WN) * 128 + (lane & 15) * 128 + c16;
+    const unsigned c16_b = LINES ? (((lane >> 4) + ((lane & 15) >> 1)) & 7) << 4 : c16;
+    const unsigned rb0 = SA * A_BYTES + wn * (SPLIT_B ? WN / 2 : WN) * 128 + (lane & 15) * 128, rb = rb0 + c16_b;
 
     // Phases: group 0 reads step v's fragments in phase 2 v and multiplies in phase 2 v + 1, group 1 a phase
     // later.  The LDS slots of step v are free from the end of phase 2 v + 1 on: group 1, multiplying step v
@@ -265,13 +290,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         // group 1 with MA live blocks belongs to a tile with at most this many).
         constexpr int NF = GRP == 0 ? PB : NO_COLS || MA == MB ? PA : WAVES_M * (MA + 1) - 1 < PA ? WAVES_M * (MA + 1) - 1 : PA;
         bf16x8 fa[2][2 * MR], fb[2][NI];
-        auto read = [&](int v) INLINE {
+        // LINES: the lane's first chunk of a step within its row's line
+        const int chunk0 = (lane >> 4) + ((lane & 15) * (K >> 3) & 7);
+        // (tail: the step may be a partial one, whose 64 columns begin tail_back bytes earlier)
+        auto read = [&](int v, auto tail) INLINE {
             const char* pa = smem + v % SA * A_BYTES;
             const char* pb = smem + v % SB * B_BYTES;
+            const char* pb1 = smem + (v + 1) % SB * B_BYTES;
+            const char* pb0 = smem + (v + SB - 1) % SB * B_BYTES;
+            const int tb = decltype(tail)::value && v == S * nk + nk - 1 ? tail_back : 0;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 const char* a = pa + (ra ^ (ks << 6));
-                const char* b = pb + (rb ^ (ks << 6));
+                const int at = ks * 4 + chunk0 - tb / 16;  // the lane's chunk, from the start of line v
+                const char* b = (LINES && at >= 8 ? pb1 : LINES && at < 0 ? pb0 : pb) +
+                                (LINES && decltype(tail)::value ? rb0 + ((rb - rb0 + (ks << 6) - tb) & 127) : rb ^ (ks << 6));
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)  // SPLIT_B: NI / 2 gate blocks, then as many up blocks
                     fb[ks][ni] = *reinterpret_cast<const bf16x8*>(
@@ -312,7 +345,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             }
         };
         constexpr int AHEAD = GRP == 0 ? SB - 1 : SA;                     // the step fetched while v is multiplied
-        constexpr int FLY = (GRP == 0 ? SB - 2 : SA - 2) * NF;            // fills behind those of step v + 1
+        constexpr bool MORE = LINES && GRP == 0;                          // a step takes its line and the next one
+        constexpr int FLY = (GRP == 0 ? SB - 2 - MORE : SA - 2) * NF;     // fills behind those of step v + 1
+        const int n_fill = nv + MORE;
         int v = S * nk;
         const int v_end = v + nk;
         if (S == 0) {  // the first steps (of B: above)
@@ -322,13 +357,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
                     for (int p = 0; p < NF; ++p) fill(gc, q, p);
                 }
-            if (nv >= AHEAD) wait_vm<(AHEAD - 1) * NF>();  // step 0 has landed
+            if (n_fill >= AHEAD) wait_vm<(AHEAD - 1 - MORE) * NF>();  // step 0 has landed
             else wait_vm<0>();
             phase_end();
             if (GRP == 1) phase_end();
         }
-        for (; v < v_end && v + AHEAD < nv; ++v) {
-            if (MA > 0) read(v);
+        for (; v < v_end && v + AHEAD < n_fill; ++v) {
+            if (MA > 0) read(v, std::false_type{});
             if (DUAL && S == 0 && v == v_end - 1 && tail_back > 0) clear_shared();
             if (GRP == 1) wait_vm<FLY>();  // A of step v + 1
             phase_end();
@@ -337,7 +372,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             phase_end();
         }
         for (; v < v_end; ++v) {
-            if (MA > 0) read(v);
+            if (MA > 0) read(v, std::true_type{});
             if (v == v_end - 1 && tail_back > 0) clear_shared();
             if (GRP == 1) wait_vm<0>();
             phase_end();
@@ -393,7 +428,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int ln = lane_again();
     char* const region = smem + wave * (32 * PITCH);
     char* const wr = region + (ln & 15) * PITCH + (ln >> 4) * 8;
-    const int rd_row = ln / LPR, rd_chunk = ln % LPR;
+    const int rd_row = ln / LPR, rd_chunk = ln % LPR;  // (lanes left over: rows past the last)
     const int c0 = wn * OC + rd_chunk * 8;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
@@ -413,8 +448,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 *reinterpret_cast<bf16x4*>(wr + h * 16 * PITCH + nb * 32) = o;
             }
 #pragma unroll
-        for (int it = 0; it < 32 / RPI; ++it) {
+        for (int it = 0; it < (32 + RPI - 1) / RPI; ++it) {
             const int r = it * RPI + rd_row;
+            if ((64 % LPR || 32 % RPI) && (rd_row >= RPI || r >= 32)) continue;
             const uint4 v = *reinterpret_cast<const uint4*>(region + r * PITCH + rd_chunk * 16);
             if (rbk + r < rows_here && c0 < width && n0 + c0 < g.N)
                 *reinterpret_cast<uint4*>(Ct + (unsigned)(rbk + r) * ldc + (unsigned)c0) = v;
@@ -422,7 +458,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B>
+template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B, bool LINES>
 int launch_pp(GemmArgs& g, hipStream_t st) {
     constexpr int BN_OUT = SWIGLU && !DUAL ? BN / 2 : BN;
     g.m_tiles_max = g.P / BM + g.E;
@@ -433,15 +469,22 @@ int launch_pp(GemmArgs& g, hipStream_t st) {
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     const int grid = ((tiles + 7) / 8 + kSplitSlots / 2) * 8;
     static std::atomic<uint64_t> lds_allowed;
-    const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, NT_B>;
+    const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, NT_B, LINES>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, as_arg(g.keys), as_arg(g.offsets), g.P, g.E, g);
     return launch_status();
 }
 template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32 = false>
 int launch_pp(GemmArgs& g, bool nt, hipStream_t st) {
-    return nt ? launch_pp<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, true>(g, st)
-              : launch_pp<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, false>(g, st);
+    return nt ? launch_pp<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, true, false>(g, st)
+              : launch_pp<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, false, false>(g, st);
+}
+// weights in rows that are no multiples of a line, past the caches
+template <int BM, int BN, int WAVES_M, int SA, int SB>
+int launch_pp_lines(GemmArgs& g, bool swiglu, hipStream_t st) {
+    if (swiglu) return launch_pp<BM, BN, WAVES_M, SA, SB, true, false, false, true, true>(g, st);
+    return g.k_parts > 1 && g.parts_f32 ? launch_pp<BM, BN, WAVES_M, SA, SB, false, false, true, true, true>(g, st)
+                                        : launch_pp<BM, BN, WAVES_M, SA, SB, false, false, false, true, true>(g, st);
 }
 
 }  // namespace
@@ -509,6 +552,56 @@ int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f3
     return choose(P, E, N, K, 1, false, false, parts_max, parts_f32, sum_launch).parts;
 }
 
+// ---- weights whose rows are no multiples of a cache line ---------------------------------------------------------
+// Fetched 128 bytes of every row at a time from where the rows begin, each line is read by two k-steps and each request touches
+// two lines: 2040 / 5624 took 17-23 % more than 2048 / 5632 from 128 to 4000 tokens.  Fetched in whole lines a step lies in
+// two, so LDS holds a step more: 128-row tiles with two steps of A, or 256-row tiles 192 columns wide.  Whole layer, us, before /
+// with gate and up fetched so: 2040 / 5624 48 tokens 124.6 / 113.5, 128 tokens 134.5 / 121.9, 300 tokens 153.9 / 136.7; 1208 /
+// 3224 128 tokens 60.3 / 50.4, 300 tokens 76.9 / 62.8; 1032 / 2760 48 tokens 47.0 / 42.1; the down product too: 2040 / 5624 48
+// tokens 124 / 117 (alone), 300 tokens 154 / 147, 900 tokens 212 / 204.  Taken where
+//   - no round of tiles is added, with even loads nor with Zipf ones (700 tokens of 1400 / 3736 98.3 / 106.8 with one more);
+//   - a plain product has tiles for half the CUs, and not fewer than it had (300 tokens of 1032 / 2760, one part, 62.6 / 71.4);
+//   - the weights are large: below, they may still lie in the memory-side cache, where cut lines cost little (760 / 2056 48
+//     tokens 29.5 / 31.4; 34.2 / 32.4 when they do not);
+//   - groups are one tall tile on average: beyond, the narrow tiles' LDS reads cost what the fills save (2500 tokens of
+//     2040 / 5624 406 / 404, 4000 tokens 653 / 664).
+// The rows have to lie in whole lines together: none is then read that is not the weights'.
+static int m_tiles(long long P, int E, int bm, bool zipf) {
+    static const std::array<double, kMaxExperts> shares = [] {
+        std::array<double, kMaxExperts> w;
+        for (int e = 0; e < kMaxExperts; ++e) w[e] = pow(e + 1, -1.1);
+        return w;
+    }();
+    double sum = 0;
+    for (int e = 0; e < E; ++e) sum += shares[e];
+    int tiles = 0;
+    for (int e = 0; e < E; ++e) tiles += (int)ceil((double)P * (zipf ? shares[e] / sum : 1.0 / E) / bm);
+    return tiles;
+}
+
+// Rows per tile of that form, 0: not taken.  bm: rows per tile of the other form
+static int line_rows(const GemmArgs& g, bool swiglu, int bm) {
+    const GemmSeg& sg = g.seg[0];
+    const int K = sg.K, parts = g.k_parts > 1 ? g.k_parts : 1;
+    auto whole = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 128 == 0; };
+    if (K % 64 == 0 || K % 8 != 0 || g.N % 8 != 0 || sg.strideB % 64 != 0 || !whole(sg.B0) || !whole(sg.B1) ||
+        (K + BK - 1) / BK < 2 * parts || (swiglu && sg.A0 != sg.A1))
+        return 0;
+    if (g.P > 256ll * g.E || (sg.strideB != 0 ? g.E : 1) * 2ll * g.N * K < (36 << 20)) return 0;
+    const int copies = parts * (!swiglu && g.C1 ? 2 : 1), per_row = swiglu ? 2 : 1;
+    for (int rows = 256; rows >= 128; rows /= 2) {
+        bool ok = true;
+        for (int zipf = 0; zipf < 2; ++zipf) {
+            const int cols = (rows == 256 ? 192 : 256) / per_row, before = 256 / per_row;
+            const int tiles = m_tiles(g.P, g.E, rows, zipf) * copies * ((g.N + cols - 1) / cols);
+            const int other = m_tiles(g.P, g.E, bm, zipf) * copies * ((g.N + before - 1) / before);
+            ok = ok && (tiles + 255) / 256 <= (other + 255) / 256 && (swiglu || (tiles >= 128 && tiles >= other));
+        }
+        if (ok) return rows;
+    }
+    return 0;
+}
+
 int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     const bool dual = swiglu && g.seg[0].A0 != g.seg[0].A1;
     const int parts = g.k_parts > 1 ? g.k_parts : 1;  // decided by the caller
@@ -529,6 +622,8 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     // groups are one tall tile (1440 / 3840 256 tokens 79.4 / 76.0, 777 tokens 91.0 / 93.6, 1000 tokens 124.4 / 119.2).
     const int line = g.seg[0].K % 64;
     const bool nt = line == 0 ? g.P <= 256 * g.E : line == 32 && g.P > 64 * g.E && g.P <= 240 * g.E;
+    if (const int rows = line_rows(g, swiglu, bm))
+        return rows == 128 ? launch_pp_lines<128, 256, 2, 2, 4>(g, swiglu, st) : launch_pp_lines<256, 192, 4, 2, 4>(g, swiglu, st);
     if (!swiglu) {
         const bool f32 = g.k_parts > 1 && g.parts_f32;
         if (bm == 64)
