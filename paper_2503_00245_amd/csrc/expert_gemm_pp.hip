@@ -559,14 +559,15 @@ int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f3
 // with gate and up fetched so: 2040 / 5624 48 tokens 124.6 / 113.5, 128 tokens 134.5 / 121.9, 300 tokens 153.9 / 136.7; 1208 /
 // 3224 128 tokens 60.3 / 50.4, 300 tokens 76.9 / 62.8; 1032 / 2760 48 tokens 47.0 / 42.1; the down product too: 2040 / 5624 48
 // tokens 124 / 117 (alone), 300 tokens 154 / 147, 900 tokens 212 / 204.  Taken where
-//   - no round of tiles is added, with even loads nor with Zipf ones (700 tokens of 1400 / 3736 98.3 / 106.8 with one more);
+//   - no round of tiles is added, with Zipf loads nor with even ones, a quarter more than the average to be on the safe
+//     side (one more: 700 tokens of 1400 / 3736 98.3 / 106.8, 512 tokens of 1440 / 3840, 128 rows per expert, 82.1 / 97.8);
 //   - a plain product has tiles for half the CUs, and not fewer than it had (300 tokens of 1032 / 2760, one part, 62.6 / 71.4);
 //   - the weights are large: below, they may still lie in the memory-side cache, where cut lines cost little (760 / 2056 48
 //     tokens 29.5 / 31.4; 34.2 / 32.4 when they do not);
 //   - groups are one tall tile on average: beyond, the narrow tiles' LDS reads cost what the fills save (2500 tokens of
 //     2040 / 5624 406 / 404, 4000 tokens 653 / 664).
 // The rows have to lie in whole lines together: none is then read that is not the weights'.
-static int m_tiles(long long P, int E, int bm, bool zipf) {
+static int m_tiles(double P, int E, int bm, bool zipf) {
     static const std::array<double, kMaxExperts> shares = [] {
         std::array<double, kMaxExperts> w;
         for (int e = 0; e < kMaxExperts; ++e) w[e] = pow(e + 1, -1.1);
@@ -575,7 +576,7 @@ static int m_tiles(long long P, int E, int bm, bool zipf) {
     double sum = 0;
     for (int e = 0; e < E; ++e) sum += shares[e];
     int tiles = 0;
-    for (int e = 0; e < E; ++e) tiles += (int)ceil((double)P * (zipf ? shares[e] / sum : 1.0 / E) / bm);
+    for (int e = 0; e < E; ++e) tiles += (int)ceil(P * (zipf ? shares[e] / sum : 1.0 / E) / bm);
     return tiles;
 }
 
@@ -593,7 +594,7 @@ static int line_rows(const GemmArgs& g, bool swiglu, int bm) {
         bool ok = true;
         for (int zipf = 0; zipf < 2; ++zipf) {
             const int cols = (rows == 256 ? 192 : 256) / per_row, before = 256 / per_row;
-            const int tiles = m_tiles(g.P, g.E, rows, zipf) * copies * ((g.N + cols - 1) / cols);
+            const int tiles = m_tiles(zipf ? g.P : 1.25 * g.P, g.E, rows, zipf) * copies * ((g.N + cols - 1) / cols);
             const int other = m_tiles(g.P, g.E, bm, zipf) * copies * ((g.N + before - 1) / before);
             ok = ok && (tiles + 255) / 256 <= (other + 255) / 256 && (swiglu || (tiles >= 128 && tiles >= other));
         }
