@@ -627,6 +627,17 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
         return rows == 128 ? launch_pp_lines<128, 256, 2, 2, 4>(g, swiglu, st) : launch_pp_lines<256, 192, 4, 2, 4>(g, swiglu, st);
     if (!swiglu) {
         const bool f32 = g.k_parts > 1 && g.parts_f32;
+        // One part and few row tiles: to fill the chip the kernel makes the tiles narrower (fit_width); where that leaves half a
+        // tile or less, the other half of its rows of B would be the last one over and over, and half of its waves idle.
+        // Whole layer, us, 256 / 128 columns: 300 tokens 1024 / 2816 53.2 / 49.7, 512 tokens 640 / 1728 40.6 / 37.9, 777 tokens 432 /
+        // 1152 32.8 / 31.0, 2048 tokens 43.9 / 40.3.  In parts, or with tall tiles, there was no gain (512 tokens 1024 / 2816
+        // 53.1 / 53.9, 432 / 1152 28.4 / 29.1), and none where the tiles are a few k-steps long (a low-rank term of rank 128, 300
+        // tokens, 128.5 / 130.8).
+        // Tiles for one round by the model above; past that the wide ones are the better fit (1024 tokens of rank 1024 on 2048 /
+        // 5632 204 / 209).
+        const double groups = g.P < g.E ? g.P : g.E, m_all = groups * 1.05 * fmax(g.P / groups / bm + 0.5, 1.0);
+        if (bm <= 128 && parts == 1 && !g.C1 && g.seg[0].K >= 512 && m_all * ((g.N + 127) / 128) <= 256)
+            return bm == 64 ? launch_pp<64, 128, 2, 8, 6, false, false>(g, nt, st) : launch_pp<128, 128, 4, 5, 5, false, false>(g, nt, st);
         if (bm == 64)
             return f32 ? launch_pp<64, 256, 2, 4, 4, false, false, true>(g, nt, st) : launch_pp<64, 256, 2, 4, 4, false, false>(g, nt, st);
         if (bm == 128)

@@ -578,6 +578,17 @@ def test_expert_ffn_weights_in_cut_lines(dev, oracle, d, F, offsets):
     _ffn_case(dev, oracle, cfg, np.array(offsets, np.int32), TOL["bf16"])
 
 
+@pytest.mark.parametrize("d,F,E,k,T", [
+    # a down projection in one part with few row tiles: 64 and 128 rows, widths below, at and past 128 columns and not multiples of
+    # 16, K of 512 and a ragged one, and more tiles than a round
+    (120, 512, 4, 2, 70), (128, 520, 4, 2, 130), (136, 1000, 8, 2, 300), (640, 1728, 8, 2, 512), (440, 1152, 3, 3, 400), (1024, 576, 8, 2, 1000),
+    (1032, 576, 8, 2, 1000),
+])
+def test_forward_narrow_down_tiles(dev, oracle, d, F, E, k, T):
+    cfg = _cfg(name="narrow", d=d, F=F, E=E, k=k, dtype="bf16", seed=1870 + d + T, r=0, std=0.04)
+    _forward_case(dev, oracle, cfg, T, residual=bool(T % 4))
+
+
 @pytest.mark.parametrize("T,k,E", [(32, 2, 5), (9, 3, 40)])
 def test_forward_few_tokens_with_nan_logits(dev, T, k, E):
     # every pair may land in one expert or in none: the call ends and leaves other tokens' memory alone
