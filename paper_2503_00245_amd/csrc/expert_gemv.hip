@@ -609,9 +609,9 @@ static int launch_gemv(GemvArgs& a, int mode, hipStream_t st) {
 // one output row per token (the kernel takes any number of tokens up to 64 pairs).  Every pair
 // streams its expert's rows from memory -- the weight loads are non-temporal, and pairs of different
 // tokens that chose the same expert are not neighbours -- so the step costs about 22 us per token
-// on the 2048 / 5632 layer: 60 us at two tokens against 69 for the grouped GEMM, which streams
-// each selected expert once, but 82 against 72 at three and 193 against 98 at eight.  Layers with
-// a shared base (whose per-row products serve one token) keep the grouped GEMM.
+// on the 2048 / 5632 layer, and three tokens are faster on the grouped products, which stream each selected expert
+// once; so are two of many dense layers (few_two_tokens) and small fp32 layers (launch_token_layer_f32).  Layers with
+// a shared base (whose per-row products serve one token) keep the grouped products.
 constexpr int kMaxDecodeTokens = 2;
 bool decode_supported(const moe_shape& s) {
     if (s.n_tokens == 1) return true;
