@@ -10,7 +10,7 @@
 // What bounds these kernels is launches: each dependent one costs 4-5 us however little it does, and
 // the data (2 MB for 24 layers of 2048 tokens) is read in about that time.  So every entry point is
 // one or two launches, and what is left of serial work runs on a workgroup instead of a thread
-// (all four calls on 24 x 2048 tokens, 2 of 8 experts: 120 us before, 29 now).
+// (all four calls on 24 x 2048 tokens, 2 of 8 experts: 120 us before, 28 now; on short traces, one launch each, 18).
 #include "common.h"
 
 namespace moe {
@@ -121,7 +121,18 @@ __global__ __launch_bounds__(kMetricThreads) void bles_partial_kernel(
     }
 }
 
-// out = {H, H_norm, L, L_norm, loss} (Eq. 5, 6, 7).  One workgroup: thread i adds the partials
+// out = {H, H_norm, L, L_norm, loss} (Eq. 5, 6, 7)
+__device__ __forceinline__ void write_bles(double* out, double L, unsigned long long H, int B, int T, int K) {
+    const double Hn = T > 1 ? (double)(H / 2) / ((double)B * K * (T - 1)) : 0.0;
+    const double Ln = L / ((double)B * T);
+    out[0] = (double)H;
+    out[1] = Hn;
+    out[2] = L;
+    out[3] = Ln;
+    out[4] = Hn * Ln;
+}
+
+// One workgroup: thread i adds the partials
 // i, i + 256, ... in fp64 and the threads meet in a fixed tree (deterministic).  (One thread adding
 // all of them was a chain of 1536 dependent load-and-adds at 24 x 2048 tokens: 64 us.)
 __global__ __launch_bounds__(kMetricThreads) void bles_finalize_kernel(
@@ -147,16 +158,167 @@ __global__ __launch_bounds__(kMetricThreads) void bles_finalize_kernel(
         }
         __syncthreads();
     }
+    if (threadIdx.x == 0) write_bles(out, s_soft[0], s_hard[0], B, T, K);
+}
+
+// ---- short traces: one workgroup, one launch ------------------------------------------------------------------
+// What takes two launches for want of a sum over workgroups takes one where a single workgroup reads the whole trace in less
+// time than the other launch costs.  Several turns' loads are requested together: none is conditional.
+constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / kWave, kOneTurns = 4;
+constexpr int kBallotExperts = 16;  // up to here lane e counts expert e by ballots (8192 tokens 6.6 us, by LDS atomics 10.4)
+
+// Experts replaced after token i of the n = B T (two at least), KT of K: a constant, or 0
+template <int KT>
+__device__ __forceinline__ unsigned long long replaced_after(const int32_t* __restrict__ S, int i, int n, int T, int K, int E) {
+    const int k = KT ? KT : K;
+    const int32_t* s0 = S + (size_t)min(i, n - 2) * k;
+    const unsigned long long d = expert_mask(s0, k, E) ^ expert_mask(s0 + k, k, E);
+    return i < n - 1 && i % T != T - 1 ? d : 0ull;
+}
+
+template <int KT>
+__global__ __launch_bounds__(kOneThreads) void replacements_one_kernel(
+    ptr_arg aS, int B, int T, int K, int E, ptr_arg aHe, ptr_arg aH) {
+    const int32_t* const S = from_arg<const int32_t>(aS);
+    __shared__ int s_cnt[kOneWaves][kMaxExperts];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n = B * T;
+    s_cnt[wave][lane] = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int i0 = wave * kWave; i0 < n; i0 += kOneTurns * kOneThreads) {
+        unsigned long long d[kOneTurns];
+#pragma unroll
+        for (int u = 0; u < kOneTurns; ++u) d[u] = replaced_after<KT>(S, i0 + lane + u * kOneThreads, n, T, K, E);
+        if (E <= kBallotExperts) {
+            for (int e = 0; e < E; ++e) {
+                int c = 0;
+#pragma unroll
+                for (int u = 0; u < kOneTurns; ++u) c += __popcll(__ballot(d[u] >> e & 1));
+                mine += lane == e ? c : 0;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kOneTurns; ++u)
+                for (; d[u]; d[u] &= d[u] - 1) atomicAdd(&s_cnt[wave][__ffsll((long long)d[u]) - 1], 1);
+        }
+    }
+    if (E <= kBallotExperts) s_cnt[wave][lane] = mine;
+    __syncthreads();
+    if (wave != 0) return;
+    unsigned long long c = 0;
+    for (int w = 0; w < kOneWaves; ++w) c += (unsigned)s_cnt[w][lane];
+    if (lane < E) from_arg<unsigned long long>(aHe)[lane] = c;
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) c += __shfl_xor(c, m, kWave);
+    if (lane == 0) *from_arg<unsigned long long>(aH) = c;
+}
+
+template <int KT>
+__global__ __launch_bounds__(kOneThreads) void bles_one_kernel(
+    ptr_arg aW, ptr_arg aS, int B, int T, int K, int E, int vec, ptr_arg a_out) {
+    const float* const W = from_arg<const float>(aW);
+    const int32_t* const S = from_arg<const int32_t>(aS);
+    __shared__ double s_soft[kOneWaves];
+    __shared__ unsigned long long s_hard[kOneWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n = B * T;
+    unsigned long long hard = 0;
+    for (int i0 = threadIdx.x; i0 < n; i0 += kOneTurns * kOneThreads)
+#pragma unroll
+        for (int u = 0; u < kOneTurns; ++u) hard += __popcll(replaced_after<KT>(S, i0 + u * kOneThreads, n, T, K, E));
+    double soft = 0.0;
+    const int q = vec ? E / 4 : E, last = (n - 2) * q + q - 1;  // chunks of a row, the last one with a successor
+    for (int c0 = threadIdx.x; c0 <= last; c0 += kOneTurns * kOneThreads) {
+        float d[kOneTurns];
+#pragma unroll
+        for (int u = 0; u < kOneTurns; ++u) {
+            const int c = min(c0 + u * kOneThreads, last);
+            if (vec) {  // rows of W are whole, aligned 16-byte chunks
+                const f32x4* w = reinterpret_cast<const f32x4*>(W) + c;
+                const f32x4 v = w[q] - w[0];
+                d[u] = (fabsf(v[0]) + fabsf(v[1])) + (fabsf(v[2]) + fabsf(v[3]));
+            } else {
+                d[u] = fabsf(W[c + q] - W[c]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kOneTurns; ++u) {
+            const int c = c0 + u * kOneThreads;
+            if (c <= last && (c / q) % T != T - 1) soft += (double)d[u];
+        }
+    }
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+        soft += __shfl_xor(soft, m, kWave);
+        hard += __shfl_xor(hard, m, kWave);
+    }
+    if (lane == 0) {
+        s_soft[wave] = soft;
+        s_hard[wave] = hard;
+    }
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    L = s_soft[0];
-    H = s_hard[0];
-    const double Hn = T > 1 ? (double)(H / 2) / ((double)B * K * (T - 1)) : 0.0;
-    const double Ln = L / ((double)B * T);
-    out[0] = (double)H;
-    out[1] = Hn;
-    out[2] = L;
-    out[3] = Ln;
-    out[4] = Hn * Ln;
+    for (int w = 1; w < kOneWaves; ++w) {
+        soft += s_soft[w];
+        hard += s_hard[w];
+    }
+    write_bles(from_arg<double>(a_out), soft, hard, B, T, K);
+}
+
+constexpr int kOneLayers = 256;  // layers of a trace at most
+
+// Waves take layers in turn.  The sums are those of the kernels below, in the same order.
+__global__ __launch_bounds__(kOneThreads) void balance_one_kernel(
+    ptr_arg a_trace, int L, int TK, int E, ptr_arg a_counts, ptr_arg a_delta, ptr_arg a_mean) {
+    const int32_t* const trace = from_arg<const int32_t>(a_trace);
+    double* const delta = from_arg<double>(a_delta);
+    __shared__ int s_cnt[kOneWaves][kMaxExperts];
+    __shared__ double s_dev[kOneWaves][kMaxExperts], s_delta[kOneLayers];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    for (int l0 = 0; l0 < L; l0 += kOneWaves) {  // (in step: the waves meet at the barriers)
+        const int l = l0 + wave;
+        s_cnt[wave][lane] = 0;
+        __syncthreads();
+        if (l < L) {
+            const int32_t* tr = trace + (size_t)l * TK;
+            for (int i0 = lane; i0 < TK; i0 += 2 * kOneTurns * kWave) {
+                int e[2 * kOneTurns];
+#pragma unroll
+                for (int u = 0; u < 2 * kOneTurns; ++u) e[u] = tr[min(i0 + u * kWave, TK - 1)];
+#pragma unroll
+                for (int u = 0; u < 2 * kOneTurns; ++u)
+                    if (i0 + u * kWave < TK && (unsigned)e[u] < (unsigned)E) atomicAdd(&s_cnt[wave][e[u]], 1);
+            }
+        }
+        __syncthreads();
+        if (l < L && lane < E) {
+            const unsigned long long c = (unsigned)s_cnt[wave][lane];
+            from_arg<unsigned long long>(a_counts)[(size_t)l * E + lane] = c;
+            const double dev = (double)c / (double)TK - 1.0 / (double)E;
+            s_dev[wave][lane] = dev < 0 ? -dev : dev;
+        }
+        __syncthreads();
+        if (l < L && lane == 0) {
+            double dl = 0.0;
+#pragma unroll 8
+            for (int e = 0; e < E; ++e) dl += s_dev[wave][e];
+            if (delta) delta[l] = dl;
+            s_delta[l] = dl;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double total = 0.0;
+    for (int l = 0; l < L; ++l) total += s_delta[l];
+    *from_arg<double>(a_mean) = total / (double)L;
+}
+
+// Where that pays: at most this many pairs, and (token, expert) pairs.  Two launches cost the host 7.5 us a call, one 4.6.  On the
+// GPU, two launches / one, us: 27 layers of 85 tokens, 2 of 8 experts, replacements 4.1 / 3.7, loss 5.2 / 5.1, balance 4.4 / 4.9;
+// 8 of 512 4.1 / 4.1, 5.2 / 6.6, 4.4 / 3.9; 24 of 341 4.3 / 6.6, 5.2 / 10.5, 4.4 / 6.8; 8 of 1024, 4 of 16, 4.7 / 19, 5.8 / 27, 5.1 / 6.4.
+// All four calls, the host's time: 8 of 512 28.3 / 18.9.
+constexpr int kOnePairs = 16384, kOneElements = 32768;
+static bool short_trace(int L, int T, int K, int E) {
+    return (long long)L * T * K <= kOnePairs && (long long)L * T * E <= kOneElements;
 }
 
 constexpr int kLayerThreads = 1024;  // kernels with one workgroup per layer
@@ -280,6 +442,11 @@ int moe_expert_replacements(const int32_t* S, int32_t B, int32_t T, int32_t K, i
     hipStream_t st = as_stream(stream);
     unsigned long long* he = reinterpret_cast<unsigned long long*>(H_e);
     unsigned long long* h = reinterpret_cast<unsigned long long*>(H);
+    if (T > 1 && short_trace(B, T, K, E)) {
+        const auto kern = K == 1 ? replacements_one_kernel<1> : K == 2 ? replacements_one_kernel<2> : replacements_one_kernel<0>;
+        hipLaunchKernelGGL(kern, dim3(1), dim3(kOneThreads), 0, st, as_arg(S), B, T, K, E, as_arg(he), as_arg(h));
+        return launch_status();
+    }
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(kMetricThreads), 0, st, as_arg(he), E, as_arg(h));
     if (T > 1)
         hipLaunchKernelGGL(replacements_kernel, dim3((B * T - 1) / kMetricThreads + 1), dim3(kMetricThreads), 0, st,
@@ -303,6 +470,12 @@ int moe_bles_loss(const float* probs, const int32_t* S, int32_t B, int32_t T, in
     if (!probs || !S || !out) return MOE_ERR_INVALID;
     if (!workspace || workspace_bytes < moe_bles_workspace_bytes(B, T, E)) return MOE_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
+    if (T > 1 && short_trace(B, T, K, E)) {
+        const auto kern = K == 1 ? bles_one_kernel<1> : K == 2 ? bles_one_kernel<2> : bles_one_kernel<0>;
+        hipLaunchKernelGGL(kern, dim3(1), dim3(kOneThreads), 0, st, as_arg(probs), as_arg(S), B, T, K, E,
+                           E % 4 == 0 && aligned16(probs) ? 1 : 0, as_arg(out));
+        return launch_status();
+    }
     // 12 bytes of partial sums per workgroup; the size query has room for 4 per 256 differences of W beside 768
     // bytes, and a workgroup takes at least 1024 elements, more where that is too many workgroups (T = 2)
     char* const first = reinterpret_cast<char*>(round_up(reinterpret_cast<uintptr_t>(workspace), sizeof(double)));
@@ -342,6 +515,10 @@ int moe_delta_uniform(const int32_t* trace, int32_t L, int32_t T, int32_t K, int
     hipStream_t st = as_stream(stream);
     unsigned long long* cnt = reinterpret_cast<unsigned long long*>(counts);
     const int TK = T * K;  // < 2^31 by check_trace_shape
+    if ((long long)L * TK <= kOnePairs && L <= kOneLayers) {
+        hipLaunchKernelGGL(balance_one_kernel, dim3(1), dim3(kOneThreads), 0, st, as_arg(trace), L, TK, E, as_arg(cnt), as_arg(delta), as_arg(mean));
+        return launch_status();
+    }
     if (TK <= kOneChunkPairs) {
         hipLaunchKernelGGL(balance_count_kernel<true>, dim3(1, L), dim3(kLayerThreads), 0, st, as_arg(trace), TK, E, as_arg(cnt));
     } else {

@@ -1033,6 +1033,37 @@ def test_bles_loss_value_matches_oracle(dev, oracle, B, T, K, E):
         assert abs(got[i] - ref[key]) <= 2e-6 * max(abs(ref[key]), 1e-30), (key, got[i], ref[key])
 
 
+@pytest.mark.parametrize("B,T,K,E", [
+    # traces of one workgroup: the shortest, turns that are not full, sequences shorter and longer than a turn, one expert a
+    # token, ballots and atomics, the longest by pairs and by elements and the first sizes past them, many layers
+    (1, 2, 1, 2), (1, 2, 2, 3), (5, 63, 2, 8), (2, 1025, 1, 16), (3, 341, 4, 17), (4, 128, 8, 64), (1, 4096, 2, 8), (1, 4097, 2, 8),
+    (2, 1024, 8, 16), (1, 2049, 8, 9), (256, 8, 2, 8), (257, 8, 2, 8), (256, 1, 2, 4), (700, 5, 3, 7),
+])
+def test_trace_statistics_of_short_traces(dev, oracle, B, T, K, E):
+    S = _random_trace(B + T, B, T, K, E)
+    W = np.random.default_rng(B + T).random((B, T, E), np.float32)
+    He, H = torch.full((E,), -1, dtype=torch.int64, device=dev), torch.full((1,), -1, dtype=torch.int64, device=dev)
+    counts = torch.full((B, E), -1, dtype=torch.int64, device=dev)
+    delta, mean = torch.full((B,), -1.0, dtype=torch.float64, device=dev), torch.full((1,), -1.0, dtype=torch.float64, device=dev)
+    out = torch.full((5,), -1.0, dtype=torch.float64, device=dev)
+    ws = torch.empty(pkg.moe_bles_workspace_bytes(B, T, E), dtype=torch.uint8, device=dev)
+    S_gpu = to_device(S, dev)
+    pkg.moe_expert_replacements(S_gpu, E, He, H)
+    pkg.moe_bles_loss(to_device(W, dev), S_gpu, out, ws)
+    pkg.moe_delta_uniform(S_gpu, E, counts, delta, mean)
+    torch.cuda.synchronize()
+    rH, rHe = oracle.expert_replacements(S, E)
+    assert int(H.item()) == rH and np.array_equal(He.cpu().numpy(), rHe)
+    # differences and the sum of four in fp32 (up to 6 roundings of 2^-24 each), the rest in fp64
+    ref = np.abs(np.diff(W.astype(np.float64), axis=1)).sum() if T > 1 else 0.0
+    got = out.cpu().numpy()
+    assert got[0] == rH and abs(got[2] - ref) <= 6 * 2.0 ** -24 * ref and got[4] == got[1] * got[3]
+    r_mean, r_delta, r_counts = oracle.delta_uniform(S, E)
+    assert np.array_equal(counts.cpu().numpy(), r_counts)
+    assert np.allclose(delta.cpu().numpy(), r_delta, rtol=1e-14, atol=1e-16)
+    assert abs(mean.item() - r_mean) <= 1e-13 * max(r_mean, 1e-30) + 1e-16
+
+
 @pytest.mark.parametrize("B,T,E,offset", [(1, 2048, 64, 0), (3, 700, 8, 0), (2, 999, 7, 0), (1, 4096, 64, 1), (9000, 2, 8, 0)])
 def test_bles_loss_adds_its_differences_in_fp64(dev, B, T, E, offset):
     # Probabilities that alternate between 0 and c: every difference is c, and so is exact, as are the sums of
