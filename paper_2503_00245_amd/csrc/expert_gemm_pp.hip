@@ -647,8 +647,7 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     if (dual) {
         if (bm == 64) return launch_pp<64, 128, 2, 8, 6, true, true>(g, nt, st);
         if (bm == 128) return launch_pp<128, 128, 4, 4, 5, true, true>(g, nt, st);
-        // (a k-step of A more than the latency model's two: its fills bound this tile, 2048 tokens of rank 1024 127.9 -> 122.0)
-        return launch_pp<256, 128, 4, 3, 4, true, true>(g, nt, st);
+        return launch_pp<256, 128, 4, 2, 3, true, true>(g, nt, st);
     }
     if (bm == 64) return launch_pp<64, 256, 2, 4, 4, true, false>(g, nt, st);
     if (bm == 128) return launch_pp<128, 256, 2, 4, 3, true, false>(g, nt, st);
