@@ -517,7 +517,7 @@ static int run_gemm(const moe_shape& s, GemmArgs& g, bool swiglu, hipStream_t st
     bool fast = s.act_dtype != MOE_F32;
     for (int i = 0; i < g.nseg; ++i) fast &= g.seg[i].K >= 8 && g.seg[i].K % 8 == 0;  // rows are read in 16-byte chunks
     const bool few = fast && gemm_few_supported(g);
-    if (!fast || !(few || gemm_pp_supported(g))) g.k_parts = 0;
+    if (g.k_parts > 1 && !few && !(fast && gemm_pp_supported(g))) return MOE_ERR_UNSUPPORTED;  // (the consumer expects the parts)
     if (g.C1 && !fast) {  // only the bf16 kernels take two products per launch: run them one by one
         GemmArgs second = g;
         second.C = g.C1;
@@ -603,7 +603,7 @@ static int few_rows(const moe_shape& s) {
 // of 8 17.3 / 19.7)
 bool few_two_tokens(const moe_shape& s) {
     return s.n_tokens == 2 && few_rows(s) && s.rank == 0 && s.top_k > 1 && 2ll * s.top_k * s.d_ff * 4 > 32 * 1024 &&
-           s.d_model <= 2048 && down_cut_supported(s) && gemm_few_split(s.d_ff, 2, kMaxParts);
+           s.d_model <= 2048 && down_cut_supported(s) && gemm_few_split(2ll * s.top_k, s.d_model, s.d_ff, 2, kMaxParts);
 }
 
 SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes) {
@@ -619,7 +619,7 @@ SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes) {
         const int K = s.rank > 0 ? s.rank : s.d_ff;
         const int bf16_max = bf16_parts_max(P, s.n_experts, s.d_model, K);
         p.down_f32 = bf16_max == 1;
-        p.down = few ? gemm_few_split(K, 2, at_most(kMaxParts, down_bytes, P * s.d_model * 4)) : 0;  // (in fp32: cut)
+        p.down = few ? gemm_few_split(P, s.d_model, K, 2, at_most(kMaxParts, down_bytes, P * s.d_model * 4)) : 0;  // (in fp32: cut)
         if (p.down) p.down_f32 = true;
         else p.down = gemm_pp_split(P, s.n_experts, s.d_model, K,
                                     at_most(p.down_f32 ? kMaxParts : bf16_max, down_bytes, P * s.d_model * (p.down_f32 ? 4 : 2)),
@@ -627,13 +627,13 @@ SplitPlan split_plan(const moe_shape& s, size_t down_bytes, size_t rank_bytes) {
     }
     if (s.rank > 0 && (!base || token_base)) {
         const int room = at_most(kMaxParts, rank_bytes, P * s.rank * 4);
-        p.rank_down = few ? gemm_few_split(s.d_ff, 1, room) : 0;
+        p.rank_down = few ? gemm_few_split(P, s.rank, s.d_ff, 1, room) : 0;
         if (!p.rank_down) p.rank_down = gemm_pp_split(P, s.n_experts, s.rank, s.d_ff, room, true, true);
     }
     if (token_base) {
         const FfnLayout l = ffn_layout(s);  // its parts lie in what h .. bu held
         const int room = at_most(kMaxParts, l.end - l.h, (long long)s.n_tokens * s.d_model * 4);
-        p.base_down = few ? gemm_few_split(s.d_ff, 2, room) : 0;
+        p.base_down = few ? gemm_few_split(s.n_tokens, s.d_model, s.d_ff, 2, room) : 0;
         if (!p.base_down) p.base_down = gemm_pp_split(s.n_tokens, 1, s.d_model, s.d_ff, room, true, false);
     }
     return p;

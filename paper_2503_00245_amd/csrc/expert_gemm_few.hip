@@ -406,19 +406,24 @@ int few_steps(int K, int parts) {
 // base with rank 64 94 / 70.  With four row blocks the activations do not fit the registers: 64 tokens 111 / 247.
 bool gemm_few_rows(long long P, int top_k) { return P <= kKeyWords * kWave && P <= 32ll * top_k; }
 
-int gemm_few_split(int K, int parts_min, int parts_max) {
+// What the kernels demand of a product's sizes, its K in `parts` parts: the plan of a call and the choice of a kernel ask the same
+static bool few_sizes_supported(long long P, int N, int K, int parts) {
+    return P <= kKeyWords * kWave && few_steps(K, parts) <= kMaxSteps && K >= 8 && K % 8 == 0 && K < (1 << 23) &&
+           (long long)N * K * 2 < (1ll << 32);
+}
+
+int gemm_few_split(long long P, int N, int K, int parts_min, int parts_max) {
     int q = parts_min;
-    while (q <= parts_max && few_steps(K, q) > kMaxSteps) ++q;
+    while (q <= parts_max && !few_sizes_supported(P, N, K, q)) ++q;
     return q <= parts_max ? q : 0;
 }
 
 bool gemm_few_supported(const GemmArgs& g) {
     const GemmSeg& sg = g.seg[0];
-    const int s = few_steps(sg.K, g.k_parts > 1 ? g.k_parts : 1);
+    const int parts = g.k_parts > 1 ? g.k_parts : 1;
     const bool dual = sg.A0 != sg.A1;
-    return g.nseg == 1 && !g.add0 && g.few > 0 && g.P <= kKeyWords * kWave && s <= kMaxSteps && sg.K >= 8 && sg.K % 8 == 0 &&
-           (g.k_parts <= 1 || g.parts_f32) && !(dual && (g.C1 || !dual_fits(g.few <= 16 ? 1 : 2, s))) && sg.K < (1 << 23) &&
-           (long long)g.N * sg.K * 2 < (1ll << 32);
+    return g.nseg == 1 && !g.add0 && g.few > 0 && few_sizes_supported(g.P, g.N, sg.K, parts) && (parts == 1 || g.parts_f32) &&
+           !(dual && (g.C1 || !dual_fits(g.few <= 16 ? 1 : 2, few_steps(sg.K, parts))));
 }
 
 int run_gemm_few(const GemmArgs& g, bool swiglu, hipStream_t st) {

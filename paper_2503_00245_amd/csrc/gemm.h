@@ -315,8 +315,9 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st);
 int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f32, bool sum_launch);
 // bf16 products of few rows per group (expert_gemm_few.hip)
 bool gemm_few_rows(long long P, int top_k);
-// Parts of K, at least parts_min, that these kernels need, or 0 if that is more than parts_max
-int gemm_few_split(int K, int parts_min, int parts_max);
+// Parts of K, at least parts_min, in which these kernels take a plain product of P rows, or 0 if that is more than parts_max
+// or they do not take it
+int gemm_few_split(long long P, int N, int K, int parts_min, int parts_max);
 bool gemm_few_supported(const GemmArgs& g);
 int run_gemm_few(const GemmArgs& g, bool swiglu, hipStream_t st);
 int launch_sum_parts(const float* parts, int q, long long n, void* out, hipStream_t st);

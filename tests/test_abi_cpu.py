@@ -3,10 +3,12 @@ workspaces, and rejects bad arguments on the host before any launch."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
 import paper_2503_00245_amd as pkg
+from paper_2503_00245_amd import build as hip_build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -154,3 +156,16 @@ def test_static_entry_point_refuses_what_its_scratch_cannot_hold():
     assert L.moe_forward_static(C.byref(pkg.make_shape(8, 100, 256, 4, 2)), C.byref(w), ok, y, None, None, None) == -2
     one = pkg.make_shape(1, 2048, 5632, 8, 2)
     assert 0 < pkg.moe_workspace_bytes(one) <= pkg.STATIC_WORKSPACE_BYTES
+
+
+def test_a_product_planned_in_parts_has_a_kernel_that_writes_them(tmp_path):
+    # host code alone, on the library's own objects: every width up to matrices of 4 GB and more, every kind of layer
+    objs = [os.path.join(hip_build.OBJ, src.replace(".hip", ".o")) for src in hip_build.SOURCES]
+    if not all(os.path.exists(o) for o in objs):
+        hip_build.build()
+    main, exe = str(tmp_path / "check.o"), str(tmp_path / "check")
+    subprocess.run([hip_build._hipcc(), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    hip_build.CSRC, "-c", os.path.join(ROOT, "tests", "split_plan_check.cpp"), "-o", main], check=True)
+    subprocess.run([hip_build._hipcc(), main, *objs, "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
