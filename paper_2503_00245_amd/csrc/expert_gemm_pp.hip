@@ -612,17 +612,20 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     // runs at 6.0 TB/s without the hint and at 6.7 with it.  (2048 / 5632 layer at 8 tokens 95 -> 86 us, 64
     // tokens 124 -> 114, 256 tokens 129 -> 120; where the m-tiles of an expert share its weights in L2 it
     // hurts: 2048 tokens 313 -> 326.)  Drawn at an average of 256 rows per expert, one tile of the tallest kind:
-    // 512 tokens 1024 / 2816 55.9 -> 51.9, 777 tokens 1440 / 3840 94.7 -> 91.7.
+    // 512 tokens 1024 / 2816 55.9 -> 51.9.
     // The smaller tiles follow the same line (whole layer, us, hint at every size / by this rule: 1100 tokens 432 / 1152
     // 37.9 / 33.2, 1024 / 2816 80.1 / 78.4, 400 / 1064 of rank 200 51.6 / 45.3; 2048 tokens on a shared base 282.8 / 280.4; two
     // of 32 sizes were faster with it, 512 tokens on the shared base of 2048 / 5632 142.7 without and 138.3 with).
     // Rows that are no multiples of a line: a k-step ends inside a line, the next one reads that line again, and with the hint
     // it comes from HBM again.  Whole layer, us, with / without: 2040 / 5624 40 tokens 161.7 / 125.6, 256 tokens 171.6 / 149.4,
     // 1024 tokens 305.5 / 259.0; 1032 / 2760 54.2 / 47.4, 128 tokens 58.1 / 50.2, 1024 tokens 104.7 / 97.1; 520 / 1400, 4 experts,
-    // 150 tokens 24.7 / 21.5.  Where rows are whole half-lines only every other row is cut; there the hint stays while most
-    // groups are one tall tile (1440 / 3840 256 tokens 79.4 / 76.0, 777 tokens 91.0 / 93.6, 1000 tokens 124.4 / 119.2).
-    const int line = g.seg[0].K % 64;
-    const bool nt = line == 0 ? g.P <= 256 * g.E : line == 32 && g.P > 64 * g.E && g.P <= 240 * g.E;
+    // 150 tokens 24.7 / 21.5.  The same where rows are whole half-lines and only every other one is cut (a chain of layers past the
+    // memory-side cache on one workspace): 480 / 1312 400 tokens 30.4 / 29.1, 864 / 2336 256 tokens 44.2 / 42.3, 1440 / 3840 600 tokens
+    // 87.0 / 85.5, 777 tokens 92.6 / 91.4, 1000 tokens 127.8 / 122.6, 1952 / 5216 1000 tokens 201.6 / 182.9; none of nine widths at eleven
+    // sizes was 1 % faster with it.  Where calls take turns on several workspaces the hint keeps those in that cache: three of
+    // them, 1440 / 3840 600 to 900 tokens 86.1-99.9 / 88.6-101.1, 1440 / 3872 777 tokens 91.9 / 95.0, but 864 / 2336, 1760 / 4704 and 1952 /
+    // 5216 at 777 tokens 54.6 / 54.4, 151.4 / 140.1, 173.3 / 161.2: no rule.
+    const bool nt = g.seg[0].K % 64 == 0 && g.P <= 256 * g.E;
     if (const int rows = line_rows(g, swiglu, bm))
         return rows == 128 ? launch_pp_lines<128, 256, 2, 2, 4>(g, swiglu, st) : launch_pp_lines<256, 192, 4, 2, 4>(g, swiglu, st);
     if (!swiglu) {
