@@ -560,10 +560,12 @@ def test_expert_ffn_few_rows_per_group(dev, oracle, d, F, r, offsets):
 
 
 @pytest.mark.parametrize("d,F,E,k,r,T", [
-    # weights of more than 36 MB in rows of 1, 2, 3, 4, 5 and 7 eighths of a line past whole ones, both widths and k-steps that
+    # large weights in rows of 1, 2, 3, 4, 5 and 7 eighths of a line past whole ones, both widths and k-steps that
     # end before, at and after the shift of a row; one to four parts; groups of less than a tile, of one and of several
     (1032, 2760, 8, 2, 0, 40), (1056, 2784, 8, 2, 0, 129), (1240, 3224, 8, 2, 0, 257), (1000, 2728, 8, 2, 0, 384), (1016, 2808, 8, 1, 0, 700),
     (1400, 3736, 4, 2, 0, 257), (2040, 5624, 2, 1, 0, 384), (1992, 3160, 3, 3, 0, 129), (1040, 2776, 7, 2, 0, 384), (2040, 2728, 8, 2, 1160, 129),
+    # gate and up alone, and the first sizes at which they are
+    (904, 2440, 8, 2, 0, 129), (856, 2304, 8, 2, 0, 41), (840, 2336, 8, 2, 0, 300),
 ])
 def test_forward_weights_in_cut_lines(dev, oracle, d, F, E, k, r, T):
     cfg = _cfg(name="cut", d=d, F=F, E=E, k=k, dtype="bf16", seed=1800 + d + T, r=r, std=0.03)
