@@ -163,22 +163,22 @@ __global__ __launch_bounds__(kMetricThreads) void bles_finalize_kernel(
 
 // ---- short traces: one workgroup, one launch ------------------------------------------------------------------
 // What takes two launches for want of a sum over workgroups takes one where a single workgroup reads the whole trace in less
-// time than the other launch costs.  Several turns' loads are requested together: none is conditional.
+// time than the other launch costs on the GPU.  Several turns' loads are requested together: none is conditional.
 constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / kWave, kOneTurns = 4;
-constexpr int kBallotExperts = 16;  // up to here lane e counts expert e by ballots (8192 tokens 6.6 us, by LDS atomics 10.4)
+// Up to here lane e counts expert e by ballots, above by LDS atomics (3072 tokens, 4 and 8 experts, 3.2 and 3.7 us against 5.3 and
+// 5.1; 2048 tokens, 16 experts, 4.6 against 3.6)
+constexpr int kBallotExperts = 8;
 
-// Experts replaced after token i of the n = B T (two at least), KT of K: a constant, or 0
-template <int KT>
-__device__ __forceinline__ unsigned long long replaced_after(const int32_t* __restrict__ S, int i, int n, int T, int K, int E) {
-    const int k = KT ? KT : K;
-    const int32_t* s0 = S + (size_t)min(i, n - 2) * k;
-    const unsigned long long d = expert_mask(s0, k, E) ^ expert_mask(s0 + k, k, E);
+// Experts replaced after token i of the n = B T (two at least), K of them selected per token
+template <int K>
+__device__ __forceinline__ unsigned long long replaced_after(const int32_t* __restrict__ S, int i, int n, int T, int E) {
+    const int32_t* s0 = S + (size_t)min(i, n - 2) * K;
+    const unsigned long long d = expert_mask(s0, K, E) ^ expert_mask(s0 + K, K, E);
     return i < n - 1 && i % T != T - 1 ? d : 0ull;
 }
 
-template <int KT>
-__global__ __launch_bounds__(kOneThreads) void replacements_one_kernel(
-    ptr_arg aS, int B, int T, int K, int E, ptr_arg aHe, ptr_arg aH) {
+template <int K>
+__global__ __launch_bounds__(kOneThreads) void replacements_one_kernel(ptr_arg aS, int B, int T, int E, ptr_arg aHe, ptr_arg aH) {
     const int32_t* const S = from_arg<const int32_t>(aS);
     __shared__ int s_cnt[kOneWaves][kMaxExperts];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n = B * T;
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kOneThreads) void replacements_one_kernel(
     for (int i0 = wave * kWave; i0 < n; i0 += kOneTurns * kOneThreads) {
         unsigned long long d[kOneTurns];
 #pragma unroll
-        for (int u = 0; u < kOneTurns; ++u) d[u] = replaced_after<KT>(S, i0 + lane + u * kOneThreads, n, T, K, E);
+        for (int u = 0; u < kOneTurns; ++u) d[u] = replaced_after<K>(S, i0 + lane + u * kOneThreads, n, T, E);
         if (E <= kBallotExperts) {
             for (int e = 0; e < E; ++e) {
                 int c = 0;
@@ -213,9 +213,8 @@ __global__ __launch_bounds__(kOneThreads) void replacements_one_kernel(
     if (lane == 0) *from_arg<unsigned long long>(aH) = c;
 }
 
-template <int KT>
-__global__ __launch_bounds__(kOneThreads) void bles_one_kernel(
-    ptr_arg aW, ptr_arg aS, int B, int T, int K, int E, int vec, ptr_arg a_out) {
+template <int K>
+__global__ __launch_bounds__(kOneThreads) void bles_one_kernel(ptr_arg aW, ptr_arg aS, int B, int T, int E, int vec, ptr_arg a_out) {
     const float* const W = from_arg<const float>(aW);
     const int32_t* const S = from_arg<const int32_t>(aS);
     __shared__ double s_soft[kOneWaves];
@@ -224,7 +223,7 @@ __global__ __launch_bounds__(kOneThreads) void bles_one_kernel(
     unsigned long long hard = 0;
     for (int i0 = threadIdx.x; i0 < n; i0 += kOneTurns * kOneThreads)
 #pragma unroll
-        for (int u = 0; u < kOneTurns; ++u) hard += __popcll(replaced_after<KT>(S, i0 + u * kOneThreads, n, T, K, E));
+        for (int u = 0; u < kOneTurns; ++u) hard += __popcll(replaced_after<K>(S, i0 + u * kOneThreads, n, T, E));
     double soft = 0.0;
     const int q = vec ? E / 4 : E, last = (n - 2) * q + q - 1;  // chunks of a row, the last one with a successor
     for (int c0 = threadIdx.x; c0 <= last; c0 += kOneTurns * kOneThreads) {
@@ -264,7 +263,7 @@ __global__ __launch_bounds__(kOneThreads) void bles_one_kernel(
     write_bles(from_arg<double>(a_out), soft, hard, B, T, K);
 }
 
-constexpr int kOneLayers = 256;  // layers of a trace at most
+constexpr int kOneLayers = 2 * kOneWaves;  // layers of a trace at most
 
 // Waves take layers in turn.  The sums are those of the kernels below, in the same order.
 __global__ __launch_bounds__(kOneThreads) void balance_one_kernel(
@@ -312,14 +311,21 @@ __global__ __launch_bounds__(kOneThreads) void balance_one_kernel(
     *from_arg<double>(a_mean) = total / (double)L;
 }
 
-// Where that pays: at most this many pairs, and (token, expert) pairs.  Two launches cost the host 7.5 us a call, one 4.6.  On the
-// GPU, two launches / one, us: 27 layers of 85 tokens, 2 of 8 experts, replacements 4.1 / 3.7, loss 5.2 / 5.1, balance 4.4 / 4.9;
-// 8 of 512 4.1 / 4.1, 5.2 / 6.6, 4.4 / 3.9; 24 of 341 4.3 / 6.6, 5.2 / 10.5, 4.4 / 6.8; 8 of 1024, 4 of 16, 4.7 / 19, 5.8 / 27, 5.1 / 6.4.
-// All four calls, the host's time: 8 of 512 28.3 / 18.9.
-constexpr int kOnePairs = 16384, kOneElements = 32768;
-static bool short_trace(int L, int T, int K, int E) {
-    return (long long)L * T * K <= kOnePairs && (long long)L * T * E <= kOneElements;
-}
+// Where that pays.  The host saves 2.5-3 us a call (two launches 7-8 us, one 4.6-5.2), but a call behind other work, or in a graph, costs
+// its time on the GPU alone: the lines lie where that is longer by some half a microsecond at most.  In a graph of 64 calls, us a
+// call, two launches / one:
+//   replacements, 2 of 8 experts: 1024 tokens 3.9 / 3.2, 3072 3.9 / 3.7, 4096 3.9 / 4.0, 8192 3.8 / 5.7.  With atomics it matters how
+//     often an expert is replaced: 2 of 16, random / the same four at every token: 1024 tokens 3.8 / 2.7 and 4.5 / 5.3, 2048 3.9 / 3.6 and
+//     4.5 / 8.8.  Four of 8 experts a token, whose loads are no constant number: 64 tokens 4.0 / 4.8; 4 of 16, 1024 tokens, 4.3 / 7.9
+//   loss, 2 of 8: 2048 tokens 4.8 / 4.2, 3072 4.9 / 5.4, 4096 4.9 / 6.3; 2 of 16: 1024 tokens 5.1 / 4.1, 2048 5.1 / 5.5; 2 of 64: 256 tokens 6.1 /
+//     3.8, 1024 6.5 / 8.0; 2 of 7, rows no whole chunks: 585 tokens 5.3 / 3.8, 2048 5.6 / 7.6
+//   balance, random / Zipf / all tokens with the same experts, where the LDS atomics meet: 16 layers of 64 tokens, 2 of 2, 3.8 / 3.5 each;
+//     2 layers of 1024, 2 of 4, 4.0 / 3.5, 4.1 / 3.5, 4.2 / 3.7; 8 of 512, 2 of 8, 4.3 / 3.7, 4.3 / 4.8, 4.3 / 5.6; 16 of 256 4.3 / 4.0, 4.3 / 5.1, 4.3 /
+//     6.0; 16 of 512, 1 of 8, 4.4 / 4.0, 4.3 / 6.2, 4.4 / 9.4; two turns of the waves: 24 of 64, 4 of 16, 4.7 / 4.3, 27 of 64, 2 of 8, 4.2 / 4.6,
+//     24 of 170 4.1 / 4.7; 9 of 179, 8 of 8, 4.1 / 3.7; one layer, one wave, of 2048 3.9 / 4.7
+constexpr int kOneTokens = 4096, kOneManyTokens = 2048, kOneChunks = 6144, kOnePairs = 16384, kOneLayerPairs = 2048;
+// many: more experts than ballots are for, or layers than waves
+static bool short_trace(int L, int T, bool many) { return (long long)L * T <= (many ? kOneManyTokens : kOneTokens); }
 
 constexpr int kLayerThreads = 1024;  // kernels with one workgroup per layer
 // Up to this many pairs a layer is one workgroup's: it reads 128 KB in about the 9 us that clearing the
@@ -442,9 +448,9 @@ int moe_expert_replacements(const int32_t* S, int32_t B, int32_t T, int32_t K, i
     hipStream_t st = as_stream(stream);
     unsigned long long* he = reinterpret_cast<unsigned long long*>(H_e);
     unsigned long long* h = reinterpret_cast<unsigned long long*>(H);
-    if (T > 1 && short_trace(B, T, K, E)) {
-        const auto kern = K == 1 ? replacements_one_kernel<1> : K == 2 ? replacements_one_kernel<2> : replacements_one_kernel<0>;
-        hipLaunchKernelGGL(kern, dim3(1), dim3(kOneThreads), 0, st, as_arg(S), B, T, K, E, as_arg(he), as_arg(h));
+    if (T > 1 && K <= 2 && short_trace(B, T, E > kBallotExperts)) {
+        const auto kern = K == 1 ? replacements_one_kernel<1> : replacements_one_kernel<2>;
+        hipLaunchKernelGGL(kern, dim3(1), dim3(kOneThreads), 0, st, as_arg(S), B, T, E, as_arg(he), as_arg(h));
         return launch_status();
     }
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(kMetricThreads), 0, st, as_arg(he), E, as_arg(h));
@@ -470,10 +476,10 @@ int moe_bles_loss(const float* probs, const int32_t* S, int32_t B, int32_t T, in
     if (!probs || !S || !out) return MOE_ERR_INVALID;
     if (!workspace || workspace_bytes < moe_bles_workspace_bytes(B, T, E)) return MOE_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
-    if (T > 1 && short_trace(B, T, K, E)) {
-        const auto kern = K == 1 ? bles_one_kernel<1> : K == 2 ? bles_one_kernel<2> : bles_one_kernel<0>;
-        hipLaunchKernelGGL(kern, dim3(1), dim3(kOneThreads), 0, st, as_arg(probs), as_arg(S), B, T, K, E,
-                           E % 4 == 0 && aligned16(probs) ? 1 : 0, as_arg(out));
+    const int vec = E % 4 == 0 && aligned16(probs) ? 1 : 0;  // rows are whole 16-byte chunks
+    if (T > 1 && K <= 2 && short_trace(B, T, false) && B * T * E / (vec ? 4 : 1) <= kOneChunks) {
+        const auto kern = K == 1 ? bles_one_kernel<1> : bles_one_kernel<2>;
+        hipLaunchKernelGGL(kern, dim3(1), dim3(kOneThreads), 0, st, as_arg(probs), as_arg(S), B, T, E, vec, as_arg(out));
         return launch_status();
     }
     // 12 bytes of partial sums per workgroup; the size query has room for 4 per 256 differences of W beside 768
@@ -489,7 +495,7 @@ int moe_bles_loss(const float* probs, const int32_t* S, int32_t B, int32_t T, in
         nblocks = (B * T - 1) / tokens_per_block + 1;
         hard_part = reinterpret_cast<int*>(soft_part + nblocks);
         hipLaunchKernelGGL(bles_partial_kernel, dim3(nblocks), dim3(kMetricThreads), 0, st, as_arg(probs), as_arg(S), B, T, K, E,
-                           tokens_per_block, E % 4 == 0 && aligned16(probs) ? 1 : 0, as_arg(soft_part), as_arg(hard_part));
+                           tokens_per_block, vec, as_arg(soft_part), as_arg(hard_part));
     }
     hipLaunchKernelGGL(bles_finalize_kernel, dim3(1), dim3(kMetricThreads), 0, st, as_arg(soft_part), as_arg(hard_part), nblocks, B, T, K,
                        as_arg(out));
@@ -515,7 +521,7 @@ int moe_delta_uniform(const int32_t* trace, int32_t L, int32_t T, int32_t K, int
     hipStream_t st = as_stream(stream);
     unsigned long long* cnt = reinterpret_cast<unsigned long long*>(counts);
     const int TK = T * K;  // < 2^31 by check_trace_shape
-    if ((long long)L * TK <= kOnePairs && L <= kOneLayers) {
+    if (L <= kOneLayers && short_trace(L, T, L > kOneWaves) && TK <= kOneLayerPairs && (long long)L * TK <= kOnePairs) {
         hipLaunchKernelGGL(balance_one_kernel, dim3(1), dim3(kOneThreads), 0, st, as_arg(trace), L, TK, E, as_arg(cnt), as_arg(delta), as_arg(mean));
         return launch_status();
     }
