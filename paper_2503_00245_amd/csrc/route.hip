@@ -39,6 +39,10 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
 // both kernels give bit-identical logits.  For E <= kRouteLdsMaxE and E * d * 4 bytes of LDS.
 // (One token at a time read 64 KB of LDS and waited for its chunks one by one: 16384 tokens, 2048 wide, 8
 // experts 42 us, 34 now.)
+// Up to 8 experts a wave takes four tokens at a time, from 9 on as many as its registers hold without scratch: four of 12
+// accumulators each (with 16 each, 28 bytes a lane went to scratch), two of 16, and three where that is all a wave has.  us, four with scratch /
+// this, 2048 wide: 16 experts 9000 tokens 47.3 / 38.0, 12288 49.8 / 40.4, 16384 54.7 / 54.4, 32768 98.9 / 98.6; 12 experts 12288
+// tokens 39.5 / 33.6, 16384 43.2 / 40.5, 32768 78.6 / 73.1 (three tokens at a time 56.4, 85.6); 9 experts, 512 wide, 16384 tokens 16.8 / 15.7.
 constexpr int kRouteLdsMaxE = 16;
 constexpr int kRouteLdsBytes = 128 * 1024;
 
@@ -129,10 +133,12 @@ static int launch_route_lds(const moe_shape& s, const T* x, const float* rw, con
                            s.top_k, tokens_per_wave);
         return launch_status();
     };
-    static std::atomic<uint64_t> allowed[4];
+    static std::atomic<uint64_t> allowed[5];
     if (s.n_experts <= 8)
         return tokens_per_wave > 2 ? launch(route_lds_kernel<T, 4, 8>, allowed[0]) : launch(route_lds_kernel<T, 2, 8>, allowed[1]);
-    return tokens_per_wave > 2 ? launch(route_lds_kernel<T, 4, 16>, allowed[2]) : launch(route_lds_kernel<T, 2, 16>, allowed[3]);
+    if (tokens_per_wave == 3) return launch(route_lds_kernel<T, 3, 16>, allowed[2]);
+    if (tokens_per_wave > 3 && s.n_experts <= 12) return launch(route_lds_kernel<T, 4, 12>, allowed[3]);
+    return launch(route_lds_kernel<T, 2, 16>, allowed[4]);
 }
 
 int launch_route(const moe_shape& s, const void* x, const float* rw, const float* rb,

@@ -205,9 +205,10 @@ def test_permute_in_chunks_of_any_length(dev, oracle, T, k, E, room):
 
 @pytest.mark.parametrize("T,d,E,k,dtype", [
     (8192, 72, 5, 2, "bf16"), (16385, 520, 8, 3, "bf16"), (8193, 1032, 9, 1, "bf16"), (12289, 264, 16, 4, "bf16"), (8195, 68 * 4, 7, 2, "f32"),
+    (12290, 520, 12, 2, "bf16"), (20483, 72, 10, 3, "f32"), (12287, 136, 16, 2, "bf16"), (12291, 1032, 13, 2, "bf16"),
 ])
 def test_route_several_tokens_per_wave(dev, oracle, T, d, E, k, dtype):
-    # two and four tokens at a time, remainders of a wave's share, ragged chunks, up to 8 and up to 16 experts
+    # two, three and four tokens at a time, remainders of a wave's share, ragged chunks, up to 8, 12 and 16 experts
     cfg = _cfg(d=d, F=8, E=E, k=k, dtype=dtype, seed=2100 + T + E)
     w_np = wl.make_layer_weights(cfg)
     x_np = wl.make_inputs(cfg, T)
