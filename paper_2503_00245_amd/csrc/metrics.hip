@@ -316,14 +316,14 @@ __global__ __launch_bounds__(kOneThreads) void balance_one_kernel(
 // call, two launches / one:
 //   replacements, 2 of 8 experts: 1024 tokens 3.9 / 3.2, 3072 3.9 / 3.7, 4096 3.9 / 4.0, 8192 3.8 / 5.7.  With atomics it matters how
 //     often an expert is replaced: 2 of 16, random / the same four at every token: 1024 tokens 3.8 / 2.7 and 4.5 / 5.3, 2048 3.9 / 3.6 and
-//     4.5 / 8.8.  Four of 8 experts a token, whose loads are no constant number: 64 tokens 4.0 / 4.8; 4 of 16, 1024 tokens, 4.3 / 7.9
+//     4.5 / 8.8, 3072 3.9 / 4.4 (1 of 16 3.7 / 3.2).  Four of 8 experts a token, whose loads are no constant number: 64 tokens 4.0 / 4.8; 4 of 16, 1024 tokens, 4.3 / 7.9
 //   loss, 2 of 8: 2048 tokens 4.8 / 4.2, 3072 4.9 / 5.4, 4096 4.9 / 6.3; 2 of 16: 1024 tokens 5.1 / 4.1, 2048 5.1 / 5.5; 2 of 64: 256 tokens 6.1 /
 //     3.8, 1024 6.5 / 8.0; 2 of 7, rows no whole chunks: 585 tokens 5.3 / 3.8, 2048 5.6 / 7.6
 //   balance, random / Zipf / all tokens with the same experts, where the LDS atomics meet: 16 layers of 64 tokens, 2 of 2, 3.8 / 3.5 each;
 //     2 layers of 1024, 2 of 4, 4.0 / 3.5, 4.1 / 3.5, 4.2 / 3.7; 8 of 512, 2 of 8, 4.3 / 3.7, 4.3 / 4.8, 4.3 / 5.6; 16 of 256 4.3 / 4.0, 4.3 / 5.1, 4.3 /
 //     6.0; 16 of 512, 1 of 8, 4.4 / 4.0, 4.3 / 6.2, 4.4 / 9.4; two turns of the waves: 24 of 64, 4 of 16, 4.7 / 4.3, 27 of 64, 2 of 8, 4.2 / 4.6,
-//     24 of 170 4.1 / 4.7; 9 of 179, 8 of 8, 4.1 / 3.7; one layer, one wave, of 2048 3.9 / 4.7
-constexpr int kOneTokens = 4096, kOneManyTokens = 2048, kOneChunks = 6144, kOnePairs = 16384, kOneLayerPairs = 2048;
+//     24 of 170 4.1 / 4.7, 24 of 341 4.4 / 6.5; 9 of 179, 8 of 8, 4.1 / 3.7; one layer, one wave, of 2048 3.9 / 4.7
+constexpr int kOneTokens = 4096, kOneManyTokens = 3072, kOneChunks = 6144, kOnePairs = 16384, kOneLayerPairs = 2048;
 // many: more experts than ballots are for, or layers than waves
 static bool short_trace(int L, int T, bool many) { return (long long)L * T <= (many ? kOneManyTokens : kOneTokens); }
 
