@@ -564,7 +564,7 @@ int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f3
 //     skewed than that may still add one (984 / 2624, 570 tokens, 47 % of them with one expert, 65.2 / 78.4): with a quarter more of
 //     the Zipf loads too, that case and two more of 170 drawn ones are spared 7-20 %, and 13 lose 3-10 % (mean gain 6.0 %, 6.1 without);
 //   - a plain product has tiles for half the CUs, and not fewer than it had (300 tokens of 1032 / 2760, one part, 62.6 / 71.4);
-//   - the weights are large, a matrix of all experts 40 MB or each of a pair 30.  Below, a launch is short, and the step more that its
+//   - the weights are large, a matrix of all experts 30 MB for gate and up, 50 each for two plain products, 40 for a single one.  Below, a launch is short, and the step more that its
 //     tiles start with costs what the lines save.  Weights cold (as many copies of the layer in turn as are past the memory-side
 //     cache, the state of any model of several layers), whole layer, without / with gate and up fetched so: 664 / 1800 (2 x 18 MB) 48
 //     tokens 31.2 / 31.4, 500 tokens 43.7 / 43.2; 712 / 1944 (21 MB) 32.7 / 32.6, 46.7 / 45.6; 4 experts of 1096 / 2968 (25 MB), 150
@@ -572,7 +572,10 @@ int gemm_pp_split(long long P, int E, int N, int K, int parts_max, bool parts_f3
 //     178 tokens 42.6 / 38.8; 904 / 2440 (34 MB) 48 tokens 41.0 / 37.4, 500 tokens 59.9 / 57.5; 1400 / 3736 (80 MB) 66.0 / 56.5 at 48.  The
 //     down product alone: 952 / 2568 (37 MB) 48 tokens 42.7 / 43.3, 128 tokens 44.8 / 45.9; 4 experts of 1400 / 3736 (40 MB), 64 tokens,
 //     46.8 / 48.9; 1032 / 2760 (43 MB) 47.1 / 46.4 and, 128 tokens with Zipf loads, 53.9 / 56.3; 4 experts of 1448 / 3928 (43 MB), 509
-//     tokens, 85.8 / 82.8; 1400 / 3736 (80 MB) 66.0 / 64.1, 78.2 / 79.0.  Where one layer runs alone and its weights stay in that cache,
+//     tokens, 85.8 / 82.8; 1400 / 3736 (80 MB) 66.0 / 64.1, 78.2 / 79.0.  The two rank
+//     products, 16 experts: rank 640 on 1272 / 3408 (25 MB) 253 tokens 86.9 / 92.1, 768 on 1528 / 4120 (36 MB) 164 tokens 111.3 / 117.8, 832 on
+//     1672 / 4520 (43 MB) 38 tokens 109.2 / 113.8, 912 on 1824 / 4904 (51 MB) 602 tokens 193.3 / 190.2, 1024 on 2040 / 5584 (64 MB) 1579 tokens
+//     275.5 / 266.9.  Where one layer runs alone and its weights stay in that cache,
 //     cut lines cost little: 760 / 2056 48 tokens 29.4 / 32.5, 1304 / 3560 50.3 / 52.3;
 //   - groups are one tall tile on average: beyond, the narrow tiles' LDS reads cost what the fills save (2500 tokens of
 //     2040 / 5624 406 / 404, 4000 tokens 653 / 664).
@@ -598,7 +601,7 @@ static int line_rows(const GemmArgs& g, bool swiglu, int bm) {
     if (K % 64 == 0 || K % 8 != 0 || g.N % 8 != 0 || sg.strideB % 64 != 0 || !whole(sg.B0) || !whole(sg.B1) ||
         (K + BK - 1) / BK < 2 * parts || (swiglu && sg.A0 != sg.A1))
         return 0;
-    if (g.P > 256ll * g.E || (sg.strideB != 0 ? g.E : 1) * 2ll * g.N * K < (swiglu || g.C1 ? 30 << 20 : 40 << 20)) return 0;
+    if (g.P > 256ll * g.E || (sg.strideB != 0 ? g.E : 1) * 2ll * g.N * K < ((swiglu ? 30 : g.C1 ? 50 : 40) << 20)) return 0;
     const int copies = parts * (!swiglu && g.C1 ? 2 : 1), per_row = swiglu ? 2 : 1;
     for (int rows = 256; rows >= 128; rows /= 2) {
         bool ok = true;
