@@ -592,14 +592,43 @@ def test_forward_narrow_down_tiles(dev, oracle, d, F, E, k, T):
     _forward_case(dev, oracle, cfg, T, residual=bool(T % 4))
 
 
-@pytest.mark.parametrize("T,k,E", [(32, 2, 5), (9, 3, 40)])
-def test_forward_few_tokens_with_nan_logits(dev, T, k, E):
-    # every pair may land in one expert or in none: the call ends and leaves other tokens' memory alone
-    cfg = _cfg(name="nan", d=264, F=520, E=E, k=k, dtype="bf16", seed=1790 + E)
+def _forward_guarded(w_t, x_t, k, act):
+    """moe_forward on y, idx, gate and workspace that each lie between guard bytes, which have to be as they were."""
+    T, shape = x_t.shape[0], pkg.shape_for(w_t, x_t.shape[0], k, act)
+    sizes = [x_t.numel() * x_t.element_size(), T * k * 4, T * k * 4, pkg.moe_workspace_bytes(shape)]
+    bufs = [torch.full((4096 + n + 4096,), 0xA5, dtype=torch.uint8, device=x_t.device) for n in sizes]
+    y, idx, gate, ws = (b[4096:4096 + n] for b, n in zip(bufs, sizes))
+    y, idx, gate = y.view(x_t.dtype).view(x_t.shape), idx.view(torch.int32).view(T, k), gate.view(torch.float32).view(T, k)
+    idx.fill_(-1)
+    pkg.moe_forward(shape, pkg.make_weights(w_t), x_t, y, idx, gate, ws)
+    torch.cuda.synchronize()
+    for b, n, what in zip(bufs, sizes, ("y", "idx", "gate", "workspace")):
+        assert bool((b[:4096] == 0xA5).all()) and bool((b[4096 + n:] == 0xA5).all()), f"written outside {what}"
+    return y, idx, gate
+
+
+@pytest.mark.parametrize("same_experts", [False, True])
+@pytest.mark.parametrize("T,k,E,dtype", [(32, 2, 5, "bf16"), (9, 3, 40, "bf16"), (17, 2, 5, "f32")])
+def test_forward_few_tokens_some_with_nan_logits(dev, T, k, E, dtype, same_experts):
+    # such a token's pairs may land in one expert or in none.  The others are, bit for bit, what they are beside finite tokens (a
+    # row of a tile does not depend on where it lies or what the others hold), also where all tokens share their experts
+    cfg = _cfg(name="nan", d=264, F=520, E=E, k=k, dtype=dtype, seed=1790 + E)
     w_t = weights_to_device(wl.make_layer_weights(cfg), dev)
-    w_t["router_w"].fill_(float("nan"))
-    y, _, _ = _forward_gpu(dev, w_t, to_device(wl.make_inputs(cfg, T), dev), k, pkg.MOE_BF16)
-    assert y.shape == (T, 264)
+    if same_experts:
+        w_t["router_b"] = torch.zeros(E, dtype=torch.float32, device=dev)
+        w_t["router_b"][E - k:] = 100.0
+    x_t = to_device(wl.make_inputs(cfg, T), dev)
+    clean = _forward_guarded(w_t, x_t, k, DT[dtype])
+    assert bool(torch.isfinite(clean[0]).all()) and (not same_experts or bool((clean[1] >= E - k).all()))
+    bad = torch.zeros(T, dtype=torch.bool, device=dev)
+    bad[[0, T // 2, T - 1]] = True
+    x_bad = x_t.clone()
+    x_bad[bad] = float("nan")
+    mixed = _forward_guarded(w_t, x_bad, k, DT[dtype])
+    for got, want, what in zip(mixed, clean, ("y", "idx", "gate")):
+        assert torch.equal(got[~bad], want[~bad]), what
+    x_t.fill_(float("nan"))  # no finite token at all: the call ends, inside its memory
+    _forward_guarded(w_t, x_t, k, DT[dtype])
 
 
 @pytest.mark.parametrize("d,F,E,k,T", [
