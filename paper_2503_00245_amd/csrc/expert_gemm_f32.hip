@@ -210,7 +210,12 @@ struct TokenLayer {
 };
 // acc[m] += A row of the lane . B[m] row of the lane over the k-steps first, first + stride, ... of K.  (The next D on
 // their way beside the present ones: slower, 17.3 -> 21.3 us for 32 tokens of 256 / 640, fewer waves fit.)
-template <int D, int NM>
+// The products of D steps are summed in 4 CHAINS chains apart, which meet pair by pair: one chain over all steps was up to 96 products
+// long, and two tokens, whose lanes' chains on the matrix-vector path are of a few, were 1.5 times as far from 64 bits as there (120 layers of
+// 2 to 8 experts, 64 to 512 wide, geometric mean; 1.00 now, 1.04 with CHAINS 1.  Three tokens and more against the stage by stage way: 0.95, 0.61 now).
+// CHAINS 2 for two tokens alone: where the chip is full its registers and sums cost time (4 experts of 256 / 640, 64 tokens, 18.2 us before,
+// 18.4 with 1, 20.0 with 2; two tokens of 2 experts 8.9, 9.2, 9.8; on the matrix-vector path 12 and more).
+template <int D, int CHAINS, int NM>
 __device__ __forceinline__ void token_tile(const float* pa, const float* const (&pb)[NM], int K, int first, int stride, f32x4 (&acc)[NM]) {
     const int quad = (threadIdx.x & (kWave - 1)) >> 4, steps = (K + 15) / 16;
     for (int st = first; st < steps; st += D * stride) {
@@ -222,20 +227,35 @@ __device__ __forceinline__ void token_tile(const float* pa, const float* const (
 #pragma unroll
             for (int m = 0; m < NM; ++m) b[m][q] = *reinterpret_cast<const f32x4*>(pb[m] + k);
         }
+        f32x4 part[NM][CHAINS][4];
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int i = 0; i < CHAINS; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) part[m][i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int q = 0; q < D; ++q) {
-            if (st + q * stride >= steps) break;
+            if (q > 0 && st + q * stride >= steps) break;
             const bool in = (st + q * stride) * 16 + quad * 4 < K;  // beyond K: both operands cleared
 #pragma unroll
             for (int m = 0; m < NM; ++m)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a[q][c] : 0.f, in ? b[m][q][c] : 0.f, acc[m], 0, 0, 0);
+                for (int c = 0; c < 4; ++c) {
+                    f32x4& p = part[m][q % CHAINS][c];
+                    p = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a[q][c] : 0.f, in ? b[m][q][c] : 0.f, p, 0, 0, 0);
+                }
+        }
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            f32x4 sum = (part[m][0][0] + part[m][0][1]) + (part[m][0][2] + part[m][0][3]);
+            if (CHAINS == 2) sum += (part[m][CHAINS - 1][0] + part[m][CHAINS - 1][1]) + (part[m][CHAINS - 1][2] + part[m][CHAINS - 1][3]);
+            acc[m] += sum;
         }
     }
 }
 
-template <int D>
+template <int D, int CHAINS>
 __global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(const TokenLayer g) {
     const int route_blocks = g.route_blocks;
     if ((int)blockIdx.x < route_blocks) {
@@ -252,7 +272,7 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(c
     const size_t row = ((size_t)e * g.F + min(f0 + i, g.F - 1)) * g.d;
     const float* const pb[2] = {g.w_gate + row, g.w_up + row};
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    token_tile<D, 2>(pa, pb, g.d, wave, kRouteWaves, acc);
+    token_tile<D, CHAINS, 2>(pa, pb, g.d, wave, kRouteWaves, acc);
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -264,11 +284,12 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(c
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int w = 0; w < kRouteWaves; ++w) z[m] += s_part[m][w][t][c];
+        for (int w = 0; w < kRouteWaves; w += 4)
+            z[m] += (s_part[m][w][t][c] + s_part[m][w + 1][t][c]) + (s_part[m][w + 2][t][c] + s_part[m][w + 3][t][c]);
     g.h[((size_t)e * g.T + t0 + t) * g.F + f0 + c] = silu_f32(z[0]) * z[1];
 }
 
-template <int D>
+template <int D, int CHAINS>
 __global__ __launch_bounds__(kTokenWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void token_down_f32_kernel(const TokenLayer g) {
     __shared__ float s_part[kTokenWaves][16][17];
     const int lane = threadIdx.x & (kWave - 1);
@@ -283,7 +304,7 @@ __global__ __launch_bounds__(kTokenWaves* kWave) __attribute__((amdgpu_waves_per
     f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
     if (e < g.E) {
         const float* const pb[1] = {g.w_down + ((size_t)e * g.d + min(n0 + i, g.d - 1)) * g.F};
-        token_tile<D, 1>(g.h + ((size_t)e * g.T + min(t0 + i, g.T - 1)) * g.F, pb, g.F, ks, g.slices, acc);
+        token_tile<D, CHAINS, 1>(g.h + ((size_t)e * g.T + min(t0 + i, g.T - 1)) * g.F, pb, g.F, ks, g.slices, acc);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) s_part[wave][4 * quad + r][i] = acc[0][r];
@@ -292,9 +313,12 @@ __global__ __launch_bounds__(kTokenWaves* kWave) __attribute__((amdgpu_waves_per
     float total = 0.f;
     for (int j = 0; j < g.k; ++j) {
         const int ej = min(max(g.idx[t * g.k + j], 0), g.E - 1);
-        float sum = 0.f;
-        for (int sl = 0; sl < g.slices; ++sl) sum += s_part[ej * g.slices + sl][threadIdx.x >> 4][threadIdx.x & 15];
-        total = fmaf(g.gate[t * g.k + j], sum, total);
+        float sum[2] = {0.f, 0.f};
+        for (int sl = 0; sl < g.slices; sl += CHAINS)
+#pragma unroll
+            for (int i = 0; i < CHAINS; ++i)
+                if (i == 0 || sl + i < g.slices) sum[i] += s_part[ej * g.slices + sl + i][threadIdx.x >> 4][threadIdx.x & 15];
+        total = fmaf(g.gate[t * g.k + j], sum[0] + sum[1], total);
     }
     g.y[(size_t)t * g.d + n] = total + res;
 }
@@ -322,14 +346,15 @@ int launch_token_layer_f32(const moe_shape& s, const moe_weights& w, const void*
                        static_cast<float*>(y), static_cast<const float*>(residual), slices, w.router_w, w.router_b, route_blocks};
     const int tb = (s.n_tokens + 15) / 16;
     const dim3 grid(route_blocks + tb * s.n_experts * ((s.d_ff + 15) / 16));
-    if (s.d_model <= 16 * kRouteWaves)
-        hipLaunchKernelGGL(token_gate_up_f32_kernel<1>, grid, dim3(kRouteWaves * kWave), 0, st, g);
-    else
-        hipLaunchKernelGGL(token_gate_up_f32_kernel<4>, grid, dim3(kRouteWaves * kWave), 0, st, g);
+    const bool two = s.n_tokens == 2;
+    const auto first = s.d_model <= 16 * kRouteWaves       ? token_gate_up_f32_kernel<1, 1>
+                       : s.d_model <= 2 * 16 * kRouteWaves ? (two ? token_gate_up_f32_kernel<2, 2> : token_gate_up_f32_kernel<2, 1>)
+                                                           : (two ? token_gate_up_f32_kernel<4, 2> : token_gate_up_f32_kernel<4, 1>);
+    hipLaunchKernelGGL(first, grid, dim3(kRouteWaves * kWave), 0, st, g);
     int rc = launch_status();
     if (rc != MOE_OK) return rc;
     stage_mark(timer, "route_gate_up_swiglu");
-    hipLaunchKernelGGL(token_down_f32_kernel<4>, dim3((s.d_model + 15) / 16, tb), dim3(kTokenWaves * kWave), 0, st, g);
+    hipLaunchKernelGGL((two ? token_down_f32_kernel<4, 2> : token_down_f32_kernel<4, 1>), dim3((s.d_model + 15) / 16, tb), dim3(kTokenWaves * kWave), 0, st, g);
     rc = launch_status();
     stage_mark(timer, "gemm_down_combine");
     return rc;
