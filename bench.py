@@ -80,13 +80,13 @@ FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 TRAFFIC_SOURCE = {
     # gate/up grouped GEMM with the SiLU * mul epilogue (256 x 256 tiles, filled straight into LDS)
     "phone_prefill": ("phone_prefill_kernels_and_hbm_traffic.txt",
-                      r"gemm_pp_kernel<256, 256, 2, 2, 3, true, false, false, false>"),
+                      r"gemm_pp_kernel<256, 256, 2, 2, 3, true, false, false, false, false>"),
     # routing, gate/up matrix-vector products and SwiGLU of the single-token step
-    "phone_decode": ("phone_decode_kernels_and_hbm_traffic.txt", r"decode_first_kernelIDF16bLi4ELb1E"),
+    "phone_decode": ("phone_decode_kernels_and_hbm_traffic.txt", r"decode_first_kernel<bf16, 4, true>"),
 }
 MEASURED_KIB = {  # workload: (FETCH_SIZE mean, WRITE_SIZE mean), KiB per dispatch as the tool reports them
-    "phone_prefill": (335740.0, 45143.6),
-    "phone_decode": (45391.7, 23.7),
+    "phone_prefill": (325998.9, 45143.6),
+    "phone_decode": (45391.1, 24.1),
 }
 MEASURED_TRAFFIC_BYTES = {w: int((f * FETCH_SCALE + wr * WRITE_SCALE) * 1024) for w, (f, wr) in MEASURED_KIB.items()}
 
