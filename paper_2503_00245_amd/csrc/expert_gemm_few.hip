@@ -401,9 +401,13 @@ int few_steps(int K, int parts) {
 }  // namespace
 
 // Where these kernels are taken: up to 32 rows in a group, two MFMA row blocks (a token meets an expert once, so 32
-// tokens).  Whole layer, us, against the direct-fill kernels: 2048 / 5632 8 tokens 111 / 95, 32 tokens 118 / 104; 2040 / 5624 150 / 95,
-// 161 / 102; 1024 / 2816 37.5 / 35.2, 38.5 / 39.1; 432 / 1152 23.2 / 18.7, 24.4 / 20.7; rank 1024 on 2040 / 5464, 16 tokens 104 / 83; shared
-// base with rank 64 94 / 70.  With four row blocks the activations do not fit the registers: 64 tokens 111 / 247.
+// tokens).  Whole layer, us, weights cold, direct-fill kernels / these.  Up to 16 tokens these are the faster at every size
+// measured: 2048 / 5632 3 tokens 89 / 73, 16 tokens 120 / 102; 1024 / 2816 3, 8 and 16 tokens 31.2 / 27.8, 36.0 / 33.9, 37.5 / 35.5;
+// 432 / 1152 16 tokens 25.3 / 21.1.  From 17 on they are so for narrow layers, few experts, cut lines, rank factors and a shared base (32
+// tokens: 432 / 1152 24.7 / 21.7, 768 / 2048 30.4 / 28.0, 4 experts of 1024 / 2816 30.5 / 27.5, 2040 / 5624 107.9 / 103.3, rank 1024 on 2048 / 5632
+// 93.9 / 86.8, shared base with rank 64 95.6 / 79.6) and about even for 8 experts of whole lines: 1024 / 2816 38.2 / 38.8 (4 chosen 40.5 /
+// 41.7, the worst found), 1280 / 3456 48.6 / 49.0, 1792 / 4864 81.4 / 82.0; 2048 / 5632 takes 99-122 there by where its matrices lie, here
+// 102-105.  With four row blocks the activations do not fit the registers: 64 tokens 111 / 247.
 bool gemm_few_rows(long long P, int top_k) { return P <= kKeyWords * kWave && P <= 32ll * top_k; }
 
 // What the kernels demand of a product's sizes, its K in `parts` parts: the plan of a call and the choice of a kernel ask the same

@@ -635,9 +635,9 @@ int run_gemm_pp(GemmArgs& g, bool swiglu, hipStream_t st) {
     // 150 tokens 24.7 / 21.5.  The same where rows are whole half-lines and only every other one is cut (a chain of layers past the
     // memory-side cache on one workspace): 480 / 1312 400 tokens 30.4 / 29.1, 864 / 2336 256 tokens 44.2 / 42.3, 1440 / 3840 600 tokens
     // 87.0 / 85.5, 777 tokens 92.6 / 91.4, 1000 tokens 127.8 / 122.6, 1952 / 5216 1000 tokens 201.6 / 182.9; none of nine widths at eleven
-    // sizes was 1 % faster with it.  Where calls take turns on several workspaces the hint keeps those in that cache: three of
-    // them, 1440 / 3840 600 to 900 tokens 86.1-99.9 / 88.6-101.1, 1440 / 3872 777 tokens 91.9 / 95.0, but 864 / 2336, 1760 / 4704 and 1952 /
-    // 5216 at 777 tokens 54.6 / 54.4, 151.4 / 140.1, 173.3 / 161.2: no rule.
+    // sizes was 1 % faster with it.  Where calls take turns on several workspaces, whose lines the weights
+    // then drive out of that cache, part of it is lost again: 8 experts of 1056 to 1440 wide, 120 to 194 rows per expert, 1-2 % slower without
+    // (1440 / 3840 777 tokens 90.4 / 92.5; on one workspace 90.4 / 87.8), wider ones and 16 experts 1-8 % faster all the same.
     const bool nt = g.seg[0].K % 64 == 0 && g.P <= 256 * g.E;
     if (const int rows = line_rows(g, swiglu, bm))
         return rows == 128 ? launch_pp_lines<128, 256, 2, 2, 4>(g, swiglu, st) : launch_pp_lines<256, 192, 4, 2, 4>(g, swiglu, st);
