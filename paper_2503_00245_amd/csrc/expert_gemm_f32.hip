@@ -191,7 +191,7 @@ int run_gemm_f32(GemmArgs& g, bool swiglu, hipStream_t st) {
 // ---- small layers of dense experts: two launches ----------------------------------------------------------------
 // What bounds a small layer is launches, each a chain of memory latencies: routing, sorting inside the gate/up product,
 // the down product and the combine took 16.0 us for 32 tokens of a 128 / 256 layer with 4 experts; the two launches here
-// take 9.9 (64 / 136 with 8 experts 15.0 and 8.7, 256 / 640 with 2 18.9 and 11.3).  Every token
+// take 9.3 (64 / 136 with 8 experts 15.0 and 8.7, 256 / 640 with 2 18.9 and 11.3).  Every token
 // meets every expert, so that no product waits for the routing: the tokens' rows are MFMA rows, h [E, T, F] holds them all,
 // the routing runs beside the first product, and who chose whom matters only where the last one adds up.
 //   token_gate_up  h[e, t] = silu(W_gate[e] x_t) * (W_up[e] x_t); the first route_blocks workgroups route
@@ -217,16 +217,23 @@ struct TokenLayer {
 // 18.4 with 1, 20.0 with 2; two tokens of 2 experts 8.9, 9.2, 9.8; on the matrix-vector path 12 and more).
 template <int D, int CHAINS, int NM>
 __device__ __forceinline__ void token_tile(const float* pa, const float* const (&pb)[NM], int K, int first, int stride, f32x4 (&acc)[NM]) {
-    const int quad = (threadIdx.x & (kWave - 1)) >> 4, steps = (K + 15) / 16;
-    for (int st = first; st < steps; st += D * stride) {
-        f32x4 a[D], b[NM][D];
+    const int quad = (threadIdx.x & (kWave - 1)) >> 4;
+    int st = first, left = uniform_div((K + 15) / 16 - first + stride - 1, stride);  // the wave's steps
+    // N steps at once: as many as there are, so that no load is for nothing and none stands behind a branch around a step's products,
+    // where the compiler moves it (N memory latencies in a row).  Whole layer, us, with such branches / without: 32 tokens of
+    // 128 / 256, 4 experts, 9.9 / 9.3, 5 tokens of 200 / 488 11.1 / 9.5, 2 experts of 448 / 1200, 3 tokens, 13.2 / 11.4; 14 shapes 1.07
+    // (geometric mean, 1.00 the least).  D loads at all times: 1 of 8 experts of 64 / 160, 200 tokens, 12.9 / 13.9.
+    auto batch = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        f32x4 a[N], b[NM][N];
 #pragma unroll
-        for (int q = 0; q < D; ++q) {  // (past the row's end: its last 16 bytes)
+        for (int q = 0; q < N; ++q) {  // (past the row's end: its last 16 bytes)
             const int k = min((st + q * stride) * 16 + quad * 4, K - 4);
             a[q] = *reinterpret_cast<const f32x4*>(pa + k);
 #pragma unroll
             for (int m = 0; m < NM; ++m) b[m][q] = *reinterpret_cast<const f32x4*>(pb[m] + k);
         }
+        __builtin_amdgcn_sched_barrier(0);
         f32x4 part[NM][CHAINS][4];
 #pragma unroll
         for (int m = 0; m < NM; ++m)
@@ -235,8 +242,7 @@ __device__ __forceinline__ void token_tile(const float* pa, const float* const (
 #pragma unroll
                 for (int c = 0; c < 4; ++c) part[m][i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < D; ++q) {
-            if (q > 0 && st + q * stride >= steps) break;
+        for (int q = 0; q < N; ++q) {
             const bool in = (st + q * stride) * 16 + quad * 4 < K;  // beyond K: both operands cleared
 #pragma unroll
             for (int m = 0; m < NM; ++m)
@@ -252,12 +258,20 @@ __device__ __forceinline__ void token_tile(const float* pa, const float* const (
             if (CHAINS == 2) sum += (part[m][CHAINS - 1][0] + part[m][CHAINS - 1][1]) + (part[m][CHAINS - 1][2] + part[m][CHAINS - 1][3]);
             acc[m] += sum;
         }
-    }
+        st += N * stride;
+        left -= N;
+    };
+    while (left >= D) batch(std::integral_constant<int, D>{});
+    if (left <= 0) return;
+    static_for<D - 1>([&](auto n) {
+        if (left == n + 1) batch(std::integral_constant<int, n + 1>{});
+    });
 }
 
 template <int D, int CHAINS>
-__global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(const TokenLayer g) {
-    const int route_blocks = g.route_blocks;
+__global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(
+    ptr_arg ax, ptr_arg a_gate, ptr_arg a_up, int route_blocks, int T, int d, int F, int E, const TokenLayer g) {
+    const float* const x = from_arg<const float>(ax);
     if ((int)blockIdx.x < route_blocks) {
         route_tokens<float, 4, kRouteTok>(g.x, g.rw, g.rb, g.idx, g.gate, nullptr, g.T, g.d, g.E, g.k, blockIdx.x);
         return;
@@ -265,62 +279,69 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void token_gate_up_f32_kernel(c
     __shared__ float s_part[2][kRouteWaves][16][17];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int blocks = (g.F + 15) / 16, at = (int)blockIdx.x - route_blocks;
-    const int te = at / blocks, f0 = (at - te * blocks) * 16, e = te % g.E, t0 = te / g.E * 16;
+    const int blocks = (F + 15) / 16, at = (int)blockIdx.x - route_blocks;
+    const int te = uniform_div(at, blocks), f0 = (at - te * blocks) * 16, tb = uniform_div(te, E), e = te - tb * E, t0 = tb * 16;
     const int i = lane & 15, quad = lane >> 4;
-    const float* pa = g.x + (size_t)min(t0 + i, g.T - 1) * g.d;
-    const size_t row = ((size_t)e * g.F + min(f0 + i, g.F - 1)) * g.d;
-    const float* const pb[2] = {g.w_gate + row, g.w_up + row};
+    const float* pa = x + (size_t)min(t0 + i, T - 1) * d;
+    const size_t row = ((size_t)e * F + min(f0 + i, F - 1)) * d;
+    const float* const pb[2] = {from_arg<const float>(a_gate) + row, from_arg<const float>(a_up) + row};
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    token_tile<D, CHAINS, 2>(pa, pb, g.d, wave, kRouteWaves, acc);
+    token_tile<D, CHAINS, 2>(pa, pb, d, wave, kRouteWaves, acc);
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int r = 0; r < 4; ++r) s_part[m][wave][4 * quad + r][i] = acc[m][r];
     __syncthreads();
     const int t = threadIdx.x >> 4, c = threadIdx.x & 15;
-    if (t >= 16 || t0 + t >= g.T || f0 + c >= g.F) return;
+    if (t >= 16 || t0 + t >= T || f0 + c >= F) return;
     float z[2] = {0.f, 0.f};
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int w = 0; w < kRouteWaves; w += 4)
             z[m] += (s_part[m][w][t][c] + s_part[m][w + 1][t][c]) + (s_part[m][w + 2][t][c] + s_part[m][w + 3][t][c]);
-    g.h[((size_t)e * g.T + t0 + t) * g.F + f0 + c] = silu_f32(z[0]) * z[1];
+    g.h[((size_t)e * T + t0 + t) * F + f0 + c] = silu_f32(z[0]) * z[1];
 }
 
 template <int D, int CHAINS>
-__global__ __launch_bounds__(kTokenWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void token_down_f32_kernel(const TokenLayer g) {
+__global__ __launch_bounds__(kTokenWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void token_down_f32_kernel(
+    ptr_arg ah, ptr_arg aw, ptr_arg ai, ptr_arg ag, int T, int d, int F, int E, int slices, int k, const TokenLayer g) {
+    const float *const h = from_arg<const float>(ah), *const w_down = from_arg<const float>(aw), *const gates = from_arg<const float>(ag);
+    const int32_t* const idx = from_arg<const int32_t>(ai);
     __shared__ float s_part[kTokenWaves][16][17];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int n0 = blockIdx.x * 16, t0 = blockIdx.y * 16;
-    const int e = wave / g.slices, ks = wave - e * g.slices;
+    const int e = uniform_div(wave, slices), ks = wave - e * slices;
     const int i = lane & 15, quad = lane >> 4;
     const int t = t0 + (int)(threadIdx.x >> 4), n = n0 + (int)(threadIdx.x & 15);  // what the thread adds up
-    const bool mine = threadIdx.x < 256 && t < g.T && n < g.d;
-    float res = 0.f;
-    if (mine && g.residual) res = g.residual[(size_t)t * g.d + n];
+    const bool mine = threadIdx.x < 256 && t < T && n < d;
+    // The first two experts and gates, and the residual, are requested with the products' operands.  (No load is conditional:
+    // the compiler would wait for it where the branch ends.)
+    const int pair = min(t, T - 1) * k;
+    const int e0 = idx[pair], e1 = idx[pair + min(1, k - 1)];
+    const float gate0 = gates[pair], gate1 = gates[pair + min(1, k - 1)];
+    const float res = g.residual ? g.residual[(size_t)min(t, T - 1) * d + min(n, d - 1)] : 0.f;
     f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
-    if (e < g.E) {
-        const float* const pb[1] = {g.w_down + ((size_t)e * g.d + min(n0 + i, g.d - 1)) * g.F};
-        token_tile<D, CHAINS, 1>(g.h + ((size_t)e * g.T + min(t0 + i, g.T - 1)) * g.F, pb, g.F, ks, g.slices, acc);
+    if (e < E) {
+        const float* const pb[1] = {w_down + ((size_t)e * d + min(n0 + i, d - 1)) * F};
+        token_tile<D, CHAINS, 1>(h + ((size_t)e * T + min(t0 + i, T - 1)) * F, pb, F, ks, slices, acc);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) s_part[wave][4 * quad + r][i] = acc[0][r];
     __syncthreads();
     if (!mine) return;
     float total = 0.f;
-    for (int j = 0; j < g.k; ++j) {
-        const int ej = min(max(g.idx[t * g.k + j], 0), g.E - 1);
+    for (int j = 0; j < k; ++j) {
+        const int ej = min(max(j == 0 ? e0 : j == 1 ? e1 : idx[t * k + j], 0), E - 1);
         float sum[2] = {0.f, 0.f};
-        for (int sl = 0; sl < g.slices; sl += CHAINS)
+        for (int sl = 0; sl < slices; sl += CHAINS)
 #pragma unroll
             for (int i = 0; i < CHAINS; ++i)
-                if (i == 0 || sl + i < g.slices) sum[i] += s_part[ej * g.slices + sl + i][threadIdx.x >> 4][threadIdx.x & 15];
-        total = fmaf(g.gate[t * g.k + j], sum[0] + sum[1], total);
+                if (i == 0 || sl + i < slices) sum[i] += s_part[ej * slices + sl + i][threadIdx.x >> 4][threadIdx.x & 15];
+        total = fmaf(j == 0 ? gate0 : j == 1 ? gate1 : gates[t * k + j], sum[0] + sum[1], total);
     }
-    g.y[(size_t)t * g.d + n] = total + res;
+    g.y[(size_t)t * d + n] = total + res;
 }
 
 // Where this is the faster way (whole layer, us, stage by stage / this): the down product's workgroups, one per 16 columns,
@@ -347,14 +368,17 @@ int launch_token_layer_f32(const moe_shape& s, const moe_weights& w, const void*
     const int tb = (s.n_tokens + 15) / 16;
     const dim3 grid(route_blocks + tb * s.n_experts * ((s.d_ff + 15) / 16));
     const bool two = s.n_tokens == 2;
+    // (3 and not 4 steps at once of the longest rows: 94 registers would be two workgroups a CU for three, 48 tokens of 320 / 760 18.7 / 17.6)
     const auto first = s.d_model <= 16 * kRouteWaves       ? token_gate_up_f32_kernel<1, 1>
                        : s.d_model <= 2 * 16 * kRouteWaves ? (two ? token_gate_up_f32_kernel<2, 2> : token_gate_up_f32_kernel<2, 1>)
-                                                           : (two ? token_gate_up_f32_kernel<4, 2> : token_gate_up_f32_kernel<4, 1>);
-    hipLaunchKernelGGL(first, grid, dim3(kRouteWaves * kWave), 0, st, g);
+                                                           : (two ? token_gate_up_f32_kernel<3, 2> : token_gate_up_f32_kernel<3, 1>);
+    hipLaunchKernelGGL(first, grid, dim3(kRouteWaves * kWave), 0, st, as_arg(x), as_arg(w.w_gate), as_arg(w.w_up), route_blocks, s.n_tokens, s.d_model,
+                       s.d_ff, s.n_experts, g);
     int rc = launch_status();
     if (rc != MOE_OK) return rc;
     stage_mark(timer, "route_gate_up_swiglu");
-    hipLaunchKernelGGL((two ? token_down_f32_kernel<4, 2> : token_down_f32_kernel<4, 1>), dim3((s.d_model + 15) / 16, tb), dim3(kTokenWaves * kWave), 0, st, g);
+    hipLaunchKernelGGL((two ? token_down_f32_kernel<4, 2> : token_down_f32_kernel<4, 1>), dim3((s.d_model + 15) / 16, tb), dim3(kTokenWaves * kWave), 0, st,
+                       as_arg(h), as_arg(w.w_down), as_arg(idx), as_arg(gate), s.n_tokens, s.d_model, s.d_ff, s.n_experts, slices, s.top_k, g);
     rc = launch_status();
     stage_mark(timer, "gemm_down_combine");
     return rc;

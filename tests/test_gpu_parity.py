@@ -644,6 +644,15 @@ def test_forward_small_fp32_layer(dev, oracle, d, F, E, k, T):
     _forward_case(dev, oracle, cfg, T, residual=bool(T % 2))
 
 
+@pytest.mark.parametrize("d,F,E,k,T", [
+    # k-steps of a wave of the two products: none and 1, 1 and 2, 2 and 3, 3 and 4, 4 and 5, 7 and 8 -- whole turns of 3 or 4 and what is left
+    (56, 104, 4, 2, 3), (136, 264, 4, 1, 2), (136, 264, 4, 1, 19), (264, 488, 4, 2, 3), (392, 1000, 2, 2, 20), (520, 600, 2, 2, 2), (520, 600, 2, 1, 17),
+    (968, 904, 3, 2, 4),
+])
+def test_forward_small_fp32_layer_k_steps_of_a_wave(dev, oracle, d, F, E, k, T):
+    _forward_case(dev, oracle, _cfg(name="steps", d=d, F=F, E=E, k=k, dtype="f32", seed=1850 + d + T, std=0.05), T)
+
+
 @pytest.mark.parametrize("T,k,E", [(20, 2, 5), (3, 4, 16)])
 def test_forward_small_fp32_layer_with_infinite_experts(dev, T, k, E):
     # an expert that a token did not choose leaves no trace in it, whatever its weights
