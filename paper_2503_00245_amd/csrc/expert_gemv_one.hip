@@ -20,10 +20,11 @@ constexpr int kOneCus = 256;
 // Every workgroup routes the token for itself: 64 KB of router rows from its L2 per CU, a wave per
 // expert, and all of it in one round trip, in place of a launch that leaves 255 CUs idle.  With one
 // workgroup per CU that is 16 MB out of the L2s.  A wave then takes (pair, row) units gw, gw + W, ..., where gw counts the
-// workgroups first and their waves second: the units beyond the last whole turn of all W waves are then spread over all CUs and not
-// over the first of them (whole layer, waves first / workgroups first: 1024 x 2816, 5632 units on 4096 waves, 11.8 / 11.4 us, 2048 x 5632
-// 27.5 / 27.2, a shared base's 5632 rows on 3968 waves 25.3 / 23.9).  A wave
-// holds the token's row in registers and requests both rows of its next unit (8 KB at 2048 wide)
+// workgroups first and their waves second, so that no CU has more than another of the units beyond the last whole turn of all W waves
+// (whole layer, waves first / workgroups first: 1024 x 2816, 5632 units on 4096 waves, 11.8 / 11.4 us, 2048 x 5632
+// 27.5 / 27.2, a shared base's 5632 rows on 3968 waves 25.3 / 23.9); where there is one turn, waves first, so that a workgroup's results are
+// neighbours (400 x 1072 8.2 / 8.4, 720 x 1920, one expert, 8.4 / 8.6).  It holds
+// the token's row in registers and requests both rows of its next unit (8 KB at 2048 wide)
 // before it sums the current one.  2048 x 5632, 92 MB: 18.9 us with the routing, where a router launch and
 // a wave per row took 3.8 + 17.6; 1024 x 2816, 23 MB: 8.4 us for 3.1 + 8.9.  What is left beside the stream
 // (5.6 TB/s) is the prologue, 2-2.5 us.
@@ -138,7 +139,8 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
         for (int q = 0; q < VEC; ++q) xv[NC - 1][q] = S::from_f32(0.f);
     }
     Rows r0, r1;
-    Unit u0 = settle(Unit{0, wave * blocks + (int)blockIdx.x - first_block});
+    const int in_order = (int)blockIdx.x - first_block;
+    Unit u0 = settle(Unit{0, (long long)k * rows > stride ? wave * blocks + in_order : in_order * kOneWaves + wave});
     if (u0.j < k) load(r0, u0);
     if (blockIdx.x == 0 && wave == 0) {  // the gates, for the last stage: behind the first requests
         const RouterPick pick = router_weigh(lane, E, logit, slot, vmax);
@@ -329,7 +331,8 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     constexpr int VEC = S::VEC, CH = kWave * VEC;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int at = wave * (int)gridDim.x + (int)blockIdx.x, waves = (int)gridDim.x * kOneWaves / k;  // per pair
+    const int waves = (int)gridDim.x * kOneWaves / k;  // per pair; in the order of decode_first_kernel
+    const int at = rows > waves ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kOneWaves + wave;
     const int j = at % k;
     int row = at / k;
     if (row >= waves || row >= rows) return;
