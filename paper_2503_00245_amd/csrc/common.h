@@ -98,6 +98,35 @@ inline int allow_dynamic_lds(const void* kernel, size_t bytes, std::atomic<uint6
     return MOE_OK;
 }
 
+#if defined(__HIP_DEVICE_COMPILE__)
+#define MOE_READLANE(v, l) __builtin_amdgcn_readlane(v, l)
+#else
+#define MOE_READLANE(v, l) (v)
+#endif
+// a / b for a >= 0, b > 0: the estimate is off by a few hundred at most (2^31 times the rounding of the three
+// float steps), the second one, of the remainder, by one.  The compiler's integer division is forty
+// dependent instructions, and a workgroup makes half a dozen before its first load.
+__device__ __forceinline__ int quick_div(int a, int b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float inv = __builtin_amdgcn_rcpf((float)b);
+    int q = (int)((float)a * inv);
+    int r = (int)((unsigned)a - (unsigned)q * (unsigned)b);
+    const int more = (int)((float)r * inv);
+    q += more, r -= more * b;
+    q += (r >= b ? 1 : 0) - (r < 0 ? 1 : 0);
+    return q;
+#else
+    return a / b;
+#endif
+}
+__device__ __forceinline__ int uniform_div(int a, int b) {  // wave-uniform a, b
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_readfirstlane(quick_div(a, b));
+#else
+    return a / b;
+#endif
+}
+
 // A device pointer in a kernel's argument list, as a number: a launch takes longer on the host for every argument of pointer type
 // (a call of two launches that waits for the host: 8.9-9.3 us with six of them, 8.4-8.7 with the same as numbers).
 typedef unsigned long long ptr_arg;

@@ -659,11 +659,28 @@ static int decode_t(const moe_shape& s, const moe_weights& w, const void* x, int
     }
     if (r > 0 && first) {
         f.W0 = w.rg; f.W1 = w.ru; f.stride = (long long)r * d; f.rows = r; f.out0 = tg; f.out1 = tu;
-        if (base_scratch && base) {  // shared base, one token: four launches (expert_gemv_one.hip)
+        if (base_scratch && base) {  // shared base, one token: three or four launches (expert_gemv_one.hip)
             float *b0 = base_scratch, *b1 = b0 + F;
+            const bool parts = decode_base_parts_supported(s);
+            if (parts) {  // (no hidden vectors are kept: the rank vectors first, then the parts)
+                tg = h;
+                tu = tg + (size_t)k * r;
+                f.out0 = tg; f.out1 = tu;
+            }
             f.base_W0 = w.w_gate; f.base_W1 = w.w_up; f.base0 = b0; f.base1 = b1; f.base_rows = F;
             if ((rc = launch_decode_first(s.act_dtype, f, false, st)) != MOE_OK) return rc;
             stage_mark(timer, "gemv_base_and_rank_gate_up");
+            if (parts) {
+                float* const p = tu + (size_t)k * r;
+                const BaseHiddenStage bh{w.lg, w.lu, w.rd, tg, tu, b0, b1, p, F, r, s.n_experts, k, 0, idx, gate};
+                if ((rc = launch_decode_base_hidden(bh, st)) != MOE_OK) return rc;
+                stage_mark(timer, "gemv_gate_up_swiglu_and_rank_down");
+                const BaseLastStage bl{w.w_down, w.ld, b0, p, d, F, r, s.n_experts, k, 0, idx, gate,
+                                       (s.flags & MOE_FLAG_RESIDUAL) ? x : nullptr, y};
+                if ((rc = launch_decode_base_last(bl, st)) != MOE_OK) return rc;
+                stage_mark(timer, "gemv_down_combine");
+                return MOE_OK;
+            }
             LowRankStage lr{w.lg, w.lu, (long long)F * r, tg, tu, b0, b1, h, F, r, s.n_experts, k, 0, idx, gate, nullptr, nullptr};
             if ((rc = launch_decode_low_rank(lr, true, st)) != MOE_OK) return rc;
             stage_mark(timer, "gemv_gate_up_swiglu");

@@ -16,6 +16,7 @@ namespace moe {
 
 constexpr int kOneWaves = 16;  // per workgroup: 4 per SIMD, so a wave may hold 128 registers
 constexpr int kOneCus = 256;
+constexpr int kBaseSums = 256, kBasePairs = kBaseSums / 8;  // k r, k of decode_base_parts_supported
 
 // Every workgroup routes the token for itself: 64 KB of router rows from its L2 per CU, a wave per
 // expert, and all of it in one round trip, in place of a launch that leaves 255 CUs idle.  With one
@@ -235,8 +236,7 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
 // beside the rank products in the first launch and beside the rank-down product in the third, and two
 // launches of this kernel add the low-rank part.  64 / lanes rows per wave (a row of L is r long: 128
 // bytes at rank 64), two pairs' rows requested at once.
-// The four launches take 11.2 + 4.1 + 8.5 + 3.4 us at 2048 x 5632, rank 64 (layer 25.4 us); five launches
-// one after the other took 40.8.
+// (2048 x 5632, rank 128: layer 27.0 us.  Rank 64: 25.4 us, 40.8 in five launches one after the other, and 21.8 in three, as below.)
 //   HIDDEN: h_j = silu(b0 + L0_j t0_j) * (b1 + L1_j t1_j) and their mix b0 <- sum_j gate_j h_j; without a
 //           base (b0 NULL) the hidden vectors alone
 //   else:   y = b0 + sum_j gate_j L0_j t0_j (+ residual)
@@ -453,6 +453,186 @@ __global__ __launch_bounds__(kMidWaves* kWave) __attribute__((amdgpu_waves_per_e
     }
 }
 
+// ---- a shared base, rank-down products in parts ---------------------------------------------------------------
+// td_j = R_d,j h_j is a sum over the hidden rows, so a workgroup that forms 64 of them adds up its share of all k r
+// sums while it has them, from columns of R_d that it requested at its start, and the last stage, every workgroup of
+// which needs all of td, adds up the workgroups' shares (45 KB at 2048 x 5632, rank 64) under its stream of base
+// rows: a launch less, and no hidden vectors in memory.  2048 x 5632, rank 64: 9.6 + 4.6 + 8.5 us, layer 23.9 -> 21.8; 12 shapes of 400 to
+// 2048 wide, 2 and 4 experts, 1.07 times as fast (geometric mean, 1.03 the least).  Up to 64 sums per hidden row of a workgroup and
+// pair: longer ranks would take more hidden rows a workgroup, or the parts more room than the vectors whose place they take (128
+// rows a workgroup, rank 128: 512 x 1400 14.6 -> 19.0, 2048 x 5632 27.0 -> 28.0).
+//   decode_base_hidden_kernel  h_j and their mix as decode_low_rank_kernel, parts[block][j][:] = R_d,j[:, its rows] h_j
+//   decode_base_last_kernel    y = W_down mix + sum_j gate_j L_d,j td_j (+ residual)
+// NQ: 64 rows of the k R_d's each.
+constexpr int kBaseRows = 64;
+template <typename T, int NQ>
+__global__ __launch_bounds__(8 * kBaseRows) void decode_base_hidden_kernel(
+    ptr_arg ai, ptr_arg ard, ptr_arg aL0, ptr_arg aL1, int r, int rows, int k, int lanes, int E, const BaseHiddenStage a) {
+    typedef typename Store<T>::vec_t vec_t;
+    constexpr int VEC = Store<T>::VEC, FB = kBaseRows, THREADS = 8 * FB, CHUNKS = FB / VEC;  // 16-byte chunks of a row of R_d here
+    static_assert(THREADS / CHUNKS == 64 && CHUNKS == 8, "64 rows of R_d at a time, a row in eight lanes");
+    __shared__ f32x4 s_h[kBasePairs][FB / 4];
+    const int32_t* idx = from_arg<const int32_t>(ai);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int f0 = (int)blockIdx.x * FB, kr = k * r;
+    const int my_e = min(max(idx[min(lane, k - 1)], 0), E - 1);  // lane j: the j-th expert
+    // the columns of R_d: nothing of what they meet is needed to request them
+    const int chunk = threadIdx.x % CHUNKS;
+    const bool chunk_in = f0 + chunk * VEC < rows;  // (rows is a multiple of VEC)
+    vec_t rd[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int at = min((int)threadIdx.x / CHUNKS + q * 64, kr - 1), j = quick_div(at, r);
+        const int e = __shfl(my_e, j, kWave);
+        rd[q] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(
+            from_arg<const T>(ard) + ((size_t)e * r + (at - j * r)) * rows + min(f0 + chunk * VEC, rows - VEC)));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int group = lane / lanes, sub = lane & (lanes - 1), per_wave = kWave / lanes;
+    for (int local = wave * per_wave + group; local < FB; local += THREADS / lanes) {
+        const int row = min(f0 + local, rows - 1);
+        const bool mine = sub == 0 && f0 + local < rows;
+        const float b0 = a.b0[row], b1 = a.b1[row];
+        const int i = min(sub * VEC, r - VEC);
+        const bool in = sub * VEC < r;
+        float mix = 0.f;
+        for (int j0 = 0; j0 < k; j0 += 2) {
+            vec_t w[2][2];
+            f32x4 v[2][2][VEC / 4];
+            float g[2];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int j = min(j0 + p, k - 1), e = MOE_READLANE(my_e, j);
+                const size_t at = ((size_t)e * rows + row) * r + i;
+                w[p][0] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(from_arg<const T>(aL0) + at));
+                w[p][1] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(from_arg<const T>(aL1) + at));
+#pragma unroll
+                for (int q = 0; q < VEC / 4; ++q) {
+                    v[p][0][q] = *reinterpret_cast<const f32x4*>(a.t0 + (size_t)j * r + i + 4 * q);
+                    v[p][1][q] = *reinterpret_cast<const f32x4*>(a.t1 + (size_t)j * r + i + 4 * q);
+                }
+                g[p] = a.gate[j];
+            }
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                float acc[2] = {0.f, 0.f};
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int q = 0; q < VEC; ++q) acc[m] = fmaf(in ? Store<T>::get(w[p][m], q) : 0.f, in ? v[p][m][q / 4][q % 4] : 0.f, acc[m]);
+                for (int o = 1; o < lanes; o *= 2) {
+                    acc[0] += __shfl_xor(acc[0], o, kWave);
+                    acc[1] += __shfl_xor(acc[1], o, kWave);
+                }
+                if (j0 + p < k) {
+                    const float h = silu_f32(b0 + acc[0]) * (b1 + acc[1]);
+                    if (sub == 0) reinterpret_cast<float*>(&s_h[j0 + p][0])[local] = mine ? h : 0.f;
+                    mix = fmaf(g[p], h, mix);
+                }
+            }
+        }
+        if (mine) a.b0[row] = mix;  // read above by this group of lanes alone
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int at = min((int)threadIdx.x / CHUNKS + q * 64, kr - 1), j = quick_div(at, r);
+        const f32x4 lo = s_h[j][chunk * 2], hi = s_h[j][chunk * 2 + 1];
+        float s = 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s = fmaf(chunk_in ? Store<T>::get(rd[q], c) : 0.f, lo[c], s);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s = fmaf(chunk_in ? Store<T>::get(rd[q], 4 + c) : 0.f, hi[c], s);
+        s += dpp_f32<kDppSwap1>(s);
+        s += dpp_f32<kDppSwap2>(s);
+        s += dpp_f32<kDppHalfMirror>(s);
+        if (chunk == 0 && (int)threadIdx.x / CHUNKS + q * 64 < kr) a.parts[(size_t)blockIdx.x * kr + at] = s;
+    }
+}
+
+// A wave takes a slice of a base row, all its chunks requested before anything else but the parts.
+template <typename T, int NC>
+__global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_base_last_kernel(
+    ptr_arg aw, ptr_arg ap, ptr_arg av, ptr_arg ai, ptr_arg ag, int n, int slices, int r, int k, int blocks, int rows, const BaseLastStage a) {
+    typedef typename Store<T>::vec_t vec_t;
+    constexpr int VEC = Store<T>::VEC, CH = kWave * VEC, VL = VEC / 4, NB = 4;
+    __shared__ f32x4 s_sum[kOneWaves * kWave];
+    __shared__ float s_td[kBaseSums], s_part[kOneWaves];
+    const int32_t* idx = from_arg<const int32_t>(ai);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int local_row = uniform_div(wave, slices), slice = wave - local_row * slices, rows_here = uniform_div(kOneWaves, slices);
+    const int row = min((int)blockIdx.x * rows_here + local_row, rows - 1);
+    // the parts: thread (share, four sums) adds up blocks share, share + shares, ...
+    const int kr = k * r, quads = kr / 4, shares = min(uniform_div(kOneWaves * kWave, quads), (blocks + NB - 1) / NB);
+    const int share = quick_div(threadIdx.x, quads), quad = (int)threadIdx.x - share * quads;
+    const f32x4* const parts = from_arg<const f32x4>(ap) + quad;
+    const bool adds = share < shares;
+    f32x4 pv[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) pv[b] = parts[(size_t)min(share + b * shares, blocks - 1) * quads];
+    // the low-rank rows' place and gate (lane: 8 of the k r elements; thread: one of them)
+    const int l_at = min(lane * VEC, kr - VEC), l_j = quick_div(l_at, r), l_e = idx[l_j];
+    const int t_at = min((int)threadIdx.x, kr - 1);
+    const float gate = from_arg<const float>(ag)[quick_div(t_at, r)];
+    int off[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) off[c] = min((slice + c * slices) * CH + lane * VEC, n - VEC);
+    const bool tail_in = (slice + (NC - 1) * slices) * CH + lane * VEC < n;
+    const T* w = from_arg<const T>(aw) + (size_t)row * n;
+    vec_t wv[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) wv[c] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(w + off[c]));
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        if (adds && share + b * shares < blocks) sum += pv[b];
+    for (int b = share + NB * shares; adds && b < blocks; b += shares) sum += parts[(size_t)b * quads];
+    if (adds) s_sum[share * quads + quad] = sum;
+    const int e = min(max(l_e, 0), a.E - 1);
+    const vec_t l = __builtin_nontemporal_load(
+        reinterpret_cast<const vec_t*>(static_cast<const T*>(a.ld) + ((size_t)e * rows + row) * r + (l_at - l_j * r)));
+    f32x4 x[NC][VL];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = 0; i < VL; ++i) x[c][i] = *reinterpret_cast<const f32x4*>(from_arg<const float>(av) + off[c] + 4 * i);
+    const int my_row = (int)blockIdx.x * rows_here + (int)threadIdx.x;
+    const bool mine = (int)threadIdx.x < rows_here && my_row < rows;
+    // (not conditional, or the compiler waits for it, and all before it, where the branch ends; w_down: any valid place)
+    const T res = *(a.residual ? static_cast<const T*>(a.residual) + min(my_row, rows - 1) : from_arg<const T>(aw));
+    __syncthreads();
+    if ((int)threadIdx.x < kr) {
+        const float* const sums = reinterpret_cast<const float*>(s_sum) + threadIdx.x;
+        float td = 0.f;
+        for (int i = 0; i < shares; ++i) td += sums[i * kr];
+        s_td[threadIdx.x] = gate * td;
+    }
+    __syncthreads();
+    float s = 0.f;
+    if (slice == 0 && lane * VEC < kr) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) s = fmaf(Store<T>::get(l, i), s_td[lane * VEC + i], s);
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const bool in = c + 1 < NC || tail_in;
+            s = fmaf(in ? Store<T>::get(wv[c], i) : 0.f, in ? x[c][i / 4][i % 4] : 0.f, s);
+        }
+    s = wave_sum(s);
+    if (lane == 0) s_part[wave] = s;
+    __syncthreads();
+    if (mine) {
+        float total = a.residual ? Store<T>::to_f32(res) : 0.f;
+        for (int sl = 0; sl < slices; ++sl) total += s_part[threadIdx.x * slices + sl];
+        static_cast<T*>(a.y)[my_row] = Store<T>::from_f32(total);
+    }
+}
+
 template <typename T>
 static constexpr int chunks_of(int n) { return (n + kWave * Store<T>::VEC - 1) / (kWave * Store<T>::VEC); }
 
@@ -566,6 +746,48 @@ static int launch_mid_nc(const MidStage& a, int nc, hipStream_t st) {
 bool decode_base_supported(const moe_shape& s) {
     return decode_first_supported(s) && s.act_dtype == MOE_BF16 && token_base_supported(s) && s.d_model <= s.d_ff &&
            (long long)s.top_k * s.rank + s.d_model < (1 << 24) && mid_slices(s.top_k * s.rank + s.d_model, s.d_ff) != 0;
+}
+
+// Slices per base row: as many as there are CUs for, a chunk at least to each
+static int base_slices(int rows, int n) {
+    const int chunks = chunks_of<bf16_t>(n);
+    int s = 1;
+    while ((chunks + s - 1) / s > last_max_chunks<bf16_t, float>()) s *= 2;
+    while ((long long)rows * s * 2 <= kOneCus * kOneWaves && chunks >= 2 * s && s < kOneWaves) s *= 2;
+    return s <= kOneWaves ? s : 0;
+}
+
+bool decode_base_parts_supported(const moe_shape& s) {
+    return decode_base_supported(s) && s.rank <= kBaseRows && s.top_k * s.rank <= kBaseSums && base_slices(s.d_model, s.d_ff) != 0;
+}
+
+int launch_decode_base_hidden(BaseHiddenStage a, hipStream_t st) {
+    a.lanes = 1;
+    while (a.lanes * Store<bf16_t>::VEC < a.r) a.lanes *= 2;
+    const auto kern = a.k * a.r <= 64    ? decode_base_hidden_kernel<bf16_t, 1>
+                      : a.k * a.r <= 128 ? decode_base_hidden_kernel<bf16_t, 2>
+                                         : decode_base_hidden_kernel<bf16_t, 4>;
+    hipLaunchKernelGGL(kern, dim3((a.rows + kBaseRows - 1) / kBaseRows), dim3(8 * kBaseRows), 0, st, as_arg(a.idx), as_arg(a.rd), as_arg(a.L0), as_arg(a.L1),
+                       a.r, a.rows, a.k, a.lanes, a.E, a);
+    return launch_status();
+}
+
+template <int NC>
+static int launch_base_last_nc(const BaseLastStage& a, int nc, hipStream_t st) {
+    if constexpr (NC > last_max_chunks<bf16_t, float>()) {
+        return MOE_ERR_UNSUPPORTED;
+    } else {
+        if (nc != NC) return launch_base_last_nc<NC + 1>(a, nc, st);
+        const int rows_here = kOneWaves / a.slices;
+        hipLaunchKernelGGL((decode_base_last_kernel<bf16_t, NC>), dim3((a.rows + rows_here - 1) / rows_here), dim3(kOneWaves * kWave), 0, st, as_arg(a.w_down),
+                           as_arg(a.parts), as_arg(a.mix), as_arg(a.idx), as_arg(a.gate), a.n, a.slices, a.r, a.k, (a.n + kBaseRows - 1) / kBaseRows, a.rows, a);
+        return launch_status();
+    }
+}
+int launch_decode_base_last(BaseLastStage a, hipStream_t st) {
+    a.slices = base_slices(a.rows, a.n);
+    if (!a.slices) return MOE_ERR_UNSUPPORTED;
+    return launch_base_last_nc<1>(a, (chunks_of<bf16_t>(a.n) + a.slices - 1) / a.slices, st);
 }
 
 int launch_decode_mid(MidStage a, hipStream_t st) {

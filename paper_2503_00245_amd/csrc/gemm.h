@@ -103,11 +103,6 @@ __device__ __forceinline__ int group_end(const int32_t* __restrict__ offsets, in
 // lo, hi: in lane e of every wave, group e's bounds (group_bounds; 0, 0 in lanes from E on).  The sums run on
 // scalar registers through readlane.  (A loop of dependent scalar loads over the offsets cost
 // 2.6-3.3 us per tile here, a twentieth of a 256 x 256 tile's duration.)
-#if defined(__HIP_DEVICE_COMPILE__)
-#define MOE_READLANE(v, l) __builtin_amdgcn_readlane(v, l)
-#else
-#define MOE_READLANE(v, l) (v)
-#endif
 __device__ __forceinline__ void group_bounds(const int32_t* __restrict__ offsets, int E, int P, int& lo, int& hi) {
     const int lane = threadIdx.x & (kWave - 1);
     lo = hi = 0;
@@ -115,29 +110,6 @@ __device__ __forceinline__ void group_bounds(const int32_t* __restrict__ offsets
         lo = group_begin(offsets, lane);
         hi = group_end(offsets, lane, P);
     }
-}
-// a / b for a >= 0, b > 0: the estimate is off by a few hundred at most (2^31 times the rounding of the three
-// float steps), the second one, of the remainder, by one.  The compiler's integer division is forty
-// dependent instructions, and a workgroup makes half a dozen before its first load.
-__device__ __forceinline__ int quick_div(int a, int b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    const float inv = __builtin_amdgcn_rcpf((float)b);
-    int q = (int)((float)a * inv);
-    int r = (int)((unsigned)a - (unsigned)q * (unsigned)b);
-    const int more = (int)((float)r * inv);
-    q += more, r -= more * b;
-    q += (r >= b ? 1 : 0) - (r < 0 ? 1 : 0);
-    return q;
-#else
-    return a / b;
-#endif
-}
-__device__ __forceinline__ int uniform_div(int a, int b) {  // wave-uniform a, b
-#if defined(__HIP_DEVICE_COMPILE__)
-    return __builtin_amdgcn_readfirstlane(quick_div(a, b));
-#else
-    return a / b;
-#endif
 }
 // N_INNER (a power of two): tile order inside an expert in blocks of this many n-tiles, block outer, the
 // expert's m-tiles in the middle, the block's n-tiles inner (1: n-tile outer, m-tiles inner).

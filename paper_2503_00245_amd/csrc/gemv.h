@@ -66,6 +66,33 @@ struct MidStage {
     int slices;               // waves per row; set by the launcher
     const int32_t* idx;
 };
+// or, where the rank-down products' partial sums are few (decode_base_parts_supported),
+//   base hidden  h_j, their mix and, per workgroup's share of the rows, partial sums of R_d h_j      base last  y
+struct BaseHiddenStage {
+    const void *L0, *L1, *rd;  // [E, rows, r] twice, [E, r, rows]
+    const float *t0, *t1;      // [k][r]
+    float* b0;                 // [rows]; replaced by the mix
+    const float* b1;           // [rows]
+    float* parts;              // [blocks][k][r]
+    int rows, r, E, k;
+    int lanes;                 // lanes per row; set by the launcher
+    const int32_t* idx;
+    const float* gate;
+};
+struct BaseLastStage {
+    const void *w_down, *ld;   // [rows, n], [E, rows, r]
+    const float *mix, *parts;  // [n], [blocks][k][r]
+    int rows, n, r, E, k;
+    int slices;                // waves per row; set by the launcher
+    const int32_t* idx;
+    const float* gate;
+    const void* residual;
+    void* y;
+};
+bool decode_base_parts_supported(const moe_shape& s);
+// tg, tu [k][r] and the parts take the place of the hidden vectors: at most k (d_ff + 3 r) floats
+int launch_decode_base_hidden(BaseHiddenStage a, hipStream_t st);
+int launch_decode_base_last(BaseLastStage a, hipStream_t st);
 bool decode_base_supported(const moe_shape& s);
 inline size_t decode_base_bytes(const moe_shape& s) { return 2 * sizeof(float) * (size_t)s.d_ff; }
 int launch_decode_low_rank(LowRankStage a, bool hidden, hipStream_t st);

@@ -871,6 +871,21 @@ def test_forward_one_token(dev, oracle, d, F, E, k, r, base, dtype, residual):
     _forward_case(dev, oracle, cfg, 1, residual=residual)
 
 
+@pytest.mark.parametrize("d,F,E,k,r", [
+    # blocks of 64 hidden rows whole and not, one block, ranks of one vector and whole ones, the most pairs and the most sums; the first
+    # sizes past it: a longer rank, more sums
+    (64, 64, 4, 4, 8), (200, 1096, 8, 2, 64), (1032, 4104, 16, 4, 64), (328, 8200, 32, 32, 8), (136, 200, 8, 8, 32), (1000, 2680, 8, 2, 24),
+    (200, 456, 4, 4, 72), (264, 520, 8, 5, 56),
+])
+def test_forward_one_token_shared_base_rank_down_in_parts(dev, oracle, d, F, E, k, r):
+    cfg = _cfg(d=d, F=F, E=E, k=k, dtype="bf16", seed=540 + d + k, r=r, base=True, std=0.05)
+    w_np = wl.make_layer_weights(cfg)
+    w_t = weights_to_device(w_np, dev)
+    for residual in (False, True):
+        _forward_case(dev, oracle, cfg, 1, w_np=w_np, w_t=w_t, residual=residual)
+    _forward_guarded(w_t, to_device(wl.make_inputs(cfg, 1), dev), k, pkg.MOE_BF16)
+
+
 @pytest.mark.parametrize("E", [5, 40])
 def test_forward_one_token_with_nan_logits(dev, E):
     # no order among NaN logits: whichever lanes a round names, the weights read are an expert's
