@@ -79,6 +79,19 @@ __device__ __forceinline__ float silu_f32(float z) {
 #endif
 }
 
+// Sum of v over this lane and those below it
+__device__ __forceinline__ int wave_scan(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // within a row of 16 lanes: from 1, 2, 4 and 8 lanes below
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // the last lane of rows 0 and 2 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2 and 3
+#endif
+    return v;
+}
+
 // ---- host side ---------------------------------------------------------------------------
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 

@@ -25,8 +25,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N* KS * 64) void gemm_f32_kernel(con
     int e, row0, row_end, nt;
     constexpr int NTHR = WAVES_M * WAVES_N * KS * 64;
     static_assert(NTHR == kF32DispatchThreads, "dispatch by whole workgroups");
-    __shared__ int s_count[kKeyChunks * NTHR / kWave][kMaxExperts];
-    __shared__ int s_pair[BM];
+    __shared__ int s_count[NTHR / kWave][kMaxExperts];
+    __shared__ int s_pair[BM + kWave];
     int lo, hi;
     PairKeys<NTHR> keys;
     if (g.keys) {
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N* KS * 64) void gemm_f32_kernel(con
     if (!find_tile(lo, hi, g.E, BM, [&](int) { return g.n_tiles; }, e, row0, row_end, nt)) return;
     if (g.keys) {
         const int rows = min(row_end - row0, BM);
-        keys.rows(e, row0 - MOE_READLANE(lo, e), rows, s_count, s_pair);
+        keys.rows(e, row0 - MOE_READLANE(lo, e), rows, BM, s_count, s_pair);
         if (nt == 0) {  // one column tile of each row tile writes the sorted order
             for (int r = threadIdx.x; r < rows; r += NTHR) {
                 const int p = s_pair[r];

@@ -77,6 +77,16 @@ __device__ __forceinline__ void phase_end() {
 #endif
 }
 
+// The arguments beyond those that arrive in registers, all of them at this place: their loads, from memory that no cache holds yet, are
+// then one latency, under that of the keys or bounds, where the compiler left one before every stage of a tile's way to its first fill.
+__device__ __forceinline__ void arguments_here(const GemmArgs& g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const GemmSeg& s = g.seg[0];
+    asm volatile("" ::"s"(s.A0), "s"(s.A1), "s"(s.B0), "s"(s.B1), "s"(s.strideB), "s"(s.K), "s"(s.gather), "s"(g.C), "s"(g.C1), "s"(g.N), "s"(g.offsets),
+                 "s"(g.row_map), "s"(g.row_div), "s"(g.hidden_a), "s"(g.k_parts), "s"(g.parts), "s"(g.fit_width), "s"(g.inv_perm));
+#endif
+}
+
 // BN: rows of the B tile.  SWIGLU: its first half are gate rows, the second half the matching up rows.
 // DUAL (SwiGLU with two activation operands, the rank products of a weight-decomposed expert): the tile
 // is BN gate rows for the first K / 64 steps, over A0, and the matching BN up rows for as many more, over A1,
@@ -126,12 +136,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     };
     // (in the last slot of B, which is first filled after the first phase)
     int (*const s_count)[kMaxExperts] = reinterpret_cast<int (*)[kMaxExperts]>(smem + SA * A_BYTES + (SB - 1) * B_BYTES);
-    int* const s_pair = &s_count[kKeyChunks * kThreads / kWave][0];
-    static_assert((kKeyChunks * kThreads / kWave * kMaxExperts + BM) * 4 <= B_BYTES, "dispatch scratch");
+    int* const s_pair = &s_count[kThreads / kWave][0];
+    static_assert((kThreads / kWave * kMaxExperts + BM + kWave) * 4 <= B_BYTES, "dispatch scratch");
     int lo, hi;
     PairKeys<kThreads> keys;
     if (g_keys) {
         keys.load(g_keys, g_P);
+        arguments_here(g);
         keys.bounds(g_E, s_count, lo, hi);
         const int lane_ = threadIdx.x & 63;
         if (blockIdx.x == 0 && threadIdx.x < 64) {
@@ -140,6 +151,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
     } else {
         group_bounds(g_offsets, g_E, g_P, lo, hi);
+        arguments_here(g);
     }
     // SwiGLU products of 256-row tiles: blocks of four n-tiles with the expert's m-tiles inside, so that the 32
     // tiles in flight on an XCD share eight A and four B tiles in its L2 instead of all m-tiles of one
@@ -234,9 +246,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 for (int p = 0; p < PB; ++p) fill(std::integral_constant<int, 0>{}, q, p);
             }
     }
-    if (g.keys) {
+    if (g_keys) {
         const int rows = min(rows_here, BM);
-        keys.rows(e, row0 - MOE_READLANE(lo, e), rows, s_count, s_pair);
+        keys.rows(e, row0 - MOE_READLANE(lo, e), rows, BM, s_count, s_pair);
         if (nt == 0 && copy == 0) {  // one column tile of each row tile writes the sorted order
             for (int r = threadIdx.x; r < rows; r += kThreads) {
                 const int p = s_pair[r];
@@ -251,7 +263,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int p = 0; p < PA; ++p) arow[p] = min(row0 + f_row + 32 * p, row_end - 1);
         if (sg.gather) {
 #pragma unroll
-            for (int p = 0; p < PA; ++p) arow[p] = g.keys ? s_pair[arow[p] - row0] : g.row_map[arow[p]];
+            for (int p = 0; p < PA; ++p) arow[p] = g_keys ? s_pair[arow[p] - row0] : g.row_map[arow[p]];
 #pragma unroll
             for (int p = 0; p < PA; ++p) arow[p] = quick_div(min(max(arow[p], 0), g.P - 1), g.row_div);
         }

@@ -118,11 +118,8 @@ __device__ __forceinline__ bool find_tile(int lo, int hi, int E, int BM, NTiles 
                                           int& row0, int& row_end, int& nt_out) {
     const int lane = threadIdx.x & (kWave - 1);
     const int cnt = (hi - lo + BM - 1) / BM;  // m-tiles of group `lane` (0 beyond E)
-    int total = 0, before = 0;                // m-tiles of all groups, of those below `lane`
-    for (int e = 0; e < E; ++e) {
-        before = lane == e ? total : before;
-        total += MOE_READLANE(cnt, e);
-    }
+    const int upto = wave_scan(cnt), before = upto - cnt;  // m-tiles of the groups up to and below `lane`
+    int total = MOE_READLANE(upto, kWave - 1);
     const int n_tiles = n_tiles_of(total);
     total *= n_tiles;
     const int per_xcd = (total + 7) / 8;
@@ -180,8 +177,8 @@ __device__ __forceinline__ bool find_tile(int lo, int hi, int E, int BM, NTiles 
 // more of the product (measured, layer of 300 tokens, 432 x 1152: 31.3 -> 27.4 us; 2048 tokens, 432 x 1152:
 // 47.3 -> 41.6; 777 tokens, 1440 x 3840: 98.3 -> 93.5; 4096 tokens, 720 x 1920: 123.5 -> 116.0).  Every tile
 // counts again: at 2048 tokens, 2048 x 5632, three rounds of tiles, it is even (310 us), so the line lies at the
-// keys that the threads of one workgroup hold.  Thread t holds keys 4 t .. 4 t + 3 of every chunk
-// of 4 NTHR keys, so that order by thread is order by pair.
+// keys that the threads of one workgroup hold.  A thread holds neighbouring keys, as many as another (a multiple of 4), so that order by
+// thread is order by pair.
 constexpr int kKeyChunks = 4;
 __device__ __forceinline__ int lanes_below(unsigned long long mask) {  // set bits of mask below this lane
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -193,13 +190,15 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {  // set bi
 template <int NTHR>
 struct PairKeys {
     int k[kKeyChunks][4];
-    int chunks;  // in use (wave-uniform)
+    int chunks;  // of 4 keys, of every thread (wave-uniform)
+
+    __device__ __forceinline__ int pair(int c) const { return ((int)threadIdx.x * chunks + c) * 4; }  // of k[c][0]
 
     __device__ __forceinline__ void load(const int32_t* __restrict__ keys, int P) {
         chunks = (P + 4 * NTHR - 1) / (4 * NTHR);
 #pragma unroll
         for (int c = 0; c < kKeyChunks; ++c) {
-            const int p = (c * NTHR + (int)threadIdx.x) * 4;
+            const int p = pair(c);
             int4 v = make_int4(-1, -1, -1, -1);
             if (c < chunks) {
                 if (p + 3 < P) {
@@ -214,60 +213,101 @@ struct PairKeys {
         }
     }
 
-    // group bounds in lane e of every wave (as group_bounds); s_count [chunks * waves][kMaxExperts] receives
-    // every chunk's and wave's count of every expert
-    __device__ __forceinline__ void bounds(int E, int (*s_count)[kMaxExperts], int& lo, int& hi) const {
-        constexpr int NW = NTHR / kWave;
-        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    // Lane e: keys of the wave that are expert e, e < 8.  Counted per lane in the eight bytes of a word (16 keys at most), then
+    // summed over the wave in fields of 16 bits, four registers of two.
+    __device__ __forceinline__ int count_eight() const {
+        unsigned lo = 0, hi = 0;
 #pragma unroll
         for (int c = 0; c < kKeyChunks; ++c) {
             if (c >= chunks) break;
-            int* const count = s_count[c * NW + wave];  // (a wave's LDS operations complete in order)
-            count[lane] = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if ((unsigned)k[c][j] < (unsigned)E) atomicAdd(&count[k[c][j]], 1);
+            for (int j = 0; j < 4; ++j) {
+                const unsigned f = (unsigned)k[c][j], one = 1u << (f * 8 & 31);
+                lo += f < 4 ? one : 0;
+                hi += f - 4 < 4 ? one : 0;
+            }
+        }
+        const int lane = threadIdx.x & (kWave - 1);
+        auto sum = [&](unsigned v) {  // of a 16-bit field over the wave
+            int s = (int)v;
+            s += dpp_i32<kDppSwap1>(s);
+            s += dpp_i32<kDppSwap2>(s);
+            s += dpp_i32<kDppHalfMirror>(s);
+            s += dpp_i32<kDppMirror>(s);
+            return (MOE_READLANE(s, 0) + MOE_READLANE(s, 16)) + (MOE_READLANE(s, 32) + MOE_READLANE(s, 48));
+        };
+        const int lo02 = sum(lo & 0x00ff00ffu), lo13 = sum(lo >> 8 & 0x00ff00ffu), hi02 = sum(hi & 0x00ff00ffu), hi13 = sum(hi >> 8 & 0x00ff00ffu);
+        const int both = lane & 1 ? (lane & 4 ? hi13 : lo13) : (lane & 4 ? hi02 : lo02);
+        return lane & 2 ? (int)((unsigned)both >> 16) : both & 0xffff;
+    }
+
+    // group bounds in lane e of every wave (as group_bounds); s_count [waves][kMaxExperts] receives every wave's count of every
+    // expert.  From 2049 pairs on, up to 8 experts, the lanes' counts are added up in registers: LDS atomics meet on few addresses, and the
+    // more where experts are chosen unevenly (4096 skewed pairs of 8 experts 2500 clocks, 1650 now; 16 experts even 2048 tokens of 1024 / 2816 188.9 / 191.6).
+    // Below, atomics without a branch: 2400 clocks of 1024 pairs, 1040 now.  With the sums over lanes in find_tile and here, and all arguments
+    // in one place (expert_gemm_pp.hip), a tile's way to its first fill went from 5650 to 4050 clocks there, from 7260 to 3880 at 4096 pairs; whole layer, us,
+    // before / now: 300 tokens of 432 / 1152 26.1 / 24.6, 512 tokens of 1024 / 2816 53.1 / 51.6, 64 tokens, 4 of 16 experts, 66.2 / 61.5, 200
+    // tokens of 2048 / 5632 121.4 / 119.3, 777 tokens of 1440 / 3840 92.4 / 90.4, 2048 skewed tokens of 432 / 1152 46.4 / 40.6, 4096 tokens of
+    // 1024 / 2816 178.3 / 174.0, 2048 tokens of 2048 / 5632 308.9 / 306.7 (the power limit).
+    __device__ __forceinline__ void bounds(int E, int (*s_count)[kMaxExperts], int& lo, int& hi) const {
+        constexpr int NW = NTHR / kWave;
+        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+        int* const count = s_count[wave];
+        if (E <= 8 && chunks > 1) {
+            count[lane] = count_eight();  // (lanes from E on: not read)
+        } else {
+            count[lane] = 0;  // (a wave's LDS operations complete in order)
+#pragma unroll
+            for (int c = 0; c < kKeyChunks; ++c) {
+                if (c >= chunks) break;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {  // (no key: nothing, to an address of the lane's own)
+                    const bool is = (unsigned)k[c][j] < (unsigned)E;
+                    atomicAdd(&count[is ? k[c][j] : lane], is ? 1 : 0);
+                }
+            }
         }
         __syncthreads();
         int total = 0;
 #pragma unroll
-        for (int c = 0; c < kKeyChunks; ++c) {
-            if (c >= chunks) break;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) total += s_count[c * NW + w][lane];
-        }
-        int at = 0;  // (on scalar registers: a shuffle per step of a scan is an LDS round trip)
-        lo = hi = 0;
-        for (int e = 0; e < E; ++e) {
-            const int n = MOE_READLANE(total, e);
-            if (lane == e) lo = at, hi = at + n;
-            at += n;
-        }
+        for (int w = 0; w < NW; ++w) total += s_count[w][lane];
+        total = lane < E ? total : 0;
+        hi = wave_scan(total);
+        lo = hi - total;
     }
 
-    // pairs of rows [first, first + n) of expert e's group (counted from its start) to s_pair[0 .. n)
-    __device__ __forceinline__ void rows(int e, int first, int n, const int (*s_count)[kMaxExperts], int* s_pair) const {
+    // pairs of rows [first, first + n) of expert e's group (counted from its start) to s_pair[0 .. n), n <= room; what is not asked for goes to
+    // s_pair[room .. room + 64), an address per lane, with no branch around a write.  (Behind a wave's fills straight into LDS its LDS operations
+    // wait: 3000 clocks of a tile here, 1200 with the fills behind; the fills came first all the same, as the weights are what a tile waits for: whole layer
+    // 0.7 % faster in the geometric mean of 15.)
+    __device__ __forceinline__ void rows(int e, int first, int n, int room, const int (*s_count)[kMaxExperts], int* s_pair) const {
         constexpr int NW = NTHR / kWave;
         const int wave = threadIdx.x / kWave;
-        int before = 0;  // rows of e in earlier chunks
+        int at = -first, mine = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int before = s_count[w][e];
+            at += w < wave ? before : 0;
+        }
 #pragma unroll
         for (int c = 0; c < kKeyChunks; ++c) {
             if (c >= chunks) break;
-            int at = before - first;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) at += lanes_below(__ballot(k[c][j] == e));
+            for (int j = 0; j < 4; ++j) mine += k[c][j] == e ? 1 : 0;
+        }
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const int cw = s_count[c * NW + w][e];
-                if (w < wave) at += cw;
-                before += cw;
-            }
+        for (int b = 0; b < 5; ++b) {  // 4 chunks at most
+            if (b == 3 && chunks == 1) break;
+            at += lanes_below(__ballot(mine >> b & 1)) << b;
+        }
+#pragma unroll
+        for (int c = 0; c < kKeyChunks; ++c) {
+            if (c >= chunks) break;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (k[c][j] == e) {
-                    if ((unsigned)at < (unsigned)n) s_pair[at] = (c * NTHR + (int)threadIdx.x) * 4 + j;
-                    ++at;
-                }
+                const bool is = k[c][j] == e;
+                s_pair[is && (unsigned)at < (unsigned)n ? at : room + ((int)threadIdx.x & (kWave - 1))] = pair(c) + j;
+                at += is ? 1 : 0;
             }
         }
         __syncthreads();

@@ -920,6 +920,31 @@ def test_forward_sorts_the_pairs_in_its_first_product(dev, E, k, T, dtype):
     assert rel_err(to_f64(y), to_f64(y2)) < (1e-6 if dtype == "f32" else 1e-3)
 
 
+@pytest.mark.parametrize("E,k,T", [
+    # both ways of counting and both sides of their lines (2048 pairs, 8 experts), pairs that are no multiple of 4, every thread full
+    (8, 1, 2047), (8, 1, 2049), (8, 2, 1025), (9, 1, 2051), (9, 3, 683), (5, 1, 6143), (2, 1, 8191), (8, 4, 2048), (64, 2, 4093),
+])
+@pytest.mark.parametrize("skew", [False, True])
+def test_forward_counts_the_pairs_of_an_expert(dev, E, k, T, skew):
+    # expert e is 2^(e % 8) times one and the same expert: a pair in a wrong group, or a row of another token, is off by its whole size
+    cfg = _cfg(d=64, F=64, E=E, k=k, dtype="bf16", seed=730 + T, std=0.05)
+    w_t = weights_to_device(wl.make_layer_weights(cfg), dev)
+    if skew:
+        w_t["router_b"] = torch.linspace(2.0, 0.0, E, dtype=torch.float32, device=dev)
+    for name in ("w_gate", "w_up", "w_down"):
+        w_t[name] = w_t[name][:1].expand_as(w_t[name]).contiguous()
+    w_t["w_down"] *= torch.exp2(torch.arange(E, device=dev) % 8).to(torch.bfloat16).view(E, 1, 1)  # (exact: powers of two)
+    x_t = to_device(wl.make_inputs(cfg, T), dev)
+    y, idx, gate = _forward_gpu(dev, w_t, x_t, k, pkg.MOE_BF16)
+    x, w = x_t.double(), {n: w_t[n][0].double() for n in ("w_gate", "w_up", "w_down")}
+    z = x @ w["w_gate"].T
+    one = ((z * torch.sigmoid(z)) * (x @ w["w_up"].T)) @ w["w_down"].T
+    times = torch.from_numpy((np.exp2(idx % 8) * gate).sum(1)).to(dev)
+    ref = one * times[:, None]
+    # (h, the pairs' outputs and y are rounded to bf16: the tolerance of the parity tests)
+    assert row_rel_err(to_f64(y), ref.cpu().numpy()) < TOL["bf16"]
+
+
 def test_forward_is_deterministic_and_matches_the_staged_calls(dev, oracle):
     cfg = wl.shrink(wl.CONFIGS["wearables"], d_model=512, d_ff=1024)
     w_np = wl.make_layer_weights(cfg)
