@@ -482,12 +482,12 @@ static int launch_bf16_deep(GemmArgs& g, hipStream_t st) {
     constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
     constexpr int NTHR = (BM / WM) * (BN / WN) * 64 * KG;
     static_assert(NTHR <= 1024, "workgroup size");
-    g.m_tiles_max = g.P / BM + g.E;
+    g.m_tiles_max = m_tiles_bound(g.P, g.E, BM);
     g.n_tiles = (g.N + BN_OUT - 1) / BN_OUT * ((!SWIGLU && g.C1) ? 2 : 1);
     const int total = g.m_tiles_max * g.n_tiles;
     constexpr size_t lds = lds_bytes<BM, BN, BK, DUAL_A, KG>();
     static_assert(lds <= 160 * 1024, "LDS stages exceed the CU's 160 KB");
-    const int grid = ((total + 7) / 8 + split_slots<BM, BN, BK, WM, WN, DUAL_A, KG>() / 2) * 8;
+    const int grid = find_tile_grid(total, split_slots<BM, BN, BK, WM, WN, DUAL_A, KG>());
     bool tail = false;
     for (int i = 0; i < g.nseg; ++i) {
         const int K = g.seg[i].K;  // rows are read in 16-byte chunks; a K tail only without k-groups

@@ -169,9 +169,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N* KS * 64) void gemm_f32_kernel(con
 template <int MI, int NI, int WAVES_M, int WAVES_N, int KS>
 static int launch_f32(GemmArgs& g, bool swiglu, hipStream_t st) {
     constexpr int BM = 16 * MI * WAVES_M, BN = 16 * NI * WAVES_N;
-    g.m_tiles_max = g.P / BM + g.E;
+    g.m_tiles_max = m_tiles_bound(g.P, g.E, BM);
     g.n_tiles = (g.N + BN - 1) / BN;
-    const dim3 grid((g.m_tiles_max * g.n_tiles + 7) / 8 * 8), block(WAVES_M * WAVES_N * KS * 64);
+    const dim3 grid(find_tile_grid(g.m_tiles_max * g.n_tiles, 0)), block(WAVES_M * WAVES_N * KS * 64);
     if (swiglu)
         hipLaunchKernelGGL((gemm_f32_kernel<MI, NI, WAVES_M, WAVES_N, KS, true>), grid, block, 0, st, g);
     else

@@ -473,13 +473,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 template <int BM, int BN, int WAVES_M, int SA, int SB, bool SWIGLU, bool DUAL, bool F32, bool NT_B, bool LINES>
 int launch_pp(GemmArgs& g, hipStream_t st) {
     constexpr int BN_OUT = SWIGLU && !DUAL ? BN / 2 : BN;
-    g.m_tiles_max = g.P / BM + g.E;
+    g.m_tiles_max = m_tiles_bound(g.P, g.E, BM);
     g.n_tiles = (g.N + BN_OUT - 1) / BN_OUT * ((!SWIGLU && g.C1) ? 2 : 1) * (g.k_parts > 1 ? g.k_parts : 1);
     int tiles = g.m_tiles_max * g.n_tiles;
     if (tiles < 256 * g.fit_width) tiles = (tiles + 255) / 256 * 256;
     constexpr size_t lds = (SA * BM + SB * BN) * BK * 2;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
-    const int grid = ((tiles + 7) / 8 + kSplitSlots / 2) * 8;
+    const int grid = find_tile_grid(tiles, kSplitSlots);
     static std::atomic<uint64_t> lds_allowed;
     const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, NT_B, LINES>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;

@@ -170,6 +170,24 @@ __device__ __forceinline__ bool find_tile(int lo, int hi, int E, int BM, NTiles 
     return true;
 }
 
+// Tiles of BM rows that P rows in E groups can need at most: a group of r rows takes 1 + (r - 1) / BM, an empty one none
+inline int m_tiles_bound(int P, int E, int BM) {
+    const int groups = P < E ? P : E;
+    return groups + (P - groups) / BM;
+}
+// Workgroups for up to `tiles` tiles on find_tile<., split_slots>.  A last round cut into halves fills a round at most, so a launch
+// needs no more than whole rounds, and none beside the tiles where they are one.  A surplus workgroup is not free: it finds the
+// bounds before it leaves, and with all of a CU's LDS to its name it starts only when a tile has ended: 256 of them are 1.1 us at a
+// launch's end.  Whole layer, us, with P / BM + E row tiles and half a round beside them / by this rule: 64 tokens of 1024 / 2816
+// 36.7 / 35.5, 300 tokens 47.0 / 46.1, 512 tokens 51.4 / 48.8, 777 tokens of 1440 / 3840 90.3 / 88.9, 2048 tokens of
+// 2048 / 5632 302.1 / 298.5.
+inline int find_tile_grid(int tiles, int split_slots) {
+    const int per_xcd = (tiles + 7) / 8;
+    if (split_slots == 0 || per_xcd <= split_slots) return per_xcd * 8;
+    const int rounds = (per_xcd + split_slots - 1) / split_slots * split_slots, halves = per_xcd + split_slots / 2;
+    return (rounds < halves ? rounds : halves) * 8;
+}
+
 // ---- dispatch inside a product -----------------------------------------------------------------------------
 // The pairs of a layer are sorted by expert (stable) so that each expert's rows are one group.  For up to a
 // few thousand pairs a workgroup finds what it needs of that from the P keys itself -- the groups' bounds

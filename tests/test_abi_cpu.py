@@ -169,3 +169,11 @@ def test_a_product_planned_in_parts_has_a_kernel_that_writes_them(tmp_path):
     subprocess.run([hip_build._hipcc(), main, *objs, "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+def test_a_launch_has_a_workgroup_for_every_tile(tmp_path):
+    exe = str(tmp_path / "check")
+    subprocess.run([hip_build._hipcc(), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    hip_build.CSRC, os.path.join(ROOT, "tests", "tile_grid_check.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout

@@ -288,6 +288,16 @@ def test_expert_ffn_dense_bf16(dev, oracle, d, F, offsets):
     _ffn_case(dev, oracle, cfg, np.array(offsets, np.int32), TOL["bf16"])
 
 
+# as many tiles as the rows can need: one row past whole tiles of 64, 128 and 256 rows in every group
+@pytest.mark.parametrize("d,F,dtype,loads", [
+    (256, 384, "bf16", [257, 1, 513, 1, 1, 257, 1, 1]), (256, 2048, "bf16", [129] * 5 + [1] * 3), (128, 704, "bf16", [65] * 16),
+    (256, 5760, "bf16", [1537, 1]), (64, 128, "f32", [17, 33, 1, 49]),
+])
+def test_expert_ffn_at_the_bound_of_tiles(dev, oracle, d, F, dtype, loads):
+    cfg = _cfg(d=d, F=F, E=len(loads), dtype=dtype, seed=431 + d, std=0.05)
+    _ffn_case(dev, oracle, cfg, np.cumsum([0] + loads).astype(np.int32), TOL[dtype])
+
+
 @pytest.mark.parametrize("d,F,r,offsets", [
     # gate/up products on 256-row tiles (two experts, 45 column tiles): one, two, three k-steps, tails of 8, 56
     # and 8 columns, groups that end 1 and 255 rows into a tile
