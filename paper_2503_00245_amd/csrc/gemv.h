@@ -21,7 +21,8 @@ struct FirstStage {
     const void *base_W0, *base_W1;  // [base_rows, d]
     float *base0, *base1;
     int base_rows;
-    int route_blocks;     // set by the launcher
+    int route_blocks;     // set by the launcher, as are these (first_stage_turns)
+    int turns, base_turns;
 };
 bool decode_first_supported(const moe_shape& s);
 int launch_decode_first(int act_dtype, const FirstStage& a, bool swiglu, hipStream_t st);

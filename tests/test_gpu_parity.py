@@ -881,6 +881,17 @@ def test_forward_one_token(dev, oracle, d, F, E, k, r, base, dtype, residual):
     _forward_case(dev, oracle, cfg, 1, residual=residual)
 
 
+@pytest.mark.parametrize("d,F,E,k,r,base,dtype", [
+    # more (pair, row) units than waves (4096): a rest of 8, of three quarters and 8 more, none; rows of no whole lines, then of whole lines
+    (72, 8200, 4, 1, 0, False, "bf16"), (72, 5640, 4, 2, 0, False, "bf16"), (72, 5632, 4, 2, 0, False, "bf16"), (72, 4096, 4, 2, 0, False, "bf16"),
+    (64, 4104, 4, 1, 0, False, "bf16"), (64, 5640, 4, 2, 0, False, "bf16"), (64, 5632, 4, 2, 0, False, "bf16"), (40, 4104, 4, 3, 0, False, "f32"),
+    (72, 4104, 4, 2, 16, True, "bf16"), (128, 8000, 4, 2, 16, True, "bf16"),  # a shared base's rows, on the other workgroups
+])
+def test_forward_one_token_rest_of_the_rows(dev, oracle, d, F, E, k, r, base, dtype):
+    cfg = _cfg(name="rest", d=d, F=F, E=E, k=k, r=r, base=base, dtype=dtype, seed=977 + d, std=0.05)
+    _forward_case(dev, oracle, cfg, 1)
+
+
 @pytest.mark.parametrize("d,F,E,k,r", [
     # blocks of 64 hidden rows whole and not, one block, ranks of one vector and whole ones, the most pairs and the most sums; the first
     # sizes past it: a longer rank, more sums
