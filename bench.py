@@ -85,7 +85,7 @@ TRAFFIC_SOURCE = {
     "phone_decode": ("phone_decode_kernels_and_hbm_traffic.txt", r"decode_first_kernel<bf16, 4, true>"),
 }
 MEASURED_KIB = {  # workload: (FETCH_SIZE mean, WRITE_SIZE mean), KiB per dispatch as the tool reports them
-    "phone_prefill": (325998.9, 45143.6),
+    "phone_prefill": (334906.8, 45143.6),
     "phone_decode": (45391.1, 24.1),
 }
 MEASURED_TRAFFIC_BYTES = {w: int((f * FETCH_SCALE + wr * WRITE_SCALE) * 1024) for w, (f, wr) in MEASURED_KIB.items()}
