@@ -10,9 +10,13 @@
 
 namespace moe {
 
+enum { ADD_NONE, ADD_ONE, ADD_PARTS };  // no addend, one of type T, several fp32 parts of one
+
 // PARTS: partial outputs of y_perm, of type Y (known at compile time, so that the loads of a row are all in flight
 // together: 8 tokens of a 1024 / 2816 layer 38.9 -> 37.1 us)
-template <typename T, typename Y, int PARTS>
+// ADD: the addend's form.  (Known at compile time: the four fp32 parts that only a layer with a base has are 32 registers, and from 65 on a
+// CU holds less than eight workgroups.  2048 tokens of 2048, a workgroup each, with / without them: one expert 4.92 / 4.35 us, two 5.95 / 5.53.)
+template <typename T, typename Y, int PARTS, int ADD>
 __global__ __launch_bounds__(256) void combine_kernel(ptr_arg a_inv, ptr_arg a_gate, ptr_arg a_perm, int d, int k, int P, int addend_parts,
                                                       ptr_arg a_residual, ptr_arg a_addend, ptr_arg a_y) {
     const int32_t* const inv_perm = from_arg<const int32_t>(a_inv);
@@ -29,19 +33,19 @@ __global__ __launch_bounds__(256) void combine_kernel(ptr_arg a_inv, ptr_arg a_g
 #pragma unroll
         for (int q = 0; q < VEC; ++q) acc[q] = 0.f;
         // Everything that a chunk needs is requested ahead of the sums: the residual, a shared part, and two pairs' rows at a time.  (One
-        // after the other they were up to four memory latencies: 16384 tokens of 2048 35.7 us, 33.4 now; layer of 8 tokens on a shared base of
-        // 2048 / 5632 65.4 and 63.8, of 24 tokens, 4 of 16 experts, 43.1 and 42.5.)
+        // after the other they were up to four memory latencies: 16384 tokens of 2048, two experts, 36.6 us, 33.9 now, 8192 tokens of 720,
+        // eight experts, 32.0 and 23.9; layer of 8 tokens on a shared base of 2048 / 5632 65.4 and 63.8, of 24 tokens, 4 of 16 experts, 43.1 and 42.5.)
         vec_t res{}, add{};
-        f32x4 add_part[kMaxParts][VEC / 4] = {};
+        f32x4 add_part[ADD == ADD_PARTS ? kMaxParts : 1][VEC / 4] = {};
         if (residual) res = *reinterpret_cast<const vec_t*>(residual + (size_t)t * d + i);
-        if (addend && addend_parts > 1) {
+        if constexpr (ADD == ADD_PARTS) {
             const float* a = reinterpret_cast<const float*>(addend) + (size_t)t * d + i;
 #pragma unroll
             for (int part = 0; part < kMaxParts; ++part)
                 if (part < addend_parts)
 #pragma unroll
                     for (int q = 0; q < VEC / 4; ++q) add_part[part][q] = reinterpret_cast<const f32x4*>(a + (size_t)part * gridDim.x * d)[q];
-        } else if (addend) {
+        } else if constexpr (ADD == ADD_ONE) {
             add = *reinterpret_cast<const vec_t*>(addend + (size_t)t * d + i);
         }
         auto pairs = [&](int j, auto n) {
@@ -72,13 +76,13 @@ __global__ __launch_bounds__(256) void combine_kernel(ptr_arg a_inv, ptr_arg a_g
 #pragma unroll
             for (int q = 0; q < VEC; ++q) acc[q] += S::get(res, q);
         }
-        if (addend && addend_parts > 1) {
+        if constexpr (ADD == ADD_PARTS) {
 #pragma unroll
             for (int part = 0; part < kMaxParts; ++part)
                 if (part < addend_parts)
 #pragma unroll
                     for (int q = 0; q < VEC; ++q) acc[q] += add_part[part][q / 4][q % 4];
-        } else if (addend) {
+        } else if constexpr (ADD == ADD_ONE) {
 #pragma unroll
             for (int q = 0; q < VEC; ++q) acc[q] += S::get(add, q);
         }
@@ -92,7 +96,10 @@ __global__ __launch_bounds__(256) void combine_kernel(ptr_arg a_inv, ptr_arg a_g
 template <typename T, typename Y, int PARTS>
 static int combine_on(const moe_shape& s, const void* y_perm, const int32_t* inv_perm, const float* topk_gate,
                       const void* residual, void* y, hipStream_t st, const void* addend, int addend_parts) {
-    hipLaunchKernelGGL((combine_kernel<T, Y, PARTS>), dim3(s.n_tokens), dim3(256), 0, st, as_arg(inv_perm), as_arg(topk_gate),
+    const auto kern = !addend            ? combine_kernel<T, Y, PARTS, ADD_NONE>
+                      : addend_parts > 1 ? combine_kernel<T, Y, PARTS, ADD_PARTS>
+                                         : combine_kernel<T, Y, PARTS, ADD_ONE>;
+    hipLaunchKernelGGL(kern, dim3(s.n_tokens), dim3(256), 0, st, as_arg(inv_perm), as_arg(topk_gate),
                        as_arg(y_perm), s.d_model, s.top_k, s.n_tokens * s.top_k, addend_parts, as_arg(residual), as_arg(addend),
                        as_arg(y));
     return launch_status();

@@ -177,3 +177,15 @@ def test_a_launch_has_a_workgroup_for_every_tile(tmp_path):
                     hip_build.CSRC, os.path.join(ROOT, "tests", "tile_grid_check.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+def test_the_combine_of_a_layer_without_a_base_leaves_a_cu_eight_workgroups(tmp_path):
+    # eight workgroups of 256 threads are eight waves a SIMD, of 512 registers a lane
+    out = str(tmp_path / "combine.s")
+    subprocess.run([hip_build._hipcc(), *hip_build.FLAGS, "--offload-device-only", "-S", os.path.join(hip_build.CSRC, "combine.hip"), "-o", out],
+                   check=True, capture_output=True)
+    text = open(out).read()
+    used = {n: int(v) for n, v in re.findall(r"\.name:\s+(_ZN3moe14combine_kernel\S+)[\s\S]*?\.vgpr_count:\s+(\d+)", text)}
+    small = {n: v for n, v in used.items() if not re.search(r"Li\d+ELi2EE", n)}  # (the last argument: fp32 parts of an addend)
+    assert max(small.values()) <= 64, small
+    assert len(used) > len(small)
