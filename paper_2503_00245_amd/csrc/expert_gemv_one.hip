@@ -329,10 +329,15 @@ __global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(
 // ---- rank experts without a base (M_e = L_e R_e) --------------------------------------------------------
 // h_j = silu(L0_j t0_j) * (L1_j t1_j) for rows of r > 256: a wave belongs to one pair, whose two rank vectors
 // it keeps in registers, and requests both rows of its next unit before it sums the current one.
+// spread: the waves are counted workgroups first, so that the last turn's rows lie on all CUs (whole layer, us, 2 of 8 experts, waves first / so:
+// 2048 / 5632 of rank 1024, 2.75 turns, 27.6 / 27.1; 1600 / 4264 of 800, 2.08, 23.9 / 23.0; 1000 / 2680 of 504, 1.31, 16.9 / 16.5; 2040 /
+// 5552 of 1016, rows of no whole lines, 2.71, 28.3 / 28.1; 1920 / 5120 of 960, 4 experts, 5 whole turns, 40.7 / 40.3).  Not where they
+// lie on more than three quarters of them anyway (1440 / 3840 of 720, 1.88, 21.50 / 21.61; 1472 / 3952 of 736, 1.93, 21.78 / 21.86; 1360 / 3632 of
+// 680, 1.77, 21.28 / 21.23), nor in one turn.
 // NC: 1 KB chunks per row.
 template <typename T, int NC>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_hidden_kernel(
-    ptr_arg ai, ptr_arg aL0, ptr_arg aL1, long long stride, int n, int rows, int k, int E,
+    ptr_arg ai, ptr_arg aL0, ptr_arg aL1, long long stride, int n, int rows, int k, int E, int waves /* per pair */, int spread,
     const LowRankStage a) {
     const int32_t* idx = from_arg<const int32_t>(ai);
     typedef Store<T> S;
@@ -340,8 +345,7 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     constexpr int VEC = S::VEC, CH = kWave * VEC;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int waves = (int)gridDim.x * kOneWaves / k;  // per pair; in the order of decode_first_kernel
-    const int at = rows > waves ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kOneWaves + wave;
+    const int at = spread ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kOneWaves + wave;
     const int j = at % k;
     int row = at / k;
     if (row >= waves || row >= rows) return;
@@ -829,7 +833,7 @@ int launch_decode_low_rank(LowRankStage a, bool hidden, hipStream_t st) {
     return launch_status();
 }
 
-constexpr int kHiddenMaxChunks = 3;  // two rank vectors and two units of two rows in 128 registers
+constexpr int kHiddenMaxChunks = 3;  // (decode_hidden_kernel) two rank vectors and two units of two rows in 128 registers
 
 bool decode_rank_supported(const moe_shape& s) {
     return decode_first_supported(s) && s.act_dtype == MOE_BF16 && s.rank > 0 && !(s.flags & MOE_FLAG_SHARED_BASE) &&
@@ -840,12 +844,11 @@ int launch_decode_hidden(const LowRankStage& a, hipStream_t st) {
     if (a.r <= kWave / 2 * Store<bf16_t>::VEC) return launch_decode_low_rank(a, true, st);  // two and more rows per wave
     const long long units = (long long)a.k * a.rows;
     const dim3 grid((unsigned)std::min<long long>(kOneCus, (units + kOneWaves - 1) / kOneWaves)), block(kOneWaves * kWave);
-    switch (chunks_of<bf16_t>(a.r)) {
-        case 1: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 1>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, a); break;
-        case 2: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 2>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, a); break;
-        case 3: hipLaunchKernelGGL((decode_hidden_kernel<bf16_t, 3>), grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, a); break;
-        default: return MOE_ERR_UNSUPPORTED;
-    }
+    const int waves = (int)grid.x * kOneWaves / a.k, rest = a.rows % waves, spread = a.rows > waves && 4 * rest <= 3 * waves;
+    const int chunks = chunks_of<bf16_t>(a.r);
+    if (chunks > kHiddenMaxChunks) return MOE_ERR_UNSUPPORTED;
+    const auto kern = chunks == 1 ? decode_hidden_kernel<bf16_t, 1> : chunks == 2 ? decode_hidden_kernel<bf16_t, 2> : decode_hidden_kernel<bf16_t, 3>;
+    hipLaunchKernelGGL(kern, grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, waves, spread, a);
     return launch_status();
 }
 

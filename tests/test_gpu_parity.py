@@ -892,6 +892,14 @@ def test_forward_one_token_rest_of_the_rows(dev, oracle, d, F, E, k, r, base, dt
     _forward_case(dev, oracle, cfg, 1)
 
 
+@pytest.mark.parametrize("F,k,r", [
+    # rows of a pair's rank factors on 4096 / k waves: one turn, a row past it, a last turn of three quarters and 8 rows more, two whole turns
+    (2048, 2, 264), (2056, 2, 520), (3584, 2, 264), (3592, 2, 264), (4096, 2, 1032), (2384, 3, 264), (2392, 3, 264), (4104, 1, 520), (1800, 4, 264),
+])
+def test_forward_one_token_rank_experts_last_turn_of_rows(dev, oracle, F, k, r):
+    _forward_case(dev, oracle, _cfg(name="turn", d=72, F=F, E=4, k=k, r=r, dtype="bf16", seed=1210 + F, std=0.05), 1)
+
+
 @pytest.mark.parametrize("d,F,E,k,r", [
     # blocks of 64 hidden rows whole and not, one block, ranks of one vector and whole ones, the most pairs and the most sums; the first
     # sizes past it: a longer rank, more sums
