@@ -34,8 +34,10 @@ constexpr int kBaseSums = 256, kBasePairs = kBaseSums / 8;  // k r, k of decode_
 // before it sums the current one.  2048 x 5632, 92 MB: 18.9 us with the routing, where a router launch and
 // a wave per row took 3.8 + 17.6; 1024 x 2816, 23 MB: 8.4 us for 3.1 + 8.9.  What is left beside the stream
 // (5.6 TB/s) is the prologue, 2-2.5 us.
-// NC: 1 KB chunks per row.
-template <typename T, int NC, bool SWIGLU>
+// NC: 1 KB chunks per row.  DEAL: some of the units are not dealt waves first.  (Known at compile time, and the rest's place worked out behind
+// the first requests: the order's arithmetic ahead of them was 0.05-0.15 us of a layer of one turn, 456 x 1216, 2 of 4 experts, 8.18 / 8.04,
+// 512 x 1376 of rank 256, one expert, 12.78 / 12.64.)
+template <typename T, int NC, bool SWIGLU, bool DEAL>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_first_kernel(
     ptr_arg ax, ptr_arg aw, ptr_arg ab, int n, int E, int route_blocks, const FirstStage a) {
     typedef Store<T> S;
@@ -146,11 +148,8 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     }
     Rows r0, r1;
     const int in_order = (int)blockIdx.x - first_block;
-    const int by_xcd = blocks % 8 == 0 ? (in_order & 7) * (blocks >> 3) + (in_order >> 3) : in_order;
-    const int to_rest = stride + wave * blocks + by_xcd - (in_order * kOneWaves + wave);  // (from the last whole turn; one at least)
-    int turns = base ? a.base_turns : a.turns;
-    auto next = [&](const Unit& u) { return settle(Unit{u.j, u.row + (--turns == 0 ? to_rest : stride)}); };
-    Unit u0 = settle(Unit{0, turns < 0 ? wave * blocks + in_order : in_order * kOneWaves + wave});
+    int turns = !DEAL ? 0 : base ? a.base_turns : a.turns;
+    Unit u0 = settle(Unit{0, DEAL && turns < 0 ? wave * blocks + in_order : in_order * kOneWaves + wave});
     if (u0.j < k) load(r0, u0);
     if (blockIdx.x == 0 && wave == 0) {  // the gates, for the last stage: behind the first requests
         const RouterPick pick = router_weigh(lane, E, logit, slot, vmax);
@@ -159,6 +158,9 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
             a.gate[slot] = pick.p / pick.sel_sum;
         }
     }
+    const int by_xcd = blocks % 8 == 0 ? (in_order & 7) * (blocks >> 3) + (in_order >> 3) : in_order;
+    const int to_rest = stride + wave * blocks + by_xcd - (in_order * kOneWaves + wave);  // (from the last whole turn; one at least)
+    auto next = [&](const Unit& u) { return settle(Unit{u.j, u.row + (DEAL && --turns == 0 ? to_rest : stride)}); };
     while (u0.j < k) {
         const Unit u1 = next(u0);
         if (u1.j < k) load(r1, u1);
@@ -662,10 +664,10 @@ bool decode_first_supported(const moe_shape& s) {
 template <typename T, int NC>
 static void launch_first_nc(const FirstStage& a, bool swiglu, dim3 grid, hipStream_t st) {
     const dim3 block(kOneWaves * kWave);
-    if (swiglu)
-        hipLaunchKernelGGL((decode_first_kernel<T, NC, true>), grid, block, 0, st, as_arg(a.x), as_arg(a.router_w), as_arg(a.router_b), a.d, a.E, a.route_blocks, a);
-    else
-        hipLaunchKernelGGL((decode_first_kernel<T, NC, false>), grid, block, 0, st, as_arg(a.x), as_arg(a.router_w), as_arg(a.router_b), a.d, a.E, a.route_blocks, a);
+    const bool deal = a.turns || a.base_turns;
+    const auto kern = swiglu ? (deal ? decode_first_kernel<T, NC, true, true> : decode_first_kernel<T, NC, true, false>)
+                             : (deal ? decode_first_kernel<T, NC, false, true> : decode_first_kernel<T, NC, false, false>);
+    hipLaunchKernelGGL(kern, grid, block, 0, st, as_arg(a.x), as_arg(a.router_w), as_arg(a.router_b), a.d, a.E, a.route_blocks, a);
 }
 
 // How the units are dealt to the waves (the kernel's comment): whole turns of all waves before the rest is spread over the workgroups, 0

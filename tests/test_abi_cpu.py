@@ -189,3 +189,18 @@ def test_the_combine_of_a_layer_without_a_base_leaves_a_cu_eight_workgroups(tmp_
     small = {n: v for n, v in used.items() if not re.search(r"Li\d+ELi2EE", n)}  # (the last argument: fp32 parts of an addend)
     assert max(small.values()) <= 64, small
     assert len(used) > len(small)
+
+
+def test_a_first_stage_without_a_rest_does_without_the_order_of_one(tmp_path):
+    # the instances for layers of whole turns read no count of turns: what stands ahead of their first request is what it was without the order
+    out = str(tmp_path / "one.s")
+    subprocess.run([hip_build._hipcc(), *hip_build.FLAGS, "--offload-device-only", "-S", os.path.join(hip_build.CSRC, "expert_gemv_one.hip"), "-o", out],
+                   check=True, capture_output=True)
+    read = {}  # kernel: the dwords of its arguments that it loads
+    for name, body in re.findall(r"^(_ZN3moe19decode_first_kernel\w+):[^\n]*\n([\s\S]*?)\.end_amdhsa_kernel", open(out).read(), re.M):
+        read[name] = {int(at, 16) + 4 * i for n, at in re.findall(r"s_load_dword(x\d+)? s\S+, s\S+, (0x[0-9a-f]+)", body)
+                      for i in range(int(n[1:] or 1))}
+    pairs = [(n, n.replace("ELb1EEEv", "ELb0EEEv")) for n in read if "ELb1EEEv" in n]  # (the last template argument: with a rest)
+    assert len(pairs) == 16  # two types, four row lengths, with and without SwiGLU
+    for spread, plain in pairs:
+        assert read[spread] - read[plain], spread
