@@ -14,8 +14,6 @@
 
 namespace moe {
 
-constexpr int kOneWaves = 16;  // per workgroup: 4 per SIMD, so a wave may hold 128 registers
-constexpr int kOneCus = 256;
 constexpr int kBaseSums = 256, kBasePairs = kBaseSums / 8;  // k r, k of decode_base_parts_supported
 
 // Every workgroup routes the token for itself: 64 KB of router rows from its L2 per CU, a wave per
@@ -158,8 +156,7 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
             a.gate[slot] = pick.p / pick.sel_sum;
         }
     }
-    const int by_xcd = blocks % 8 == 0 ? (in_order & 7) * (blocks >> 3) + (in_order >> 3) : in_order;
-    const int to_rest = stride + wave * blocks + by_xcd - (in_order * kOneWaves + wave);  // (from the last whole turn; one at least)
+    const int to_rest = stride + place_in_rest(in_order, wave, blocks) - (in_order * kOneWaves + wave);  // (from the last whole turn; one at least)
     auto next = [&](const Unit& u) { return settle(Unit{u.j, u.row + (DEAL && --turns == 0 ? to_rest : stride)}); };
     while (u0.j < k) {
         const Unit u1 = next(u0);
@@ -331,15 +328,11 @@ __global__ __launch_bounds__(kLowRankWaves* kWave) void decode_low_rank_kernel(
 // ---- rank experts without a base (M_e = L_e R_e) --------------------------------------------------------
 // h_j = silu(L0_j t0_j) * (L1_j t1_j) for rows of r > 256: a wave belongs to one pair, whose two rank vectors
 // it keeps in registers, and requests both rows of its next unit before it sums the current one.
-// spread: the waves are counted workgroups first, so that the last turn's rows lie on all CUs (whole layer, us, 2 of 8 experts, waves first / so:
-// 2048 / 5632 of rank 1024, 2.75 turns, 27.6 / 27.1; 1600 / 4264 of 800, 2.08, 23.9 / 23.0; 1000 / 2680 of 504, 1.31, 16.9 / 16.5; 2040 /
-// 5552 of 1016, rows of no whole lines, 2.71, 28.3 / 28.1; 1920 / 5120 of 960, 4 experts, 5 whole turns, 40.7 / 40.3).  Not where they
-// lie on more than three quarters of them anyway (1440 / 3840 of 720, 1.88, 21.50 / 21.61; 1472 / 3952 of 736, 1.93, 21.78 / 21.86; 1360 / 3632 of
-// 680, 1.77, 21.28 / 21.23), nor in one turn.
+// turns: the order of the units (hidden_turns); DEAL: it is not 0 (a layer of one turn, 720 / 1936 of rank 264, 14.4 us without this / 14.2).
 // NC: 1 KB chunks per row.
-template <typename T, int NC>
+template <typename T, int NC, bool DEAL>
 __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_hidden_kernel(
-    ptr_arg ai, ptr_arg aL0, ptr_arg aL1, long long stride, int n, int rows, int k, int E, int waves /* per pair */, int spread,
+    ptr_arg ai, ptr_arg aL0, ptr_arg aL1, long long stride, int n, int rows, int k, int E, int waves /* per pair */, int turns,
     const LowRankStage a) {
     const int32_t* idx = from_arg<const int32_t>(ai);
     typedef Store<T> S;
@@ -347,9 +340,9 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
     constexpr int VEC = S::VEC, CH = kWave * VEC;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int at = spread ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kOneWaves + wave;
-    const int j = at % k;
-    int row = at / k;
+    const int at = DEAL && turns < 0 ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kOneWaves + wave;
+    int row = uniform_div(at, k);
+    const int j = at - row * k;
     if (row >= waves || row >= rows) return;
     int off[NC];
 #pragma unroll
@@ -394,13 +387,15 @@ __global__ __launch_bounds__(kOneWaves* kWave) __attribute__((amdgpu_waves_per_e
         s1 = wave_sum(s1);
         if (lane == 0) h[i] = silu_f32(s0) * s1;
     };
+    const int to_rest = waves + place_in_rest((int)blockIdx.x, uniform_div(wave, k), kOneCus) - row;  // (from the last whole turn)
+    auto next_of = [&](int i) { return i + (DEAL && --turns == 0 ? to_rest : waves); };
     for (;;) {
-        const int next = row + waves;
+        const int next = next_of(row);
         if (next < rows) load(r1, next);
         __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the sums
         finish(r0, row);
         if (next >= rows) return;
-        row = next + waves;
+        row = next_of(next);
         if (row < rows) load(r0, row);
         __builtin_amdgcn_sched_barrier(0);
         finish(r1, next);
@@ -846,11 +841,14 @@ int launch_decode_hidden(const LowRankStage& a, hipStream_t st) {
     if (a.r <= kWave / 2 * Store<bf16_t>::VEC) return launch_decode_low_rank(a, true, st);  // two and more rows per wave
     const long long units = (long long)a.k * a.rows;
     const dim3 grid((unsigned)std::min<long long>(kOneCus, (units + kOneWaves - 1) / kOneWaves)), block(kOneWaves * kWave);
-    const int waves = (int)grid.x * kOneWaves / a.k, rest = a.rows % waves, spread = a.rows > waves && 4 * rest <= 3 * waves;
+    const int waves = (int)grid.x * kOneWaves / a.k;
     const int chunks = chunks_of<bf16_t>(a.r);
     if (chunks > kHiddenMaxChunks) return MOE_ERR_UNSUPPORTED;
-    const auto kern = chunks == 1 ? decode_hidden_kernel<bf16_t, 1> : chunks == 2 ? decode_hidden_kernel<bf16_t, 2> : decode_hidden_kernel<bf16_t, 3>;
-    hipLaunchKernelGGL(kern, grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, waves, spread, a);
+    const int turns = hidden_turns(a.rows, waves, a.k, a.r * (int)sizeof(bf16_t));
+    const auto kern = chunks == 1   ? (turns ? decode_hidden_kernel<bf16_t, 1, true> : decode_hidden_kernel<bf16_t, 1, false>)
+                      : chunks == 2 ? (turns ? decode_hidden_kernel<bf16_t, 2, true> : decode_hidden_kernel<bf16_t, 2, false>)
+                                    : (turns ? decode_hidden_kernel<bf16_t, 3, true> : decode_hidden_kernel<bf16_t, 3, false>);
+    hipLaunchKernelGGL(kern, grid, block, 0, st, as_arg(a.idx), as_arg(a.L0), as_arg(a.L1), a.stride, a.r, a.rows, a.k, a.E, waves, turns, a);
     return launch_status();
 }
 

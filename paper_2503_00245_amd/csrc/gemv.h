@@ -5,6 +5,30 @@
 
 namespace moe {
 
+constexpr int kOneWaves = 16;  // waves of a workgroup: 4 per SIMD, so a wave may hold 128 registers
+constexpr int kOneCus = 256;
+
+// Units beyond the last whole turn of all waves, spread over the workgroups: which of them is the w-th wave's of a workgroup.  Neighbours lie on one
+// XCD (workgroups go to the XCDs in turn).
+__host__ __device__ inline int place_in_rest(int block, int w, int blocks) {
+    return w * blocks + (blocks % 8 == 0 ? (block & 7) * (blocks >> 3) + (block >> 3) : block);
+}
+// Order of a pair's rows of rank factors on its `waves` waves (decode_hidden_kernel): 0, waves first, so that neighbouring rows are a workgroup's; -1,
+// workgroups first, so that the last turn's rows lie on all CUs; the number of whole turns, waves first and the rest alone on place_in_rest.
+//   Rows of whole cache lines (whole layer, us, 2 of 8 experts, waves first / workgroups first): 2048 / 5632 of rank 1024, 2.75 turns, 27.9 / 27.5,
+//   1024 / 2816 of 512, 1.38, 16.5 / 16.1, 1704 / 4544 of 576, 2.22, 22.8 / 22.3; 1920 / 5120 of 960, 4 experts, 5 whole turns, 40.5 / 40.0.
+//   Other rows, of which neighbours share a line (waves first / workgroups first / the rest alone): 2040 / 5552 of 1016, 2.71, 28.3 / 28.2 / 27.9,
+//   1800 / 4800 of 600, 2.34, 23.4 / 23.1 / 22.8, 1984 / 5312 of 264, 4 experts, 5.19, 26.0 / 26.2 / 25.7, 1536 / 4096 of 264, 2 whole turns,
+//   17.3 / 17.6 / 17.3.
+// Waves first in one turn, and where the last one fills more than three quarters of them (1440 / 3840 of 720, 1.88, 21.4 / 21.5).
+inline int hidden_turns(int rows, int waves, int k, int row_bytes) {
+    const int rest = rows % waves;
+    if (rows <= waves || 4 * rest > 3 * waves) return 0;
+    if (row_bytes % 128 == 0) return -1;
+    // (where k does not divide the waves, the last workgroup lacks a wave of some pairs: none whose place is below this)
+    return rest > 0 && rest < kOneWaves / k * kOneCus ? rows / waves : 0;
+}
+
 // Route the token x [d], then out0[j] = W0[expert j] x and out1[j] = W1[expert j] x, or, with SwiGLU,
 // out0[j] = silu(W0 x) * (W1 x).
 struct FirstStage {

@@ -171,12 +171,20 @@ def test_a_product_planned_in_parts_has_a_kernel_that_writes_them(tmp_path):
     assert r.returncode == 0, r.stdout
 
 
-def test_a_launch_has_a_workgroup_for_every_tile(tmp_path):
+def _host_check(source, tmp_path):
     exe = str(tmp_path / "check")
     subprocess.run([hip_build._hipcc(), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
-                    hip_build.CSRC, os.path.join(ROOT, "tests", "tile_grid_check.cpp"), "-o", exe], check=True)
+                    hip_build.CSRC, os.path.join(ROOT, "tests", source), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+def test_a_launch_has_a_workgroup_for_every_tile(tmp_path):
+    _host_check("tile_grid_check.cpp", tmp_path)
+
+
+def test_a_single_tokens_rank_rows_are_taken_once_and_lie_together(tmp_path):
+    _host_check("rank_rows_check.cpp", tmp_path)
 
 
 def test_the_combine_of_a_layer_without_a_base_leaves_a_cu_eight_workgroups(tmp_path):

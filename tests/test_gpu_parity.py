@@ -895,9 +895,11 @@ def test_forward_one_token_rest_of_the_rows(dev, oracle, d, F, E, k, r, base, dt
 @pytest.mark.parametrize("F,k,r", [
     # rows of a pair's rank factors on 4096 / k waves: one turn, a row past it, a last turn of three quarters and 8 rows more, two whole turns
     (2048, 2, 264), (2056, 2, 520), (3584, 2, 264), (3592, 2, 264), (4096, 2, 1032), (2384, 3, 264), (2392, 3, 264), (4104, 1, 520), (1800, 4, 264),
+    (2056, 2, 320), (4096, 2, 320), (3592, 2, 320), (1800, 4, 512),  # rows of whole lines
+    (1192, 6, 264), (504, 14, 264),  # (as many rows as workgroups have waves for: the last one lacks one of some pairs)
 ])
 def test_forward_one_token_rank_experts_last_turn_of_rows(dev, oracle, F, k, r):
-    _forward_case(dev, oracle, _cfg(name="turn", d=72, F=F, E=4, k=k, r=r, dtype="bf16", seed=1210 + F, std=0.05), 1)
+    _forward_case(dev, oracle, _cfg(name="turn", d=72, F=F, E=max(4, k), k=k, r=r, dtype="bf16", seed=1210 + F, std=0.05), 1)
 
 
 @pytest.mark.parametrize("d,F,E,k,r", [
