@@ -17,17 +17,9 @@ namespace moe {
 constexpr int kBaseSums = 256, kBasePairs = kBaseSums / 8;  // k r, k of decode_base_parts_supported
 
 // Every workgroup routes the token for itself: 64 KB of router rows from its L2 per CU, a wave per
-// expert, and all of it in one round trip, in place of a launch that leaves 255 CUs idle.  With one
-// workgroup per CU that is 16 MB out of the L2s.  A wave then takes (pair, row) units gw, gw + W, ..., where gw counts the
-// workgroups first and their waves second, so that no CU has more than another of the units beyond the last whole turn of all W waves
-// (whole layer, us, waves first / workgroups first: 1024 x 2816, 5632 units on 4096 waves, 12.2 / 11.8, 2048 x 5632
-// 27.7 / 27.4, a shared base's 5632 rows on 3968 waves 25.3 / 23.9).  Waves first, so that a workgroup's rows and results are neighbours,
-//   - where there is one turn (400 x 1072 8.2 / 8.4, 720 x 1920, one expert, 8.4 / 8.6), no rest, or one of more than three quarters of
-//     the waves (1.93 turns, 1472 x 3952, 18.2 / 18.3);
-//   - in rows that are no whole cache lines, of which neighbours share one: the rest alone is spread there, neighbours on one XCD (waves first /
-//     workgroups first / this: 2040 x 5552, 2.71 turns, 27.6 / 28.2 / 27.6; 1400 x 3760, 1.84, 17.4 / 17.7 / 17.4; 1832 x 4952, 2.42, 24.3 /
-//     23.9 / 23.7; 2016 x 5376, four experts, 5.25, 50.5 / 49.7 / 49.1).
-// It holds
+// expert, in place of a launch that leaves 255 CUs idle.  With one workgroup per CU that is 16 MB out of the L2s.  (The token's row comes
+// first, then the router's, four chunks of a row at a time and a remainder of fewer one after the other: two round trips at 2048 wide, three at
+// 1024, four at 1440.)  A wave then takes (pair, row) units in the order of first_stage_turns: it holds
 // the token's row in registers and requests both rows of its next unit (8 KB at 2048 wide)
 // before it sums the current one.  2048 x 5632, 92 MB: 18.9 us with the routing, where a router launch and
 // a wave per row took 3.8 + 17.6; 1024 x 2816, 23 MB: 8.4 us for 3.1 + 8.9.  What is left beside the stream
@@ -665,22 +657,14 @@ static void launch_first_nc(const FirstStage& a, bool swiglu, dim3 grid, hipStre
     hipLaunchKernelGGL(kern, grid, block, 0, st, as_arg(a.x), as_arg(a.router_w), as_arg(a.router_b), a.d, a.E, a.route_blocks, a);
 }
 
-// How the units are dealt to the waves (the kernel's comment): whole turns of all waves before the rest is spread over the workgroups, 0
-// where it is not, -1 where all units are
-static int first_stage_turns(long long units, int blocks, bool whole_lines) {
-    const long long waves = (long long)blocks * kOneWaves, rest = units % waves;
-    if (units <= waves || rest == 0 || 4 * rest > 3 * waves) return 0;
-    return whole_lines ? -1 : (int)(units / waves);
-}
-
 template <typename T>
 static int launch_first_t(FirstStage a, bool swiglu, hipStream_t st) {
     const long long units = (long long)a.k * a.rows;
     a.route_blocks = (int)std::min<long long>(kOneCus, (units + kOneWaves - 1) / kOneWaves);
     const int base_blocks = a.base_W0 ? std::max(kOneCus / 2, kOneCus - a.route_blocks) : 0;
-    const bool whole_lines = a.d * sizeof(T) % 128 == 0;
-    a.turns = first_stage_turns(units, a.route_blocks, whole_lines);
-    a.base_turns = base_blocks ? first_stage_turns(a.base_rows, base_blocks, whole_lines) : 0;
+    const int row_bytes = a.d * (int)sizeof(T);
+    a.turns = first_stage_turns(units, a.route_blocks, row_bytes);
+    a.base_turns = base_blocks ? first_stage_turns(a.base_rows, base_blocks, row_bytes) : 0;
     const dim3 grid(a.route_blocks + base_blocks);
     switch (chunks_of<T>(a.d)) {
         case 1: launch_first_nc<T, 1>(a, swiglu, grid, st); break;

@@ -13,6 +13,21 @@ constexpr int kOneCus = 256;
 __host__ __device__ inline int place_in_rest(int block, int w, int blocks) {
     return w * blocks + (blocks % 8 == 0 ? (block & 7) * (blocks >> 3) + (block >> 3) : block);
 }
+// Order of decode_first_kernel's units (pair, row) on the waves of `blocks` workgroups: 0, waves first, so that a workgroup's rows and results are
+// neighbours; -1, workgroups first, so that no CU has more than another of the units beyond the last whole turn of all waves; the number of
+// whole turns, waves first and the rest alone on place_in_rest.  Waves first in one turn (400 / 1072 8.2 us for the layer, 8.4 workgroups first),
+// where there is no rest, and where it fills more than three quarters of the waves (1472 / 3952, 1.93 turns, 18.2 / 18.3).  Otherwise
+// (whole layer, us, waves first / workgroups first / the rest alone)
+//   - the rest alone in rows that are no whole cache lines, of which neighbours share one: 2040 / 5552, 2.71 turns, 27.6 / 28.2 / 27.6, 1400 / 3760,
+//     1.84, 17.4 / 17.7 / 17.4, 2016 / 5376, 4 experts, 5.25, 50.5 / 49.7 / 49.1; and in short ones: 1024 / 2816, 1.38, 12.1 / 12.1 / 11.9, 960 / 2560,
+//     1.25, 11.5 / 11.4 / 11.1, 832 / 2240 10.6 / 10.5 / 10.2, 1088 / 2880 14.1 / 13.8 / 13.6;
+//   - workgroups first in longer ones: even from 2.5 KB on (1280 / 3456 16.1 / 16.0 / 16.0, 1920 / 5184 25.4 / 25.2 / 25.2), and at 2048 / 5632 27.7 /
+//     27.6 / 27.7, one expert 18.2 / 16.8 / 17.1, a shared base's 5632 rows on 3968 waves 25.4 / 22.1 / 22.6.
+inline int first_stage_turns(long long units, int blocks, int row_bytes) {
+    const long long waves = (long long)blocks * kOneWaves, rest = units % waves;
+    if (units <= waves || rest == 0 || 4 * rest > 3 * waves) return 0;
+    return row_bytes % 128 == 0 && row_bytes > 2560 ? -1 : (int)(units / waves);
+}
 // Order of a pair's rows of rank factors on its `waves` waves (decode_hidden_kernel): 0, waves first, so that neighbouring rows are a workgroup's; -1,
 // workgroups first, so that the last turn's rows lie on all CUs; the number of whole turns, waves first and the rest alone on place_in_rest.
 //   Rows of whole cache lines (whole layer, us, 2 of 8 experts, waves first / workgroups first): 2048 / 5632 of rank 1024, 2.75 turns, 27.9 / 27.5,

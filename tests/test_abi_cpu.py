@@ -164,7 +164,7 @@ def test_a_product_planned_in_parts_has_a_kernel_that_writes_them(tmp_path):
     if not all(os.path.exists(o) for o in objs):
         hip_build.build()
     main, exe = str(tmp_path / "check.o"), str(tmp_path / "check")
-    subprocess.run([hip_build._hipcc(), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+    subprocess.run([hip_build._hipcc(), "-x", "hip", "--offload-host-only", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
                     hip_build.CSRC, "-c", os.path.join(ROOT, "tests", "split_plan_check.cpp"), "-o", main], check=True)
     subprocess.run([hip_build._hipcc(), main, *objs, "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
@@ -173,7 +173,7 @@ def test_a_product_planned_in_parts_has_a_kernel_that_writes_them(tmp_path):
 
 def _host_check(source, tmp_path):
     exe = str(tmp_path / "check")
-    subprocess.run([hip_build._hipcc(), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+    subprocess.run([hip_build._hipcc(), "-x", "hip", "--offload-host-only", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
                     hip_build.CSRC, os.path.join(ROOT, "tests", source), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
@@ -183,8 +183,8 @@ def test_a_launch_has_a_workgroup_for_every_tile(tmp_path):
     _host_check("tile_grid_check.cpp", tmp_path)
 
 
-def test_a_single_tokens_rank_rows_are_taken_once_and_lie_together(tmp_path):
-    _host_check("rank_rows_check.cpp", tmp_path)
+def test_a_single_tokens_rows_are_taken_once_and_lie_together(tmp_path):
+    _host_check("unit_order_check.cpp", tmp_path)
 
 
 def test_the_combine_of_a_layer_without_a_base_leaves_a_cu_eight_workgroups(tmp_path):
