@@ -3,6 +3,7 @@ workspaces, and rejects bad arguments on the host before any launch."""
 import ctypes as C
 import os
 import re
+import struct
 import subprocess
 
 import pytest
@@ -212,3 +213,34 @@ def test_a_first_stage_without_a_rest_does_without_the_order_of_one(tmp_path):
     assert len(pairs) == 16  # two types, four row lengths, with and without SwiGLU
     for spread, plain in pairs:
         assert read[spread] - read[plain], spread
+
+
+def _device_objects():
+    """The gfx950 code objects of the built library, one per source file."""
+    data = open(hip_build.ensure_built(), "rb").read()
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    at = data.find(magic)
+    while at >= 0:
+        pos = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", data, at + len(magic))[0]):
+            offset, size, n = struct.unpack_from("<3Q", data, pos)
+            if data[pos + 24:pos + 24 + n].endswith(b"gfx950"):
+                yield data[at + offset:at + offset + size]
+            pos += 24 + n
+        at = data.find(magic, at + 1)
+
+
+def test_no_wait_stands_between_the_prefill_kernels_matrix_instructions(tmp_path):
+    # the fragments have landed before the barrier that begins a phase's products
+    obj = str(tmp_path / "device.o")
+    products = 0
+    for code in _device_objects():
+        if b"gemm_pp_kernel" not in code:
+            continue
+        open(obj, "wb").write(code)
+        objdump = os.path.join(os.path.dirname(os.path.realpath(hip_build._hipcc())), "..", "lib", "llvm", "bin", "llvm-objdump")
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", "--no-leading-addr", obj], check=True, capture_output=True, text=True).stdout
+        text = re.sub(r"\s*//.*", "", text)
+        products += text.count("v_mfma")
+        assert not re.findall(r"v_mfma[^\n]*\n\s*s_waitcnt lgkmcnt[^\n]*\n(?=\s*v_mfma)", text)
+    assert products > 1000
