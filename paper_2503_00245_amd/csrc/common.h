@@ -119,7 +119,7 @@ inline int allow_dynamic_lds(const void* kernel, size_t bytes, std::atomic<uint6
 // a / b for a >= 0, b > 0: the estimate is off by a few hundred at most (2^31 times the rounding of the three
 // float steps), the second one, of the remainder, by one.  The compiler's integer division is forty
 // dependent instructions, and a workgroup makes half a dozen before its first load.
-__device__ __forceinline__ int quick_div(int a, int b) {
+__host__ __device__ __forceinline__ int quick_div(int a, int b) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const float inv = __builtin_amdgcn_rcpf((float)b);
     int q = (int)((float)a * inv);
@@ -132,7 +132,7 @@ __device__ __forceinline__ int quick_div(int a, int b) {
     return a / b;
 #endif
 }
-__device__ __forceinline__ int uniform_div(int a, int b) {  // wave-uniform a, b
+__host__ __device__ __forceinline__ int uniform_div(int a, int b) {  // wave-uniform a, b
 #if defined(__HIP_DEVICE_COMPILE__)
     return __builtin_amdgcn_readfirstlane(quick_div(a, b));
 #else

@@ -124,18 +124,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // launch is a few rounds of 256 workgroups, tiles are made narrower until the last round is full.
     int width = BN_OUT, n_base = (g.N + BN_OUT - 1) / BN_OUT;
     const int copies = SWIGLU ? 1 : g.C1 ? 2 : max(g.k_parts, 1);  // products, or k-parts, of the launch
-    bool fitted = false;
     auto n_tiles_of = [&](int m_tiles) INLINE {
-        if (m_tiles > 0) {
-            const int m_all = m_tiles * copies;
-            const int rounds = (int)((unsigned)(m_all * n_base + 255) / 256u);
-            fitted = rounds <= g.fit_width;
-            if (fitted) {
-                const int n = uniform_div(256 * rounds, m_all);  // tiles across N that fit
-                width = max(8, (uniform_div(g.N + n - 1, n) + 7) / 8 * 8);
-                n_base = uniform_div(g.N + width - 1, width);
-            }
-        }
+        if (m_tiles > 0) fit_columns(m_tiles * copies, g.N, g.fit_width, width, n_base);
         return n_base * copies;
     };
     // (in the last slot of B, which is first filled after the first phase)
@@ -479,11 +469,9 @@ int launch_pp(GemmArgs& g, hipStream_t st) {
     constexpr int BN_OUT = SWIGLU && !DUAL ? BN / 2 : BN;
     g.m_tiles_max = m_tiles_bound(g.P, g.E, BM);
     g.n_tiles = (g.N + BN_OUT - 1) / BN_OUT * ((!SWIGLU && g.C1) ? 2 : 1) * (g.k_parts > 1 ? g.k_parts : 1);
-    int tiles = g.m_tiles_max * g.n_tiles;
-    if (tiles < 256 * g.fit_width) tiles = (tiles + 255) / 256 * 256;
     constexpr size_t lds = (SA * BM + SB * BN) * BK * 2;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
-    const int grid = find_tile_grid(tiles, kSplitSlots);
+    const int grid = find_tile_grid(fitted_tiles(g.m_tiles_max * g.n_tiles, g.fit_width), kSplitSlots);
     static std::atomic<uint64_t> lds_allowed;
     const auto kern = gemm_pp_kernel<BM, BN, WAVES_M, SA, SB, SWIGLU, DUAL, F32, NT_B, LINES>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed) != MOE_OK) return MOE_ERR_LAUNCH;

@@ -100,8 +100,8 @@ __device__ __forceinline__ int group_end(const int32_t* __restrict__ offsets, in
 // and multiplies half the blocks).
 //
 // n_tiles_of(m): the launch's n-tiles when all groups together have m m-tiles.
-// lo, hi: in lane e of every wave, group e's bounds (group_bounds; 0, 0 in lanes from E on).  The sums run on
-// scalar registers through readlane.  (A loop of dependent scalar loads over the offsets cost
+// lo, hi: in lane e of every wave, group e's bounds (group_bounds; 0, 0 in lanes from E on).  The sums over groups
+// are a scan over the lanes.  (A loop of dependent scalar loads over the offsets cost
 // 2.6-3.3 us per tile here, a twentieth of a 256 x 256 tile's duration.)
 __device__ __forceinline__ void group_bounds(const int32_t* __restrict__ offsets, int E, int P, int& lo, int& hi) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -111,22 +111,15 @@ __device__ __forceinline__ void group_bounds(const int32_t* __restrict__ offsets
         hi = group_end(offsets, lane, P);
     }
 }
-// N_INNER (a power of two): tile order inside an expert in blocks of this many n-tiles, block outer, the
-// expert's m-tiles in the middle, the block's n-tiles inner (1: n-tile outer, m-tiles inner).
-template <int N_INNER = 1, int SPLIT_SLOTS = 0, typename NTiles>
-__device__ __forceinline__ bool find_tile(int lo, int hi, int E, int BM, NTiles n_tiles_of, int& e_out,
-                                          int& row0, int& row_end, int& nt_out) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int cnt = (hi - lo + BM - 1) / BM;  // m-tiles of group `lane` (0 beyond E)
-    const int upto = wave_scan(cnt), before = upto - cnt;  // m-tiles of the groups up to and below `lane`
-    int total = MOE_READLANE(upto, kWave - 1);
-    const int n_tiles = n_tiles_of(total);
-    total *= n_tiles;
+// The tile, of `total`, that workgroup `block` takes, and the half of it (-1: all of it); none: false
+template <int SPLIT_SLOTS>
+__host__ __device__ __forceinline__ bool tile_of_block(unsigned block, int total, int& tile, int& half) {
     const int per_xcd = (total + 7) / 8;
-    const int slot = blockIdx.x >> 3;
-    const int first = (blockIdx.x & 7) * per_xcd;               // this XCD's first tile
+    const int slot = block >> 3;
+    const int first = (block & 7) * per_xcd;                    // this XCD's first tile
     const int mine = max(0, min(per_xcd, total - first));       // and how many it has
-    int local_tile = slot, half = -1;
+    int local_tile = slot;
+    half = -1;
     if (SPLIT_SLOTS > 0) {
         constexpr int SLOTS = SPLIT_SLOTS > 0 ? SPLIT_SLOTS : 1;
         const int whole = (mine / SLOTS) * SLOTS;               // tiles in full rounds
@@ -138,7 +131,33 @@ __device__ __forceinline__ bool find_tile(int lo, int hi, int E, int BM, NTiles 
         }
     }
     if (local_tile >= mine) return false;
-    const int L = first + local_tile;
+    tile = first + local_tile;
+    return true;
+}
+// GemmArgs::fit_width: where m_all row tiles (of all products or k-parts) by n_base column tiles are at most that many rounds of
+// 256 workgroups, the columns of a tile and the tiles across N become those that fill the last of them
+__host__ __device__ __forceinline__ void fit_columns(int m_all, int N, int fit_width, int& width, int& n_base) {
+    const int rounds = (int)((unsigned)(m_all * n_base + 255) / 256u);
+    if (rounds > fit_width) return;
+    const int n = uniform_div(256 * rounds, m_all);  // tiles across N that fit
+    width = max(8, (uniform_div(N + n - 1, n) + 7) / 8 * 8);
+    n_base = uniform_div(N + width - 1, width);
+}
+// Tiles that a launch of up to `tiles` of them can come to have by that
+inline int fitted_tiles(int tiles, int fit_width) { return tiles < 256 * fit_width ? (tiles + 255) / 256 * 256 : tiles; }
+// N_INNER (a power of two): tile order inside an expert in blocks of this many n-tiles, block outer, the
+// expert's m-tiles in the middle, the block's n-tiles inner (1: n-tile outer, m-tiles inner).
+template <int N_INNER = 1, int SPLIT_SLOTS = 0, typename NTiles>
+__device__ __forceinline__ bool find_tile(int lo, int hi, int E, int BM, NTiles n_tiles_of, int& e_out,
+                                          int& row0, int& row_end, int& nt_out) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int cnt = (hi - lo + BM - 1) / BM;  // m-tiles of group `lane` (0 beyond E)
+    const int upto = wave_scan(cnt), before = upto - cnt;  // m-tiles of the groups up to and below `lane`
+    int total = MOE_READLANE(upto, kWave - 1);
+    const int n_tiles = n_tiles_of(total);
+    total *= n_tiles;
+    int L, half;
+    if (!tile_of_block<SPLIT_SLOTS>(blockIdx.x, total, L, half)) return false;
     // the group whose tiles hold L: the last one with tiles at or before it
     const unsigned long long at = __ballot(lane < E && cnt > 0 && before * n_tiles <= L);
     const int e = 63 - __clzll((long long)at);
@@ -179,8 +198,7 @@ inline int m_tiles_bound(int P, int E, int BM) {
 // needs no more than whole rounds, and none beside the tiles where they are one.  A surplus workgroup is not free: it finds the
 // bounds before it leaves, and with all of a CU's LDS to its name it starts only when a tile has ended: 256 of them are 1.1 us at a
 // launch's end.  Whole layer, us, with P / BM + E row tiles and half a round beside them / by this rule: 64 tokens of 1024 / 2816
-// 36.7 / 35.5, 300 tokens 47.0 / 46.1, 512 tokens 51.4 / 48.8, 777 tokens of 1440 / 3840 90.3 / 88.9, 2048 tokens of
-// 2048 / 5632 302.1 / 298.5.
+// 36.7 / 35.5, 300 tokens 47.0 / 46.1, 512 tokens 51.4 / 48.8, 777 tokens of 1440 / 3840 90.3 / 88.9.
 inline int find_tile_grid(int tiles, int split_slots) {
     const int per_xcd = (tiles + 7) / 8;
     if (split_slots == 0 || per_xcd <= split_slots) return per_xcd * 8;
@@ -260,7 +278,8 @@ struct PairKeys {
     }
 
     // group bounds in lane e of every wave (as group_bounds); s_count [waves][kMaxExperts] receives every wave's count of every
-    // expert.  From 2049 pairs on, up to 8 experts, the lanes' counts are added up in registers: LDS atomics meet on few addresses, and the
+    // expert.  Where a thread holds more than four keys (from 2049 pairs on with 512 threads, from 1025 on with 256), up to 8 experts, the lanes' counts are
+    // added up in registers: LDS atomics meet on few addresses, and the
     // more where experts are chosen unevenly (4096 skewed pairs of 8 experts 2500 clocks, 1650 now; 16 experts even 2048 tokens of 1024 / 2816 188.9 / 191.6).
     // Below, atomics without a branch: 2400 clocks of 1024 pairs, 1040 now.  With the sums over lanes in find_tile and here, and all arguments
     // in one place (expert_gemm_pp.hip), a tile's way to its first fill went from 5650 to 4050 clocks there, from 7260 to 3880 at 4096 pairs; whole layer, us,

@@ -1,5 +1,5 @@
-// Host only: a launch of the grouped products has a workgroup for every tile that the groups can need, however the rows lie in them.
-// The map from workgroups to tiles is the kernels' (find_tile), restated for a whole launch; exits with 1 where the grid is short.
+// Host only: a launch of the grouped products has a workgroup for every tile that the groups can need, however the rows lie in them and however
+// narrow the kernel makes its tiles, and no two for one.  The maps are the kernels' own (tile_of_block, fit_columns); exits with 1 on a fault.
 #include <algorithm>
 #include <cstdio>
 #include <random>
@@ -9,23 +9,26 @@
 
 using namespace moe;
 
-// workgroups per XCD that find_tile hands `tiles` tiles to
-static int slots(int tiles, int split) {
-    const int per_xcd = (tiles + 7) / 8;
-    int most = 0;
-    for (int x = 0; x < 8; ++x) {
-        const int mine = std::max(0, std::min(per_xcd, tiles - x * per_xcd));
-        const int whole = split ? mine / split * split : 0, rem = mine - whole;
-        most = std::max(most, split && whole && rem && 2 * rem <= split ? whole + 2 * rem : mine);
+// Every one of `tiles` tiles is taken by the `grid` workgroups: once, or as its two halves
+template <int SPLIT>
+static bool all_taken(int grid, int tiles) {
+    std::vector<int> whole(tiles, 0), halves(tiles, 0);
+    for (int b = 0; b < grid; ++b) {
+        int tile, half;
+        if (!tile_of_block<SPLIT>(b, tiles, tile, half)) continue;
+        if (tile < 0 || tile >= tiles || half > 1) return false;
+        half < 0 ? ++whole[tile] : halves[tile] += 1 << 4 * half;
     }
-    return most;
+    for (int t = 0; t < tiles; ++t)
+        if (!(whole[t] == 1 && halves[t] == 0) && !(whole[t] == 0 && halves[t] == 0x11)) return false;
+    return true;
 }
 
 int main() {
     std::mt19937 rng(7);
     auto below = [&](int n) { return (int)(rng() % (unsigned)n); };
-    long long launches = 0, tight = 0, faults = 0;
-    for (int it = 0; it < 200000; ++it) {
+    long long launches = 0, tight = 0, narrowed = 0, faults = 0;
+    for (int it = 0; it < 20000; ++it) {
         const int E = 1 + below(it % 5 ? 16 : 64), BM = 16 << below(5), P = 1 + below(it % 3 ? 600 : 20000);
         std::vector<int> load(E, 0);
         int left = P;
@@ -46,14 +49,20 @@ int main() {
         const int bound = m_tiles_bound(P, E, BM);
         tight += m_tiles == bound;
         faults += m_tiles > bound;
-        const int n_tiles = 1 + below(it % 2 ? 8 : 60);
-        for (int split : {0, 32, 64}) {
-            ++launches;
-            const int grid = find_tile_grid(bound * n_tiles, split);
-            if (grid % 8 == 0 && slots(m_tiles * n_tiles, split) * 8 <= grid) continue;
-            if (faults++ < 8) std::printf("%d rows in %d groups, tiles of %d rows, %d across, split %d\n", P, E, BM, n_tiles, split);
-        }
+        const int BN = 128 << below(2), N = 8 * (1 + below(it % 2 ? 128 : 768)), copies = 1 + below(4);
+        const int n_tiles = (N + BN - 1) / BN;
+        for (int split : {0, 32, 64})
+            for (int fit : {0, 2}) {
+                if (fit && split != 32) continue;
+                int width = BN, n_base = n_tiles;
+                if (fit) fit_columns(m_tiles * copies, N, fit, width, n_base);
+                narrowed += width < BN;
+                ++launches;
+                const int grid = find_tile_grid(fitted_tiles(bound * n_tiles * copies, fit), split), tiles = m_tiles * n_base * copies;
+                if (grid % 8 == 0 && (long long)n_base * width >= N && (split == 64 ? all_taken<64>(grid, tiles) : split == 32 ? all_taken<32>(grid, tiles) : all_taken<0>(grid, tiles))) continue;
+                if (faults++ < 8) std::printf("%d rows in %d groups, tiles of %d rows, %d of %d columns, %d copies, split %d, fit %d\n", P, E, BM, N, width, copies, split, fit);
+            }
     }
-    std::printf("%lld launches, %lld loads at the bound, %lld faults\n", launches, tight, faults);
-    return faults || tight < 1000;
+    std::printf("%lld launches, %lld loads at the bound, %lld with narrower tiles, %lld faults\n", launches, tight, narrowed, faults);
+    return faults || tight < 1000 || narrowed < 1000;
 }
