@@ -316,8 +316,8 @@ __global__ __launch_bounds__(kTokenWaves* kWave) __attribute__((amdgpu_waves_per
     const int i = lane & 15, quad = lane >> 4;
     const int t = t0 + (int)(threadIdx.x >> 4), n = n0 + (int)(threadIdx.x & 15);  // what the thread adds up
     const bool mine = threadIdx.x < 256 && t < T && n < d;
-    // The first two experts and gates, and the residual, are requested with the products' operands.  (No load is conditional:
-    // the compiler would wait for it where the branch ends.)
+    // The first two experts and gates, and the residual, are requested with the products' operands.  (Experts and gates without a condition: the
+    // compiler would wait for them where its branch ends.  The residual stands behind one, and its pointer, of the struct, is waited for ahead of the operands.)
     const int pair = min(t, T - 1) * k;
     const int e0 = idx[pair], e1 = idx[pair + min(1, k - 1)];
     const float gate0 = gates[pair], gate1 = gates[pair + min(1, k - 1)];
