@@ -459,7 +459,7 @@ __global__ __launch_bounds__(kMidWaves* kWave) __attribute__((amdgpu_waves_per_e
 // td_j = R_d,j h_j is a sum over the hidden rows, so a workgroup that forms 64 of them adds up its share of all k r
 // sums while it has them, from columns of R_d that it requested at its start, and the last stage, every workgroup of
 // which needs all of td, adds up the workgroups' shares (45 KB at 2048 x 5632, rank 64) under its stream of base
-// rows: a launch less, and no hidden vectors in memory.  2048 x 5632, rank 64: 9.6 + 4.6 + 8.5 us, layer 23.9 -> 21.8; 12 shapes of 400 to
+// rows: a launch less, and no hidden vectors in memory.  2048 x 5632, rank 64: 10.0 + 4.4 + 8.7 us in the trace, layer 23.9 -> 21.9; 12 shapes of 400 to
 // 2048 wide, 2 and 4 experts, 1.07 times as fast (geometric mean, 1.03 the least).  Up to 64 sums per hidden row of a workgroup and
 // pair: longer ranks would take more hidden rows a workgroup, or the parts more room than the vectors whose place they take (128
 // rows a workgroup, rank 128: 512 x 1400 14.6 -> 19.0, 2048 x 5632 27.0 -> 28.0).
