@@ -34,7 +34,9 @@ __global__ __launch_bounds__(256) void combine_kernel(ptr_arg a_inv, ptr_arg a_g
         for (int q = 0; q < VEC; ++q) acc[q] = 0.f;
         // Everything that a chunk needs is requested ahead of the sums: the residual, a shared part, and two pairs' rows at a time.  (One
         // after the other they were up to four memory latencies: 16384 tokens of 2048, two experts, 36.6 us, 33.9 now, 8192 tokens of 720,
-        // eight experts, 32.0 and 23.9; layer of 8 tokens on a shared base of 2048 / 5632 65.4 and 63.8, of 24 tokens, 4 of 16 experts, 43.1 and 42.5.)
+        // eight experts, 32.0 and 23.9; layer of 8 tokens on a shared base of 2048 / 5632 65.4 and 63.8, of 24 tokens, 4 of 16 experts, 43.1 and 42.5.
+        // fp32 rows of 2048, four experts: 512 tokens 5.2 and 4.7, 1024 tokens 8.3 and 7.5, 8192 tokens 65.9 and 65.0; only where rows and results are about what
+        // the memory-side cache holds, 4096 tokens, is it 25.5 and 25.9.)
         vec_t res{}, add{};
         f32x4 add_part[ADD == ADD_PARTS ? kMaxParts : 1][VEC / 4] = {};
         if (residual) res = *reinterpret_cast<const vec_t*>(residual + (size_t)t * d + i);
